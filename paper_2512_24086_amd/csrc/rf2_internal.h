@@ -16,6 +16,7 @@ struct rf2_plan {
   int32_t* d_inv;                  // device, N entries
   int32_t* d_row_order;            // device, [8][plain_per_xcd]: ordinary Q block of each workgroup slot of a head, -1 = none
   int32_t plain_per_xcd;
+  float mask_z, mask_slope;        // first guesses of the mask kernel's threshold search (rf2_mask_prepare)
 };
 
 // Strides (in rows of d elements) of the caller's q, k, v, o tensors: row of token n of head h of
@@ -29,8 +30,8 @@ inline rf2_strides rf2_qkv_strides(const rf2_plan* p) {
   return {Hh * N, N, 1};
 }
 
-// Per-plan preparation of the mask kernel (dynamic LDS limit); defined in rf2_mask.hip.
-int rf2_mask_prepare(const rf2_plan* plan);
+// Per-plan preparation of the mask kernel (dynamic LDS limit, search constants); defined in rf2_mask.hip.
+int rf2_mask_prepare(rf2_plan* plan);
 
 // Remembers the text of a failed HIP call for rf2_strerror (per calling thread).
 int rf2_note_hip_error(hipError_t e);

@@ -1,13 +1,27 @@
 // Block-mask prediction: S_hat = qbar kbar^T (Sec. 3.2, eq. 7) in fp32 on the matrix cores,
 // then per-row top-n selection (eq. 8) with the first-frame sink (Sec. 3.4), fused in one
-// kernel.  A workgroup owns 16 rows (Q blocks) of one head: its 4 wavefronts first fill a 16 x Tk
-// score strip in LDS (Tk = number of K blocks; the mask is Tq x Tk, square unless b_q != b_k),
-// then each wavefront selects 4 of the rows with a bitwise threshold search over
-// order-preserving integer keys and emits the ascending block list.
+// kernel.  A workgroup owns 16 rows (Q blocks) of one head: its wavefronts first fill a 16 x Tk
+// strip of order-preserving integer keys of the scores in LDS (Tk = number of K blocks; the mask
+// is Tq x Tk, square unless b_q != b_k), then each wavefront finds the threshold key of its rows
+// by a guided search and emits the ascending block lists.
 // The cumulative-mass variant (RF2_SELECT_CDF) runs the same search on probability mass
 // instead of counts: the threshold is the largest key whose upper set carries >= tau of the
 // row's softmax mass.
+//
+// What bounds it: on the 720p layer (591 x 591 scores, 40 heads) the fp32 MFMAs take 23 us of the
+// matrix cores at full rate, the search and the emission about as much of the vector and of the
+// scalar issue slots; a workgroup is a chain of load, multiply, search and store, so what counts is how
+// many of them a compute unit holds.  The Q operand is read from LDS and the K operand is
+// reloaded in place, which keeps a wavefront within 80 registers: six wavefronts per SIMD (four
+// wavefronts of 110 registers before).  A probe of the search costs a compare and a population count per 64
+// keys; the normal-distribution guess and interpolation need 4.2 of them a row on that layer where a bitwise
+// search that stops at the first exact count needs 15.5.  720p: 104 -> 72 us; cumulative mass on the
+// long video (929 x 929, 24 heads): 291 -> 140 us; with few workgroups 12-50 -> 8-15 us.  Wavefronts that
+// share a K tile (32, 48 or 64 rows per workgroup) halve the L2 reads and are slower (98-122 us on 720p).
 #include "rf2_internal.h"
+
+#include <algorithm>
+#include <cmath>
 
 namespace {
 
@@ -15,36 +29,96 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 // Order-preserving map float -> uint32 (larger float <=> larger key); -0 is folded into +0.
 __device__ __forceinline__ uint32_t order_key(float x) {
-  x = (x == 0.f) ? 0.f : x;
-  const uint32_t u = __float_as_uint(x);
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  const uint32_t u = __float_as_uint(x + 0.f);
+  return u ^ (uint32_t)(((int32_t)u >> 31) | (int32_t)0x80000000);
+}
+
+// The float whose order_key is k.
+__device__ __forceinline__ float key_value(uint32_t k) {
+  return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
+}
+
+// The same value in every lane, as a scalar.
+__device__ __forceinline__ float uniform(float x) {
+  return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(x)));
 }
 
 __device__ __forceinline__ int popc64(unsigned long long m) { return __builtin_popcountll(m); }
-
-// Butterfly reductions: every lane ends with the same bits (a + b and b + a are the same float).
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-  return v;
+// Set bits of m below this lane.
+__device__ __forceinline__ int rank_below(unsigned long long m) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-template <int D, int EMAX, bool CDF>
-__global__ void __launch_bounds__(256) predict_mask_kernel(
+// Reductions over the wavefront on the vector ALU (DPP row shifts and row broadcasts); the total forms in lane 63 and
+// is handed to every lane as a scalar.  An LDS shuffle would cost a trip through LDS for each of the six steps.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp(uint32_t old, uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)v, CTRL, ROWS, 0xf, false);
+}
+template <class Op>
+__device__ __forceinline__ uint32_t wave_reduce(uint32_t v, uint32_t neutral, Op op) {
+  v = op(v, dpp<0x111, 0xf>(neutral, v));             // lane i with lane i-1, then i-2, i-4, i-8 of its row of 16
+  v = op(v, dpp<0x112, 0xf>(neutral, v));
+  v = op(v, dpp<0x114, 0xf>(neutral, v));
+  v = op(v, dpp<0x118, 0xf>(neutral, v));
+  v = op(v, dpp<0x142, 0xa>(neutral, v));             // lane 15 / 47 to the row behind it
+  v = op(v, dpp<0x143, 0xc>(neutral, v));             // lane 31 to the upper half
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ __forceinline__ float wave_sum(float x) {
+  return __uint_as_float(wave_reduce(__float_as_uint(x), 0u, [](uint32_t a, uint32_t b) {
+    return __float_as_uint(__uint_as_float(a) + __uint_as_float(b));
+  }));
+}
+// Sum over a row of 16 lanes, in the last of them.
+__device__ __forceinline__ float row_sum(float x) {
+  x += __uint_as_float(dpp<0x111, 0xf>(0u, __float_as_uint(x)));
+  x += __uint_as_float(dpp<0x112, 0xf>(0u, __float_as_uint(x)));
+  x += __uint_as_float(dpp<0x114, 0xf>(0u, __float_as_uint(x)));
+  return x + __uint_as_float(dpp<0x118, 0xf>(0u, __float_as_uint(x)));
+}
+__device__ __forceinline__ uint32_t wave_max_u(uint32_t x) {
+  return wave_reduce(x, 0u, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
+}
+
+// First guesses of a row's threshold search (see rf2_mask_prepare).
+struct Guess {
+  float z, slope;
+};
+
+// Keys of columns that take no part in a row's search: below every candidate's (columns past the row) and above
+// (sink columns: counted by every probe and always taken).
+constexpr uint32_t PAST_KEY = 0u, SINK_KEY = 0xffffffffu;
+
+// A search keeps a bracket [lo, top] around the threshold.  The first two probes come from the guesses, then the
+// measure (count or mass) is interpolated between the ends, or the bracket halved where an interpolation has not
+// halved its keys; after MAX_SMART probes the integer range is halved (at most 32 more).  Whatever the probes are, the
+// threshold found is the same.
+constexpr int MAX_SMART = 12;
+__device__ __forceinline__ uint32_t next_probe(float t, bool smart, uint32_t lo, uint32_t top) {
+  const uint32_t k = order_key(t);
+  return (smart && k > lo && k <= top) ? k : lo + ((top - lo) >> 1) + 1u;      // any float, NaN too, is safe here
+}
+
+// NW wavefronts per workgroup of R = 16 rows.
+template <int D, int EMAX, bool CDF, int NW>
+__global__ void __launch_bounds__(NW * 64, (NW == 8 && EMAX <= (CDF ? 12 : 20)) ? 6 : 4) predict_mask_kernel(
     const float* __restrict__ qbar, const float* __restrict__ kbar, int32_t* __restrict__ blk_idx,
     int32_t* __restrict__ blk_cnt, uint8_t* __restrict__ mask_dense, float* __restrict__ scores,
-    int Tq, int Tb, int LD, int row_sink_begin, int row_sink_end, int sink_begin, int sink_end, int k_row, int k_sel,
-    float tau, float scale_log2) {
+    int Tq, int Tb, int LD, int row_sink_begin, int row_sink_end, int sink_begin, int sink_end, int k_row,
+    float tau, float scale_log2, Guess guess, int n_strips, int n_work) {
   // Tb, sink_begin, sink_end describe the COLUMNS (K blocks) from here on; rows use Tq and row_sink_*.
-  extern __shared__ __attribute__((aligned(16))) float sc[];   // [16][LD]
-  const int bh = blockIdx.y;
-  const int i0 = blockIdx.x * 16;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  constexpr int R = 16;
+  extern __shared__ __attribute__((aligned(16))) uint32_t keys[];   // [R][LD]
+  __shared__ float stat[NW][R][2];                                  // sum and sum of squares over a wavefront's columns
+  __shared__ __attribute__((aligned(16))) float qs[R][D + 4];       // (+4: the 16 rows of an operand read start in different banks)
+  // Workgroups with equal blockIdx % 8 share an XCD and take a contiguous run of the strips, numbered head by head:
+  // the strips that read one head's kbar meet in one L2.
+  const int work = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+  if (work >= n_work) return;
+  const int bh = work / n_strips;
+  const int i0 = (work % n_strips) * R;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lr = lane & 15, lk = lane >> 4;
   const float* __restrict__ qb = qbar + (size_t)bh * Tq * D;
   const float* __restrict__ kb = kbar + (size_t)bh * Tb * D;
@@ -53,48 +127,67 @@ __global__ void __launch_bounds__(256) predict_mask_kernel(
   // Lane (lr, lk) feeds row lr of each operand.  Per 16 channels it loads 4 consecutive
   // floats at 16*kk + 4*lk; MFMA step e uses element e, so "k slot lk" stands for channel
   // 16*kk + 4*lk + e in both operands (a dot product does not care about summation order).
-  f32x4 a[D / 16];
-  {
-    const int row = min(i0 + lr, Tq - 1);
-#pragma unroll
-    for (int kk = 0; kk < D / 16; ++kk) a[kk] = *reinterpret_cast<const f32x4*>(qb + (size_t)row * D + 16 * kk + 4 * lk);
-  }
   const int n_ct = (Tb + 15) / 16;
-  // the operand rows of the next column tile are requested before the products of the current one are
-  // issued (a wavefront has ~10 tiles; unpipelined, each tile waits out a full trip to L2)
-  auto load_tile = [&](f32x4 (&b)[D / 16], int ct) {
-    const int col = min(ct * 16 + lr, Tb - 1);
+  f32x4 b[D / 16];
+  const float* __restrict__ kcol = kb + 4 * lk;
 #pragma unroll
-    for (int kk = 0; kk < D / 16; ++kk) b[kk] = *reinterpret_cast<const f32x4*>(kb + (size_t)col * D + 16 * kk + 4 * lk);
-  };
-  f32x4 bcur[D / 16], bnext[D / 16];
-  if (wave < n_ct) load_tile(bcur, wave);
-  for (int ct = wave; ct < n_ct; ct += 4) {
-    if (ct + 4 < n_ct) load_tile(bnext, ct + 4);
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int kk = 0; kk < D / 16; ++kk)
+    b[kk] = *reinterpret_cast<const f32x4*>(kcol + (size_t)min(wave * 16 + lr, Tb - 1) * D + 16 * kk);
+  for (int c = threadIdx.x; c < R * (D / 4); c += NW * 64) {
+    const int row = c / (D / 4), ch = c % (D / 4) * 4;
+    *reinterpret_cast<f32x4*>(&qs[row][ch]) = *reinterpret_cast<const f32x4*>(qb + (size_t)min(i0 + row, Tq - 1) * D + ch);
+  }
+  __syncthreads();
+  float sum[4] = {}, sum2[4] = {};
+  for (int ct = wave; ct < n_ct; ct += NW) {
+    // the registers of a chunk are reloaded for the wavefront's next column tile as soon as its products are issued
+    const bool more = ct + NW < n_ct;
+    const float* __restrict__ knext = kcol + (size_t)min((ct + NW) * 16 + lr, Tb - 1) * D;
+    f32x4 acc = {}, a = *reinterpret_cast<const f32x4*>(&qs[lr][4 * lk]);
 #pragma unroll
     for (int kk = 0; kk < D / 16; ++kk) {
+      const f32x4 a_now = a;
+      if (kk + 1 < D / 16) a = *reinterpret_cast<const f32x4*>(&qs[lr][16 * (kk + 1) + 4 * lk]);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk][e], bcur[kk][e], acc, 0, 0, 0);
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a_now[e], b[kk][e], acc, 0, 0, 0);
+      if (more) b[kk] = *reinterpret_cast<const f32x4*>(knext + 16 * kk);
+      __builtin_amdgcn_sched_barrier(0);      // (left alone, the loads of all chunks are gathered in twice the registers)
     }
     // acc[i] = S_hat[i0 + 4*lk + i][ct*16 + lr]
+    const int j = ct * 16 + lr;
+    if (scores != nullptr) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) sc[(4 * lk + i) * LD + ct * 16 + lr] = acc[i];
+      for (int i = 0; i < 4; ++i)
+        if (j < Tb && i0 + 4 * lk + i < Tq) scores[((size_t)bh * Tq + i0 + 4 * lk + i) * Tb + j] = acc[i];
+    }
+    uint32_t* const kout = &keys[4 * lk * LD + j];
 #pragma unroll
-    for (int kk = 0; kk < D / 16; ++kk) bcur[kk] = bnext[kk];
+    for (int i = 0; i < 4; ++i) kout[i * LD] = min(max(order_key(acc[i]), PAST_KEY + 1u), SINK_KEY - 1u);
+    if (ct * 16 + 16 > Tb || (ct * 16 + 16 > sink_begin && ct * 16 < sink_end)) {   // columns that are no candidates
+      const bool past = j >= Tb, sink = j >= sink_begin && j < sink_end;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (past || sink) kout[i * LD] = past ? PAST_KEY : SINK_KEY;
+        acc[i] = (past || sink) ? 0.f : acc[i];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      sum[i] += acc[i];
+      sum2[i] = fmaf(acc[i], acc[i], sum2[i]);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    // the 16 lanes of a row: total in the last of them
+    const float s = row_sum(sum[i]), s2 = row_sum(sum2[i]);
+    if (lr == 15) { stat[wave][4 * lk + i][0] = s; stat[wave][4 * lk + i][1] = s2; }
   }
   __syncthreads();
 
-  if (scores != nullptr) {
-    for (int r = 0; r < 16 && i0 + r < Tq; ++r)
-      for (int j = threadIdx.x; j < Tb; j += 256)
-        scores[((size_t)bh * Tq + i0 + r) * Tb + j] = sc[r * LD + j];
-  }
-
-  // ---- selection: wavefront `wave` handles rows wave, wave+4, wave+8, wave+12 ------------
-  const int E = (Tb + 63) / 64;
-  const unsigned long long lt_mask = (1ull << lane) - 1ull;
-  for (int r = wave; r < 16; r += 4) {
+  // ---- selection: wavefront `wave` handles rows wave, wave + NW, ... ------------
+  const int n_cand = Tb - (sink_end - sink_begin);
+  for (int r = wave; r < R; r += NW) {
     const int i = i0 + r;
     if (i >= Tq) break;
     int32_t* __restrict__ out = blk_idx + ((size_t)bh * Tq + i) * k_row;
@@ -107,83 +200,112 @@ __global__ void __launch_bounds__(256) predict_mask_kernel(
     }
     uint32_t key[EMAX];
 #pragma unroll
-    for (int e = 0; e < EMAX; ++e) {
-      const int j = 64 * e + lane;
-      const bool cand = (e < E) && (j < Tb) && !(j >= sink_begin && j < sink_end);
-      key[e] = cand ? order_key(sc[r * LD + j]) : 0u;   // 0 is below the key of every finite float
-    }
-    uint32_t T = 0xffffffffu;
-    int need_eq;                                      // equal keys to take, lowest column first
+    for (int e = 0; e < EMAX; ++e) key[e] = 64 * e + lane < Tb ? keys[r * LD + 64 * e + lane] : PAST_KEY;
+    float sum_r = 0.f, sum2_r = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) { sum_r += stat[w][r][0]; sum2_r += stat[w][r][1]; }
+    const float inv_n = 1.0f / (float)max(n_cand, 1), mean = uniform(sum_r * inv_n);
+    const float sigma = uniform(__builtin_amdgcn_sqrtf(fmaxf(sum2_r * inv_n - mean * mean, 0.f)));
+    // The threshold T: every key above it is taken, of the keys equal to it the need_eq lowest columns.
+    uint32_t T, lo = PAST_KEY + 1u, top = SINK_KEY - 1u;      // bracket: the answer is in [lo, top]
+    int need_eq = 0;
+    int n_lo = Tb, n_top = Tb - n_cand;             // keys >= lo, keys > top
+    bool halve = false;
     if constexpr (!CDF) {
-      // Largest T with |{key >= T}| >= k_sel, built bit by bit: T is the k_sel-th largest key.
-      if (k_sel > 0) {
-        T = 0u;
-        for (int bit = 31; bit >= 0; --bit) {
-          const uint32_t cand = T | (1u << bit);
-          int cnt = 0;
+      // Largest T with |{key >= T}| >= k_row (sink columns count); a probe with exactly k_row keys at or above it ends
+      // the search early: any T between the k_row-th and the next key gives the same set.
+      bool exact = (n_lo == k_row);
+      float t = mean + guess.z * sigma;
+      if (n_top == k_row) { lo = SINK_KEY; exact = true; }    // only the sink columns
+      for (int p = 0; !exact && lo < top; ++p) {
+        const uint32_t cand = next_probe(t, p < MAX_SMART, lo, top);
+        int cnt = 0;
 #pragma unroll
-          for (int e = 0; e < EMAX; ++e)
-            cnt += popc64(__builtin_amdgcn_ballot_w64(key[e] >= cand));   // (keys past the row are 0 < cand)
-          if (cnt >= k_sel) T = cand;
-          // exactly k_sel keys at or above T: lower bits can only raise T towards the smallest of them
-          // without changing that set, and the tie rule below sees the same set either way
-          if (cnt == k_sel) break;
-        }
+        for (int e = 0; e < EMAX; ++e) cnt += popc64(__builtin_amdgcn_ballot_w64(key[e] >= cand));
+        const int before = n_lo - n_top;
+        if (cnt >= k_row) { lo = cand; n_lo = cnt; } else { top = cand - 1u; n_top = cnt; }
+        exact = (cnt == k_row);
+        halve = !halve && p > 1 && 2 * (n_lo - n_top) > before;
+        const float fl = key_value(lo), fh = key_value(top);
+        if (p == 0) t += (float)(cnt - k_row) * sigma * guess.slope;
+        else if (lo == PAST_KEY + 1u) t = fh - sigma * (0.25f * (float)(1 << p));      // no lower (upper) end yet
+        else if (top == SINK_KEY - 1u) t = fl + sigma * (0.25f * (float)(1 << p));
+        else t = fl + (fh - fl) * (halve ? 0.5f : (float)(n_lo - k_row) / (float)(n_lo - n_top));
       }
-      int greater = 0;
-#pragma unroll
-      for (int e = 0; e < EMAX; ++e)
-        greater += popc64(__builtin_amdgcn_ballot_w64(key[e] > T));
-      need_eq = k_sel - greater;
+      T = exact ? lo - 1u : lo;
+      need_eq = exact ? 0 : k_row - n_top;          // lo == top: the keys equal to lo share the places left
     } else {
       // Softmax mass of every candidate (relative to the row maximum, unnormalised), then the
       // largest T whose upper set {key >= T} carries at least tau of the total: the columns above
-      // T are the shortest prefix of the descending order that reaches tau, up to ties at T.
-      float mx = -INFINITY;
+      // T are the shortest prefix of the descending order that reaches tau, up to ties at T.  One key left in the
+      // bracket ends the search.
+      uint32_t kmax = PAST_KEY + 1u;
 #pragma unroll
-      for (int e = 0; e < EMAX; ++e)
-        if (key[e] != 0u) mx = fmaxf(mx, sc[r * LD + 64 * e + lane]);
-      mx = wave_max(mx);
+      for (int e = 0; e < EMAX; ++e) kmax = max(kmax, key[e] == SINK_KEY ? PAST_KEY : key[e]);
+      top = wave_max_u(kmax);
+      const float mx = key_value(top);
       float ev[EMAX], part = 0.f;
 #pragma unroll
       for (int e = 0; e < EMAX; ++e) {
-        ev[e] = (key[e] != 0u) ? __builtin_amdgcn_exp2f((sc[r * LD + 64 * e + lane] - mx) * scale_log2) : 0.f;
+        const float x = __builtin_amdgcn_exp2f((key_value(key[e]) - mx) * scale_log2);
+        ev[e] = (key[e] != PAST_KEY && key[e] != SINK_KEY) ? x : 0.f;
         part += ev[e];
       }
-      const float target = tau * wave_sum(part);
-      T = 0u;
-      for (int bit = 31; bit >= 0; --bit) {
-        const uint32_t cand = T | (1u << bit);
+      const float total = wave_sum(part), target = tau * total;
+      float m_lo = total, m_top = 0.f;
+      // (a weight exp(a s) moves the mean of a normal distribution by a sigma^2)
+      float t = mean + sigma * (sigma * scale_log2 * 0.6931472f + guess.z);
+      for (int p = 0; n_lo - n_top > 1 && lo < top; ++p) {
+        const uint32_t cand = next_probe(t, p < MAX_SMART, lo, top);
         float mass = 0.f;
+        int cnt = 0;
 #pragma unroll
-        for (int e = 0; e < EMAX; ++e) mass += (key[e] >= cand) ? ev[e] : 0.f;
-        if (wave_sum(mass) >= target) T = cand;
+        for (int e = 0; e < EMAX; ++e) {
+          const bool in = key[e] >= cand;
+          mass += in ? ev[e] : 0.f;
+          cnt += popc64(__builtin_amdgcn_ballot_w64(in));
+        }
+        mass = wave_sum(mass);
+        const int before = n_lo - n_top;
+        if (mass >= target) { lo = cand; n_lo = cnt; m_lo = mass; } else { top = cand - 1u; n_top = cnt; m_top = mass; }
+        halve = !halve && p > 1 && 2 * (n_lo - n_top) > before;
+        const float fl = key_value(lo), fh = key_value(top);
+        if (p == 0) t += (mass / total - tau) * sigma * guess.slope;
+        else if (lo == PAST_KEY + 1u) t = fh - sigma * (0.25f * (float)(1 << p));
+        else t = fl + (fh - fl) * (halve ? 0.5f : (m_lo - target) / (m_lo - m_top));
       }
-      float above = 0.f, tie = 0.f;
+      T = lo - 1u;                                    // (where the sums are no numbers lo has not moved: all are kept)
+      if (n_lo - n_top > 1) {                         // lo == top: several keys equal to it, of equal mass
+        T = lo;
+        const float tie = __builtin_amdgcn_exp2f((key_value(lo) - mx) * scale_log2);
+        const float left = ceilf((target - m_top) / tie);
+        need_eq = left <= (float)n_lo ? max(1, (int)left) : n_lo;      // (not a number: the whole row is kept)
+      } else if (n_cand == 0) {
+        T = SINK_KEY - 1u;                            // only sink columns
+      }
+    }
+    if (need_eq > 0) {                                // of the keys equal to T, the lowest columns rise above it
+      int run = 0;
 #pragma unroll
       for (int e = 0; e < EMAX; ++e) {
-        above += (key[e] > T) ? ev[e] : 0.f;
-        tie = fmaxf(tie, (key[e] == T) ? ev[e] : 0.f);
+        const bool eq = key[e] == T;
+        const unsigned long long eq_m = __builtin_amdgcn_ballot_w64(eq);
+        if (eq && run + rank_below(eq_m) < need_eq) key[e] = T + 1u;
+        run += popc64(eq_m);
       }
-      above = wave_sum(above);
-      tie = wave_max(tie);                            // equal keys have equal mass
-      need_eq = max(1, (int)ceilf((target - above) / tie));
     }
-    int eq_run = 0, out_run = 0;
+    int out_run = 0;
 #pragma unroll
     for (int e = 0; e < EMAX; ++e) {
-      if (e < E) {
-        const int j = 64 * e + lane;
-        const bool is_sink = (j < Tb) && (j >= sink_begin) && (j < sink_end);
-        const bool eq = (key[e] == T) && (CDF ? key[e] != 0u : k_sel > 0);
-        const unsigned long long eq_m = __builtin_amdgcn_ballot_w64(eq);
-        const bool sel = is_sink || (key[e] > T) || (eq && (eq_run + popc64(eq_m & lt_mask) < need_eq));
-        const unsigned long long sel_m = __builtin_amdgcn_ballot_w64(sel);
-        if (sel) out[out_run + popc64(sel_m & lt_mask)] = j;
-        if (mrow && j < Tb) mrow[j] = sel ? 1 : 0;
-        eq_run += popc64(eq_m);
-        out_run += popc64(sel_m);
-      }
+      const bool sel = key[e] > T;
+      const unsigned long long sel_m = __builtin_amdgcn_ballot_w64(sel);
+      if (sel) out[out_run + rank_below(sel_m)] = 64 * e + lane;
+      out_run += popc64(sel_m);
+    }
+    if (mrow) {
+#pragma unroll
+      for (int e = 0; e < EMAX; ++e)
+        if (64 * e + lane < Tb) mrow[64 * e + lane] = key[e] > T ? 1 : 0;
     }
     if (lane == 0) blk_cnt[(size_t)bh * Tq + i] = out_run;   // top-n: == k_row by construction
   }
@@ -192,41 +314,74 @@ __global__ void __launch_bounds__(256) predict_mask_kernel(
 // Shape of the launch for a plan, and the kernel instance that serves it.
 struct MaskLaunch {
   const void* kernel;
-  int E, LD;
+  int E, LD, NW;
   size_t lds;
 };
 
 // The kernel is instantiated for a few row widths (EMAX keys per lane): the search loops run over
 // EMAX keys without bounds checks (keys past the row are 0), so a snug width saves compares.
-template <int D>
+template <int D, int NW>
 const void* mask_kernel_for(int E, bool cdf) {
-  if (E <= 8) return cdf ? (const void*)predict_mask_kernel<D, 8, true> : (const void*)predict_mask_kernel<D, 8, false>;
-  if (E <= 12) return cdf ? (const void*)predict_mask_kernel<D, 12, true> : (const void*)predict_mask_kernel<D, 12, false>;
-  if (E <= 16) return cdf ? (const void*)predict_mask_kernel<D, 16, true> : (const void*)predict_mask_kernel<D, 16, false>;
-  if (E <= 20) return cdf ? (const void*)predict_mask_kernel<D, 20, true> : (const void*)predict_mask_kernel<D, 20, false>;
-  if (E <= 24) return cdf ? (const void*)predict_mask_kernel<D, 24, true> : (const void*)predict_mask_kernel<D, 24, false>;
-  return cdf ? (const void*)predict_mask_kernel<D, 32, true> : (const void*)predict_mask_kernel<D, 32, false>;
+#define RF2_MASK_CASE(W) \
+  if (E <= W) return cdf ? (const void*)predict_mask_kernel<D, W, true, NW> : (const void*)predict_mask_kernel<D, W, false, NW>;
+  RF2_MASK_CASE(2)
+  RF2_MASK_CASE(4)
+  RF2_MASK_CASE(6)
+  RF2_MASK_CASE(8)
+  RF2_MASK_CASE(10)
+  RF2_MASK_CASE(12)
+  RF2_MASK_CASE(16)
+  RF2_MASK_CASE(20)
+  RF2_MASK_CASE(24)
+  RF2_MASK_CASE(32)
+#undef RF2_MASK_CASE
+  return nullptr;                                   // (Tk <= 2048: E <= 32)
 }
 
 MaskLaunch mask_launch(const rf2_plan* plan) {
   MaskLaunch m;
   m.E = (plan->info.n_blocks_k + 63) / 64;
-  m.LD = m.E * 64 + 4;                              // +4: the 4 row groups of a tile store hit distinct banks
-  m.lds = (size_t)16 * m.LD * sizeof(float);
+  m.LD = (plan->info.n_blocks_k + 15) / 16 * 16 + 4;   // +4: the 4 row groups of a tile store hit distinct banks
+  m.lds = (size_t)16 * m.LD * sizeof(uint32_t);
+  // Up to one workgroup per compute unit a row's search is latency: 16 wavefronts search one row each.  Beyond, a
+  // compute unit holds three workgroups of 8 wavefronts but only one of 16.  (16 against 8 wavefronts: 9.5 / 10.3 us
+  // at 28 workgroups, 12.4 / 13.0 at 35, 20.3 / 21.2 at 136; 21.2 / 19.7 us at 320, 92 / 72 us at 1,480.)
+  const int64_t strips = (int64_t)((plan->info.n_blocks + 15) / 16) * plan->cfg.batch * plan->cfg.heads;
+  m.NW = strips <= 256 ? 16 : 8;
   const bool cdf = (plan->cfg.select_mode == RF2_SELECT_CDF);
-  m.kernel = plan->cfg.head_dim == 128 ? mask_kernel_for<128>(m.E, cdf) : mask_kernel_for<64>(m.E, cdf);
+  if (plan->cfg.head_dim == 128) m.kernel = m.NW == 8 ? mask_kernel_for<128, 8>(m.E, cdf) : mask_kernel_for<128, 16>(m.E, cdf);
+  else m.kernel = m.NW == 8 ? mask_kernel_for<64, 8>(m.E, cdf) : mask_kernel_for<64, 16>(m.E, cdf);
   return m;
+}
+
+// z with P(X > z) = p for a standard normal X, by halving on the complementary error function.
+double normal_quantile(double p) {
+  double lo = -9.0, hi = 9.0;
+  for (int it = 0; it < 60; ++it) {
+    const double mid = 0.5 * (lo + hi);
+    (0.5 * std::erfc(mid * 0.7071067811865476) > p ? lo : hi) = mid;
+  }
+  return 0.5 * (lo + hi);
 }
 
 }  // namespace
 
-// Called once by rf2_plan_create: a score strip wider than the default dynamic-LDS limit needs the limit of
-// its kernel raised.  Doing it here keeps rf2_predict_mask free of anything but the launch (so it can be
-// recorded into a HIP graph).
-int rf2_mask_prepare(const rf2_plan* plan) {
+// Called once by rf2_plan_create.  A score strip wider than the default dynamic-LDS limit needs the limit of
+// its kernel raised; doing it here keeps rf2_predict_mask free of anything but the launch (so it can be
+// recorded into a HIP graph).  The first probe of a row's threshold search is where a normal distribution with the
+// mean and variance of the row's scores would have it, the second a Newton step from there: z and 1 / density.
+int rf2_mask_prepare(rf2_plan* plan) {
   const MaskLaunch m = mask_launch(plan);
-  if (m.lds > 48 * 1024)
+  if (m.lds > 32 * 1024)
     RF2_HIP(hipFuncSetAttribute(m.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)m.lds));
+  const rf2_info& in = plan->info;
+  const int n_cand = in.n_blocks_k - (in.sink_block_end_k - in.sink_block_begin_k);
+  const bool cdf = (plan->cfg.select_mode == RF2_SELECT_CDF);
+  const double n = cdf ? 1.0 : (double)std::max(n_cand, 1);
+  const double p = cdf ? (double)plan->cfg.cdf_threshold : in.k_sel / n;
+  const double z = (p > 0.0 && p < 1.0) ? normal_quantile(p) : 0.0;
+  plan->mask_z = (float)z;
+  plan->mask_slope = (float)(2.5066282746310002 * std::exp(0.5 * z * z) / n);
   return RF2_OK;
 }
 
@@ -241,11 +396,13 @@ extern "C" int rf2_predict_mask(const rf2_plan* plan, const float* qbar, const f
   const MaskLaunch m = mask_launch(plan);
   int Tq = in.n_blocks, Tk = in.n_blocks_k, LD = m.LD;   // rows and columns of the block mask
   int rb = in.sink_block_begin, re = in.sink_block_end, cb = in.sink_block_begin_k, ce = in.sink_block_end_k;
-  int k_row = in.k_row, k_sel = in.k_sel;
+  int k_row = in.k_row;
   float tau = c.cdf_threshold, scale_log2 = (float)(1.4426950408889634 / sqrt((double)c.head_dim));
+  Guess guess{plan->mask_z, plan->mask_slope};
+  int n_strips = (Tq + 16 - 1) / 16, n_work = n_strips * c.batch * c.heads;    // at most 128 x 65,535
   void* args[] = {&qbar, &kbar, &blk_idx, &blk_cnt, &mask_dense, &scores, &Tq, &Tk, &LD, &rb, &re, &cb, &ce,
-                  &k_row, &k_sel, &tau, &scale_log2};
-  const dim3 grid((Tq + 15) / 16, c.batch * c.heads, 1);
-  RF2_HIP(hipLaunchKernel(m.kernel, grid, dim3(256), args, m.lds, (hipStream_t)stream));
+                  &k_row, &tau, &scale_log2, &guess, &n_strips, &n_work};
+  const dim3 grid((unsigned)((n_work + 7) / 8 * 8), 1, 1);
+  RF2_HIP(hipLaunchKernel(m.kernel, grid, dim3(m.NW * 64), args, m.lds, (hipStream_t)stream));
   return RF2_OK;
 }

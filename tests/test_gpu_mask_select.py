@@ -1,0 +1,127 @@
+"""Block selection on given block means: the lists of rf2_predict_mask against the selection rule applied on the host
+to the scores the same call returns.  Top-n must agree entry by entry, whatever the scores (ties, infinities, NaN)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2512_24086_amd import rf2
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def order_key(x):
+    """Order of eq. (8): larger float, larger key; -0 equals +0; NaN beyond the infinity of its sign."""
+    u = (x + np.float32(0)).view(np.uint32).astype(np.int64)
+    return np.where(u >> 31 == 1, 0xffffffff - u, u + 0x80000000)
+
+
+def host_lists(S, sink, k_sel):
+    """Mask of one head by a stable sort of the keys (first of equal keys: the lower column)."""
+    cand = np.ones(S.shape[1], dtype=bool)
+    cand[sink[0]:sink[1]] = False
+    cols = np.flatnonzero(cand)
+    M = np.zeros(S.shape, dtype=bool)
+    M[:, sink[0]:sink[1]] = True
+    order = np.argsort(-order_key(S[:, cols]), axis=1, kind="stable")[:, :k_sel]
+    np.put_along_axis(M, cols[order], True, axis=1)
+    return M
+
+
+def predict(plan, qbar, kbar):
+    i, c = plan.info, plan.cfg
+    idx = torch.full((c.batch, c.heads, i.n_blocks, i.k_row), -1, dtype=torch.int32, device=DEV)
+    cnt = torch.full((c.batch, c.heads, i.n_blocks), -1, dtype=torch.int32, device=DEV)
+    S = torch.full((c.batch, c.heads, i.n_blocks, i.n_blocks_k), -7.0, device=DEV)
+    mask = torch.full(S.shape, 9, dtype=torch.uint8, device=DEV)
+    plan.rf2_predict_mask(qbar, kbar, idx, cnt, mask, S)
+    torch.cuda.synchronize()
+    return [x[0].cpu().numpy() for x in (idx, cnt, S, mask)]
+
+
+def means(plan, kind, seed):
+    i, c = plan.info, plan.cfg
+    g = torch.Generator().manual_seed(seed)
+    out = [torch.randn(c.batch, c.heads, n, c.head_dim, generator=g) for n in (i.n_blocks, i.n_blocks_k)]
+    if kind == "ties":                      # a few distinct scores: most boundaries fall among equal ones
+        out = [x.sign() * (torch.arange(c.head_dim) < 3) for x in out]
+    if kind == "equal":                     # one score in all columns
+        out = [torch.zeros_like(x) for x in out]
+    if kind == "special":                   # infinities, NaN, huge and tiny scores among ordinary ones
+        for n, v in enumerate((float("inf"), float("nan"), -float("inf"), 1e30, -1e30, 1e-38)):
+            out[1][..., n::11, :] = v
+    return [x.to(DEV) for x in out]
+
+
+# (tokens, block, block_k, heads, sink frames of one block each, head_dim): row widths around the steps of the kernel's
+# instances (64 columns a lane), strips of one row and of 16 + 1, few workgroups (16 wavefronts) and many (8)
+SHAPES = [(64, 64, 64, 1, 0, 64), (15 * 64, 64, 64, 2, 0, 128), (16 * 64 + 1, 64, 64, 3, 1, 64),
+          (17 * 64, 64, 64, 150, 1, 64), (64 * 64, 64, 64, 2, 0, 128), (65 * 64, 64, 64, 66, 2, 128), (128 * 64 + 5, 64, 64, 2, 1, 64),
+          (129 * 64, 128, 64, 1, 3, 128), (385 * 64, 256, 64, 1, 1, 64), (513 * 64, 64, 128, 9, 1, 64), (640 * 64, 256, 64, 1, 0, 128),
+          (641 * 64, 256, 64, 2, 1, 64), (1025 * 64, 256, 64, 1, 1, 128), (1281 * 64, 256, 64, 1, 1, 64),
+          (1537 * 64, 256, 64, 17, 1, 128), (2048 * 64, 256, 64, 1, 2, 64)]
+
+
+def make(shape, **over):
+    tokens, block, block_k, heads, sink, d = shape
+    frames = max(sink + 1, 2) if sink else 1
+    kw = dict(batch=1, heads=heads, head_dim=d, T=frames, H=1, W=tokens if not sink else 64, block=block, block_k=block_k,
+              sparsity=0.7, sink_frames=sink, window=(1, 1, 8))
+    if sink:                                # frames of 64 tokens, the rest as many frames as it takes
+        kw["T"] = max(sink + 1, tokens // 64)
+    kw.update(over)
+    return rf2.Plan(**kw)
+
+
+@pytest.mark.parametrize("kind", ["random", "ties", "equal", "special"])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_top_n_lists(shape, kind):
+    plan = make(shape)
+    i = plan.info
+    idx, cnt, S, mask = predict(plan, *means(plan, kind, 3))
+    sink_rows = slice(i.sink_block_begin, i.sink_block_end)
+    for h in range(plan.cfg.heads):
+        want = host_lists(S[h], (i.sink_block_begin_k, i.sink_block_end_k), i.k_sel)
+        want[sink_rows] = True
+        assert np.array_equal(mask[h].astype(bool), want) and mask[h].max() <= 1
+        plain = np.ones(i.n_blocks, dtype=bool)
+        plain[sink_rows] = False
+        assert (cnt[h][plain] == i.k_row).all() and (cnt[h][~plain] == i.n_blocks_k).all()
+        rows, cols = np.nonzero(want[plain])
+        assert np.array_equal(idx[h][plain], cols.reshape(-1, i.k_row))
+        assert (idx[h][~plain] == np.arange(i.k_row)).all()
+    plan.close()
+
+
+@pytest.mark.parametrize("kind", ["random", "ties", "equal", "special"])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_cumulative_mass_lists(shape, kind):
+    """The kept candidates are the shortest prefix of the descending order that reaches tau, cut at most where the mass
+    in 64 bits is within 2e-5 of it (fp32 sums of up to 2,048 terms); a row without finite sums is kept whole."""
+    tau = 0.8
+    plan = make(shape, cdf_threshold=tau)
+    i = plan.info
+    idx, cnt, S, mask = predict(plan, *means(plan, kind, 4))
+    cand = np.ones(i.n_blocks_k, dtype=bool)
+    cand[i.sink_block_begin_k:i.sink_block_end_k] = False
+    cols = np.flatnonzero(cand)
+    for h in range(plan.cfg.heads):
+        M = mask[h].astype(bool)
+        assert M[:, ~cand].all() and np.array_equal(cnt[h], M.sum(1))
+        for r in range(i.n_blocks):
+            assert np.array_equal(idx[h, r, :cnt[h, r]], np.flatnonzero(M[r]))
+            if i.sink_block_begin <= r < i.sink_block_end or not cols.size:
+                assert M[r].all()
+                continue
+            s = S[h, r, cols].astype(np.float64)
+            order = np.argsort(-order_key(S[h, r, cols]), kind="stable")
+            n = int(M[r, cols].sum())
+            assert n >= 1 and M[r, cols[order[:n]]].all(), "not a prefix of the descending order"
+            with np.errstate(invalid="ignore"):
+                p = np.exp((s - s.max()) / np.sqrt(plan.cfg.head_dim))[order]
+            if not np.isfinite(p.sum()):
+                assert n == cols.size
+                continue
+            c = np.cumsum(p) / p.sum()
+            assert c[n - 1] >= tau - 2e-5 and (n == 1 or c[n - 2] <= tau + 2e-5)
+    plan.close()
