@@ -1,10 +1,13 @@
 // Block-sparse flash attention (Sec. 3.1, eqs. 1-4 with the block skip rule) for gfx950.
 //
-// One workgroup owns one Q block (b_q rows) of one (batch, head) and walks that row's list of
-// kept K/V blocks (b_k rows each; b_q and b_k may differ).  Every wavefront owns 32 query rows
-// and sees all keys, so there is nothing to merge at the end; a workgroup needs at most 80 KiB of
-// LDS and 256 registers per lane, so two workgroups share a compute unit (two wavefronts per
+// One workgroup owns one Q block (b_q rows, or 128 of 256) of one (batch, head) and walks that row's
+// list of kept K/V blocks (b_k rows each; b_q and b_k may differ).  Every wavefront owns 32 query rows
+// and sees all keys of the list, so there is nothing to merge at the end; a workgroup needs at most 80 KiB
+// of LDS and 256 registers per lane, so two workgroups share a compute unit (two wavefronts per
 // SIMD) and each hides the barriers, LDS latencies and vector-ALU phases of the other.
+// Launches that would leave compute units idle or wait for a few long lists instead give a list to KS such
+// groups of wavefronts, each with a contiguous share of it and with rings of its own, which merge their
+// results through LDS (attn_cut has the rule and the measurements).
 //
 // Both products are computed transposed so that no register shuffling is needed between them
 // (v_mfma_f32_32x32x16_bf16, D = A(32xk) * B(kx32) + C):
@@ -39,10 +42,11 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 // BQ rows per Q block (one workgroup), BK rows per K/V block (Sec. 3.1: b_q and b_k).
-template <int D, int BQ, int BK>
+// KS groups of NW wavefronts walk a contiguous share of the row's list each and merge at the end.
+template <int D, int BQ, int BK, int KS>
 struct AttnCfg {
   static constexpr int NW = BQ / 32;            // wavefronts, 32 query rows each
-  static constexpr int NT = NW * 64;
+  static constexpr int NT = NW * 64;            // threads of a group
   static constexpr int KH = BK / 2;             // K block rows r and r + KH share a part (see rf2.h)
   static constexpr int PB = BK / 64;            // 64-key parts per K/V block
   static constexpr int UB = BK / 32;            // 32-key units per K/V block
@@ -52,6 +56,9 @@ struct AttnCfg {
   static constexpr int PART_BYTES = 64 * D * 2;
   static constexpr int LPW = PART_BYTES / 1024 / NW;   // 1 KiB direct-to-LDS loads per wavefront per part
   static constexpr int NK = 3, NV = 2;                 // ring depths in parts
+  static constexpr int RING_BYTES = (NK + NV) * PART_BYTES;   // per group
+  // the merge passes a group's accumulators and row statistics through its rings
+  static_assert(KS == 1 || NW * (DT * 4096 + 256) <= RING_BYTES, "merge buffer");
   static_assert(LPW >= 1 && 2 * LPW < 63, "vmcnt range");
 };
 
@@ -130,22 +137,23 @@ __device__ __forceinline__ void ring_barrier() {
   asm volatile("" ::: "memory");
 }
 
-// (second launch bound: wavefronts per SIMD the register budget is sized for; a 64-row Q block has only
-// two wavefronts per workgroup, which LDS limits to one per SIMD anyway; a 256-row Q block is one
-// workgroup of eight wavefronts per compute unit)
-template <int D, int BQ, int BK>
-__global__ void __launch_bounds__(BQ * 2, BQ >= 128 ? 2 : 1) block_sparse_attn_kernel(
+// (second launch bound: wavefronts per SIMD the register budget is sized for, which is what LDS admits: two
+// workgroups of 80 KiB rings per compute unit at d = 128, four of 40 KiB at d = 64, whatever KS; a 64-row Q block has
+// two wavefronts per group; a 256-row Q block of d = 128 is one workgroup of eight wavefronts per compute unit)
+template <int D, int BQ, int BK, int KS>
+__global__ void __launch_bounds__(BQ * 2 * KS, D == 64 ? (BQ == 128 ? 4 : 2) : (BQ >= 128 ? 2 : 1)) block_sparse_attn_kernel(
     const __bf16* __restrict__ qp, const __bf16* __restrict__ kp, const __bf16* __restrict__ vp,
     const int32_t* __restrict__ blk_idx, const int32_t* __restrict__ blk_cnt, __bf16* __restrict__ op,
     float* __restrict__ lse, const int32_t* __restrict__ row_order, int plain_per_xcd, int n_bh, int sink_row_begin,
     int n_sink_rows, int sink_slots,
     int Tq, int Tb, int k_row, int last_valid, float scale_log2, const int32_t* __restrict__ scatter, int n_tokens,
-    int heads, rf2_strides st) {
-  // Tq: Q blocks per head (rows of the block mask); Tb: K/V blocks per head (its columns); last_valid:
+    int heads, rf2_strides st, int split) {
+  // split: log2 of the workgroups that share a list (a Q block of the mask has BQ << split rows); they are neighbours
+  // on one XCD.  Tq: Q blocks per head (rows of the block mask); Tb: K/V blocks per head (its columns); last_valid:
   // tokens in the last K/V block.
-  using C = AttnCfg<D, BQ, BK>;
+  using C = AttnCfg<D, BQ, BK, KS>;
   // Part P lives in slot P % NK of the K ring (first) and slot P % NV of the V^T ring (behind it).
-  __shared__ __attribute__((aligned(1024))) unsigned char ring[(C::NK + C::NV) * C::PART_BYTES];
+  __shared__ __attribute__((aligned(1024))) unsigned char ring[KS * C::RING_BYTES];
   constexpr uint32_t VRING = C::NK * C::PART_BYTES;
 
   // ---- which Q block ---------------------------------------------------------------
@@ -153,7 +161,7 @@ __global__ void __launch_bounds__(BQ * 2, BQ >= 128 ? 2 : 1) block_sparse_attn_k
   // rows head by head.  A sink row is several times longer than an ordinary one; issued first (longest
   // jobs first) none of them is left running alone at the end, and the short rows fill the tail evenly.
   // (workgroups with equal blockIdx % 8 share an XCD; which of the eight it is varies from launch to launch)
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int xcd = blockIdx.x & 7, share = (int)(blockIdx.x >> 3) & ((1 << split) - 1), slot = (int)(blockIdx.x >> 3) >> split;
   int bh, qi;
   if (slot < sink_slots) {
     // The sink rows of all heads, numbered head by head, are cut into 8 contiguous runs of sink_slots
@@ -178,23 +186,28 @@ __global__ void __launch_bounds__(BQ * 2, BQ >= 128 ? 2 : 1) block_sparse_attn_k
   const bool dense = (cnt == Tb);
   cnt = dense ? Tb : min(max(cnt, 0), k_row);
   const int32_t* __restrict__ list = blk_idx + row_id * k_row;
-  const int U = cnt * C::UB;                            // 32-key units to process (even)
   const int NPARTS = cnt * C::PB;
+  // group `grp` walks the parts from P0 on.  Every group takes as many steps (they meet at the barriers); the units
+  // past the end of the list count as masked keys.
+  const int grp = KS > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / C::NT) : 0;
+  const int parts = (NPARTS + KS - 1) / KS, P0 = grp * parts;
+  const int U = 2 * parts;                              // 32-key units to process (even)
 
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int tid = KS > 1 ? (int)threadIdx.x % C::NT : (int)threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wavefront-uniform, kept in a scalar register
   const uint32_t tid16 = (uint32_t)tid * 16u;
   const int l32 = lane & 31, lh = lane >> 5;
-  const size_t q_head_off = (size_t)bh * Tq * BQ * D;   // elements; qp and op
+  const size_t q_head_off = (size_t)bh * (Tq << split) * BQ * D;   // elements; qp and op
+  const int q_row = ((qi << split) + share) * BQ + 32 * wave + l32;   // this lane's query row in its head
   const size_t k_head_off = (size_t)bh * Tb * BK * D;   // kp and vp
   const unsigned char* const kbase = uniform_ptr(kp + k_head_off);
   const unsigned char* const vbase = uniform_ptr(vp + k_head_off);
   // LDS byte offsets of this lane's first operand chunk inside a K part / a V^T part, for the
   // first 32-key tile of the part; the second tile lies K_TILE / V_TILE bytes further.
-  const uint32_t k_lane = (uint32_t)((lh * 64 + l32) * 16);
-  const uint32_t v_lane = (uint32_t)((lh * D + l32) * 16);
+  const uint32_t k_lane = (uint32_t)(grp * C::RING_BYTES + (lh * 64 + l32) * 16);
+  const uint32_t v_lane = (uint32_t)(grp * C::RING_BYTES + (lh * D + l32) * 16);
   constexpr uint32_t K_TILE = 32 * 16, V_TILE = 4 * D * 16;
-  // Part P of the walk is part P % PB of listed block P / PB (P clamped: loads past the end
+  // Part P of the list is part P % PB of listed block P / PB (P clamped: loads past the end
   // re-fetch the last part into a free slot, which keeps the outstanding-load count uniform).
   // A list entry is read one odd step before it is needed (list_entry) and turned into an offset
   // only when it is used (part_off), so that no step waits for a scalar memory load.
@@ -207,14 +220,17 @@ __global__ void __launch_bounds__(BQ * 2, BQ >= 128 ? 2 : 1) block_sparse_attn_k
     const int j = min(max(entry, 0), Tb - 1);            // a corrupt list can give wrong results, never a fault
     return (uint32_t)j * (uint32_t)C::TILE_BYTES + ((unsigned)min(P, NPARTS - 1) % (unsigned)C::PB) * (uint32_t)C::PART_BYTES;
   };
-  auto part_at = [&](int P) { return (size_t)part_off(list_entry(P), P); };
-  const uint32_t ring_lds = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char*)ring;
+  auto part_at = [&](int P) { return (size_t)part_off(list_entry(P0 + P), P0 + P); };
+  unsigned char* const gring = ring + grp * C::RING_BYTES;
+  const uint32_t ring_lds = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char*)gring;
   // Only the last listed block can be the ragged last block of the sequence (lists ascend).
   int partial_begin = U;
   if (U > 0 && last_valid < BK) {
     const int jl = dense ? cnt - 1 : list[cnt - 1];
-    if (min(max(jl, 0), Tb - 1) == Tb - 1) partial_begin = (cnt - 1) * C::UB;
+    if (min(max(jl, 0), Tb - 1) == Tb - 1) partial_begin = max((cnt - 1) * C::UB - 2 * P0, 0);
   }
+  const int u_real = max(min(2 * (NPARTS - P0), U), 0);   // units of this group that exist
+  if (KS > 1) partial_begin = min(partial_begin, u_real);
 
   bf16x8 qf[C::DS];
   f32x16 o[C::DT];
@@ -299,14 +315,16 @@ __global__ void __launch_bounds__(BQ * 2, BQ >= 128 ? 2 : 1) block_sparse_attn_k
 #pragma unroll
         for (int e = 0; e < 8; ++e) Pprev[ks][e] = (__bf16)0.f;
       if (s >= partial_begin) {
-        const int t = s & 1, p = (s >> 1) % C::PB;
+        const int t = s & 1, p = (P0 + (s >> 1)) % C::PB;
+        const int valid = KS > 1 && s >= u_real ? 0 : last_valid;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
           const int key = t * C::KH + 32 * p + 8 * (i / 4) + 4 * lh + (i % 4);
-          if (key >= last_valid) S[i] = -INFINITY;
+          if (key >= valid) S[i] = -INFINITY;
         }
       }
-      const float mx = rowmax(S);
+      // (a group without any part of its own has no valid key: its reference is a number all the same)
+      const float mx = KS > 1 ? fmaxf(rowmax(S), -1e30f) : rowmax(S);
       // first unit: exact reference (it has at least one valid key); later: only upwards
       const bool move = (s == 0) ? true : (mx > m_ref);
       if (__builtin_amdgcn_ballot_w64(move) != 0ull) {
@@ -345,8 +363,8 @@ __global__ void __launch_bounds__(BQ * 2, BQ >= 128 ? 2 : 1) block_sparse_attn_k
       const int P = s >> 1;
       k_dst = ring_lds + (uint32_t)(kfree * C::PART_BYTES + wave * 1024);
       v_dst = ring_lds + VRING + (uint32_t)(vfree * C::PART_BYTES + wave * 1024);
-      k_voff = tid16 + part_off(entry_k, P + C::NK);
-      v_voff = tid16 + part_off(entry_v, P + C::NV - 1);
+      k_voff = tid16 + part_off(entry_k, P0 + P + C::NK);
+      v_voff = tid16 + part_off(entry_v, P0 + P + C::NV - 1);
     }
     // the entries fetched by the previous odd step are consumed before the next fetches are issued:
     // scalar loads return out of order, so a wait for the old ones would also wait for new ones
@@ -357,8 +375,8 @@ __global__ void __launch_bounds__(BQ * 2, BQ >= 128 ? 2 : 1) block_sparse_attn_k
     for (int g = 0; g < PD; ++g) opnd[g] = operand(k_addr, v_addr, g);
     if constexpr (ODD) {
       const int P = s >> 1;
-      entry_k = list_entry(P + 1 + C::NK);   // for the next odd step
-      entry_v = list_entry(P + C::NV);
+      entry_k = list_entry(P0 + P + 1 + C::NK);   // for the next odd step
+      entry_v = list_entry(P0 + P + C::NV);
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -416,14 +434,14 @@ __global__ void __launch_bounds__(BQ * 2, BQ >= 128 ? 2 : 1) block_sparse_attn_k
     // (at raised priority: a row that starts has nothing to compute on until its first parts arrive; +0.3 %)
     __builtin_amdgcn_s_setprio(3);
 #pragma unroll
-    for (int P = 0; P < C::NK; ++P) dma_part<C::NW, C::LPW>(ring + P * C::PART_BYTES, kbase + part_at(P), wave, tid16);
+    for (int P = 0; P < C::NK; ++P) dma_part<C::NW, C::LPW>(gring + P * C::PART_BYTES, kbase + part_at(P), wave, tid16);
 #pragma unroll
     for (int P = 0; P < C::NV - 1; ++P)
-      dma_part<C::NW, C::LPW>(ring + VRING + P * C::PART_BYTES, vbase + part_at(P), wave, tid16);
+      dma_part<C::NW, C::LPW>(gring + VRING + P * C::PART_BYTES, vbase + part_at(P), wave, tid16);
     // the slot of "part -1" (read by step 0 with zero probabilities) gets finite data
-    dma_part<C::NW, C::LPW>(ring + VRING + (C::NV - 1) * C::PART_BYTES, vbase + part_at(0), wave, tid16);
+    dma_part<C::NW, C::LPW>(gring + VRING + (C::NV - 1) * C::PART_BYTES, vbase + part_at(0), wave, tid16);
     {
-      const __bf16* qrow = qp + q_head_off + ((size_t)qi * BQ + 32 * wave + l32) * D + 8 * lh;
+      const __bf16* qrow = qp + q_head_off + (size_t)q_row * D + 8 * lh;
 #pragma unroll
       for (int ds = 0; ds < C::DS; ++ds) qf[ds] = *reinterpret_cast<const bf16x8*>(qrow + 16 * ds);
     }
@@ -443,8 +461,8 @@ __global__ void __launch_bounds__(BQ * 2, BQ >= 128 ? 2 : 1) block_sparse_attn_k
       for (int e = 0; e < 8; ++e) Pb[ks][e] = (__bf16)0.f;   // "P_{-1}": step 0 adds V * 0
 #pragma unroll
     for (int i = 0; i < 16; ++i) Sb[i] = 0.f;
-    entry_k = list_entry(C::NK);
-    entry_v = list_entry(C::NV - 1);
+    entry_k = list_entry(P0 + C::NK);
+    entry_v = list_entry(P0 + C::NV - 1);
 
     __builtin_amdgcn_s_setprio(0);
     // ---- steady state: two steps per part ---------------------------------------------------
@@ -476,9 +494,57 @@ __global__ void __launch_bounds__(BQ * 2, BQ >= 128 ? 2 : 1) block_sparse_attn_k
 
   // ---- normalise (the final division of eq. 4) and write the 32 rows of this wavefront ----------
   const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
-  const float l_tot = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+  float l_tot = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+  // ---- merge of the groups: group dt * KS / DT finishes channel tile dt ---------------------------
+  // Every group leaves the tiles it does not finish and its row statistics in its own rings (free once all
+  // wavefronts have passed the barrier) and rescales what it reads to the largest reference of the row.
+  auto finishes = [&](int dt) { return KS == 1 || grp == dt * KS / C::DT; };
+  if constexpr (KS > 1) {
+    float4* const tiles = reinterpret_cast<float4*>(gring) + wave * C::DT * 256 + lane;
+    float2* const stats = reinterpret_cast<float2*>(gring + C::NW * C::DT * 4096) + wave * 32 + l32;
+    __syncthreads();
+#pragma unroll
+    for (int dt = 0; dt < C::DT; ++dt)
+      if (!finishes(dt))
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          tiles[(dt * 4 + g) * 64] = make_float4(o[dt][4 * g], o[dt][4 * g + 1], o[dt][4 * g + 2], o[dt][4 * g + 3]);
+    if (lh == 0) *stats = make_float2(m_ref, l_tot);
+    __syncthreads();
+    float m_all = m_ref;
+    float2 st_of[KS];
+#pragma unroll
+    for (int k = 0; k < KS; ++k) {
+      st_of[k] = *reinterpret_cast<const float2*>(reinterpret_cast<const unsigned char*>(stats) + (k - grp) * C::RING_BYTES);
+      m_all = fmaxf(m_all, st_of[k].x);
+    }
+    const float own = __builtin_amdgcn_exp2f((m_ref - m_all) * scale_log2);
+    l_tot = 0.f;
+#pragma unroll
+    for (int dt = 0; dt < C::DT; ++dt)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) o[dt][i] *= own;
+#pragma unroll
+    for (int k = 0; k < KS; ++k) {
+      const float w = __builtin_amdgcn_exp2f((st_of[k].x - m_all) * scale_log2);
+      l_tot = fmaf(st_of[k].y, w, l_tot);
+      const float4* const from = reinterpret_cast<const float4*>(reinterpret_cast<const unsigned char*>(tiles) + (k - grp) * C::RING_BYTES);
+#pragma unroll
+      for (int dt = 0; dt < C::DT; ++dt)
+        if (k != grp && finishes(dt))
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            const float4 x = from[(dt * 4 + g) * 64];
+            o[dt][4 * g] = fmaf(x.x, w, o[dt][4 * g]);
+            o[dt][4 * g + 1] = fmaf(x.y, w, o[dt][4 * g + 1]);
+            o[dt][4 * g + 2] = fmaf(x.z, w, o[dt][4 * g + 2]);
+            o[dt][4 * g + 3] = fmaf(x.w, w, o[dt][4 * g + 3]);
+          }
+    }
+    m_ref = m_all;
+  }
   const float f = l_tot > 0.f ? 1.0f / l_tot : 0.f;      // a row with no kept key yields zeros
-  const size_t row = (size_t)qi * BQ + 32 * wave + l32;
+  const size_t row = (size_t)q_row;
   // plain output: row `row` of the permuted layout; fused inverse permutation: the token's raster row
   const int target = scatter ? scatter[row] : (int)row;
   if (target < 0) return;                                 // padding row of the last block
@@ -486,52 +552,101 @@ __global__ void __launch_bounds__(BQ * 2, BQ >= 128 ? 2 : 1) block_sparse_attn_k
                          : op + q_head_off + row * D;
 #pragma unroll
   for (int dt = 0; dt < C::DT; ++dt)
+    if (finishes(dt))
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      bf16x4 pk;
+      for (int g = 0; g < 4; ++g) {
+        bf16x4 pk;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) pk[e] = (__bf16)(o[dt][4 * g + e] * f);
-      *reinterpret_cast<bf16x4*>(orow + 32 * dt + 8 * g + 4 * lh) = pk;
-    }
-  if (lse != nullptr && lh == 0)
-    lse[scatter ? (size_t)bh * n_tokens + target : (size_t)bh * Tq * BQ + row] =
+        for (int e = 0; e < 4; ++e) pk[e] = (__bf16)(o[dt][4 * g + e] * f);
+        *reinterpret_cast<bf16x4*>(orow + 32 * dt + 8 * g + 4 * lh) = pk;
+      }
+  if (lse != nullptr && lh == 0 && grp == 0)
+    lse[scatter ? (size_t)bh * n_tokens + target : (size_t)bh * (Tq << split) * BQ + row] =
         m_ref * scale_log2 * 0.6931471805599453f + __logf(l_tot);
 }
 
-template <int D, int BQ, int BK>
+template <int D, int BQ, int BK, int KS>
 int launch_attn(const rf2_plan* plan, const void* qp, const void* kp, const void* vp, const int32_t* blk_idx,
                 const int32_t* blk_cnt, void* op, float* lse, bool scatter, hipStream_t st) {
-  using C = AttnCfg<D, BQ, BK>;
+  using C = AttnCfg<D, BQ, BK, KS>;
   const rf2_config& c = plan->cfg;
   const rf2_info& in = plan->info;
   const float scale_log2 = (float)(1.4426950408889634 / sqrt((double)D));
   const int n_bh = c.batch * c.heads;
+  const int split = c.block > BQ ? 1 : 0;
   // slots of an XCD: its run of the sink rows of all heads, then plain_per_xcd ordinary rows of every head
   const int n_sink_rows = in.sink_block_end - in.sink_block_begin;
   const int sink_slots = (int)(((int64_t)n_bh * n_sink_rows + 7) / 8);
-  const unsigned grid = 8u * ((unsigned)sink_slots + (unsigned)n_bh * (unsigned)plan->plain_per_xcd);
+  const unsigned grid = (8u * ((unsigned)sink_slots + (unsigned)n_bh * (unsigned)plan->plain_per_xcd)) << split;
   if (grid == 0) return RF2_OK;
-  block_sparse_attn_kernel<D, BQ, BK><<<dim3(grid), dim3(C::NT), 0, st>>>(
+  block_sparse_attn_kernel<D, BQ, BK, KS><<<dim3(grid), dim3(C::NT * KS), 0, st>>>(
       (const __bf16*)qp, (const __bf16*)kp, (const __bf16*)vp, blk_idx, blk_cnt, (__bf16*)op, lse, plan->d_row_order,
       plan->plain_per_xcd, n_bh, in.sink_block_begin, n_sink_rows, sink_slots, in.n_blocks, in.n_blocks_k, in.k_row, in.last_block_valid_k,
-      scale_log2, scatter ? plan->d_perm : nullptr, (int)in.N, c.heads, rf2_qkv_strides(plan));
+      scale_log2, scatter ? plan->d_perm : nullptr, (int)in.N, c.heads, rf2_qkv_strides(plan), split);
   RF2_LAUNCH_CHECK();
   return RF2_OK;
+}
+
+// How a launch is cut, from the sizes of the plan alone (so that both exits of a layer give the same bits).
+// A row of the mask is one workgroup of KS groups of wavefronts that share its list (KS = 1: no merge); a Q block
+// of 256 rows is one workgroup of eight wavefronts or two of 128 rows.
+// jobs = the launch's work in units of its longest list: with jobs <= 256 and KS = 1 compute units stand idle, or wait
+// for the all-column sink rows of a few heads.  Groups shorten the longest list and cost a merge and a common barrier.
+// Measured, KS = 1 -> 2 (us), 480p layer (rows of 40, sink rows of 256 blocks), d = 128: 1 head (51 jobs) 469 -> 332,
+// 4 heads (204) 580 -> 448, 6 heads (306) 687 -> 616, 8 heads (408) 797 -> 832, 20 heads 1,919 -> 2,060; 64-row blocks,
+// 2 heads (206) 461 -> 309, 4 heads (412) 518 -> 555.  Equal rows (3,072-token image, 24 rows of 10 blocks), d = 128:
+// 192 jobs 25.0 -> 24.5, 288 jobs 35.2 -> 46.0.
+// d = 64 holds twice the workgroups: 480p, 306 jobs 483 -> 374, 408 jobs 543 -> 480, 510 jobs 613 -> 602, 714 jobs 792 ->
+// 817; 64-row blocks, equal rows, 384 jobs 24.0 -> 18.7, 576 jobs 25.4 -> 27.6; equal 128-row blocks 288 jobs 23.7 -> 24.2.
+// KS = 4 against 2: 480p, 51 jobs 250 -> 204, 204 jobs 313 -> 288; 64-row blocks 180 -> 133; but rows of 20 parts, 128-row
+// blocks 14.5 -> 17.2.
+// 256-row blocks, one workgroup -> two (us): d = 128, 512 workgroups 683 -> 586 (KS = 2: 452), 760: 576 -> 516, 480 of equal
+// length 101 -> 92, 1,024: 813 -> 827, 5,120: 3,830 -> 3,914 (the larger one reads K and V less often); d = 64,
+// 1,024: 597 -> 534, 1,280: 641 -> 607, 2,560: 1,115 -> 1,128.
+struct AttnCut {
+  int groups;
+  bool halves;      // a 256-row Q block as two workgroups
+};
+AttnCut attn_cut(const rf2_plan* plan) {
+  const rf2_info& in = plan->info;
+  const rf2_config& c = plan->cfg;
+  const int64_t lists = (int64_t)c.batch * c.heads, rows = lists * in.n_blocks;
+  const bool d64 = c.head_dim == 64;
+  AttnCut cut{1, c.block == 256};
+  const int64_t wgs = rows * (c.block == 256 ? 2 : 1);
+  const int64_t longest = in.sink_block_end > in.sink_block_begin ? in.n_blocks_k : in.k_row;
+  // (cumulative mass: the lengths are not known, taken as equal)
+  const int64_t jobs = in.kept_pairs_per_head < 0 ? wgs : (c.block == 256 ? 2 : 1) * lists * in.kept_pairs_per_head / longest;
+  const bool unequal = wgs >= 2 * jobs;
+  if (d64) {
+    if (jobs <= 512 && (jobs <= 256 || unequal || c.block == 64)) cut.groups = 2;
+    if (jobs <= 256 && (c.block == 64 || longest * (in.block_k / 64) >= 64)) cut.groups = 4;
+  } else if (jobs <= (unequal ? 320 : 256)) {
+    cut.groups = 2;
+  }
+  if (c.block == 256 && cut.groups == 1) cut.halves = rows < (d64 ? 2048 : 1024);
+  return cut;
+}
+
+template <int D, int BK>
+int dispatch_rows(const rf2_plan* plan, const void* qp, const void* kp, const void* vp, const int32_t* blk_idx,
+                  const int32_t* blk_cnt, void* out, float* lse, bool scatter, hipStream_t st) {
+  const AttnCut cut = attn_cut(plan);
+#define RF2_ATTN_CASE(Q, KS) return launch_attn<D, Q, BK, KS>(plan, qp, kp, vp, blk_idx, blk_cnt, out, lse, scatter, st)
+  if (plan->cfg.block == 256 && !cut.halves) RF2_ATTN_CASE(256, 1);
+  if constexpr (D == 64)
+    if (cut.groups == 4) { if (plan->cfg.block == 64) RF2_ATTN_CASE(64, 4); RF2_ATTN_CASE(128, 4); }
+  if (cut.groups == 2) { if (plan->cfg.block == 64) RF2_ATTN_CASE(64, 2); RF2_ATTN_CASE(128, 2); }
+  if (plan->cfg.block == 64) RF2_ATTN_CASE(64, 1);
+  RF2_ATTN_CASE(128, 1);
+#undef RF2_ATTN_CASE
 }
 
 template <int D>
 int dispatch_blocks(const rf2_plan* plan, const void* qp, const void* kp, const void* vp, const int32_t* blk_idx,
                     const int32_t* blk_cnt, void* out, float* lse, bool scatter, hipStream_t st) {
-  const int bq = plan->cfg.block, bk = plan->info.block_k;
-#define RF2_ATTN_CASE(Q, K) \
-  if (bq == Q && bk == K) return launch_attn<D, Q, K>(plan, qp, kp, vp, blk_idx, blk_cnt, out, lse, scatter, st);
-  RF2_ATTN_CASE(128, 128)
-  RF2_ATTN_CASE(64, 64)
-  RF2_ATTN_CASE(128, 64)
-  RF2_ATTN_CASE(64, 128)
-  RF2_ATTN_CASE(256, 128)
-  RF2_ATTN_CASE(256, 64)
-#undef RF2_ATTN_CASE
+  if (plan->info.block_k == 128) return dispatch_rows<D, 128>(plan, qp, kp, vp, blk_idx, blk_cnt, out, lse, scatter, st);
+  if (plan->info.block_k == 64) return dispatch_rows<D, 64>(plan, qp, kp, vp, blk_idx, blk_cnt, out, lse, scatter, st);
   return RF2_ERR_UNSUPPORTED;
 }
 

@@ -1,0 +1,77 @@
+"""The attention kernel in each way a launch is cut (groups of wavefronts per list, halves of a 256-row Q block), on lists
+of every length from none to all columns: rows shorter than the number of groups, odd numbers of parts, a ragged last
+block, logits whose reference differs from group to group.  Reference: masked softmax attention in 64 bits."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2512_24086_amd import rf2
+from tests import helpers as hp
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+# (tokens, block, block_k, head_dim, heads): few jobs = several groups, many = one (see attn_cut in rf2_attn.hip)
+SHAPES = [(1000, 128, 128, 128, 2), (1000, 128, 128, 128, 33), (1024, 128, 64, 128, 3), (999, 64, 64, 128, 2),
+          (999, 64, 128, 128, 17), (700, 64, 64, 64, 2), (700, 64, 128, 64, 3), (1000, 64, 64, 64, 20),
+          (1000, 128, 128, 64, 2), (6200, 128, 64, 64, 1), (6200, 128, 128, 64, 1), (1000, 256, 128, 128, 2),
+          (1000, 256, 64, 128, 41), (900, 256, 128, 64, 2), (900, 256, 64, 64, 70), (40, 64, 64, 64, 1), (130, 256, 128, 128, 1)]
+
+
+def lists(plan, seed):
+    """Masks [heads][Tq, Tk]: rows of 0, 1, 2, ... columns, of k_row, and of all."""
+    i, rng = plan.info, np.random.default_rng(seed)
+    out = []
+    for _ in range(plan.cfg.heads):
+        M = np.zeros((i.n_blocks, i.n_blocks_k), dtype=bool)
+        for r in range(i.n_blocks):
+            n = (r % 6 if r % 6 < 4 else i.k_row if r % 6 == 4 else i.n_blocks_k) if i.n_blocks > 2 else i.k_row
+            n = n if n == i.n_blocks_k else min(n, i.k_row)
+            M[r, rng.choice(i.n_blocks_k, n, replace=False)] = True
+        out.append(M)
+    return out
+
+
+@pytest.mark.parametrize("scale", [1.0, 24.0])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_lists_of_every_length(shape, scale):
+    tokens, block, block_k, d, heads = shape
+    print(f"[case] {shape} scale {scale}", flush=True)
+    plan = rf2.Plan(batch=1, heads=heads, head_dim=d, T=1, H=1, W=tokens, block=block, block_k=block_k, sparsity=0.3,
+                    window=(1, 1, 16))
+    i = plan.info
+    g = torch.Generator().manual_seed(7)
+    q, k, v = (torch.randn(1, heads, tokens, d, generator=g) for _ in range(3))
+    # later keys are larger: the softmax reference has to move, by other amounts in each group
+    k = k * torch.linspace(1.0, scale, tokens)[:, None]
+    q, k, v = (x.to(torch.bfloat16) for x in (q, k, v))
+    masks = lists(plan, 5)
+    idx, cnt = hp.lists_to_device(masks, i.k_row, i.n_blocks, DEV)
+    buf = plan.alloc(DEV, lse=True)
+    plan.rf2_permute(*(x.to(DEV) for x in (q, k, v)), buf["qp"], buf["kp"], buf["vp"])
+    buf["op"].fill_(float("nan"))
+    plan.rf2_block_sparse_attn(buf["qp"], buf["kp"], buf["vp"], idx, cnt, buf["op"], buf["lse"])
+    o = torch.full_like(buf["o"], float("nan"))
+    lse = torch.full((1, heads, tokens), float("nan"), device=DEV)
+    plan.rf2_block_sparse_attn_unpermuted(buf["qp"], buf["kp"], buf["vp"], idx, cnt, o, lse)
+    torch.cuda.synchronize()
+    perm = plan.rf2_plan_perm()[0]
+    assert torch.equal(o[:, :, perm].view(torch.int16), buf["op"][:, :, :tokens].view(torch.int16))
+    assert torch.equal(lse[:, :, perm], buf["lse"][:, :, :tokens])
+    for h in sorted({0, heads // 2, heads - 1}):
+        Q, K, V = (x[0, h][perm].double() for x in (q, k, v))
+        keep = torch.from_numpy(masks[h]).repeat_interleave(block, 0).repeat_interleave(block_k, 1)[:tokens, :tokens]
+        S = (Q @ K.T / d ** 0.5).masked_fill(~keep, -torch.inf)
+        empty = ~keep.any(1)
+        P = torch.softmax(S, 1).nan_to_num(0.0)     # a row without a block: zeros, lse = -inf
+        want = P @ V
+        err = (buf["op"][0, h, :tokens].cpu().double() - want).abs()
+        # probabilities and outputs rounded to bf16 (2^-8 each, relative), fp32 logits of up to ~1e3 (1e-3 at most)
+        assert (err <= 2.0 ** -8 * (P @ V.abs() + want.abs()) + 1e-3).all(), (h, err.max())
+        assert err.mean() <= hp.ATTN_MEAN_ABS, (h, err.mean())
+        got = buf["lse"][0, h, :tokens].cpu().double()
+        ref = torch.logsumexp(S, 1)
+        assert torch.equal(torch.isneginf(got), empty)
+        # fp32 logits and sums: 2e-3 as everywhere, and a few units in the last place of the largest logits
+        assert ((got - ref)[~empty].abs() <= 2e-3 + 1e-6 * ref[~empty].abs()).all()
+    plan.close()
