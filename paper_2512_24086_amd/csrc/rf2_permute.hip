@@ -1,6 +1,6 @@
 // Token permutation (Sec. 3.3 / 3.4) fused with block-mean pooling (Sec. 3.2, eqs. 5-6),
 // the key-major re-tiling of V for the attention kernel, and the inverse permutation.
-// All three kernels are pure HBM traffic: every row moves as 16-byte vectors, a group of
+// Both kernels are pure HBM traffic: every row moves as 16-byte vectors, a group of
 // d/8 neighbouring lanes moving one whole row.
 #include "rf2_internal.h"
 
@@ -11,7 +11,7 @@ typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 
 // Every row is read once and written once: non-temporal accesses keep the stream from displacing
 // other data in the caches on its way (measured on the 720p layer: loads alone -4 %, stores alone
-// +0.5 %, both -9 % of the time of the three kernels).
+// +0.5 %, both -9 % of the time).
 __device__ __forceinline__ uint4 ld_stream(const uint4* p) {
   const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
   return make_uint4(v.x, v.y, v.z, v.w);
@@ -30,14 +30,14 @@ __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w 
 // KH = BLK/2, the 16-byte chunk c of block row r lands in part (r % KH) / 32 at chunk slot
 // c*64 + (r / KH)*32 + r % 32 -- the order in which the attention kernel's matrix-core
 // operand reads walk it (a part holds one 32-key tile of each key half).
+template <int D>
+using pool_rows = float[256 / (D / 8)][D + 1];
 template <int D, int BLK, bool IS_K>
-__global__ void __launch_bounds__(256) permute_pool_kernel(
+__device__ __forceinline__ void permute_pool_block(
     const uint4* __restrict__ x, uint4* __restrict__ xp, float* __restrict__ mean, const int32_t* __restrict__ perm,
-    int N, int n_blocks, int last_valid, int heads, rf2_strides st) {
+    int n_blocks, int last_valid, int heads, const rf2_strides& st, int blk, int bh, pool_rows<D>& part) {
   constexpr int CH = D / 8;          // 16-byte chunks per row
   constexpr int RG = 256 / CH;       // rows moved per pass
-  const int blk = blockIdx.x;
-  const int bh = blockIdx.y;
   const uint4* __restrict__ src = x + ((bh / heads) * st.batch + (bh % heads) * st.head) * CH;
   uint4* __restrict__ dst = xp + ((size_t)bh * n_blocks + blk) * BLK * CH;
   // Q: CH neighbouring lanes move one row (row-major stores).  K: 8 neighbouring lanes move half a row
@@ -65,7 +65,6 @@ __global__ void __launch_bounds__(256) permute_pool_kernel(
     acc[6] += bf16_lo(v.w); acc[7] += bf16_hi(v.w);
   }
   if (mean == nullptr) return;
-  __shared__ float part[RG][D + 1];
 #pragma unroll
   for (int e = 0; e < 8; ++e) part[rg][c * 8 + e] = acc[e];
   __syncthreads();
@@ -88,16 +87,17 @@ __device__ __forceinline__ int rho(int r) { return (r & 3) | ((r & 4) << 1) | ((
 // g = (s / KH)*4 + (s % 32) / 8, element s % 8; the 16-byte chunk (part, g, ch) holds
 // channel ch of those 8 keys.  A part thus holds the block rows 32*part .. 32*part+31 and
 // KH + 32*part .. KH + 32*part + 31 (the reordering stays inside a 16-key group).
+template <int D>
+using v_rows = u16[64 * (D + 2)];
 template <int D, int BLK>
-__global__ void __launch_bounds__(256) permute_vtile_kernel(
-    const uint4* __restrict__ v, uint4* __restrict__ vp, const int32_t* __restrict__ perm, int N, int n_blocks,
-    int heads, rf2_strides st) {
+__device__ __forceinline__ void permute_vtile_part(
+    const uint4* __restrict__ v, uint4* __restrict__ vp, const int32_t* __restrict__ perm, int n_blocks, int heads,
+    const rf2_strides& st, int block_part, int bh, v_rows<D>& tile) {
   constexpr int CH = D / 8;
   constexpr int RG = 256 / CH;
   constexpr int PITCH = D + 2;       // u16 elements per LDS row: odd number of dwords
   constexpr int PB = BLK / 64, KH = BLK / 2;
-  __shared__ __attribute__((aligned(16))) u16 tile[64 * PITCH];
-  const int blk = blockIdx.x / PB, part = blockIdx.x % PB, bh = blockIdx.y;
+  const int blk = block_part / PB, part = block_part % PB;
   const uint4* __restrict__ src = v + ((bh / heads) * st.batch + (bh % heads) * st.head) * CH;
   const int c = threadIdx.x % CH, rg = threadIdx.x / CH;
 #pragma unroll
@@ -125,6 +125,38 @@ __global__ void __launch_bounds__(256) permute_vtile_kernel(
   }
 }
 
+// The three tensors in one launch: first the Q blocks of all heads, then the K blocks, then the V parts.
+// Bound by HBM (each byte is read once and written once) where there is enough of it, by the launch elsewhere.  One launch
+// against one for each tensor (us): 4,096 tokens x 24 heads 35.9 -> 27.9, x 2 heads 17.4 -> 8.6, 480p x 5 heads 51.9 ->
+// 44.8, x 40 344 -> 341 (5.9 TB/s), 720p x 40 784 -> 790; d = 64: 480p x 40 176 -> 168.  With the heads in the outer place
+// (Q, K, V of a head in turn) the streams of three tensors are mixed: 30.9, 8.6, 46.4, 342, 796 and 168 us.
+struct PermuteArgs {
+  const uint4 *q, *k, *v;
+  uint4 *qp, *kp, *vp;
+  float *qbar, *kbar;
+  const int32_t* perm;
+  uint32_t n_q, n_k, bh;            // Q and K blocks of a head, heads of all batches
+  int last_q, last_k, heads;
+  rf2_strides st;
+};
+template <int D, int BQ, int BK>
+__global__ void __launch_bounds__(256) permute_kernel(PermuteArgs a) {
+  __shared__ __attribute__((aligned(16))) union { pool_rows<D> sums; v_rows<D> tile; } lds;
+  uint32_t id = blockIdx.y * gridDim.x + blockIdx.x;
+  if (id < a.n_q * a.bh) {
+    permute_pool_block<D, BQ, false>(a.q, a.qp, a.qbar, a.perm, a.n_q, a.last_q, a.heads, a.st, id % a.n_q, id / a.n_q, lds.sums);
+    return;
+  }
+  id -= a.n_q * a.bh;
+  if (id < a.n_k * a.bh) {
+    permute_pool_block<D, BK, true>(a.k, a.kp, a.kbar, a.perm, a.n_k, a.last_k, a.heads, a.st, id % a.n_k, id / a.n_k, lds.sums);
+    return;
+  }
+  id -= a.n_k * a.bh;
+  const uint32_t parts = a.n_k * (BK / 64);
+  if (id < parts * a.bh) permute_vtile_part<D, BK>(a.v, a.vp, a.perm, a.n_k, a.heads, a.st, id % parts, id / parts, lds.tile);
+}
+
 // o[n] = op[inv[n]]: gathered reads, fully sequential writes.
 template <int D>
 __global__ void __launch_bounds__(256) unpermute_kernel(
@@ -148,45 +180,27 @@ __global__ void __launch_bounds__(256) unpermute_kernel(
 
 namespace {
 
-template <int D, int BQ>
-void launch_permute_q(const rf2_plan* plan, const void* q, void* qp, float* qbar, hipStream_t st) {
-  const rf2_info& in = plan->info;
-  const dim3 grid(in.n_blocks, plan->cfg.batch * plan->cfg.heads, 1);
-  permute_pool_kernel<D, BQ, false><<<grid, 256, 0, st>>>((const uint4*)q, (uint4*)qp, qbar, plan->d_perm, (int)in.N,
-                                                           in.n_blocks, in.last_block_valid, plan->cfg.heads,
-                                                           rf2_qkv_strides(plan));
-}
-
-template <int D, int BK>
-void launch_permute_kv(const rf2_plan* plan, const void* k, const void* v, void* kp, void* vp, float* kbar,
-                       hipStream_t st) {
-  const rf2_info& in = plan->info;
-  const dim3 grid(in.n_blocks_k, plan->cfg.batch * plan->cfg.heads, 1);
-  permute_pool_kernel<D, BK, true><<<grid, 256, 0, st>>>((const uint4*)k, (uint4*)kp, kbar, plan->d_perm, (int)in.N,
-                                                          in.n_blocks_k, in.last_block_valid_k, plan->cfg.heads,
-                                                          rf2_qkv_strides(plan));
-  const dim3 grid_v(in.n_blocks_k * (BK / 64), plan->cfg.batch * plan->cfg.heads, 1);   // one workgroup per 64-key part
-  permute_vtile_kernel<D, BK><<<grid_v, 256, 0, st>>>((const uint4*)v, (uint4*)vp, plan->d_perm, (int)in.N,
-                                                       in.n_blocks_k, plan->cfg.heads, rf2_qkv_strides(plan));
+template <int D, int BQ, int BK>
+int launch_permute(const PermuteArgs& a, hipStream_t st) {
+  // at most (2,048 + 2,048 + 4,096) x 65,535 workgroups, in rows of 4 Mi (a grid dimension holds fewer than 2^32 threads)
+  const uint32_t n = (a.n_q + a.n_k * (1 + BK / 64)) * a.bh, row = n < (1u << 22) ? n : 1u << 22;
+  permute_kernel<D, BQ, BK><<<dim3(row, (n + row - 1) / row), 256, 0, st>>>(a);
+  RF2_LAUNCH_CHECK();
+  return RF2_OK;
 }
 
 template <int D>
-int permute_for_dim(const rf2_plan* plan, const void* q, const void* k, const void* v, void* qp, void* kp, void* vp,
-                    float* qbar, float* kbar, hipStream_t st) {
-  switch (plan->cfg.block) {
-    case 64: launch_permute_q<D, 64>(plan, q, qp, qbar, st); break;
-    case 128: launch_permute_q<D, 128>(plan, q, qp, qbar, st); break;
-    case 256: launch_permute_q<D, 256>(plan, q, qp, qbar, st); break;
-    default: return RF2_ERR_UNSUPPORTED;
-  }
-  RF2_LAUNCH_CHECK();
-  switch (plan->info.block_k) {
-    case 64: launch_permute_kv<D, 64>(plan, k, v, kp, vp, kbar, st); break;
-    case 128: launch_permute_kv<D, 128>(plan, k, v, kp, vp, kbar, st); break;
-    default: return RF2_ERR_UNSUPPORTED;
-  }
-  RF2_LAUNCH_CHECK();
-  return RF2_OK;
+int permute_for_dim(const rf2_plan* plan, const PermuteArgs& a, hipStream_t st) {
+  const int bq = plan->cfg.block, bk = plan->info.block_k;
+#define RF2_PERMUTE_CASE(Q, K) if (bq == Q && bk == K) return launch_permute<D, Q, K>(a, st);
+  RF2_PERMUTE_CASE(64, 64)
+  RF2_PERMUTE_CASE(64, 128)
+  RF2_PERMUTE_CASE(128, 64)
+  RF2_PERMUTE_CASE(128, 128)
+  RF2_PERMUTE_CASE(256, 64)
+  RF2_PERMUTE_CASE(256, 128)
+#undef RF2_PERMUTE_CASE
+  return RF2_ERR_UNSUPPORTED;
 }
 
 }  // namespace
@@ -197,8 +211,13 @@ extern "C" int rf2_permute(const rf2_plan* plan, const void* q, const void* k, c
   if ((qbar == nullptr) != (kbar == nullptr)) return RF2_ERR_INVALID_ARG;
   if (const int rc = rf2_check_device(plan)) return rc;
   hipStream_t st = (hipStream_t)stream;
-  if (plan->cfg.head_dim == 128) return permute_for_dim<128>(plan, q, k, v, qp, kp, vp, qbar, kbar, st);
-  if (plan->cfg.head_dim == 64) return permute_for_dim<64>(plan, q, k, v, qp, kp, vp, qbar, kbar, st);
+  const rf2_info& in = plan->info;
+  const PermuteArgs a{(const uint4*)q, (const uint4*)k, (const uint4*)v, (uint4*)qp, (uint4*)kp, (uint4*)vp, qbar, kbar,
+                      plan->d_perm, (uint32_t)in.n_blocks, (uint32_t)in.n_blocks_k,
+                      (uint32_t)(plan->cfg.batch * plan->cfg.heads), in.last_block_valid, in.last_block_valid_k,
+                      plan->cfg.heads, rf2_qkv_strides(plan)};
+  if (plan->cfg.head_dim == 128) return permute_for_dim<128>(plan, a, st);
+  if (plan->cfg.head_dim == 64) return permute_for_dim<64>(plan, a, st);
   return RF2_ERR_UNSUPPORTED;
 }
 
