@@ -590,16 +590,20 @@ int launch_attn(const rf2_plan* plan, const void* qp, const void* kp, const void
 // How a launch is cut, from the sizes of the plan alone (so that both exits of a layer give the same bits).
 // A row of the mask is one workgroup of KS groups of wavefronts that share its list (KS = 1: no merge); a Q block
 // of 256 rows is one workgroup of eight wavefronts or two of 128 rows.
-// jobs = the launch's work in units of its longest list: with jobs <= 256 and KS = 1 compute units stand idle, or wait
-// for the all-column sink rows of a few heads.  Groups shorten the longest list and cost a merge and a common barrier.
+// jobs = the launch's work in units of its longest list.  With few jobs and KS = 1 compute units stand idle, or wait for
+// the all-column sink rows of a few heads; groups shorten the longest list, and cost a merge, a common barrier and
+// half of the workgroups a compute unit holds.  Where the rows are many and short beside the longest (a long tail: video
+// with a sink frame) the jobs decide, else how the workgroups themselves fill the compute units.
 // Measured, KS = 1 -> 2 (us), 480p layer (rows of 40, sink rows of 256 blocks), d = 128: 1 head (51 jobs) 469 -> 332,
 // 4 heads (204) 580 -> 448, 6 heads (306) 687 -> 616, 8 heads (408) 797 -> 832, 20 heads 1,919 -> 2,060; 64-row blocks,
 // 2 heads (206) 461 -> 309, 4 heads (412) 518 -> 555.  Equal rows (3,072-token image, 24 rows of 10 blocks), d = 128:
-// 192 jobs 25.0 -> 24.5, 288 jobs 35.2 -> 46.0.
+// 192 workgroups 25.0 -> 24.5, 288 35.2 -> 46.0.  Images with text (2 long rows of 20): 320 workgroups 49.6 -> 40.7,
+// 400 51.7 -> 58.0, 64-row blocks 312 43.0 -> 32.9, 468 45.4 -> 46.4.
 // d = 64 holds twice the workgroups: 480p, 306 jobs 483 -> 374, 408 jobs 543 -> 480, 510 jobs 613 -> 602, 714 jobs 792 ->
-// 817; 64-row blocks, equal rows, 384 jobs 24.0 -> 18.7, 576 jobs 25.4 -> 27.6; equal 128-row blocks 288 jobs 23.7 -> 24.2.
-// KS = 4 against 2: 480p, 51 jobs 250 -> 204, 204 jobs 313 -> 288; 64-row blocks 180 -> 133; but rows of 20 parts, 128-row
-// blocks 14.5 -> 17.2.
+// 817; equal rows, 64-row blocks, 384 workgroups 24.0 -> 18.7, 576 25.4 -> 27.6, 128-row blocks 192 18.2 -> 15.8, 288 23.7 ->
+// 24.2; with text, 64-row blocks, 300 jobs 33.2 -> 31.1, 360 34.9 -> 35.6.
+// KS = 4 against 2 (us): 480p, 51 jobs 250 -> 204, 204 jobs 313 -> 288; 64-row blocks 180 -> 133; with text, 64-row blocks,
+// 264 workgroups 28.8 -> 26.0, 312 20.9 -> 24.5; but rows of 20 parts, 128-row blocks 14.5 -> 17.2.
 // 256-row blocks, one workgroup -> two (us): d = 128, 512 workgroups 683 -> 586 (KS = 2: 452), 760: 576 -> 516, 480 of equal
 // length 101 -> 92, 1,024: 813 -> 827, 5,120: 3,830 -> 3,914 (the larger one reads K and V less often); d = 64,
 // 1,024: 597 -> 534, 1,280: 641 -> 607, 2,560: 1,115 -> 1,128.
@@ -610,21 +614,20 @@ struct AttnCut {
 AttnCut attn_cut(const rf2_plan* plan) {
   const rf2_info& in = plan->info;
   const rf2_config& c = plan->cfg;
-  const int64_t lists = (int64_t)c.batch * c.heads, rows = lists * in.n_blocks;
-  const bool d64 = c.head_dim == 64;
+  const int64_t lists = (int64_t)c.batch * c.heads, rows = lists * in.n_blocks, share = c.block == 256 ? 2 : 1;
   AttnCut cut{1, c.block == 256};
-  const int64_t wgs = rows * (c.block == 256 ? 2 : 1);
-  const int64_t longest = in.sink_block_end > in.sink_block_begin ? in.n_blocks_k : in.k_row;
+  const int64_t wgs = rows * share, longest = in.sink_block_end > in.sink_block_begin ? in.n_blocks_k : in.k_row;
+  const int64_t longest_parts = longest * (in.block_k / 64);
   // (cumulative mass: the lengths are not known, taken as equal)
-  const int64_t jobs = in.kept_pairs_per_head < 0 ? wgs : (c.block == 256 ? 2 : 1) * lists * in.kept_pairs_per_head / longest;
-  const bool unequal = wgs >= 2 * jobs;
-  if (d64) {
-    if (jobs <= 512 && (jobs <= 256 || unequal || c.block == 64)) cut.groups = 2;
-    if (jobs <= 256 && (c.block == 64 || longest * (in.block_k / 64) >= 64)) cut.groups = 4;
-  } else if (jobs <= (unequal ? 320 : 256)) {
+  const int64_t jobs = in.kept_pairs_per_head < 0 ? wgs : share * lists * in.kept_pairs_per_head / longest;
+  const bool uneven = wgs >= 2 * jobs, tail = wgs >= 3 * jobs;
+  if (c.head_dim == 64) {
+    if (tail ? jobs <= 512 : uneven ? jobs <= 320 : wgs <= (c.block == 64 ? 512 : 256)) cut.groups = 2;
+    if ((tail ? jobs <= 256 : wgs <= 280) && (c.block == 64 || longest_parts >= 64)) cut.groups = 4;
+  } else if (tail ? jobs <= (longest_parts >= 256 ? 320 : 256) : wgs <= (uneven ? 320 : 256)) {
     cut.groups = 2;
   }
-  if (c.block == 256 && cut.groups == 1) cut.halves = rows < (d64 ? 2048 : 1024);
+  if (c.block == 256 && cut.groups == 1) cut.halves = rows < (c.head_dim == 64 ? 2048 : 1024);
   return cut;
 }
 
