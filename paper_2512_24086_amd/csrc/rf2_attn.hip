@@ -32,6 +32,7 @@
 // parts, 2 V^T parts); the workgroup meets at one barrier per part (every second step).
 #include "rf2_internal.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace {
@@ -604,6 +605,11 @@ int launch_attn(const rf2_plan* plan, const void* qp, const void* kp, const void
 // 24.2; with text, 64-row blocks, 300 jobs 33.2 -> 31.1, 360 34.9 -> 35.6.
 // KS = 4 against 2 (us): 480p, 51 jobs 250 -> 204, 204 jobs 313 -> 288; 64-row blocks 180 -> 133; with text, 64-row blocks,
 // 264 workgroups 28.8 -> 26.0, 312 20.9 -> 24.5; but rows of 20 parts, 128-row blocks 14.5 -> 17.2.
+// A list has to be long enough to pay for the merge (equal rows of 64-key parts, KS = 1 -> 2, us): d = 128, 64 workgroups,
+// 8 parts 14.0 -> 14.6, 16 parts 21.0 -> 19.7; 192 workgroups, 16 parts 23.6 -> 24.0, 32 parts 38.0 -> 35.2; 256 workgroups,
+// 32 parts 41.5 -> 42.0, 64 parts 70.4 -> 65.9; 64-row blocks, 2 parts 8.9 -> 9.2, 4 parts 10.4 -> 10.1; d = 64, 8 parts 10.3 ->
+// 10.2, 16 parts 15.7 -> 14.3; 64-row blocks, 4 parts 8.8 -> 8.9, 8 parts 10.0 -> 8.8 (KS = 4: 9.1); 2 -> 4, 128-row
+// blocks, 32 parts 21.9 -> 21.8, 64 parts 36.0 -> 33.2; 64-row blocks, 16 parts 10.8 -> 10.9.
 // 256-row blocks, one workgroup -> two (us): d = 128, 512 workgroups 683 -> 586 (KS = 2: 452), 760: 576 -> 516, 480 of equal
 // length 101 -> 92, 1,024: 813 -> 827, 5,120: 3,830 -> 3,914 (the larger one reads K and V less often); d = 64,
 // 1,024: 597 -> 534, 1,280: 641 -> 607, 2,560: 1,115 -> 1,128.
@@ -622,9 +628,11 @@ AttnCut attn_cut(const rf2_plan* plan) {
   const int64_t jobs = in.kept_pairs_per_head < 0 ? wgs : share * lists * in.kept_pairs_per_head / longest;
   const bool uneven = wgs >= 2 * jobs, tail = wgs >= 3 * jobs;
   if (c.head_dim == 64) {
-    if (tail ? jobs <= 512 : uneven ? jobs <= 320 : wgs <= (c.block == 64 ? 512 : 256)) cut.groups = 2;
-    if ((tail ? jobs <= 256 : wgs <= 280) && (c.block == 64 || longest_parts >= 64)) cut.groups = 4;
-  } else if (tail ? jobs <= (longest_parts >= 256 ? 320 : 256) : wgs <= (uneven ? 320 : 256)) {
+    if ((tail ? jobs <= 512 : uneven ? jobs <= 320 : wgs <= (c.block == 64 ? 512 : 256)) &&
+        longest_parts >= (c.block == 64 ? 4 : 12)) cut.groups = 2;
+    if ((tail ? jobs <= 256 : wgs <= 280) && longest_parts >= (c.block == 64 ? 24 : 64)) cut.groups = 4;
+  } else if ((tail ? jobs <= (longest_parts >= 256 ? 320 : 256) : wgs <= (uneven ? 320 : 256)) &&
+             longest_parts >= (c.block == 64 ? 4 : std::max<int64_t>(12, jobs / 6))) {
     cut.groups = 2;
   }
   if (c.block == 256 && cut.groups == 1) cut.halves = rows < (c.head_dim == 64 ? 2048 : 1024);
