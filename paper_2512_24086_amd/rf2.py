@@ -84,17 +84,18 @@ def _check(code: int, where: str) -> None:
         raise Rf2Error(code, where)
 
 
-def _ptr(t) -> C.c_void_p:
+def _ptr(t):
+    """Address of a tensor, or None (the argument types of SIGNATURES turn both into a void*)."""
     if t is None:
-        return C.c_void_p(0)
+        return None
     assert t.is_contiguous(), "tensors handed to librf2 must be contiguous"
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _stream(stream) -> C.c_void_p:
+def _stream(stream):
     if stream is None:
         stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream)
+    return stream.cuda_stream
 
 
 def rf2_measure_peaks(stream=None):
@@ -209,6 +210,7 @@ class Plan:
 
     def layer_fused(self, q, k, v, buf, stream=None):
         """The whole layer with the inverse permutation fused into the attention epilogue; returns buf['o']."""
+        stream = torch.cuda.current_stream() if stream is None else stream
         self.rf2_permute(q, k, v, buf["qp"], buf["kp"], buf["vp"], buf["qbar"], buf["kbar"], stream)
         self.rf2_predict_mask(buf["qbar"], buf["kbar"], buf["blk_idx"], buf["blk_cnt"], buf.get("mask_dense"),
                               buf.get("scores"), None, stream)
@@ -218,6 +220,7 @@ class Plan:
 
     def layer(self, q, k, v, buf, stream=None):
         """The whole layer, in order; returns buf['o']."""
+        stream = torch.cuda.current_stream() if stream is None else stream
         self.rf2_permute(q, k, v, buf["qp"], buf["kp"], buf["vp"], buf["qbar"], buf["kbar"], stream)
         self.rf2_predict_mask(buf["qbar"], buf["kbar"], buf["blk_idx"], buf["blk_cnt"], buf.get("mask_dense"),
                               buf.get("scores"), None, stream)
