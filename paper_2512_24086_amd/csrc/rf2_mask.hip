@@ -228,8 +228,8 @@ __global__ void __launch_bounds__(NW * 64, (NW == 8 && EMAX <= (CDF ? 12 : 20)) 
         halve = !halve && p > 1 && 2 * (n_lo - n_top) > before;
         const float fl = key_value(lo), fh = key_value(top);
         if (p == 0) t += (float)(cnt - k_row) * sigma * guess.slope;
-        else if (lo == PAST_KEY + 1u) t = fh - sigma * (0.25f * (float)(1 << p));      // no lower (upper) end yet
-        else if (top == SINK_KEY - 1u) t = fl + sigma * (0.25f * (float)(1 << p));
+        else if (lo == PAST_KEY + 1u) t = fh - sigma * (0.25f * (float)(1 << min(p, 12)));      // no lower (upper) end yet
+        else if (top == SINK_KEY - 1u) t = fl + sigma * (0.25f * (float)(1 << min(p, 12)));
         else t = fl + (fh - fl) * (halve ? 0.5f : (float)(n_lo - k_row) / (float)(n_lo - n_top));
       }
       T = exact ? lo - 1u : lo;
@@ -271,7 +271,7 @@ __global__ void __launch_bounds__(NW * 64, (NW == 8 && EMAX <= (CDF ? 12 : 20)) 
         halve = !halve && p > 1 && 2 * (n_lo - n_top) > before;
         const float fl = key_value(lo), fh = key_value(top);
         if (p == 0) t += (mass / total - tau) * sigma * guess.slope;
-        else if (lo == PAST_KEY + 1u) t = fh - sigma * (0.25f * (float)(1 << p));
+        else if (lo == PAST_KEY + 1u) t = fh - sigma * (0.25f * (float)(1 << min(p, 12)));
         else t = fl + (fh - fl) * (halve ? 0.5f : (m_lo - target) / (m_lo - m_top));
       }
       T = lo - 1u;                                    // (where the sums are no numbers lo has not moved: all are kept)
