@@ -182,9 +182,10 @@ namespace {
 
 template <int D, int BQ, int BK>
 int launch_permute(const PermuteArgs& a, hipStream_t st) {
-  // at most (2,048 + 2,048 + 4,096) x 65,535 workgroups, in rows of 4 Mi (a grid dimension holds fewer than 2^32 threads)
-  const uint32_t n = (a.n_q + a.n_k * (1 + BK / 64)) * a.bh, row = n < (1u << 22) ? n : 1u << 22;
-  permute_kernel<D, BQ, BK><<<dim3(row, (n + row - 1) / row), 256, 0, st>>>(a);
+  // at most (2,048 + 2,048 + 4,096) x 65,535 workgroups, in equal rows of at most 65,536 (a grid dimension holds fewer
+  // than 2^32 threads)
+  const uint32_t n = (a.n_q + a.n_k * (1 + BK / 64)) * a.bh, rows = (n + 65535u) / 65536u;
+  permute_kernel<D, BQ, BK><<<dim3((n + rows - 1) / rows, rows), 256, 0, st>>>(a);
   RF2_LAUNCH_CHECK();
   return RF2_OK;
 }
