@@ -65,10 +65,20 @@ __device__ __forceinline__ uint32_t wave_reduce(uint32_t v, uint32_t neutral, Op
   v = op(v, dpp<0x143, 0xc>(neutral, v));             // lane 31 to the upper half
   return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
+// Sum over the wavefront, every lane with lane ^ 32, then ^ 16, 8, 4, 2, 1: this order of the additions is part of the result
+// (a cumulative-mass row is cut where these fp32 sums say).  Halves and rows of 16 trade places through permlane swaps;
+// after them all lanes of a row hold values of period 8, 4, 2, 1, so a rotation by as much reaches the same partner's value.
 __device__ __forceinline__ float wave_sum(float x) {
-  return __uint_as_float(wave_reduce(__float_as_uint(x), 0u, [](uint32_t a, uint32_t b) {
-    return __float_as_uint(__uint_as_float(a) + __uint_as_float(b));
-  }));
+  const auto add = [](uint32_t a, uint32_t b) { return __uint_as_float(a) + __uint_as_float(b); };
+  uint32_t v = __float_as_uint(x);
+  const auto h = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  v = __float_as_uint(add(h[0], h[1]));
+  const auto q = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  v = __float_as_uint(add(q[0], q[1]));
+  v = __float_as_uint(add(v, dpp<0x128, 0xf>(v, v)));
+  v = __float_as_uint(add(v, dpp<0x124, 0xf>(v, v)));
+  v = __float_as_uint(add(v, dpp<0x122, 0xf>(v, v)));
+  return uniform(add(v, dpp<0x121, 0xf>(v, v)));
 }
 // Sum over a row of 16 lanes, in the last of them.
 __device__ __forceinline__ float row_sum(float x) {

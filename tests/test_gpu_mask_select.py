@@ -125,3 +125,44 @@ def test_cumulative_mass_lists(shape, kind):
             c = np.cumsum(p) / p.sum()
             assert c[n - 1] >= tau - 2e-5 and (n == 1 or c[n - 2] <= tau + 2e-5)
     plan.close()
+
+
+@pytest.mark.parametrize("shape", [(2048 * 64, 64, 64, 12, 1, 64), (900 * 64, 64, 64, 16, 2, 128), (600 * 64, 256, 64, 1, 0, 64)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_cumulative_mass_is_cut_where_the_fp32_sums_say(shape):
+    """The lists are whole numbers and follow from the scores exactly: weights exp2 of fp32 differences, a lane's columns
+    (every 64th) added in ascending order, lanes then by halves (lane ^ 32, 16, 8, 4, 2, 1), the row cut at the largest
+    key whose upper set reaches tau times the total.  (An order of the additions of its own would move about one row in
+    10,000 by a column.)"""
+    tau = 0.8
+    plan = make(shape, cdf_threshold=tau)
+    i, c = plan.info, plan.cfg
+    qbar, kbar = means(plan, "random", 6)
+    idx, cnt, S, mask = predict(plan, qbar, kbar)
+    plain = [r for r in range(i.n_blocks) if not i.sink_block_begin <= r < i.sink_block_end]
+    scale = torch.tensor(np.float32(1.4426950408889634 / np.sqrt(float(c.head_dim))), device=DEV)
+    cols = torch.arange(i.n_blocks_k, device=DEV)
+    cand = (cols < i.sink_block_begin_k) | (cols >= i.sink_block_end_k)
+    pad = -i.n_blocks_k % 64
+
+    def wave_sum(x):                        # [rows, Tk] -> [rows]
+        x = torch.nn.functional.pad(x, (0, pad)).view(x.shape[0], -1, 64)
+        part = torch.zeros_like(x[:, 0])
+        for e in range(x.shape[1]):
+            part = part + x[:, e]
+        for step in (32, 16, 8, 4, 2, 1):
+            part = part + part[:, torch.arange(64, device=DEV) ^ step]
+        return part[:, 0]
+
+    wrong = 0
+    for h in range(c.heads):
+        s = torch.from_numpy(S[h][plain]).to(DEV)
+        kept = torch.from_numpy(mask[h][plain]).to(DEV).bool() & cand
+        top = s.masked_fill(~cand, -torch.inf).amax(1, keepdim=True)
+        w = torch.exp2((s - top) * scale).masked_fill(~cand, 0.0)
+        target = torch.tensor(np.float32(tau), device=DEV) * wave_sum(w)
+        lowest = s.masked_fill(~kept, torch.inf).amin(1, keepdim=True)
+        assert torch.equal(kept, (s >= lowest) & cand)          # (random scores: no ties at the cut)
+        wrong += int(((wave_sum(w * kept) < target) | (wave_sum(w * (kept & (s > lowest))) >= target)).sum())
+    assert wrong == 0
+    plan.close()
