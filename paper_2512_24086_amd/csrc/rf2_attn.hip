@@ -33,6 +33,7 @@
 #include "rf2_internal.h"
 
 #include <algorithm>
+#include <cfloat>
 #include <type_traits>
 
 namespace {
@@ -187,12 +188,19 @@ __global__ void __launch_bounds__(BQ * 2 * KS, D == 64 ? (BQ == 128 ? 4 : 2) : (
   const bool dense = (cnt == Tb);
   cnt = dense ? Tb : min(max(cnt, 0), k_row);
   const int32_t* __restrict__ list = blk_idx + row_id * k_row;
-  const int NPARTS = cnt * C::PB;
-  // group `grp` walks the parts from P0 on.  Every group takes as many steps (they meet at the barriers); the units
-  // past the end of the list count as masked keys.
+  // Only the last listed block can be the ragged last block of the sequence (lists ascend).
+  bool ragged = false;
+  if (cnt > 0 && last_valid < BK) {
+    const int jl = dense ? cnt - 1 : list[cnt - 1];
+    ragged = min(max(jl, 0), Tb - 1) == Tb - 1;
+  }
+  int NPARTS = cnt * C::PB;
+  // (a last part without any valid key is left out, so that every group has a valid key in its first unit)
+  if (KS > 1 && C::PB > 1 && ragged && last_valid <= 32) --NPARTS;
+  // Group `grp` walks the parts from P0 on, as many as there are; all groups pass the same number of barriers.
   const int grp = KS > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / C::NT) : 0;
   const int parts = (NPARTS + KS - 1) / KS, P0 = grp * parts;
-  const int U = 2 * parts;                              // 32-key units to process (even)
+  const int U = KS > 1 ? 2 * max(min(parts, NPARTS - P0), 0) : 2 * parts;   // 32-key units to process (even)
 
   const int tid = KS > 1 ? (int)threadIdx.x % C::NT : (int)threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wavefront-uniform, kept in a scalar register
@@ -224,14 +232,7 @@ __global__ void __launch_bounds__(BQ * 2 * KS, D == 64 ? (BQ == 128 ? 4 : 2) : (
   auto part_at = [&](int P) { return (size_t)part_off(list_entry(P0 + P), P0 + P); };
   unsigned char* const gring = ring + grp * C::RING_BYTES;
   const uint32_t ring_lds = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char*)gring;
-  // Only the last listed block can be the ragged last block of the sequence (lists ascend).
-  int partial_begin = U;
-  if (U > 0 && last_valid < BK) {
-    const int jl = dense ? cnt - 1 : list[cnt - 1];
-    if (min(max(jl, 0), Tb - 1) == Tb - 1) partial_begin = max((cnt - 1) * C::UB - 2 * P0, 0);
-  }
-  const int u_real = max(min(2 * (NPARTS - P0), U), 0);   // units of this group that exist
-  if (KS > 1) partial_begin = min(partial_begin, u_real);
+  const int partial_begin = ragged ? max((cnt - 1) * C::UB - 2 * P0, 0) : U;   // first unit of the ragged block
 
   bf16x8 qf[C::DS];
   f32x16 o[C::DT];
@@ -242,7 +243,8 @@ __global__ void __launch_bounds__(BQ * 2 * KS, D == 64 ? (BQ == 128 ? 4 : 2) : (
   // Softmax reference m_ref (per query column, in units of the raw products q.k) and nmc = -m_ref * c,
   // the addend of the multiply-add in front of every exp2.  l_run lags one unit behind: rs_last, the
   // row sum of the latest unit, is still to be added.
-  float m_ref = 0.f, nmc = 0.f, l_run = 0.f, rs_last = 0.f;
+  // (a group without any part of its own weighs nothing in the merge, however small the others' references are)
+  float m_ref = KS > 1 && U == 0 ? -FLT_MAX : 0.f, nmc = 0.f, l_run = 0.f, rs_last = 0.f;
 
   // ---- building blocks ------------------------------------------------------------------
   // One step has NQ + NP "slots" of one MFMA each: slots 0..NQ-1 are the k-steps of
@@ -270,12 +272,14 @@ __global__ void __launch_bounds__(BQ * 2 * KS, D == 64 ? (BQ == 128 ? 4 : 2) : (
     const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     return fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
   };
-  // Moves the reference by delta (per query column): everything accumulated so far is rescaled
+  // Moves the reference to `to` (per query column, where `move`): everything accumulated so far is rescaled
   // (eqs. 3, 4).  The accumulators hold raw products, so nothing else changes.
-  auto move_reference = [&](float delta) {
+  auto move_reference = [&](bool move, float to) {
+    const float delta = move ? to - m_ref : 0.f;
     // (the very first move may go down; nothing has been accumulated then, any finite factor will do)
     const float alpha = __builtin_amdgcn_exp2f(-fmaxf(delta, 0.f) * scale_log2);
-    m_ref += delta;
+    if constexpr (KS > 1) m_ref = move ? to : m_ref;     // (from -FLT_MAX a difference does not lead to `to`)
+    else m_ref += delta;
     nmc = -m_ref * scale_log2;
     l_run *= alpha;
 #pragma unroll
@@ -287,7 +291,7 @@ __global__ void __launch_bounds__(BQ * 2 * KS, D == 64 ? (BQ == 128 ? 4 : 2) : (
   // earlier units, so the reference moves up and P (and rs_last) are recomputed.
   auto redo_unit = [&](f32x16& S, bf16x8 (&P)[2]) {
     const float mx = rowmax(S);
-    move_reference(mx > m_ref ? mx - m_ref : 0.f);
+    move_reference(mx > m_ref, mx);
     rs_last = 0.f;
 #pragma unroll
     for (int i = 0; i < 16; i += 2) {
@@ -317,21 +321,20 @@ __global__ void __launch_bounds__(BQ * 2 * KS, D == 64 ? (BQ == 128 ? 4 : 2) : (
         for (int e = 0; e < 8; ++e) Pprev[ks][e] = (__bf16)0.f;
       if (s >= partial_begin) {
         const int t = s & 1, p = (P0 + (s >> 1)) % C::PB;
-        const int valid = KS > 1 && s >= u_real ? 0 : last_valid;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
           const int key = t * C::KH + 32 * p + 8 * (i / 4) + 4 * lh + (i % 4);
-          if (key >= valid) S[i] = -INFINITY;
+          if (key >= last_valid) S[i] = -INFINITY;
         }
       }
-      // (a group without any part of its own has no valid key: its reference is a number all the same)
-      const float mx = KS > 1 ? fmaxf(rowmax(S), -1e30f) : rowmax(S);
+      // (minus infinity in all products of a later unit of a list is no reference: it weighs nothing, also where a group begins)
+      const float mx = KS > 1 && grp > 0 ? fmaxf(rowmax(S), -FLT_MAX) : rowmax(S);
       // first unit: exact reference (it has at least one valid key); later: only upwards
       const bool move = (s == 0) ? true : (mx > m_ref);
       if (__builtin_amdgcn_ballot_w64(move) != 0ull) {
         l_run += rs_last;                                  // unit s-1 is in O now: rescale it with the rest
         rs_last = 0.f;
-        move_reference(move ? mx - m_ref : 0.f);
+        move_reference(move, mx);
       }
     }
   };
@@ -439,8 +442,8 @@ __global__ void __launch_bounds__(BQ * 2 * KS, D == 64 ? (BQ == 128 ? 4 : 2) : (
 #pragma unroll
     for (int P = 0; P < C::NV - 1; ++P)
       dma_part<C::NW, C::LPW>(gring + VRING + P * C::PART_BYTES, vbase + part_at(P), wave, tid16);
-    // the slot of "part -1" (read by step 0 with zero probabilities) gets finite data
-    dma_part<C::NW, C::LPW>(gring + VRING + (C::NV - 1) * C::PART_BYTES, vbase + part_at(0), wave, tid16);
+    // the slot of "part -1" (read by step 0 with zero probabilities) gets the list's first part, as finite as the list is
+    dma_part<C::NW, C::LPW>(gring + VRING + (C::NV - 1) * C::PART_BYTES, vbase + part_off(list_entry(0), 0), wave, tid16);
     {
       const __bf16* qrow = qp + q_head_off + (size_t)q_row * D + 8 * lh;
 #pragma unroll
@@ -482,6 +485,8 @@ __global__ void __launch_bounds__(BQ * 2 * KS, D == 64 ? (BQ == 128 ? 4 : 2) : (
       vc = (vc == C::NV - 1) ? 0 : vc + 1;
     }
     // ---- last product: O += V P_{U-1} (tile 1 of the last part; P_{U-1} is in Pb) ---------------
+    if constexpr (KS > 1)
+      for (int s = U; s < 2 * parts; s += 2) __builtin_amdgcn_s_barrier();   // (the longer groups are still walking)
     ring_barrier<0>();
     if (redo) redo_unit(Sb, Pb);
     l_run += rs_last;
@@ -493,6 +498,8 @@ __global__ void __launch_bounds__(BQ * 2 * KS, D == 64 ? (BQ == 128 ? 4 : 2) : (
         o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_operand(v_addr, dt, ks), Pb[ks], o[dt], 0, 0, 0);
       }
     }
+  } else if (KS > 1 && parts > 0) {
+    for (int s = -4; s < 2 * parts; s += 2) __builtin_amdgcn_s_barrier();    // prologue, one per part, last product
   }
 
   // ---- normalise (the final division of eq. 4) and write the 32 rows of this wavefront ----------
