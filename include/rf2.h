@@ -174,6 +174,8 @@ int rf2_plan_perm(const rf2_plan* plan, int32_t* perm_host, int32_t* inv_host);
  *             qp / kp (the last block divides by last_block_valid).  Pass both
  *             NULL to skip pooling.                                        (out)
  * v/vp or q/qp/k/kp groups may not be NULL individually: all six are required.
+ * Q, K and V are written as if one after the other: kp and kbar may lie over q, vp over q or k (a caller short of
+ * memory whose projections are not needed again).  Such a call takes three launches, any other one.
  */
 int rf2_permute(const rf2_plan* plan, const void* q, const void* k, const void* v,
                 void* qp, void* kp, void* vp, float* qbar, float* kbar, void* stream);

@@ -136,6 +136,7 @@ struct PermuteArgs {
   float *qbar, *kbar;
   const int32_t* perm;
   uint32_t n_q, n_k, bh;            // Q and K blocks of a head, heads of all batches
+  uint32_t q_wgs, k_wgs, v_wgs;     // workgroups of the launch for each tensor
   int last_q, last_k, heads;
   rf2_strides st;
 };
@@ -143,18 +144,18 @@ template <int D, int BQ, int BK>
 __global__ void __launch_bounds__(256) permute_kernel(PermuteArgs a) {
   __shared__ __attribute__((aligned(16))) union { pool_rows<D> sums; v_rows<D> tile; } lds;
   uint32_t id = blockIdx.y * gridDim.x + blockIdx.x;
-  if (id < a.n_q * a.bh) {
+  if (id < a.q_wgs) {
     permute_pool_block<D, BQ, false>(a.q, a.qp, a.qbar, a.perm, a.n_q, a.last_q, a.heads, a.st, id % a.n_q, id / a.n_q, lds.sums);
     return;
   }
-  id -= a.n_q * a.bh;
-  if (id < a.n_k * a.bh) {
+  id -= a.q_wgs;
+  if (id < a.k_wgs) {
     permute_pool_block<D, BK, true>(a.k, a.kp, a.kbar, a.perm, a.n_k, a.last_k, a.heads, a.st, id % a.n_k, id / a.n_k, lds.sums);
     return;
   }
-  id -= a.n_k * a.bh;
+  id -= a.k_wgs;
   const uint32_t parts = a.n_k * (BK / 64);
-  if (id < parts * a.bh) permute_vtile_part<D, BK>(a.v, a.vp, a.perm, a.n_k, a.heads, a.st, id % parts, id / parts, lds.tile);
+  if (id < a.v_wgs) permute_vtile_part<D, BK>(a.v, a.vp, a.perm, a.n_k, a.heads, a.st, id % parts, id / parts, lds.tile);
 }
 
 // o[n] = op[inv[n]]: gathered reads, fully sequential writes.
@@ -180,20 +181,47 @@ __global__ void __launch_bounds__(256) unpermute_kernel(
 
 namespace {
 
+// Whether what is written for one of the three tensors shares memory with what is read or written for another: a caller
+// may lay kp over q, and vp over k or q, to save a buffer.
+bool tensors_overlap(const rf2_plan* plan, const PermuteArgs& a) {
+  const rf2_info& in = plan->info;
+  const uint64_t row = (uint64_t)a.bh * plan->cfg.head_dim * 2;
+  struct Range { const void* at; uint64_t bytes; int tensor; bool written; };
+  const Range r[] = {{a.q, row * in.N, 0, false}, {a.k, row * in.N, 1, false}, {a.v, row * in.N, 2, false},
+                     {a.qp, row * in.N_pad, 0, true}, {a.kp, row * in.N_pad_k, 1, true}, {a.vp, row * in.N_pad_k, 2, true},
+                     {a.qbar, a.qbar ? row * 2 * a.n_q : 0, 0, true}, {a.kbar, a.kbar ? row * 2 * a.n_k : 0, 1, true}};
+  for (const Range& x : r)
+    for (const Range& y : r)
+      if (x.written && x.tensor != y.tensor && (uint64_t)x.at < (uint64_t)y.at + y.bytes &&
+          (uint64_t)y.at < (uint64_t)x.at + x.bytes)
+        return true;
+  return false;
+}
+
 template <int D, int BQ, int BK>
-int launch_permute(const PermuteArgs& a, hipStream_t st) {
+int launch_permute(PermuteArgs a, uint32_t q_wgs, uint32_t k_wgs, uint32_t v_wgs, hipStream_t st) {
   // at most (2,048 + 2,048 + 4,096) x 65,535 workgroups, in equal rows of at most 65,536 (a grid dimension holds fewer
   // than 2^32 threads)
-  const uint32_t n = (a.n_q + a.n_k * (1 + BK / 64)) * a.bh, rows = (n + 65535u) / 65536u;
+  const uint32_t n = q_wgs + k_wgs + v_wgs, rows = (n + 65535u) / 65536u;
+  a.q_wgs = q_wgs, a.k_wgs = k_wgs, a.v_wgs = v_wgs;
   permute_kernel<D, BQ, BK><<<dim3((n + rows - 1) / rows, rows), 256, 0, st>>>(a);
   RF2_LAUNCH_CHECK();
   return RF2_OK;
 }
 
+template <int D, int BQ, int BK>
+int permute_all(const rf2_plan* plan, const PermuteArgs& a, hipStream_t st) {
+  const uint32_t q = a.n_q * a.bh, k = a.n_k * a.bh, v = k * (BK / 64);
+  if (!tensors_overlap(plan, a)) return launch_permute<D, BQ, BK>(a, q, k, v, st);
+  if (const int rc = launch_permute<D, BQ, BK>(a, q, 0, 0, st)) return rc;
+  if (const int rc = launch_permute<D, BQ, BK>(a, 0, k, 0, st)) return rc;
+  return launch_permute<D, BQ, BK>(a, 0, 0, v, st);
+}
+
 template <int D>
 int permute_for_dim(const rf2_plan* plan, const PermuteArgs& a, hipStream_t st) {
   const int bq = plan->cfg.block, bk = plan->info.block_k;
-#define RF2_PERMUTE_CASE(Q, K) if (bq == Q && bk == K) return launch_permute<D, Q, K>(a, st);
+#define RF2_PERMUTE_CASE(Q, K) if (bq == Q && bk == K) return permute_all<D, Q, K>(plan, a, st);
   RF2_PERMUTE_CASE(64, 64)
   RF2_PERMUTE_CASE(64, 128)
   RF2_PERMUTE_CASE(128, 64)
@@ -215,7 +243,7 @@ extern "C" int rf2_permute(const rf2_plan* plan, const void* q, const void* k, c
   const rf2_info& in = plan->info;
   const PermuteArgs a{(const uint4*)q, (const uint4*)k, (const uint4*)v, (uint4*)qp, (uint4*)kp, (uint4*)vp, qbar, kbar,
                       plan->d_perm, (uint32_t)in.n_blocks, (uint32_t)in.n_blocks_k,
-                      (uint32_t)(plan->cfg.batch * plan->cfg.heads), in.last_block_valid, in.last_block_valid_k,
+                      (uint32_t)(plan->cfg.batch * plan->cfg.heads), 0, 0, 0, in.last_block_valid, in.last_block_valid_k,
                       plan->cfg.heads, rf2_qkv_strides(plan)};
   if (plan->cfg.head_dim == 128) return permute_for_dim<128>(plan, a, st);
   if (plan->cfg.head_dim == 64) return permute_for_dim<64>(plan, a, st);

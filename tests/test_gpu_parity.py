@@ -319,6 +319,33 @@ def test_large_logits_take_the_reference_reset_path(scale):
     plan.close()
 
 
+@pytest.mark.parametrize("over", [dict(kp="q"), dict(vp="k"), dict(kp="q", vp="k"), dict(vp="q"), dict(kbar="q")],
+                         ids=lambda o: "-".join(f"{a}_over_{b}" for a, b in o.items()))
+@pytest.mark.parametrize("shape", [(8, 128, 128, 128, 4096), (8, 64, 64, 128, 4096), (3, 128, 256, 64, 4096),
+                                   (360, 64, 64, 64, 12800)], ids=lambda s: "x".join(map(str, s)))
+def test_operand_tiles_over_inputs_that_are_done_with(shape, over):
+    """kp and kbar may lie over q, vp over q or k: Q, K and V are written as if one after the other.  (The last shape has
+    more than 65,536 workgroups for each tensor.)"""
+    from paper_2512_24086_amd import rf2
+    heads, d, block, block_k, tokens = shape
+    print(f"[case] {shape} {over}", flush=True)
+    plan = rf2.Plan(batch=1, heads=heads, head_dim=d, T=4, H=16, W=tokens // 64, block=block, block_k=block_k, sparsity=0.5)
+    g = torch.Generator(device=DEV).manual_seed(31)
+    x = {n: torch.randn(1, heads, tokens, d, generator=g, device=DEV, dtype=torch.bfloat16) for n in "qkv"}
+    names = ("qp", "kp", "vp", "qbar", "kbar")
+    want = plan.alloc(DEV)
+    plan.rf2_permute(x["q"], x["k"], x["v"], *(want[n] for n in names))
+    got = plan.alloc(DEV)
+    for out, src in over.items():
+        n = got[out].numel() * got[out].element_size()
+        got[out] = x[src].view(torch.uint8).flatten()[:n].view(got[out].dtype).view(got[out].shape)
+    plan.rf2_permute(x["q"], x["k"], x["v"], *(got[n] for n in names))
+    torch.cuda.synchronize()
+    for n in names:
+        assert torch.equal(want[n].view(torch.int16), got[n].view(torch.int16)), n
+    plan.close()
+
+
 @pytest.mark.parametrize("name", ["tiny", "ragged_d128_b128"])
 def test_token_major_layout_gives_identical_results(name):
     """q, k, v, o held as [B, N, Hh, d]: every intermediate and the output are bit-identical to the
