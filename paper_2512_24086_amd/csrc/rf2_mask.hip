@@ -90,6 +90,9 @@ __device__ __forceinline__ float row_sum(float x) {
 __device__ __forceinline__ uint32_t wave_max_u(uint32_t x) {
   return wave_reduce(x, 0u, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
 }
+__device__ __forceinline__ uint32_t wave_min_u(uint32_t x) {
+  return wave_reduce(x, ~0u, [](uint32_t a, uint32_t b) { return a < b ? a : b; });
+}
 
 // First guesses of a row's threshold search (see rf2_mask_prepare).
 struct Guess {
@@ -100,14 +103,31 @@ struct Guess {
 // (sink columns: counted by every probe and always taken).
 constexpr uint32_t PAST_KEY = 0u, SINK_KEY = 0xffffffffu;
 
-// A search keeps a bracket [lo, top] around the threshold.  The first two probes come from the guesses, then the
-// measure (count or mass) is interpolated between the ends, or the bracket halved where an interpolation has not
-// halved its keys; after MAX_SMART probes the integer range is halved (at most 32 more).  Whatever the probes are, the
-// threshold found is the same.
-constexpr int MAX_SMART = 12;
-__device__ __forceinline__ uint32_t next_probe(float t, bool smart, uint32_t lo, uint32_t top) {
+// A search keeps a bracket [lo, top] around the threshold.  Its first two probes come from the guesses, then the measure
+// (count or mass) is interpolated between the ends, or the bracket halved where that has not halved its keys.  Where
+// scores are not bell-shaped (outliers, several levels, many magnitudes) interpolation gains little: after MAX_GUIDED
+// probes, for counts also after three in a row that leave more than half of the bracket's keys, the bracket is drawn in to
+// the keys it holds and its integer range halved, at a third of the time for a count (a mass costs more than its
+// guess), and drawn in again every TIGHTEN probes (equal scores end there).  Whatever the probes are, the threshold found
+// is the same.
+constexpr int TIGHTEN = 8;
+__device__ __forceinline__ uint32_t halfway(uint32_t lo, uint32_t top) { return lo + ((top - lo) >> 1) + 1u; }
+__device__ __forceinline__ uint32_t next_probe(float t, uint32_t lo, uint32_t top) {
   const uint32_t k = order_key(t);
-  return (smart && k > lo && k <= top) ? k : lo + ((top - lo) >> 1) + 1u;      // any float, NaN too, is safe here
+  return (k > lo && k <= top) ? k : halfway(lo, top);      // any float, NaN too, is safe here
+}
+// The smallest and the largest key of the bracket (which holds one) become its ends.
+template <int EMAX>
+__device__ __forceinline__ void draw_in(const uint32_t (&key)[EMAX], uint32_t& lo, uint32_t& top) {
+  uint32_t least = ~0u, most = 0u;
+#pragma unroll
+  for (int e = 0; e < EMAX; ++e) {
+    const bool in = key[e] - lo <= top - lo;
+    least = min(least, in ? key[e] : ~0u);
+    most = max(most, in ? key[e] : 0u);
+  }
+  lo = wave_min_u(least);
+  top = wave_max_u(most);
 }
 
 // NW wavefronts per workgroup of R = 16 rows.
@@ -119,6 +139,7 @@ __global__ void __launch_bounds__(NW * 64, (NW == 8 && EMAX <= (CDF ? 12 : 20)) 
     float tau, float scale_log2, Guess guess, int n_strips, int n_work) {
   // Tb, sink_begin, sink_end describe the COLUMNS (K blocks) from here on; rows use Tq and row_sink_*.
   constexpr int R = 16;
+  constexpr int MAX_GUIDED = CDF ? 12 : 8;
   extern __shared__ __attribute__((aligned(16))) uint32_t keys[];   // [R][LD]
   __shared__ float stat[NW][R][2];                                  // sum and sum of squares over a wavefront's columns
   __shared__ __attribute__((aligned(16))) float qs[R][D + 4];       // (+4: the 16 rows of an operand read start in different banks)
@@ -220,27 +241,34 @@ __global__ void __launch_bounds__(NW * 64, (NW == 8 && EMAX <= (CDF ? 12 : 20)) 
     uint32_t T, lo = PAST_KEY + 1u, top = SINK_KEY - 1u;      // bracket: the answer is in [lo, top]
     int need_eq = 0;
     int n_lo = Tb, n_top = Tb - n_cand;             // keys >= lo, keys > top
-    bool halve = false;
     if constexpr (!CDF) {
+      int stalled = 0;                              // probes in a row that left more than half of the bracket's keys
       // Largest T with |{key >= T}| >= k_row (sink columns count); a probe with exactly k_row keys at or above it ends
       // the search early: any T between the k_row-th and the next key gives the same set.
       bool exact = (n_lo == k_row);
       float t = mean + guess.z * sigma;
       if (n_top == k_row) { lo = SINK_KEY; exact = true; }    // only the sink columns
-      for (int p = 0; !exact && lo < top; ++p) {
-        const uint32_t cand = next_probe(t, p < MAX_SMART, lo, top);
+      const auto probe = [&](uint32_t cand) {
         int cnt = 0;
 #pragma unroll
         for (int e = 0; e < EMAX; ++e) cnt += popc64(__builtin_amdgcn_ballot_w64(key[e] >= cand));
-        const int before = n_lo - n_top;
         if (cnt >= k_row) { lo = cand; n_lo = cnt; } else { top = cand - 1u; n_top = cnt; }
         exact = (cnt == k_row);
-        halve = !halve && p > 1 && 2 * (n_lo - n_top) > before;
+        return cnt;
+      };
+      for (int p = 0; !exact && lo < top && p < MAX_GUIDED && stalled < 3; ++p) {
+        const int before = n_lo - n_top;
+        const int cnt = probe(next_probe(t, lo, top));
+        stalled = p > 0 && 2 * (n_lo - n_top) > before ? stalled + 1 : 0;
         const float fl = key_value(lo), fh = key_value(top);
         if (p == 0) t += (float)(cnt - k_row) * sigma * guess.slope;
         else if (lo == PAST_KEY + 1u) t = fh - sigma * (0.25f * (float)(1 << min(p, 12)));      // no lower (upper) end yet
         else if (top == SINK_KEY - 1u) t = fl + sigma * (0.25f * (float)(1 << min(p, 12)));
-        else t = fl + (fh - fl) * (halve ? 0.5f : (float)(n_lo - k_row) / (float)(n_lo - n_top));
+        else t = fl + (fh - fl) * ((stalled & 1) ? 0.5f : (float)(n_lo - k_row) / (float)(n_lo - n_top));
+      }
+      for (int p = 0; !exact && lo < top; ++p) {
+        if (p % TIGHTEN == 0) draw_in(key, lo, top);
+        if (lo < top) probe(halfway(lo, top));
       }
       T = exact ? lo - 1u : lo;
       need_eq = exact ? 0 : k_row - n_top;          // lo == top: the keys equal to lo share the places left
@@ -263,10 +291,10 @@ __global__ void __launch_bounds__(NW * 64, (NW == 8 && EMAX <= (CDF ? 12 : 20)) 
       }
       const float total = wave_sum(part), target = tau * total;
       float m_lo = total, m_top = 0.f;
+      bool halve = false;
       // (a weight exp(a s) moves the mean of a normal distribution by a sigma^2)
       float t = mean + sigma * (sigma * scale_log2 * 0.6931472f + guess.z);
-      for (int p = 0; n_lo - n_top > 1 && lo < top; ++p) {
-        const uint32_t cand = next_probe(t, p < MAX_SMART, lo, top);
+      const auto probe = [&](uint32_t cand) {
         float mass = 0.f;
         int cnt = 0;
 #pragma unroll
@@ -276,15 +304,25 @@ __global__ void __launch_bounds__(NW * 64, (NW == 8 && EMAX <= (CDF ? 12 : 20)) 
           cnt += popc64(__builtin_amdgcn_ballot_w64(in));
         }
         mass = wave_sum(mass);
+        const bool up = mass >= target;               // (selects: branches here left the captured variables in scratch memory)
+        lo = up ? cand : lo, n_lo = up ? cnt : n_lo, m_lo = up ? mass : m_lo;
+        top = up ? top : cand - 1u, n_top = up ? n_top : cnt, m_top = up ? m_top : mass;
+        return mass;
+      };
+      for (int p = 0; n_lo - n_top > 1 && lo < top && p < MAX_GUIDED; ++p) {
         const int before = n_lo - n_top;
-        if (mass >= target) { lo = cand; n_lo = cnt; m_lo = mass; } else { top = cand - 1u; n_top = cnt; m_top = mass; }
+        const float mass = probe(next_probe(t, lo, top));
         halve = !halve && p > 1 && 2 * (n_lo - n_top) > before;
         const float fl = key_value(lo), fh = key_value(top);
         if (p == 0) t += (mass / total - tau) * sigma * guess.slope;
         else if (lo == PAST_KEY + 1u) t = fh - sigma * (0.25f * (float)(1 << min(p, 12)));
         else t = fl + (fh - fl) * (halve ? 0.5f : (m_lo - target) / (m_lo - m_top));
       }
-      T = lo - 1u;                                    // (where the sums are no numbers lo has not moved: all are kept)
+      for (int p = 0; n_lo - n_top > 1 && lo < top; ++p) {
+        if (p % TIGHTEN == 0) draw_in(key, lo, top);
+        if (lo < top) probe(halfway(lo, top));
+      }
+      T = lo - 1u;                                    // (where the sums are no numbers lo is the least key at most: all are kept)
       if (n_lo - n_top > 1) {                         // lo == top: several keys equal to it, of equal mass
         T = lo;
         const float tie = __builtin_amdgcn_exp2f((key_value(lo) - mx) * scale_log2);

@@ -50,6 +50,16 @@ def means(plan, kind, seed):
     if kind == "special":                   # infinities, NaN, huge and tiny scores among ordinary ones
         for n, v in enumerate((float("inf"), float("nan"), -float("inf"), 1e30, -1e30, 1e-38)):
             out[1][..., n::11, :] = v
+    if kind in ("outlier", "levels", "magnitudes"):     # scores far from a normal distribution: q picks channel 0
+        out[0] = torch.zeros_like(out[0])
+        out[0][..., 0] = 1.0
+        x = out[1][..., 0]
+        if kind == "outlier":               # one column far above, one far below the others
+            x[..., 5::2048], x[..., 9::2048] = 1e6, -1e30
+        elif kind == "levels":
+            x.copy_((x * 1.5).round())
+        else:
+            x.copy_(x.sign() * torch.exp(6 * x.abs()))
     return [x.to(DEV) for x in out]
 
 
@@ -73,58 +83,92 @@ def make(shape, **over):
     return rf2.Plan(**kw)
 
 
-@pytest.mark.parametrize("kind", ["random", "ties", "equal", "special"])
-@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
-def test_top_n_lists(shape, kind):
-    plan = make(shape)
+KINDS = ["random", "ties", "equal", "special", "outlier", "levels", "magnitudes"]
+# launches of more than 256 strips (8 wavefronts a workgroup) at each width of an instance: 2, 4, 6, ... 32 keys a lane
+MANY = [(cols * 64, 256, 64, heads, 1, 0)
+        for cols, heads in [(128, 129), (250, 65), (384, 45), (500, 35), (640, 28), (705, 25), (1000, 18), (1182, 14),
+                            (1500, 12), (2048, 9)]]
+
+
+def check_top_n(plan, out, h):
     i = plan.info
-    idx, cnt, S, mask = predict(plan, *means(plan, kind, 3))
+    idx, cnt, S, mask = out
     sink_rows = slice(i.sink_block_begin, i.sink_block_end)
-    for h in range(plan.cfg.heads):
-        want = host_lists(S[h], (i.sink_block_begin_k, i.sink_block_end_k), i.k_sel)
-        want[sink_rows] = True
-        assert np.array_equal(mask[h].astype(bool), want) and mask[h].max() <= 1
-        plain = np.ones(i.n_blocks, dtype=bool)
-        plain[sink_rows] = False
-        assert (cnt[h][plain] == i.k_row).all() and (cnt[h][~plain] == i.n_blocks_k).all()
-        rows, cols = np.nonzero(want[plain])
-        assert np.array_equal(idx[h][plain], cols.reshape(-1, i.k_row))
-        assert (idx[h][~plain] == np.arange(i.k_row)).all()
-    plan.close()
+    want = host_lists(S[h], (i.sink_block_begin_k, i.sink_block_end_k), i.k_sel)
+    want[sink_rows] = True
+    assert np.array_equal(mask[h].astype(bool), want) and mask[h].max() <= 1
+    plain = np.ones(i.n_blocks, dtype=bool)
+    plain[sink_rows] = False
+    assert (cnt[h][plain] == i.k_row).all() and (cnt[h][~plain] == i.n_blocks_k).all()
+    rows, cols = np.nonzero(want[plain])
+    assert np.array_equal(idx[h][plain], cols.reshape(-1, i.k_row))
+    assert (idx[h][~plain] == np.arange(i.k_row)).all()
 
 
-@pytest.mark.parametrize("kind", ["random", "ties", "equal", "special"])
-@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
-def test_cumulative_mass_lists(shape, kind):
+def check_cumulative_mass(plan, out, h, tau):
     """The kept candidates are the shortest prefix of the descending order that reaches tau, cut at most where the mass
     in 64 bits is within 2e-5 of it (fp32 sums of up to 2,048 terms); a row without finite sums is kept whole."""
-    tau = 0.8
-    plan = make(shape, cdf_threshold=tau)
     i = plan.info
-    idx, cnt, S, mask = predict(plan, *means(plan, kind, 4))
+    idx, cnt, S, mask = out
     cand = np.ones(i.n_blocks_k, dtype=bool)
     cand[i.sink_block_begin_k:i.sink_block_end_k] = False
     cols = np.flatnonzero(cand)
+    M = mask[h].astype(bool)
+    assert M[:, ~cand].all() and np.array_equal(cnt[h], M.sum(1))
+    for r in range(i.n_blocks):
+        assert np.array_equal(idx[h, r, :cnt[h, r]], np.flatnonzero(M[r]))
+        if i.sink_block_begin <= r < i.sink_block_end or not cols.size:
+            assert M[r].all()
+            continue
+        s = S[h, r, cols].astype(np.float64)
+        order = np.argsort(-order_key(S[h, r, cols]), kind="stable")
+        n = int(M[r, cols].sum())
+        assert n >= 1 and M[r, cols[order[:n]]].all(), "not a prefix of the descending order"
+        with np.errstate(invalid="ignore"):
+            p = np.exp((s - s.max()) / np.sqrt(plan.cfg.head_dim))[order]
+        if not np.isfinite(p.sum()):
+            assert n == cols.size
+            continue
+        c = np.cumsum(p) / p.sum()
+        assert c[n - 1] >= tau - 2e-5 and (n == 1 or c[n - 2] <= tau + 2e-5)
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_top_n_lists(shape, kind):
+    plan = make(shape)
+    out = predict(plan, *means(plan, kind, 3))
     for h in range(plan.cfg.heads):
-        M = mask[h].astype(bool)
-        assert M[:, ~cand].all() and np.array_equal(cnt[h], M.sum(1))
-        for r in range(i.n_blocks):
-            assert np.array_equal(idx[h, r, :cnt[h, r]], np.flatnonzero(M[r]))
-            if i.sink_block_begin <= r < i.sink_block_end or not cols.size:
-                assert M[r].all()
-                continue
-            s = S[h, r, cols].astype(np.float64)
-            order = np.argsort(-order_key(S[h, r, cols]), kind="stable")
-            n = int(M[r, cols].sum())
-            assert n >= 1 and M[r, cols[order[:n]]].all(), "not a prefix of the descending order"
-            with np.errstate(invalid="ignore"):
-                p = np.exp((s - s.max()) / np.sqrt(plan.cfg.head_dim))[order]
-            if not np.isfinite(p.sum()):
-                assert n == cols.size
-                continue
-            c = np.cumsum(p) / p.sum()
-            assert c[n - 1] >= tau - 2e-5 and (n == 1 or c[n - 2] <= tau + 2e-5)
+        check_top_n(plan, out, h)
     plan.close()
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_cumulative_mass_lists(shape, kind):
+    plan = make(shape, cdf_threshold=0.8)
+    out = predict(plan, *means(plan, kind, 4))
+    for h in range(plan.cfg.heads):
+        check_cumulative_mass(plan, out, h, 0.8)
+    plan.close()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("shape", MANY, ids=lambda s: "x".join(map(str, s[:-1])))
+def test_lists_of_large_launches(shape, d):
+    """First, middle and last head, by count and by cumulative mass."""
+    shape = (*shape[:-1], d)
+    for over in (dict(), dict(cdf_threshold=0.8)):
+        plan = make(shape, **over)
+        i = plan.info
+        assert (i.n_blocks + 15) // 16 * plan.cfg.heads > 256
+        out = predict(plan, *means(plan, "random" if over else "magnitudes", 5))
+        for h in (0, plan.cfg.heads // 2, plan.cfg.heads - 1):
+            if over:
+                check_cumulative_mass(plan, out, h, 0.8)
+            else:
+                check_top_n(plan, out, h)
+        plan.close()
 
 
 @pytest.mark.parametrize("shape", [(2048 * 64, 64, 64, 12, 1, 64), (900 * 64, 64, 64, 16, 2, 128), (600 * 64, 256, 64, 1, 0, 64)],
