@@ -1,0 +1,56 @@
+// How a launch of the attention kernel is cut (host only; also compiled into a test).
+#pragma once
+#include <stdint.h>
+
+#include <algorithm>
+
+#include "rf2.h"
+
+// How a launch is cut, from the sizes of the plan alone (so that both exits of a layer give the same bits).
+// A row of the mask is one workgroup of `groups` (KS) groups of wavefronts that share its list (KS = 1: no merge); a Q block
+// of 256 rows is one workgroup of eight wavefronts or two of 128 rows.
+// jobs = the launch's work in units of its longest list.  With few jobs and KS = 1 compute units stand idle, or wait for
+// the all-column sink rows of a few heads; groups shorten the longest list, and cost a merge, a common barrier and
+// half of the workgroups a compute unit holds.  Where the rows are many and short beside the longest (a long tail: video
+// with a sink frame) the jobs decide, else how the workgroups themselves fill the compute units.
+// Measured, KS = 1 -> 2 (us), 480p layer (rows of 40, sink rows of 256 blocks), d = 128: 1 head (51 jobs) 469 -> 332,
+// 4 heads (204) 580 -> 448, 6 heads (306) 687 -> 616, 8 heads (408) 797 -> 832, 20 heads 1,919 -> 2,060; 64-row blocks,
+// 2 heads (206) 461 -> 309, 4 heads (412) 518 -> 555.  Equal rows (3,072-token image, 24 rows of 10 blocks), d = 128:
+// 192 workgroups 25.0 -> 24.5, 288 35.2 -> 46.0.  Images with text (2 long rows of 20): 320 workgroups 49.6 -> 40.7,
+// 400 51.7 -> 58.0, 64-row blocks 312 43.0 -> 32.9, 468 45.4 -> 46.4.
+// d = 64 holds twice the workgroups: 480p, 306 jobs 483 -> 374, 408 jobs 543 -> 480, 510 jobs 613 -> 602, 714 jobs 792 ->
+// 817; equal rows, 64-row blocks, 384 workgroups 24.0 -> 18.7, 576 25.4 -> 27.6, 128-row blocks 192 18.2 -> 15.8, 288 23.7 ->
+// 24.2; with text, 64-row blocks, 300 jobs 33.2 -> 31.1, 360 34.9 -> 35.6.
+// KS = 4 against 2 (us): 480p, 51 jobs 250 -> 204, 204 jobs 313 -> 288; 64-row blocks 180 -> 133; with text, 64-row blocks,
+// 264 workgroups 28.8 -> 26.0, 312 20.9 -> 24.5; but rows of 20 parts, 128-row blocks 14.5 -> 17.2.
+// A list has to be long enough to pay for the merge (equal rows of 64-key parts, KS = 1 -> 2, us): d = 128, 64 workgroups,
+// 8 parts 14.0 -> 14.6, 16 parts 21.0 -> 19.7; 192 workgroups, 16 parts 23.6 -> 24.0, 32 parts 38.0 -> 35.2; 256 workgroups,
+// 32 parts 41.5 -> 42.0, 64 parts 70.4 -> 65.9; 64-row blocks, 2 parts 8.9 -> 9.2, 4 parts 10.4 -> 10.1; d = 64, 8 parts 10.3 ->
+// 10.2, 16 parts 15.7 -> 14.3; 64-row blocks, 4 parts 8.8 -> 8.9, 8 parts 10.0 -> 8.8 (KS = 4: 9.1); 2 -> 4, 128-row
+// blocks, 32 parts 21.9 -> 21.8, 64 parts 36.0 -> 33.2; 64-row blocks, 16 parts 10.8 -> 10.9.
+// 256-row blocks, one workgroup -> two (us): d = 128, 512 workgroups 683 -> 586 (KS = 2: 452), 760: 576 -> 516, 480 of equal
+// length 101 -> 92, 1,024: 813 -> 827, 5,120: 3,830 -> 3,914 (the larger one reads K and V less often); d = 64,
+// 1,024: 597 -> 534, 1,280: 641 -> 607, 2,560: 1,115 -> 1,128.
+struct rf2_attn_cut {
+  int rows;         // query rows of a workgroup: those of a Q block, or 128 of 256
+  int groups;       // groups of wavefronts that share a list
+};
+inline rf2_attn_cut rf2_cut_attn(const rf2_config& c, const rf2_info& in) {
+  const int64_t lists = (int64_t)c.batch * c.heads, rows = lists * in.n_blocks, share = c.block == 256 ? 2 : 1;
+  int groups = 1;
+  const int64_t wgs = rows * share, longest = in.sink_block_end > in.sink_block_begin ? in.n_blocks_k : in.k_row;
+  const int64_t longest_parts = longest * (in.block_k / 64);
+  // (cumulative mass: the lengths are not known, taken as equal)
+  const int64_t jobs = in.kept_pairs_per_head < 0 ? wgs : share * lists * in.kept_pairs_per_head / longest;
+  const bool uneven = wgs >= 2 * jobs, tail = wgs >= 3 * jobs;
+  if (c.head_dim == 64) {
+    if ((tail ? jobs <= 512 : uneven ? jobs <= 320 : wgs <= (c.block == 64 ? 512 : 256)) &&
+        longest_parts >= (c.block == 64 ? 4 : 12)) groups = 2;
+    if ((tail ? jobs <= 256 : wgs <= 280) && longest_parts >= (c.block == 64 ? 24 : 64)) groups = 4;
+  } else if ((tail ? jobs <= (longest_parts >= 256 ? 320 : 256) : wgs <= (uneven ? 320 : 256)) &&
+             longest_parts >= (c.block == 64 ? 4 : std::max<int64_t>(12, jobs / 6))) {
+    groups = 2;
+  }
+  if (c.block != 256) return {c.block, groups};
+  return {groups > 1 || rows < (c.head_dim == 64 ? 2048 : 1024) ? 128 : 256, groups};
+}

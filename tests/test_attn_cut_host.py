@@ -1,0 +1,55 @@
+"""How the attention launches of the GPU tests are cut, evaluated on the host: every kernel instance that a plan can
+reach has to be among them."""
+import ctypes as C
+import itertools
+import os
+import subprocess
+
+import pytest
+
+from paper_2512_24086_amd import build as b
+from paper_2512_24086_amd import rf2
+from tests.test_gpu_attn_cut import NONFINITE, SHAPES
+
+SOURCE = """#include "rf2_attn_cut.h"
+extern "C" void cut(const rf2_config* c, const rf2_info* i, int* rows, int* groups) {
+  const rf2_attn_cut x = rf2_cut_attn(*c, *i);
+  *rows = x.rows;
+  *groups = x.groups;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def cut(tmp_path_factory):
+    """(head_dim, rows of a workgroup, block_k, groups) of a plan's attention launch."""
+    folder = tmp_path_factory.mktemp("cut")
+    (folder / "cut.cpp").write_text(SOURCE)
+    lib = str(folder / "cut.so")
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-O1", "-shared", "-fPIC", "-I", os.path.join(b.ROOT, "include"),
+                    "-I", b.CSRC, str(folder / "cut.cpp"), "-o", lib], check=True)
+    fn = C.CDLL(lib).cut
+
+    def of(plan):
+        rows, groups = C.c_int(), C.c_int()
+        fn(C.byref(plan.cfg), C.byref(plan.info), C.byref(rows), C.byref(groups))
+        return plan.cfg.head_dim, rows.value, plan.info.block_k, groups.value
+    return of
+
+
+def plan_of(shape, **over):
+    tokens, block, block_k, d, heads = shape
+    return rf2.Plan(**dict(dict(batch=1, heads=heads, head_dim=d, T=1, H=1, W=tokens, block=block, block_k=block_k, sparsity=0.3,
+                                window=(1, 1, 16)), **over))
+
+
+def test_the_gpu_tests_reach_every_instance(cut):
+    want = set(itertools.product((64, 128), (64, 128, 256), (64, 128), (1,))) \
+        | set(itertools.product((64, 128), (64, 128), (64, 128), (2,))) | set(itertools.product((64,), (64, 128), (64, 128), (4,)))
+    got = {cut(plan_of(s)) for s in SHAPES}
+    assert got == want, (sorted(want - got), sorted(got - want))
+
+
+def test_the_shapes_of_the_non_finite_tests_have_several_groups(cut):
+    assert all(cut(plan_of(s))[3] > 1 for s in NONFINITE)
+    assert {cut(plan_of(s))[3] for s in NONFINITE} == {2, 4}

@@ -11,13 +11,15 @@ from tests import helpers as hp
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
 
-# (tokens, block, block_k, head_dim, heads): few and long rows = several groups, many or short = one (see attn_cut in
-# rf2_attn.hip); 256-row Q blocks of few rows are cut into halves
+# (tokens, block, block_k, head_dim, heads): few and long rows = several groups, many or short = one (see
+# rf2_attn_cut.h; the host test of the cut asks for every instance); 256-row Q blocks of few rows are cut into halves
 SHAPES = [(2000, 128, 128, 128, 2), (1000, 128, 128, 128, 33), (2000, 128, 64, 128, 3), (999, 64, 64, 128, 2),
           (999, 64, 128, 128, 3), (999, 64, 128, 128, 17), (700, 64, 64, 64, 2), (700, 64, 128, 64, 3), (1000, 64, 64, 64, 20),
           (2500, 64, 64, 64, 2), (2500, 64, 128, 64, 1), (2000, 128, 128, 64, 2), (2000, 128, 64, 64, 2),
           (6200, 128, 64, 64, 1), (6200, 128, 128, 64, 1), (2500, 256, 128, 128, 2), (2500, 256, 64, 128, 2),
-          (1000, 256, 64, 128, 41), (2500, 256, 128, 64, 2), (900, 256, 64, 64, 70), (40, 64, 64, 64, 1), (130, 256, 128, 128, 1)]
+          (1000, 256, 64, 128, 41), (2500, 256, 128, 64, 2), (900, 256, 64, 64, 70), (40, 64, 64, 64, 1), (130, 256, 128, 128, 1),
+          (1000, 64, 128, 64, 40), (1000, 128, 128, 64, 40), (999, 64, 64, 128, 24), (600, 256, 64, 64, 700),
+          (600, 256, 128, 64, 700), (600, 256, 64, 128, 350), (600, 256, 128, 128, 350)]
 
 
 def lists(plan, seed):
