@@ -132,7 +132,7 @@ __device__ __forceinline__ void draw_in(const uint32_t (&key)[EMAX], uint32_t& l
 
 // NW wavefronts per workgroup of R = 16 rows.
 template <int D, int EMAX, bool CDF, int NW>
-__global__ void __launch_bounds__(NW * 64, (NW == 8 && EMAX <= (CDF ? 12 : 20)) ? 6 : 4) predict_mask_kernel(
+__global__ void __launch_bounds__(NW * 64, NW == 8 && EMAX <= 12 ? 6 : 4) predict_mask_kernel(
     const float* __restrict__ qbar, const float* __restrict__ kbar, int32_t* __restrict__ blk_idx,
     int32_t* __restrict__ blk_cnt, uint8_t* __restrict__ mask_dense, float* __restrict__ scores,
     int Tq, int Tb, int LD, int row_sink_begin, int row_sink_end, int sink_begin, int sink_end, int k_row,
