@@ -30,7 +30,6 @@
 // two units): step s issues the matrix products S_{s+1} and O += V P_{s-1} around the softmax
 // arithmetic of unit s.  K and V^T parts stream from global memory straight into LDS rings (3 K
 // parts, 2 V^T parts); the workgroup meets at one barrier per part (every second step).
-#include "rf2_attn_cut.h"
 #include "rf2_internal.h"
 
 #include <cfloat>
@@ -600,9 +599,8 @@ int launch_attn(const rf2_plan* plan, const void* qp, const void* kp, const void
 template <int D, int BK>
 int dispatch_rows(const rf2_plan* plan, const void* qp, const void* kp, const void* vp, const int32_t* blk_idx,
                   const int32_t* blk_cnt, void* out, float* lse, bool scatter, hipStream_t st) {
-  const rf2_attn_cut cut = rf2_cut_attn(plan->cfg, plan->info);
 #define RF2_ATTN_CASE(Q, KS) \
-  if (cut.rows == Q && cut.groups == KS) return launch_attn<D, Q, BK, KS>(plan, qp, kp, vp, blk_idx, blk_cnt, out, lse, scatter, st);
+  if (plan->cut.rows == Q && plan->cut.groups == KS) return launch_attn<D, Q, BK, KS>(plan, qp, kp, vp, blk_idx, blk_cnt, out, lse, scatter, st);
   RF2_ATTN_CASE(64, 1)
   RF2_ATTN_CASE(128, 1)
   RF2_ATTN_CASE(256, 1)

@@ -12,7 +12,12 @@
 // jobs = the launch's work in units of its longest list.  With few jobs and KS = 1 compute units stand idle, or wait for
 // the all-column sink rows of a few heads; groups shorten the longest list, and cost a merge, a common barrier and
 // half of the workgroups a compute unit holds.  Where the rows are many and short beside the longest (a long tail: video
-// with a sink frame) the jobs decide, else how the workgroups themselves fill the compute units.
+// with a sink frame) the jobs decide, else how the workgroups themselves fill the compute units: with two groups at d = 128
+// and four at d = 64 a compute unit holds one workgroup, with two at d = 64 two, and what a shader engine gets beyond that
+// waits for a whole list (rf2_busiest_engine; of 330 launches with equal rows every one with 8, or 16, workgroups at most on
+// the busiest engine gained, every one with more lost).  KS = 1 -> 2 (us), d = 128, 64-row blocks, rows of 25 parts, 25 rows x
+// 9 heads (9 on an engine) 30.8 -> 41.8, of 31 parts, 31 x 7 (7) 34.7 -> 26.7; 128-row blocks, 51 x 5 (9) 108 -> 133; d = 64,
+// 64-row blocks, 25 x 20 (17) 29.0 -> 30.6, 31 x 16 (16) 35.7 -> 26.5; KS = 1 -> 4, 128-row blocks, 51 x 5 (9) 77.8 -> 83.7.
 // Measured, KS = 1 -> 2 (us), 480p layer (rows of 40, sink rows of 256 blocks), d = 128: 1 head (51 jobs) 469 -> 332,
 // 4 heads (204) 580 -> 448, 6 heads (306) 687 -> 616, 8 heads (408) 797 -> 832, 20 heads 1,919 -> 2,060; 64-row blocks,
 // 2 heads (206) 461 -> 309, 4 heads (412) 518 -> 555.  Equal rows (3,072-token image, 24 rows of 10 blocks), d = 128:
@@ -35,22 +40,52 @@ struct rf2_attn_cut {
   int rows;         // query rows of a workgroup: those of a Q block, or 128 of 256
   int groups;       // groups of wavefronts that share a list
 };
+
+// Workgroups of a launch that its busiest shader engine gets, `share` workgroups to a row of the mask.  The hardware deals
+// workgroup g to XCD g % 8 and there to shader engine (g / 8) % 4, each of 8 compute units, as it comes; the grid's slots
+// without work (the kernel's numbering: sink rows of all heads in 8 runs, then every head's ordinary rows in 8 shares that
+// rotate with the head) take their turn too, so an engine can get more than its part of the rows.
+inline int rf2_busiest_engine(int64_t lists, int rows, int sink_rows, int share) {
+  const int plain = rows - sink_rows;
+  const int64_t sinks = lists * sink_rows, sink_slots = (sinks + 7) / 8;
+  int most = 0, of_share[8] = {}, slots = 0;
+  for (int r = 0; r < plain; ++r) ++of_share[(int64_t)r * 8 / plain];
+  for (int n : of_share) slots = std::max(slots, n);
+  for (int xcd = 0; xcd < 8; ++xcd) {
+    int load[4] = {};
+    for (int64_t s = 0; s < sink_slots + lists * slots; ++s) {
+      const int64_t t = s - sink_slots;
+      const bool work = t < 0 ? xcd * sink_slots + s < sinks : t % slots < of_share[(xcd + t / slots) & 7];
+      for (int i = 0; work && i < share; ++i) ++load[(s * share + i) & 3];
+    }
+    for (int n : load) most = std::max(most, n);
+  }
+  return most;
+}
+
 inline rf2_attn_cut rf2_cut_attn(const rf2_config& c, const rf2_info& in) {
   const int64_t lists = (int64_t)c.batch * c.heads, rows = lists * in.n_blocks, share = c.block == 256 ? 2 : 1;
-  int groups = 1;
-  const int64_t wgs = rows * share, longest = in.sink_block_end > in.sink_block_begin ? in.n_blocks_k : in.k_row;
-  const int64_t longest_parts = longest * (in.block_k / 64);
+  const int sink_rows = in.sink_block_end - in.sink_block_begin;
+  const bool known = in.kept_pairs_per_head >= 0;
+  const int64_t wgs = rows * share;
   // (cumulative mass: the lengths are not known, taken as equal)
-  const int64_t jobs = in.kept_pairs_per_head < 0 ? wgs : share * lists * in.kept_pairs_per_head / longest;
+  const int64_t longest = sink_rows > 0 ? in.n_blocks_k : in.k_row;
+  const int64_t parts = longest * (in.block_k / 64);
+  const int64_t jobs = known ? share * lists * in.kept_pairs_per_head / longest : wgs;
   const bool uneven = wgs >= 2 * jobs, tail = wgs >= 3 * jobs;
+  const int busiest = rows <= 2048 ? rf2_busiest_engine(lists, in.n_blocks, sink_rows, (int)share) : 1 << 20;
+  int groups = 1;
   if (c.head_dim == 64) {
-    if ((tail ? jobs <= 512 : uneven ? jobs <= 320 : wgs <= (c.block == 64 ? 512 : 256)) &&
-        longest_parts >= (c.block == 64 ? 4 : 12)) groups = 2;
-    if ((tail ? jobs <= 256 : wgs <= 280) && longest_parts >= (c.block == 64 ? 24 : 64)) groups = 4;
-  } else if ((tail ? jobs <= (longest_parts >= 256 ? 320 : 256) : wgs <= (uneven ? 320 : 256)) &&
-             longest_parts >= (c.block == 64 ? 4 : std::max<int64_t>(12, jobs / 6))) {
+    const bool fits = c.block == 64 ? busiest <= 16 && parts >= 4
+                                    : wgs <= 256 && parts >= (busiest <= 8 || sink_rows > 0 ? 12 : 32);
+    if (uneven ? jobs <= (tail ? 512 : 320) && parts >= (c.block == 64 ? 4 : 12) : fits) groups = 2;
+    if ((tail ? jobs <= 256 : wgs <= 280) && parts >= (c.block == 64 ? 24 : 64) &&
+        (tail || busiest <= 8 || (sink_rows > 0 && wgs <= 7 * parts)))
+      groups = 4;
+  } else if ((!uneven ? busiest <= 8 : (tail ? jobs <= (parts >= 256 ? 320 : 256) : wgs <= 320)) &&
+             parts >= (c.block == 64 ? 6 : std::max<int64_t>(12, jobs / 6))) {
     groups = 2;
   }
-  if (c.block != 256) return {c.block, groups};
-  return {groups > 1 || rows < (c.head_dim == 64 ? 2048 : 1024) ? 128 : 256, groups};
+  if (c.block != 256 || groups > 1) return {c.block == 256 ? 128 : c.block, groups};
+  return {rows < (c.head_dim == 64 ? 2048 : 1024) ? 128 : 256, 1};
 }

@@ -6,6 +6,7 @@
 #include <vector>
 
 #include "rf2.h"
+#include "rf2_attn_cut.h"
 
 struct rf2_plan {
   rf2_config cfg;
@@ -17,6 +18,7 @@ struct rf2_plan {
   int32_t* d_row_order;            // device, [8][plain_per_xcd]: ordinary Q block of each workgroup slot of a head, -1 = none
   int32_t plain_per_xcd;
   float mask_z, mask_slope;        // first guesses of the mask kernel's threshold search (rf2_mask_prepare)
+  rf2_attn_cut cut;                // how the attention launches are cut
 };
 
 // Strides (in rows of d elements) of the caller's q, k, v, o tensors: row of token n of head h of

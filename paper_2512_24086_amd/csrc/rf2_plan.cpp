@@ -154,6 +154,7 @@ int rf2_plan_create(const rf2_config* cfg, rf2_plan** out) {
     in.achieved_sparsity = -1.0;
   }
   in.workspace_bytes = 0;
+  p->cut = rf2_cut_attn(p->cfg, in);
 
   // Permutation tables from the closed form.
   try {

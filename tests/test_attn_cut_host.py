@@ -53,3 +53,16 @@ def test_the_gpu_tests_reach_every_instance(cut):
 def test_the_shapes_of_the_non_finite_tests_have_several_groups(cut):
     assert all(cut(plan_of(s))[3] > 1 for s in NONFINITE)
     assert {cut(plan_of(s))[3] for s in NONFINITE} == {2, 4}
+
+
+# (tokens, block, block_k, head_dim, heads, sparsity) -> groups, rows of equal length.  What the busiest shader engine gets is
+# behind it: at d = 128 two groups (at d = 64 four) leave one workgroup to a compute unit, 8 to an engine.
+@pytest.mark.parametrize("shape, groups", [
+    ((31 * 64, 64, 64, 128, 8, 0.0), 2), ((25 * 64, 64, 64, 128, 9, 0.0), 1), ((13 * 64, 64, 64, 128, 17, 0.0), 1),
+    ((33 * 64, 64, 64, 128, 7, 0.0), 2), ((63 * 128, 128, 128, 128, 4, 0.3), 2), ((51 * 128, 128, 128, 128, 5, 0.3), 1),
+    ((31 * 64, 64, 64, 64, 16, 0.5), 2), ((25 * 64, 64, 64, 64, 20, 0.5), 1), ((63 * 64, 64, 64, 64, 4, 0.3), 4),
+    ((85 * 64, 64, 64, 64, 3, 0.3), 2), ((63 * 128, 128, 64, 64, 4, 0.3), 4), ((51 * 128, 128, 64, 64, 5, 0.3), 2)],
+    ids=lambda x: "x".join(map(str, x)) if isinstance(x, tuple) else str(x))
+def test_groups_only_where_every_engine_has_room(cut, shape, groups):
+    *shape, sparsity = shape
+    assert cut(plan_of(shape, sparsity=sparsity))[3] == groups
