@@ -15,7 +15,7 @@
 // with a sink frame) the jobs decide, else how the workgroups themselves fill the compute units: with two groups at d = 128
 // and four at d = 64 a compute unit holds one workgroup, with two at d = 64 two, and what a shader engine gets beyond that
 // waits for a whole list (rf2_busiest_engine; of 330 launches with equal rows every one with 8, or 16, workgroups at most on
-// the busiest engine gained, every one with more lost).  KS = 1 -> 2 (us), d = 128, 64-row blocks, rows of 25 parts, 25 rows x
+// the busiest engine gained, with more all lost or gained 2 % at most).  KS = 1 -> 2 (us), d = 128, 64-row blocks, rows of 25 parts, 25 rows x
 // 9 heads (9 on an engine) 30.8 -> 41.8, of 31 parts, 31 x 7 (7) 34.7 -> 26.7; 128-row blocks, 51 x 5 (9) 108 -> 133; d = 64,
 // 64-row blocks, 25 x 20 (17) 29.0 -> 30.6, 31 x 16 (16) 35.7 -> 26.5; KS = 1 -> 4, 128-row blocks, 51 x 5 (9) 77.8 -> 83.7.
 // Measured, KS = 1 -> 2 (us), 480p layer (rows of 40, sink rows of 256 blocks), d = 128: 1 head (51 jobs) 469 -> 332,
@@ -26,6 +26,12 @@
 // d = 64 holds twice the workgroups: 480p, 306 jobs 483 -> 374, 408 jobs 543 -> 480, 510 jobs 613 -> 602, 714 jobs 792 ->
 // 817; equal rows, 64-row blocks, 384 workgroups 24.0 -> 18.7, 576 25.4 -> 27.6, 128-row blocks 192 18.2 -> 15.8, 288 23.7 ->
 // 24.2; with text, 64-row blocks, 300 jobs 33.2 -> 31.1, 360 34.9 -> 35.6.
+// A workgroup that shares a compute unit with fewer others is the dearer the shorter its own list is: with a tail, the
+// workgroups may be 13 times as many as the longest list has parts (d = 128; 24 and 32 at d = 64 with 128- and 64-row blocks, 7 for
+// KS = 4).  KS = 1 -> 2 (us), text images, 64-row blocks, d = 128, 750 workgroups, 75 parts (10) 1.53 times as fast, 792, 66
+// parts (12) 1.16, 816, 51 parts (16) 55.3 -> 58.8, 760, 38 parts (20) 44.4 -> 50.3; 128-row blocks, 936, 77 (12) 89.2 -> 78.7,
+// 896, 56 (16) 64.4 -> 66.7; d = 64, 64-row blocks, 1,440, 45 (32) 1.16 times, 4,800, 120 (40) 94.6 -> 113; KS = 2 -> 4, 744, 124
+// (6) 1.17 times, 1,056, 132 (8) 0.82, 1,480, 74 (20) 40.6 -> 65.2 (KS = 1: 54.5).
 // KS = 4 against 2 (us): 480p, 51 jobs 250 -> 204, 204 jobs 313 -> 288; 64-row blocks 180 -> 133; with text, 64-row blocks,
 // 264 workgroups 28.8 -> 26.0, 312 20.9 -> 24.5; but rows of 20 parts, 128-row blocks 14.5 -> 17.2.
 // A list has to be long enough to pay for the merge (equal rows of 64-key parts, KS = 1 -> 2, us): d = 128, 64 workgroups,
@@ -78,11 +84,12 @@ inline rf2_attn_cut rf2_cut_attn(const rf2_config& c, const rf2_info& in) {
   if (c.head_dim == 64) {
     const bool fits = c.block == 64 ? busiest <= 16 && parts >= 4
                                     : wgs <= 256 && parts >= (busiest <= 8 || sink_rows > 0 ? 12 : 32);
-    if (uneven ? jobs <= (tail ? 512 : 320) && parts >= (c.block == 64 ? 4 : 12) : fits) groups = 2;
+    const bool pays = jobs <= (!tail ? 320 : c.block == 64 ? 512 : 448) && wgs <= (c.block == 64 ? 32 : 24) * parts;
+    if (uneven ? pays && parts >= (c.block == 64 ? 4 : 12) : fits) groups = 2;
     if ((tail ? jobs <= 256 : wgs <= 280) && parts >= (c.block == 64 ? 24 : 64) &&
-        (tail || busiest <= 8 || (sink_rows > 0 && wgs <= 7 * parts)))
+        (busiest <= 8 || (sink_rows > 0 && wgs <= 7 * parts)))
       groups = 4;
-  } else if ((!uneven ? busiest <= 8 : (tail ? jobs <= (parts >= 256 ? 320 : 256) : wgs <= 320)) &&
+  } else if ((!uneven ? busiest <= 8 : wgs <= 13 * parts && (tail ? jobs <= (parts >= 256 ? 320 : 256) : wgs <= 320)) &&
              parts >= (c.block == 64 ? 6 : std::max<int64_t>(12, jobs / 6))) {
     groups = 2;
   }

@@ -66,3 +66,18 @@ def test_the_shapes_of_the_non_finite_tests_have_several_groups(cut):
 def test_groups_only_where_every_engine_has_room(cut, shape, groups):
     *shape, sparsity = shape
     assert cut(plan_of(shape, sparsity=sparsity))[3] == groups
+
+
+def video(**kw):
+    return rf2.Plan(**dict(dict(batch=1, heads=20, head_dim=128, T=1, H=1, W=1, block=64, sparsity=0.8), **kw))
+
+
+# many short rows beside a few all-column ones: workgroups by parts of the longest list decide
+@pytest.mark.parametrize("kw, groups", [
+    (dict(head_dim=64, H=53, W=77, text_tokens=269, sparsity=0.82), 2),              # 1,360 workgroups, 68 parts
+    (dict(head_dim=64, H=43, W=102, heads=4, text_tokens=222, sparsity=0.86), 4),    # 288, 72
+    (dict(head_dim=64, H=86, W=86, heads=40, text_tokens=244, sparsity=0.91, block_k=128), 1),     # 4,800, 120
+    (dict(H=31, W=71, text_tokens=194, sparsity=0.77), 1),                           # 760, 38
+    (dict(H=57, W=75, heads=10, text_tokens=300, sparsity=0.85), 2)])                # 720, 72
+def test_groups_only_where_short_rows_are_few_beside_the_longest_list(cut, kw, groups):
+    assert cut(video(**kw))[3] == groups
