@@ -81,3 +81,11 @@ def video(**kw):
     (dict(H=57, W=75, heads=10, text_tokens=300, sparsity=0.85), 2)])                # 720, 72
 def test_groups_only_where_short_rows_are_few_beside_the_longest_list(cut, kw, groups):
     assert cut(video(**kw))[3] == groups
+
+
+# cumulative mass, equal rows: the threshold says how many of the columns a flat row keeps
+@pytest.mark.parametrize("shape, tau, groups", [
+    ((29 * 64, 128, 64, 128, 2), 0.1, 1), ((29 * 64, 128, 64, 128, 2), 0.9, 2), ((25 * 64, 64, 64, 64, 1), 0.1, 1),
+    ((71 * 64, 64, 64, 64, 5), 0.1, 1), ((71 * 64, 64, 64, 64, 3), 0.9, 4), ((12 * 64, 128, 64, 64, 2), 0.1, 1)])
+def test_groups_of_cumulative_mass_launches_follow_the_threshold(cut, shape, tau, groups):
+    assert cut(plan_of(shape, cdf_threshold=tau))[3] == groups
