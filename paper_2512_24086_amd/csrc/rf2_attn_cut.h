@@ -26,12 +26,13 @@
 // d = 64 holds twice the workgroups: 480p, 306 jobs 483 -> 374, 408 jobs 543 -> 480, 510 jobs 613 -> 602, 714 jobs 792 ->
 // 817; equal rows, 64-row blocks, 384 workgroups 24.0 -> 18.7, 576 25.4 -> 27.6, 128-row blocks 192 18.2 -> 15.8, 288 23.7 ->
 // 24.2; with text, 64-row blocks, 300 jobs 33.2 -> 31.1, 360 34.9 -> 35.6.
-// A workgroup that shares a compute unit with fewer others is the dearer the shorter its own list is: with a tail, the
-// workgroups may be 13 times as many as the longest list has parts (d = 128; 24 and 32 at d = 64 with 128- and 64-row blocks, 7 for
-// KS = 4).  KS = 1 -> 2 (us), text images, 64-row blocks, d = 128, 750 workgroups, 75 parts (10) 1.53 times as fast, 792, 66
-// parts (12) 1.16, 816, 51 parts (16) 55.3 -> 58.8, 760, 38 parts (20) 44.4 -> 50.3; 128-row blocks, 936, 77 (12) 89.2 -> 78.7,
-// 896, 56 (16) 64.4 -> 66.7; d = 64, 64-row blocks, 1,440, 45 (32) 1.16 times, 4,800, 120 (40) 94.6 -> 113; KS = 2 -> 4, 744, 124
-// (6) 1.17 times, 1,056, 132 (8) 0.82, 1,480, 74 (20) 40.6 -> 65.2 (KS = 1: 54.5).
+// A workgroup that shares a compute unit with fewer others is the dearer the shorter its own list is: the workgroups may be 13
+// times as many as the longest list has parts (d = 128; at d = 64 12 to 32 times by the work, 7 for KS = 4).  KS = 1 -> 2 (us),
+// d = 128, images with text, 64-row blocks, 750 workgroups, 75 parts (10 times) 1.53 times as fast, 792, 66 parts (12) 1.16, 816,
+// 51 parts (16) 55.3 -> 58.8, 760, 38 parts (20) 44.4 -> 50.3; 128-row blocks, 936, 77 (12) 89.2 -> 78.7, 896, 56 (16) 64.4 ->
+// 66.7; d = 64, 64-row blocks, 186 jobs (32) 1.16 times, 317 (24) 1.27, 324 (24) 1.20, 408 (20) 1.14, 442 (24) 1.03, 366 (32) 44.4 -> 45.9, 430 (40) 94.6 ->
+// 113; without a tail, 295 (16) 1.15, 314 (24) 25.3 -> 29.2; 128-row blocks, 311 (20) 1.07, 369 (20) 1.05, 403 (2.5) 1.13, 436 (20)
+// 113 -> 117; KS = 2 -> 4, 744 workgroups, 124 parts (6) 1.17 times, 1,056, 132 (8) 0.82, 1,480, 74 (20) 40.6 -> 65.2 (KS = 1: 54.5).
 // KS = 4 against 2 (us): 480p, 51 jobs 250 -> 204, 204 jobs 313 -> 288; 64-row blocks 180 -> 133; with text, 64-row blocks,
 // 264 workgroups 28.8 -> 26.0, 312 20.9 -> 24.5; but rows of 20 parts, 128-row blocks 14.5 -> 17.2.
 // A list has to be long enough to pay for the merge (equal rows of 64-key parts, KS = 1 -> 2, us): d = 128, 64 workgroups,
@@ -88,7 +89,8 @@ inline rf2_attn_cut rf2_cut_attn(const rf2_config& c, const rf2_info& in) {
   if (c.head_dim == 64) {
     const bool fits = c.block == 64 ? busiest <= 16 && parts >= 4
                                     : wgs <= 256 && parts >= (busiest <= 8 || sink_rows > 0 ? 12 : 32);
-    const bool pays = jobs <= (!tail ? 320 : c.block == 64 ? 512 : 448) && wgs <= (c.block == 64 ? 32 : 24) * parts;
+    const int times = !tail ? 20 : c.block == 64 ? (jobs <= 320 ? 32 : 24) : (jobs <= 400 ? 24 : 12);
+    const bool pays = jobs <= (tail ? 512 : 320) && wgs <= times * parts;
     if (uneven ? pays && parts >= (c.block == 64 ? 4 : 12) : fits) groups = 2;
     if ((tail ? jobs <= 256 : wgs <= 280) && parts >= (c.block == 64 ? 24 : 64) &&
         (busiest <= 8 || (sink_rows > 0 && wgs <= 7 * parts)))

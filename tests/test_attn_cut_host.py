@@ -78,6 +78,8 @@ def video(**kw):
     (dict(head_dim=64, H=43, W=102, heads=4, text_tokens=222, sparsity=0.86), 4),    # 288, 72
     (dict(head_dim=64, H=86, W=86, heads=40, text_tokens=244, sparsity=0.91, block_k=128), 1),     # 4,800, 120
     (dict(H=31, W=71, text_tokens=194, sparsity=0.77), 1),                           # 760, 38
+    (dict(head_dim=64, T=26, H=5, W=13, heads=24, sink_frames=1, sparsity=0.51), 1), # 648, 27, hardly a tail
+    (dict(head_dim=64, T=26, H=12, W=10, heads=32, sink_frames=1, sparsity=0.76), 1),        # 1,568, 49
     (dict(H=57, W=75, heads=10, text_tokens=300, sparsity=0.85), 2)])                # 720, 72
 def test_groups_only_where_short_rows_are_few_beside_the_longest_list(cut, kw, groups):
     assert cut(video(**kw))[3] == groups
