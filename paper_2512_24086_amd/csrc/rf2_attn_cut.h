@@ -42,7 +42,11 @@
 // blocks, 32 parts 21.9 -> 21.8, 64 parts 36.0 -> 33.2; 64-row blocks, 16 parts 10.8 -> 10.9.
 // 256-row blocks, one workgroup -> two (us): d = 128, 512 workgroups 683 -> 586 (KS = 2: 452), 760: 576 -> 516, 480 of equal
 // length 101 -> 92, 1,024: 813 -> 827, 5,120: 3,830 -> 3,914 (the larger one reads K and V less often); d = 64,
-// 1,024: 597 -> 534, 1,280: 641 -> 607, 2,560: 1,115 -> 1,128.
+// 1,024: 597 -> 534, 1,280: 641 -> 607, 2,560: 1,115 -> 1,128.  Rows of equal length gain only where the halves fill the compute
+// units better (a compute unit holds one whole block at d = 128, two at d = 64, twice as many halves): 65 rows of 130 parts, d =
+// 128, 166 -> 125, 130 rows 170 -> 176, 260 381 -> 347, 390 401 -> 412, 455 424 -> 436, 520 607 -> 577, 650 617 -> 645; d = 64, 65
+// 118 -> 92, 195 123 -> 129, 260 217 -> 183, 390 233 -> 251, 455 247 -> 263, 520 361 -> 329.  Lists under 20 parts always gain, 3 % or
+// more; at d = 64 the halves of long sequences read past an XCD's L2 (16,640 tokens 404 -> 338, 31,160 tokens 237 -> 252).
 struct rf2_attn_cut {
   int rows;         // query rows of a workgroup: those of a Q block, or 128 of 256
   int groups;       // groups of wavefronts that share a list
@@ -100,5 +104,12 @@ inline rf2_attn_cut rf2_cut_attn(const rf2_config& c, const rf2_info& in) {
     groups = 2;
   }
   if (c.block != 256 || groups > 1) return {c.block == 256 ? 128 : c.block, groups};
-  return {rows < (c.head_dim == 64 ? 2048 : 1024) ? 128 : 256, 1};
+  const int64_t limit = c.head_dim == 64 ? 2048 : 1024;
+  if (rows >= limit) return {256, 1};
+  // (cumulative mass with sink rows: spread where a flat ordinary row keeps less than half of the columns)
+  const bool spread = known ? uneven : sink_rows > 0 && c.cdf_threshold * (1.0f + c.cdf_threshold) < 1.0f;
+  const int whole = rf2_busiest_engine(lists, in.n_blocks, sink_rows, 1);
+  const bool full = c.head_dim == 64 ? (whole > 4 && whole < 8) || (whole > 11 && whole <= 16) || (whole > 8 && in.N > 19456)
+                                     : (busiest + 7) / 8 >= 2 * ((whole + 7) / 8);
+  return {full && parts >= 20 && !spread ? 256 : 128, 1};
 }

@@ -91,3 +91,13 @@ def test_groups_only_where_short_rows_are_few_beside_the_longest_list(cut, kw, g
     ((71 * 64, 64, 64, 64, 5), 0.1, 1), ((71 * 64, 64, 64, 64, 3), 0.9, 4), ((12 * 64, 128, 64, 64, 2), 0.1, 1)])
 def test_groups_of_cumulative_mass_launches_follow_the_threshold(cut, shape, tau, groups):
     assert cut(plan_of(shape, cdf_threshold=tau))[3] == groups
+
+
+# 256-row Q blocks of equal length: two workgroups each where that fills the compute units better
+@pytest.mark.parametrize("shape, rows", [
+    ((65 * 256, 256, 128, 128, 1), 128), ((33 * 256, 256, 128, 128, 5), 256), ((65 * 256, 256, 128, 128, 4), 128),
+    ((65 * 256, 256, 128, 128, 6), 256), ((9 * 256, 256, 128, 128, 14), 128), ((33 * 256, 256, 128, 128, 40), 256),
+    ((65 * 256, 256, 128, 64, 3), 256), ((65 * 256, 256, 128, 64, 4), 128), ((65 * 256, 256, 128, 64, 6), 256),
+    ((122 * 256, 256, 128, 64, 5), 256), ((65 * 256, 256, 128, 64, 40), 256)])
+def test_halves_only_where_they_fill_the_compute_units_better(cut, shape, rows):
+    assert cut(plan_of(shape, sparsity=0.5))[1] == rows
