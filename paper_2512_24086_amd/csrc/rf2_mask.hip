@@ -12,12 +12,13 @@
 // matrix cores at full rate, the search and the emission about as much of the vector and of the
 // scalar issue slots; a workgroup is a chain of load, multiply, search and store, so what counts is how
 // many of them a compute unit holds.  The Q operand is read from LDS and the K operand is
-// reloaded in place, which keeps a wavefront within 80 registers: six wavefronts per SIMD (four
-// wavefronts of 110 registers before).  A probe of the search costs a compare and a population count per 64
-// keys; the normal-distribution guess and interpolation need 4.2 of them a row on that layer where a bitwise
-// search that stops at the first exact count needs 15.5.  720p: 104 -> 72 us; cumulative mass on the
-// long video (929 x 929, 24 heads): 291 -> 140 us; with few workgroups 12-50 -> 8-15 us.  Wavefronts that
-// share a K tile (32, 48 or 64 rows per workgroup) halve the L2 reads and are slower (98-122 us on 720p).
+// reloaded in place, which keeps a wavefront of up to 768 columns within 80 registers: six wavefronts per SIMD where LDS
+// holds three workgroups of eight (up to about 690 columns; two from there, one from about 1,130).  A probe of the
+// search costs a compare and a population count per 64 keys; on bell-shaped rows, as smooth fields give, the
+// normal-distribution guess and interpolation need 4 or 5 of them where a bitwise search that stops at the first exact
+// count needs 15.5 (other rows: see MAX_GUIDED).  720p: 104 -> 70 us; cumulative mass on the long video (929 x 929, 24
+// heads): 291 -> 143 us; with few workgroups 12-50 -> 8-15 us.  Wavefronts that share a K tile (32, 48 or 64 rows per
+// workgroup) halve the L2 reads and are slower (98-122 us on 720p).
 #include "rf2_internal.h"
 
 #include <algorithm>
@@ -106,10 +107,12 @@ constexpr uint32_t PAST_KEY = 0u, SINK_KEY = 0xffffffffu;
 // A search keeps a bracket [lo, top] around the threshold.  Its first two probes come from the guesses, then the measure
 // (count or mass) is interpolated between the ends, or the bracket halved where that has not halved its keys.  Where
 // scores are not bell-shaped (outliers, several levels, many magnitudes) interpolation gains little: after MAX_GUIDED
-// probes, for counts also after three in a row that leave more than half of the bracket's keys, the bracket is drawn in to
-// the keys it holds and its integer range halved, at a third of the time for a count (a mass costs more than its
-// guess), and drawn in again every TIGHTEN probes (equal scores end there).  Whatever the probes are, the threshold found
-// is the same.
+// probes, for counts also after three in a row that leave more than half of the bracket's keys, the bracket's integer range
+// is halved, at a third of the time for a count (a mass costs more than its guess), and every TIGHTEN probes it is drawn in to
+// the keys it holds (equal scores end there).  Whatever the probes are, the threshold found is the same.
+// (720p, 40 heads, us, bitwise search -> with up to 12 guided probes and none of this -> now: scores all equal 126 -> 192 -> 69,
+// over many magnitudes 99 -> 128 -> 83, one column in ten far above 101 -> 130 -> 90, smooth fields 104 -> 72 -> 70; cumulative
+// mass, four levels 171 -> 205 -> 109, smooth fields 170 -> 95 -> 95)
 constexpr int TIGHTEN = 8;
 __device__ __forceinline__ uint32_t halfway(uint32_t lo, uint32_t top) { return lo + ((top - lo) >> 1) + 1u; }
 __device__ __forceinline__ uint32_t next_probe(float t, uint32_t lo, uint32_t top) {
@@ -130,7 +133,7 @@ __device__ __forceinline__ void draw_in(const uint32_t (&key)[EMAX], uint32_t& l
   top = wave_max_u(most);
 }
 
-// NW wavefronts per workgroup of R = 16 rows.
+// NW wavefronts per workgroup of R = 16 rows.  (Second launch bound: beyond 768 columns LDS holds two workgroups at most.)
 template <int D, int EMAX, bool CDF, int NW>
 __global__ void __launch_bounds__(NW * 64, NW == 8 && EMAX <= 12 ? 6 : 4) predict_mask_kernel(
     const float* __restrict__ qbar, const float* __restrict__ kbar, int32_t* __restrict__ blk_idx,
@@ -139,7 +142,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 && EMAX <= 12 ? 6 : 4) predic
     float tau, float scale_log2, Guess guess, int n_strips, int n_work) {
   // Tb, sink_begin, sink_end describe the COLUMNS (K blocks) from here on; rows use Tq and row_sink_*.
   constexpr int R = 16;
-  constexpr int MAX_GUIDED = CDF ? 12 : 8;
+  constexpr int MAX_GUIDED = CDF ? 10 : 8;
   extern __shared__ __attribute__((aligned(16))) uint32_t keys[];   // [R][LD]
   __shared__ float stat[NW][R][2];                                  // sum and sum of squares over a wavefront's columns
   __shared__ __attribute__((aligned(16))) float qs[R][D + 4];       // (+4: the 16 rows of an operand read start in different banks)
@@ -319,7 +322,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 && EMAX <= 12 ? 6 : 4) predic
         else t = fl + (fh - fl) * (halve ? 0.5f : (m_lo - target) / (m_lo - m_top));
       }
       for (int p = 0; n_lo - n_top > 1 && lo < top; ++p) {
-        if (p % TIGHTEN == 0) draw_in(key, lo, top);
+        if (p % TIGHTEN == TIGHTEN / 2) draw_in(key, lo, top);    // (first after four: mostly two or three are left to do)
         if (lo < top) probe(halfway(lo, top));
       }
       T = lo - 1u;                                    // (where the sums are no numbers lo is the least key at most: all are kept)
@@ -392,7 +395,7 @@ MaskLaunch mask_launch(const rf2_plan* plan) {
   m.LD = (plan->info.n_blocks_k + 15) / 16 * 16 + 4;   // +4: the 4 row groups of a tile store hit distinct banks
   m.lds = (size_t)16 * m.LD * sizeof(uint32_t);
   // Up to one workgroup per compute unit a row's search is latency: 16 wavefronts search one row each.  Beyond, a
-  // compute unit holds three workgroups of 8 wavefronts but only one of 16.  (16 against 8 wavefronts: 9.5 / 10.3 us
+  // compute unit holds three workgroups of 8 wavefronts but only one of 16 (up to about 690 columns: LDS).  (16 against 8 wavefronts: 9.5 / 10.3 us
   // at 28 workgroups, 12.4 / 13.0 at 35, 20.3 / 21.2 at 136; 21.2 / 19.7 us at 320, 92 / 72 us at 1,480.)
   const int64_t strips = (int64_t)((plan->info.n_blocks + 15) / 16) * plan->cfg.batch * plan->cfg.heads;
   m.NW = strips <= 256 ? 16 : 8;
