@@ -214,6 +214,9 @@ int rf2_predict_mask(const rf2_plan* plan, const float* qbar, const float* kbar,
  *             (wrong values, never a fault).  Keys past N are masked only when the
  *             ragged last block is the LAST entry of its list, as it is in ascending
  *             lists.                                                       (in)
+ *             The order in which a list is summed follows the sizes of the plan, B * Hh among them (a
+ *             launch of few heads shares a list among wavefronts): the same call gives the same bits each time, a
+ *             head computed in a call of another B * Hh the same values up to fp32 rounding.
  *   op      : [B, Hh, N_pad, d] bf16 in permuted order; rows >= N unspecified (out)
  *   lse     : optional [B, Hh, N_pad] fp32 natural-log sum-exp of the scaled
  *             logits over the kept keys, may be NULL                       (out)

@@ -471,7 +471,8 @@ __global__ void __launch_bounds__(BQ * 2 * KS, D == 64 ? (BQ == 128 ? 4 : 2) : (
     // ---- steady state: two steps per part ---------------------------------------------------
     int k0 = 0, k1 = 1;                                   // K ring slots of parts P and P+1
     int vm = C::NV - 1, vc = 0;                           // V^T ring slots of parts P-1 and P
-    // (the loop starts on a 64-byte line of the instruction cache: +0.2 ... +0.8 % against where it otherwise falls)
+    // (the loop starts on a 64-byte line of the instruction cache: against where it otherwise falls, pairs of runs of both
+    // builds, 720p and a 256-row clip +0.5 ... +1.0 %, long video +0.1 ... +0.7, 480p and d = 64 0, 64-row blocks -0.4)
     asm volatile(".p2align 6");
     for (int s = 0; s < U; s += 2) {
       // even step: S of unit s+1 (part P, tile 1), V P of unit s-1 (part P-1, tile 1)

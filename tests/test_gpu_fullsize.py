@@ -197,8 +197,8 @@ def test_constant_values_give_constant_output(big):
 
 
 def test_maximum_number_of_heads():
-    """B x Hh = 65,535, the most a plan accepts (the second grid dimension of the permutation and mask
-    launches): five seeded heads repeated 13,107 times.  The five are checked against the oracle; every
+    """B x Hh = 65,535, the most a plan accepts (the second grid dimension of the inverse permutation; the other
+    launches number the heads themselves): five seeded heads repeated 13,107 times.  The five are checked against the oracle; every
     repetition must equal the first one bit for bit (same inputs, deterministic kernels)."""
     base = inputs.Workload("limit_heads", 8, 1, 5, 64, 8, 8, 8, 64, 0.5, 1, 0.3)
     reps = 13107

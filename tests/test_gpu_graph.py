@@ -1,4 +1,4 @@
-"""The layer as a HIP graph: its five launches are recorded once and replayed on new inputs.
+"""The layer as a HIP graph: its three launches are recorded once and replayed on new inputs.
 Every replay is checked bit for bit against an eager run, with eager work and synchronisations
 between the replays (the entry points allocate nothing and record no memset nodes)."""
 import pytest
