@@ -1,10 +1,13 @@
 // Block-sparse flash attention (Sec. 3.1, eqs. 1-4 with the block skip rule) for gfx950.
 //
+// Two kernels with the same arithmetic: block_sparse_attn_kernel (d = 64; K and V^T in LDS rings, described first) and
+// stream_attn_kernel (d = 128; operands from memory into registers, described where it begins).
+//
 // One workgroup owns one Q block (b_q rows, or 128 of 256) of one (batch, head) and walks that row's
 // list of kept K/V blocks (b_k rows each; b_q and b_k may differ).  Every wavefront owns 32 query rows
-// and sees all keys of the list, so there is nothing to merge at the end; a workgroup needs at most 80 KiB
-// of LDS and 256 registers per lane, so two workgroups share a compute unit (two wavefronts per
-// SIMD) and each hides the barriers, LDS latencies and vector-ALU phases of the other.
+// and sees all keys of the list, so there is nothing to merge at the end; a workgroup needs 40 KiB
+// of LDS and 128 registers per lane (d = 64), so four workgroups share a compute unit (four wavefronts per
+// SIMD) and each hides the barriers, LDS latencies and vector-ALU phases of the others.
 // Launches that would leave compute units idle or wait for a few long lists instead give a list to KS such
 // groups of wavefronts, each with a contiguous share of it and with rings of its own, which merge their
 // results through LDS (rf2_attn_cut.h has the rule and the measurements).
@@ -41,6 +44,7 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 // BQ rows per Q block (one workgroup), BK rows per K/V block (Sec. 3.1: b_q and b_k).
 // KS groups of NW wavefronts walk a contiguous share of the row's list each and merge at the end.
@@ -138,50 +142,60 @@ __device__ __forceinline__ void ring_barrier() {
   asm volatile("" ::: "memory");
 }
 
-// (second launch bound: wavefronts per SIMD the register budget is sized for, which is what LDS admits: two
-// workgroups of 80 KiB rings per compute unit at d = 128, four of 40 KiB at d = 64, whatever KS; a 64-row Q block has
-// two wavefronts per group; a 256-row Q block of d = 128 is one workgroup of eight wavefronts per compute unit)
+// Head and Q block of a workgroup, from its XCD and its number there.  False: no work.
+// Workgroups with equal blockIdx % 8 share an XCD (which of the eight it is varies from launch to launch).  Slots of an XCD, in
+// issue order: the all-column sink rows of every head first, then the ordinary rows head by head.  A sink row is several times
+// longer than an ordinary one; issued first (longest jobs first) none of them is left running alone at the end, and the short
+// rows fill the tail evenly.
+struct RowOrder {
+  const int32_t* shares;       // [8][per_xcd]: ordinary Q block of each slot of a head, -1 = none; null: rows in one run
+  int per_xcd;                 // slots of a head on an XCD, or of all heads
+  int n_bh, rows, sink_begin, n_sink, sink_slots;
+};
+__device__ __forceinline__ bool row_of(const RowOrder& w, int xcd, int slot, int& bh, int& qi) {
+  if (slot < w.sink_slots) {
+    // The sink rows of all heads, numbered head by head, are cut into 8 contiguous runs of sink_slots rows, one per XCD: an
+    // XCD gets whole heads where it can (with 40 heads of 29 sink rows: five heads each).  Rows of one head have the same
+    // list (every column) and the same length: side by side on one XCD they run in step and find each other's tiles in its L2.
+    const int g = xcd * w.sink_slots + slot;
+    bh = g / w.n_sink;
+    qi = w.sink_begin + g % w.n_sink;
+    return g < w.n_bh * w.n_sink;
+  }
+  const int t = slot - w.sink_slots;
+  if (w.shares == nullptr) {     // the ordinary rows likewise (see rf2_cut_stream)
+    const int plain = w.rows - w.n_sink, g = xcd * w.per_xcd + t;
+    bh = g / plain;
+    qi = g % plain;
+    qi += qi >= w.sink_begin ? w.n_sink : 0;
+    return g < w.n_bh * plain;
+  }
+  // The work table deals a head's ordinary rows to 8 shares of slightly different size (contiguous ranges); the share an XCD
+  // takes rotates with the head so that no XCD collects the large shares of every head.
+  bh = t / w.per_xcd;
+  qi = w.shares[((xcd + bh) & 7) * w.per_xcd + t % w.per_xcd];
+  return qi >= 0;
+}
+
+// (second launch bound: wavefronts per SIMD the register budget is sized for, which is what LDS admits: four workgroups of
+// 40 KiB rings per compute unit, whatever KS; a 64-row Q block has two wavefronts per group)
 template <int D, int BQ, int BK, int KS>
-__global__ void __launch_bounds__(BQ * 2 * KS, D == 64 ? (BQ == 128 ? 4 : 2) : (BQ >= 128 ? 2 : 1)) block_sparse_attn_kernel(
+__global__ void __launch_bounds__(BQ * 2 * KS, BQ == 128 ? 4 : 2) block_sparse_attn_kernel(
     const __bf16* __restrict__ qp, const __bf16* __restrict__ kp, const __bf16* __restrict__ vp,
     const int32_t* __restrict__ blk_idx, const int32_t* __restrict__ blk_cnt, __bf16* __restrict__ op,
-    float* __restrict__ lse, const int32_t* __restrict__ row_order, int plain_per_xcd, int n_bh, int sink_row_begin,
-    int n_sink_rows, int sink_slots,
-    int Tq, int Tb, int k_row, int last_valid, float scale_log2, const int32_t* __restrict__ scatter, int n_tokens,
+    float* __restrict__ lse, RowOrder order, int Tb, int k_row, int last_valid, float scale_log2, const int32_t* __restrict__ scatter, int n_tokens,
     int heads, rf2_strides st, int split) {
   // split: log2 of the workgroups that share a list (a Q block of the mask has BQ << split rows); they are neighbours
-  // on one XCD.  Tq: Q blocks per head (rows of the block mask); Tb: K/V blocks per head (its columns); last_valid:
-  // tokens in the last K/V block.
+  // on one XCD.  Tb: K/V blocks per head (columns of the block mask); last_valid: tokens in the last one.
   using C = AttnCfg<D, BQ, BK, KS>;
   // Part P lives in slot P % NK of the K ring (first) and slot P % NV of the V^T ring (behind it).
   __shared__ __attribute__((aligned(1024))) unsigned char ring[KS * C::RING_BYTES];
   constexpr uint32_t VRING = C::NK * C::PART_BYTES;
 
-  // ---- which Q block ---------------------------------------------------------------
-  // Slots of an XCD, in issue order: the all-column sink rows of every head first, then the ordinary
-  // rows head by head.  A sink row is several times longer than an ordinary one; issued first (longest
-  // jobs first) none of them is left running alone at the end, and the short rows fill the tail evenly.
-  // (workgroups with equal blockIdx % 8 share an XCD; which of the eight it is varies from launch to launch)
   const int xcd = blockIdx.x & 7, share = (int)(blockIdx.x >> 3) & ((1 << split) - 1), slot = (int)(blockIdx.x >> 3) >> split;
   int bh, qi;
-  if (slot < sink_slots) {
-    // The sink rows of all heads, numbered head by head, are cut into 8 contiguous runs of sink_slots
-    // rows, one per XCD: an XCD gets whole heads where it can (with 40 heads of 29 sink rows: five heads
-    // each).  Rows of one head have the same list (every column) and the same length: side by side on
-    // one XCD they run in step and find each other's tiles in its L2.
-    const int g = xcd * sink_slots + slot;
-    if (g >= n_bh * n_sink_rows) return;
-    bh = g / n_sink_rows;
-    qi = sink_row_begin + g % n_sink_rows;
-  } else {
-    // The work table deals a head's ordinary rows to 8 shares of slightly different size (contiguous
-    // ranges); the share an XCD takes rotates with the head so that no XCD collects the large shares of
-    // every head.
-    const int t = slot - sink_slots;
-    bh = t / plain_per_xcd;
-    qi = row_order[((xcd + bh) & 7) * plain_per_xcd + t % plain_per_xcd];
-    if (qi < 0) return;
-  }
+  if (!row_of(order, xcd, slot, bh, qi)) return;
+  const int Tq = order.rows;
   const size_t row_id = (size_t)bh * Tq + qi;
   int cnt = blk_cnt[row_id];
   const bool dense = (cnt == Tb);
@@ -411,13 +425,9 @@ __global__ void __launch_bounds__(BQ * 2 * KS, D == 64 ? (BQ == 128 ? 4 : 2) : (
         }
       }
       if constexpr (ODD) {
-        // at d = 128 the loads go into the slots of the second product (measured: +0.5 % over issuing them
-        // from slot 0 on; at d = 64, where a step has half as many slots, -1.4 %), V^T first
-        constexpr int G0 = (D == 128 && NQ + 2 * C::LPW <= NSLOT) ? NQ : 0;
-        const int gl = g - G0;
-        if (gl >= 0 && gl < C::LPW) dma_one(v_dst + gl * (C::NW * 1024), vbase + gl * (C::NW * 1024), v_voff);
-        else if (gl >= C::LPW && gl < 2 * C::LPW)
-          dma_one(k_dst + (gl - C::LPW) * (C::NW * 1024), kbase + (gl - C::LPW) * (C::NW * 1024), k_voff);
+        // from slot 0 on (-1.4 % from the slots of the second product on), V^T first
+        if (g < C::LPW) dma_one(v_dst + g * (C::NW * 1024), vbase + g * (C::NW * 1024), v_voff);
+        else if (g < 2 * C::LPW) dma_one(k_dst + (g - C::LPW) * (C::NW * 1024), kbase + (g - C::LPW) * (C::NW * 1024), k_voff);
       }
       // Slots stay in this order: the operand reads keep their PD-slot lead over the MFMAs that
       // consume them (left alone, the scheduler packs each read right in front of its consumer).
@@ -575,51 +585,461 @@ __global__ void __launch_bounds__(BQ * 2 * KS, D == 64 ? (BQ == 128 ? 4 : 2) : (
         m_ref * scale_log2 * 0.6931471805599453f + __logf(l_tot);
 }
 
-template <int D, int BQ, int BK, int KS>
-int launch_attn(const rf2_plan* plan, const void* qp, const void* kp, const void* vp, const int32_t* blk_idx,
-                const int32_t* blk_cnt, void* op, float* lse, bool scatter, hipStream_t st) {
-  using C = AttnCfg<D, BQ, BK, KS>;
-  const rf2_config& c = plan->cfg;
+// ==== d = 128: operands from memory into registers ===============================================================
+//
+// A wavefront owns 64 query rows (two tiles of 32) and loads the operands of both products straight from memory into
+// registers, two steps ahead of their use: a part of the operand layout is read in 1 KiB pieces, each of which is one
+// operand and feeds two MFMAs.  There is no LDS and no barrier between the wavefronts that work on a launch, so one
+// wavefront per SIMD (442 of its 512 registers) keeps the matrix cores 76 % busy on 720p; against rings in LDS with
+// wavefronts of 32 rows (4 to a workgroup of 128 rows, two per SIMD, 69 %) an operand is moved half as often and nothing
+// passes through LDS, which the power limit turns into clock: 1.55 GHz instead of 1.50.  720p, 40 heads, 20.7 -> 19.1 ms
+// (1,216 TFLOP/s); 480p 4.00 -> 3.73 ms; with 64-row Q blocks, where the rings leave one wavefront of 32 rows per SIMD,
+// 5.13 -> 4.03 ms and 720p, 20 heads, 13.3 -> 10.8 ms.
+//
+// A workgroup has QH x KS wavefronts: QH times 64 neighbouring query rows of a Q block, whose wavefronts ask for the same
+// tiles at about the same time and find each other's in the L1 cache (720p, QH = 2 against two workgroups of 64 rows,
+// 20.0 -> 19.2 ms), times KS shares of the list: wavefront k of a share walks parts k, k + KS, ... of it, and the
+// shares are merged through LDS at the end.  rf2_cut_stream (rf2_attn_cut.h) chooses QH and KS.
+//
+// Registers: O^T 128 and Q 64 accumulation registers, S^T of two units 64, P of two units 32, operands of two steps 128.
+
+// The S^T product in assembly, as above, with the Q operand in accumulation registers (volatile: the statements
+// keep their places between the loads and the softmax arithmetic).
+__device__ __forceinline__ void qk_stream(f32x16& S, const bf16x8& a, const bf16x8& b, bool first) {
+  if (first) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(S) : "v"(a), "a"(b));
+  else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(S) : "v"(a), "a"(b));
+}
+
+template <int D, int BK, int QH, int KS>
+__global__ void __launch_bounds__(64 * QH * KS, 1) stream_attn_kernel(
+    const __bf16* __restrict__ qp, const __bf16* __restrict__ kp, const __bf16* __restrict__ vp,
+    const int32_t* __restrict__ blk_idx, const int32_t* __restrict__ blk_cnt, __bf16* __restrict__ op,
+    float* __restrict__ lse, RowOrder order, int Tb, int k_row, int last_valid, float scale_log2,
+    const int32_t* __restrict__ scatter, int n_tokens, int heads, rf2_strides st, int split) {
+  // split: log2 of the workgroups that share a Q block; they are neighbours on one XCD.  Tb: K/V blocks per head (columns of
+  // the block mask); last_valid: tokens in the last one.
+  constexpr int BQ = 64 * QH, KH = BK / 2, PB = BK / 64, DS = D / 16, DT = D / 32;
+  constexpr int TILE_BYTES = BK * D * 2, PART_BYTES = 64 * D * 2;
+  const int xcd = blockIdx.x & 7, share = (int)(blockIdx.x >> 3) & ((1 << split) - 1), slot = (int)(blockIdx.x >> 3) >> split;
+  int bh, qi;
+  if (!row_of(order, xcd, slot, bh, qi)) return;
+  const int Tq = order.rows;
+  const size_t row_id = (size_t)bh * Tq + qi;
+  int cnt = blk_cnt[row_id];
+  const bool dense = (cnt == Tb);
+  cnt = dense ? Tb : min(max(cnt, 0), k_row);
+  const int32_t* __restrict__ list = blk_idx + row_id * k_row;
+  // Only the last listed block can be the ragged last block of the sequence (lists ascend).
+  bool ragged = false;
+  if (cnt > 0 && last_valid < BK) {
+    const int jl = dense ? cnt - 1 : list[cnt - 1];
+    ragged = min(max(jl, 0), Tb - 1) == Tb - 1;
+  }
+  int NPARTS = cnt * PB;
+  // (a last part without any valid key is left out, so that every wavefront has a valid key in its first unit)
+  if (KS > 1 && PB > 1 && ragged && last_valid <= 32) --NPARTS;
+  const int wave = QH * KS > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) : 0;
+  const int half = wave % QH, grp = wave / QH;
+  const int parts = KS > 1 ? max(NPARTS - grp + KS - 1, 0) / KS : NPARTS;    // this wavefront's: grp, grp + KS, ...
+  const int U = 2 * parts;                                                   // its 32-key units (even)
+  const int lane = (int)threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
+  const size_t q_head_off = (size_t)bh * (Tq << split) * BQ * D;             // elements; qp and op
+  const int q_row = ((qi << split) + share) * BQ + 64 * half + l32;          // this lane's query row of tile 0 in its head
+  const size_t k_head_off = (size_t)bh * Tb * BK * D;                        // kp and vp
+  // (buffer loads: scalar offsets of tile and operand beside a constant per-lane one; nothing past a head's K or V is read)
+  const unsigned head_bytes = (unsigned)Tb * (unsigned)TILE_BYTES;
+  const auto kbuf = __builtin_amdgcn_make_buffer_rsrc((void*)uniform_ptr(kp + k_head_off), 0, head_bytes, 0x00020000);
+  const auto vbuf = __builtin_amdgcn_make_buffer_rsrc((void*)uniform_ptr(vp + k_head_off), 0, head_bytes, 0x00020000);
+  const uint32_t k_lane = (uint32_t)((lh * 64 + l32) * 16), v_lane = (uint32_t)((lh * D + l32) * 16);
+  constexpr uint32_t K_TILE = 32 * 16, V_TILE = 4 * D * 16;     // the second 32-key tile of a part
+  // Operand c of the K tile, operand j = 2 dt + ks of the V^T tile, that begins at byte `off` of the head.
+  auto k_load = [&](uint32_t off, int c) {
+    return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(kbuf, k_lane + c % 2 * 2048, off + c / 2 * 4096, 0));
+  };
+  auto v_load = [&](uint32_t off, int j) {
+    return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(vbuf, v_lane + j / 2 * 512, off + j % 2 * 2 * D * 16, 0));
+  };
+  // Part P of the list is part P % PB of listed block P / PB (P clamped: loads past the end fetch the last part again).
+  auto list_entry = [&](int P) {
+    const int it = (int)((unsigned)min(P, NPARTS - 1) / (unsigned)PB);
+    return dense ? it : list[it];
+  };
+  auto part_off = [&](int entry, int P) {
+    const int j = min(max(entry, 0), Tb - 1);            // a corrupt list can give wrong results, never a fault
+    return (uint32_t)j * (uint32_t)TILE_BYTES + ((unsigned)min(P, NPARTS - 1) % (unsigned)PB) * (uint32_t)PART_BYTES;
+  };
+  auto part_of = [&](int P) { return P * KS + grp; };    // list part of this wavefront's part P
+  const int partial_begin = ragged ? 2 * (max((cnt - 1) * PB - grp + KS - 1, 0) / KS) : U;   // first unit of the ragged block
+
+  bf16x8 qf[2][DS];
+  f32x16 o[2][DT];
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) o[q][dt][i] = 0.f;
+  // Softmax state per tile and query column, as in the other kernel; m_ref is exact from the first unit of the wavefront.
+  // (a wavefront without any part of its own weighs nothing in the merge, however small the others' references are)
+  float m_ref[2], nmc[2] = {}, l_run[2] = {}, rs_last[2] = {};
+  m_ref[0] = m_ref[1] = KS > 1 && U == 0 ? -FLT_MAX : 0.f;
+  constexpr int NQ = DS, NP = DT * 2;                    // operands of a step: K, V^T
+  static_assert(NQ + NP == 16, "one pair of probabilities of each tile for every operand");
+  // k-step ks of the second product's B operand from the packed probabilities of a unit
+  auto operand_p = [](const uint32_t (&P)[8], int ks) {
+    const u32x4 w = {P[4 * ks], P[4 * ks + 1], P[4 * ks + 2], P[4 * ks + 3]};
+    return __builtin_bit_cast(bf16x8, w);
+  };
+  auto rowmax = [&](const f32x16& S) -> float {
+    float v = S[0];
+#pragma unroll
+    for (int i = 1; i < 16; ++i) v = fmaxf(v, S[i]);
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+  };
+  // The accumulators are scaled where they are, through one vector register (left to the compiler, the copies cost the
+  // registers of the loop).  The wait states in front cover a product in flight, those behind a product that follows.
+  auto move_reference = [&](int q, bool move, float to) {
+    const float delta = move ? to - m_ref[q] : 0.f;
+    const float alpha = __builtin_amdgcn_exp2f(-fmaxf(delta, 0.f) * scale_log2);
+    if constexpr (KS > 1) m_ref[q] = move ? to : m_ref[q];     // (from -FLT_MAX a difference does not lead to `to`)
+    else m_ref[q] += delta;
+    nmc[q] = -m_ref[q] * scale_log2;
+    l_run[q] *= alpha;
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        float x = o[q][dt][i], t;
+        asm volatile("v_accvgpr_read_b32 %1, %0\n\ts_nop 1\n\tv_mul_f32 %1, %1, %2\n\ts_nop 1\n\tv_accvgpr_write_b32 %0, %1"
+                     : "+a"(x), "=&v"(t) : "v"(alpha));
+        o[q][dt][i] = x;
+      }
+    asm volatile("s_nop 7" ::: "memory");
+  };
+  // The probabilities P of the unit whose accumulators are in S were out of range; O holds all earlier units, so the reference
+  // moves up and P (and rs_last) are recomputed.
+  auto redo_unit = [&](const f32x16 (&S)[2], uint32_t (&P)[2][8]) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const float mx = rowmax(S[q]);
+      move_reference(q, mx > m_ref[q], mx);
+      rs_last[q] = 0.f;
+#pragma unroll
+      for (int i = 0; i < 16; i += 2) {
+        const float p0 = __builtin_amdgcn_exp2f(fmaf(S[q][i], scale_log2, nmc[q]));
+        const float p1 = __builtin_amdgcn_exp2f(fmaf(S[q][i + 1], scale_log2, nmc[q]));
+        const bf16x2 pk = {(__bf16)p0, (__bf16)p1};
+        rs_last[q] += p0 + p1;
+        P[q][i / 2] = __builtin_bit_cast(uint32_t, pk);
+      }
+    }
+  };
+  // Keys past the end of the sequence, in the units of the ragged block.
+  auto mask_unit = [&](f32x16 (&S)[2], int s) {
+    const int t = s & 1, p = part_of(s >> 1) % PB;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int key = t * KH + 32 * p + 8 * (i / 4) + 4 * lh + (i % 4);
+      if (key >= last_valid) S[0][i] = S[1][i] = -INFINITY;
+    }
+  };
+
+  bool slow = partial_begin == 0, redo = false;   // mask the coming unit / the latest unit must be redone
+  bf16x8 kr[2][NQ], vr[2][NP];                    // operands of the coming even and odd step
+  // Step s: products S_{s+1} and V P_{s-1} around the softmax arithmetic of unit s, operand by operand.  Its registers are
+  // reloaded for step s+2 (K tile at k_off, V^T tile at v_off) as soon as both MFMAs that read them are issued.  An MFMA
+  // takes eight issue slots of the SIMD; behind the first of an operand come the exponentials of a pair of
+  // probabilities, behind the second its sum and packing and the load.
+  auto step = [&](auto odd_tag, int s, f32x16 (&Scur)[2], f32x16 (&Snext)[2], uint32_t (&Pprev)[2][8], uint32_t (&Pcur)[2][8],
+                  uint32_t k_off, uint32_t v_off) {
+    constexpr int ODD = decltype(odd_tag)::value ? 1 : 0;
+    if (slow) {
+      if (redo) redo_unit(Snext, Pprev);          // (the accumulators of unit s-1 are still in the buffer this step overwrites)
+      if (s > 0 && s >= partial_begin) mask_unit(Scur, s);
+    }
+    l_run[0] += rs_last[0];
+    l_run[1] += rs_last[1];
+    __builtin_amdgcn_sched_barrier(0);
+    float rs[2] = {}, e0 = 0.f, e1 = 0.f;
+#pragma unroll
+    for (int g = 0; g < NQ + NP; ++g) {
+      const int tile = g / 8, i = 2 * (g % 8), j = g - NQ;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        if (g < NQ) qk_stream(Snext[q], kr[ODD][g], qf[q][g], g == 0);
+        else o[q][j / 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vr[ODD][j], operand_p(Pprev[q], j % 2), o[q][j / 2], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (q == 0) {
+          e0 = __builtin_amdgcn_exp2f(fmaf(Scur[tile][i], scale_log2, nmc[tile]));
+          e1 = __builtin_amdgcn_exp2f(fmaf(Scur[tile][i + 1], scale_log2, nmc[tile]));
+          asm volatile("" : "+v"(e0), "+v"(e1));
+        } else {
+          if (g < NQ) kr[ODD][g] = k_load(k_off, g);
+          else vr[ODD][j] = v_load(v_off, j);
+          asm volatile("" ::: "memory");          // (the load stays here: the compiler would move it to its use in the next round)
+          const bf16x2 pk = {(__bf16)e0, (__bf16)e1};
+          uint32_t w = __builtin_bit_cast(uint32_t, pk);
+          rs[tile] = (i == 0) ? e0 + e1 : rs[tile] + (e0 + e1);
+          asm volatile("" : "+v"(w), "+v"(rs[tile]));
+          Pcur[tile][i / 2] = w;
+        }
+        __builtin_amdgcn_sched_barrier(0);        // the slots stay in this order
+      }
+    }
+    rs_last[0] = rs[0];
+    rs_last[1] = rs[1];
+    redo = __builtin_amdgcn_ballot_w64(!(rs[0] + rs[1] <= 1.0995e12f)) != 0ull;    // rare: above 2^40 or not finite
+    slow = redo || (s + 1 >= partial_begin);
+  };
+
+  if (U > 0) {
+    uint32_t off0 = part_off(list_entry(part_of(0)), part_of(0)), off1 = part_off(list_entry(part_of(1)), part_of(1));   // parts P, P + 1
+    bf16x8 k0[NQ];
+#pragma unroll
+    for (int c = 0; c < NQ; ++c) k0[c] = k_load(off0, c);
+#pragma unroll
+    for (int c = 0; c < NQ; ++c) kr[0][c] = k_load(off0 + K_TILE, c);
+    {
+      // (between the operands of the two steps: in the loop as many loads lie between an operand's load and its use, and the
+      // compiler's wait counts are the smaller of the two)
+      const __bf16* qrow = qp + q_head_off + (size_t)q_row * D + 8 * lh;
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int ds = 0; ds < DS; ++ds) qf[q][ds] = *reinterpret_cast<const bf16x8*>(qrow + q * 32 * D + 16 * ds);
+    }
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int c = 0; c < NQ; ++c) kr[1][c] = k_load(off1, c);
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+      vr[1][j] = v_load(off0, j);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) vr[0][j][e] = (__bf16)0.f;       // step 0 has no unit before it: it adds 0 x 0
+    }
+    f32x16 Sa[2], Sb[2];
+    uint32_t Pa[2][8], Pb[2][8];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+#pragma unroll
+      for (int ds = 0; ds < DS; ++ds) qk_stream(Sa[q], k0[ds], qf[q][ds], ds == 0);
+      asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 1" : "+v"(Sa[q]));   // (what an 8-pass MFMA needs before its result is read)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) Pb[q][e] = 0u;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) Sb[q][i] = 0.f;
+    }
+    if (partial_begin == 0) mask_unit(Sa, 0);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      // (minus infinity in all products of a later unit of a list is no reference: it weighs nothing, also where a share begins)
+      m_ref[q] = KS > 1 && grp > 0 ? fmaxf(rowmax(Sa[q]), -FLT_MAX) : rowmax(Sa[q]);
+      nmc[q] = -m_ref[q] * scale_log2;
+    }
+    // A list entry is read a round before it is turned into an offset, so that no step waits for a scalar memory load.
+    int entry = list_entry(part_of(2));
+    for (int s = 0; s < U; s += 2) {
+      const int P = s >> 1;
+      // (two wavefronts that walk one list meet every 16 parts: left alone they drift apart, out of reach of each other's
+      // tiles in L1.  720p, 24 heads, 11.25 -> 10.99 ms; every part or every 4th: as much, and dearer on short lists.  Four
+      // wavefronts of a 256-row Q block lose 2 %)
+      if (QH == 2 && KS == 1 && P % 16 == 0) __builtin_amdgcn_s_barrier();
+      const uint32_t off2 = part_off(entry, part_of(P + 2));
+      entry = list_entry(part_of(P + 3));
+      // even step: S of unit s+1 (part P, tile 1), V P of unit s-1; loads K of part P+1, tile 1 and V of part P, tile 1
+      step(std::false_type{}, s, Sa, Sb, Pb, Pa, off1 + K_TILE, off0 + V_TILE);
+      // odd step: S of unit s+2 (part P+1, tile 0), V P of unit s; loads K of part P+2, tile 0 and V of part P+1, tile 0
+      step(std::true_type{}, s + 1, Sb, Sa, Pa, Pb, off2, off1);
+      off0 = off1;
+      off1 = off2;
+    }
+    // ---- last product: O += V P_{U-1} -----------------------------------------------------------------
+    if (redo) redo_unit(Sb, Pb);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      l_run[q] += rs_last[q];
+#pragma unroll
+      for (int j = 0; j < NP; ++j)
+        o[q][j / 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vr[0][j], operand_p(Pb[q], j % 2), o[q][j / 2], 0, 0, 0);
+    }
+  }
+
+  // ---- normalise (the final division of eq. 4) and write this wavefront's rows ------------------------------------
+  float l_tot[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run[q]), __float_as_uint(l_run[q]), false, false);
+    l_tot[q] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+  }
+  // ---- merge of the shares: wavefront x KS / TILES finishes 32 x 32 tile x = q DT + dt ----------------------------
+  // Every wavefront leaves the tiles it does not finish and its row statistics in LDS and rescales what it reads to the
+  // largest reference of the row.
+  constexpr int TILES = 2 * DT;
+  auto finishes = [&](int q, int dt) { return KS == 1 || grp == (q * DT + dt) * KS / TILES; };
+  if constexpr (KS > 1) {
+    __shared__ float4 tiles[QH][KS][TILES - TILES / KS][4][64];
+    __shared__ float2 stats[QH][KS][2][32];
+    auto place = [&](int owner, int x) { return x < owner * TILES / KS ? x : x - TILES / KS; };   // (its own tiles take no place)
+#pragma unroll
+    for (int x = 0; x < TILES; ++x)
+      if (!finishes(x / DT, x % DT)) {
+        const f32x16& t = o[x / DT][x % DT];
+        float4* const to = &tiles[half][grp][place(grp, x)][0][lane];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) to[g * 64] = make_float4(t[4 * g], t[4 * g + 1], t[4 * g + 2], t[4 * g + 3]);
+      }
+    if (lh == 0) {
+      stats[half][grp][0][l32] = make_float2(m_ref[0], l_tot[0]);
+      stats[half][grp][1][l32] = make_float2(m_ref[1], l_tot[1]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      float m_all = m_ref[q];
+      float2 st_of[KS];
+#pragma unroll
+      for (int k = 0; k < KS; ++k) {
+        st_of[k] = stats[half][k][q][l32];
+        m_all = fmaxf(m_all, st_of[k].x);
+      }
+      const float own = __builtin_amdgcn_exp2f((m_ref[q] - m_all) * scale_log2);
+      l_tot[q] = 0.f;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+        if (finishes(q, dt))
+#pragma unroll
+          for (int i = 0; i < 16; ++i) o[q][dt][i] *= own;
+#pragma unroll
+      for (int k = 0; k < KS; ++k) {
+        const float w = __builtin_amdgcn_exp2f((st_of[k].x - m_all) * scale_log2);
+        l_tot[q] = fmaf(st_of[k].y, w, l_tot[q]);
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+          if (k != grp && finishes(q, dt)) {
+            const float4* const from = &tiles[half][k][place(k, q * DT + dt)][0][lane];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+              const float4 x = from[g * 64];
+              o[q][dt][4 * g] = fmaf(x.x, w, o[q][dt][4 * g]);
+              o[q][dt][4 * g + 1] = fmaf(x.y, w, o[q][dt][4 * g + 1]);
+              o[q][dt][4 * g + 2] = fmaf(x.z, w, o[q][dt][4 * g + 2]);
+              o[q][dt][4 * g + 3] = fmaf(x.w, w, o[q][dt][4 * g + 3]);
+            }
+          }
+      }
+      m_ref[q] = m_all;
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const float f = l_tot[q] > 0.f ? 1.0f / l_tot[q] : 0.f;   // a row with no kept key yields zeros
+    const size_t row = (size_t)q_row + 32 * q;
+    // plain output: row `row` of the permuted layout; fused inverse permutation: the token's raster row
+    const int target = scatter ? scatter[row] : (int)row;
+    if (target < 0) continue;                                 // padding row of the last block
+    __bf16* orow = scatter ? op + ((bh / heads) * st.batch + (bh % heads) * st.head + (long long)target * st.token) * D
+                           : op + q_head_off + row * D;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+      if (finishes(q, dt))
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          bf16x4 pk;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) pk[e] = (__bf16)(o[q][dt][4 * g + e] * f);
+          *reinterpret_cast<bf16x4*>(orow + 32 * dt + 8 * g + 4 * lh) = pk;
+        }
+    if (lse != nullptr && lh == 0 && finishes(q, 0))
+      lse[scatter ? (size_t)bh * n_tokens + target : (size_t)bh * (Tq << split) * BQ + row] =
+          m_ref[q] * scale_log2 * 0.6931471805599453f + __logf(l_tot[q]);
+  }
+}
+
+struct AttnArgs {
+  const void *qp, *kp, *vp;
+  const int32_t *blk_idx, *blk_cnt;
+  void* out;
+  float* lse;
+  bool scatter;
+};
+
+// Numbering of a plan's rows, and the slots of an XCD: its run of the sink rows of all heads, then its ordinary rows.
+RowOrder row_order(const rf2_plan* plan, unsigned* slots) {
   const rf2_info& in = plan->info;
-  const float scale_log2 = (float)(1.4426950408889634 / sqrt((double)D));
-  const int n_bh = c.batch * c.heads;
-  const int split = c.block > BQ ? 1 : 0;
-  // slots of an XCD: its run of the sink rows of all heads, then plain_per_xcd ordinary rows of every head
-  const int n_sink_rows = in.sink_block_end - in.sink_block_begin;
-  const int sink_slots = (int)(((int64_t)n_bh * n_sink_rows + 7) / 8);
-  const unsigned grid = (8u * ((unsigned)sink_slots + (unsigned)n_bh * (unsigned)plan->plain_per_xcd)) << split;
-  if (grid == 0) return RF2_OK;
-  block_sparse_attn_kernel<D, BQ, BK, KS><<<dim3(grid), dim3(C::NT * KS), 0, st>>>(
-      (const __bf16*)qp, (const __bf16*)kp, (const __bf16*)vp, blk_idx, blk_cnt, (__bf16*)op, lse, plan->d_row_order,
-      plan->plain_per_xcd, n_bh, in.sink_block_begin, n_sink_rows, sink_slots, in.n_blocks, in.n_blocks_k, in.k_row, in.last_block_valid_k,
-      scale_log2, scatter ? plan->d_perm : nullptr, (int)in.N, c.heads, rf2_qkv_strides(plan), split);
+  const int n_bh = plan->cfg.batch * plan->cfg.heads, n_sink = in.sink_block_end - in.sink_block_begin;
+  const int sink_slots = (int)(((int64_t)n_bh * n_sink + 7) / 8);
+  const int run = (int)(((int64_t)n_bh * (in.n_blocks - n_sink) + 7) / 8);
+  const bool whole = plan->cut.whole_heads;
+  *slots = (unsigned)sink_slots + (whole ? (unsigned)run : (unsigned)n_bh * (unsigned)plan->plain_per_xcd);
+  return {whole ? nullptr : plan->d_row_order, whole ? run : plan->plain_per_xcd, n_bh, in.n_blocks, in.sink_block_begin, n_sink, sink_slots};
+}
+
+template <int D, int BQ, int BK, int KS>
+int launch_ring(const rf2_plan* plan, const AttnArgs& a, hipStream_t st) {
+  using C = AttnCfg<D, BQ, BK, KS>;
+  const rf2_info& in = plan->info;
+  const int split = plan->cfg.block > BQ ? 1 : 0;
+  unsigned slots;
+  const RowOrder order = row_order(plan, &slots);
+  if (slots == 0) return RF2_OK;
+  block_sparse_attn_kernel<D, BQ, BK, KS><<<dim3((8u * slots) << split), dim3(C::NT * KS), 0, st>>>(
+      (const __bf16*)a.qp, (const __bf16*)a.kp, (const __bf16*)a.vp, a.blk_idx, a.blk_cnt, (__bf16*)a.out, a.lse, order,
+      in.n_blocks_k, in.k_row, in.last_block_valid_k, (float)(1.4426950408889634 / sqrt((double)D)),
+      a.scatter ? plan->d_perm : nullptr, (int)in.N, plan->cfg.heads, rf2_qkv_strides(plan), split);
+  RF2_LAUNCH_CHECK();
+  return RF2_OK;
+}
+
+template <int D, int BK, int QH, int KS>
+int launch_stream(const rf2_plan* plan, const AttnArgs& a, hipStream_t st) {
+  const rf2_info& in = plan->info;
+  const int share = plan->cfg.block / (64 * QH), split = share / 2;      // workgroups of a Q block: 1, 2, 4
+  if (share < 1) return RF2_ERR_UNSUPPORTED;                             // (no cut has more rows than a Q block)
+  unsigned slots;
+  const RowOrder order = row_order(plan, &slots);
+  if (slots == 0) return RF2_OK;
+  stream_attn_kernel<D, BK, QH, KS><<<dim3((8u * slots) << split), dim3(64 * QH * KS), 0, st>>>(
+      (const __bf16*)a.qp, (const __bf16*)a.kp, (const __bf16*)a.vp, a.blk_idx, a.blk_cnt, (__bf16*)a.out, a.lse, order,
+      in.n_blocks_k, in.k_row, in.last_block_valid_k, (float)(1.4426950408889634 / sqrt((double)D)),
+      a.scatter ? plan->d_perm : nullptr, (int)in.N, plan->cfg.heads, rf2_qkv_strides(plan), split);
   RF2_LAUNCH_CHECK();
   return RF2_OK;
 }
 
 template <int D, int BK>
-int dispatch_rows(const rf2_plan* plan, const void* qp, const void* kp, const void* vp, const int32_t* blk_idx,
-                  const int32_t* blk_cnt, void* out, float* lse, bool scatter, hipStream_t st) {
+int dispatch_cut(const rf2_plan* plan, const AttnArgs& a, hipStream_t st) {
+  const rf2_attn_cut& cut = plan->cut;
+  if constexpr (D == 128) {
+#define RF2_ATTN_CASE(QH, KS) \
+  if (cut.rows == 64 * QH && cut.groups == KS) return launch_stream<D, BK, QH, KS>(plan, a, st);
+    RF2_ATTN_CASE(1, 1)
+    RF2_ATTN_CASE(2, 1)
+    RF2_ATTN_CASE(4, 1)
+    RF2_ATTN_CASE(1, 2)
+    RF2_ATTN_CASE(2, 2)
+    RF2_ATTN_CASE(1, 4)
+#undef RF2_ATTN_CASE
+  } else {
 #define RF2_ATTN_CASE(Q, KS) \
-  if (plan->cut.rows == Q && plan->cut.groups == KS) return launch_attn<D, Q, BK, KS>(plan, qp, kp, vp, blk_idx, blk_cnt, out, lse, scatter, st);
-  RF2_ATTN_CASE(64, 1)
-  RF2_ATTN_CASE(128, 1)
-  RF2_ATTN_CASE(256, 1)
-  RF2_ATTN_CASE(64, 2)
-  RF2_ATTN_CASE(128, 2)
-  if constexpr (D == 64) {
+  if (cut.rows == Q && cut.groups == KS) return launch_ring<D, Q, BK, KS>(plan, a, st);
+    RF2_ATTN_CASE(64, 1)
+    RF2_ATTN_CASE(128, 1)
+    RF2_ATTN_CASE(256, 1)
+    RF2_ATTN_CASE(64, 2)
+    RF2_ATTN_CASE(128, 2)
     RF2_ATTN_CASE(64, 4)
     RF2_ATTN_CASE(128, 4)
-  }
 #undef RF2_ATTN_CASE
+  }
   return RF2_ERR_UNSUPPORTED;
 }
 
 template <int D>
-int dispatch_blocks(const rf2_plan* plan, const void* qp, const void* kp, const void* vp, const int32_t* blk_idx,
-                    const int32_t* blk_cnt, void* out, float* lse, bool scatter, hipStream_t st) {
-  if (plan->info.block_k == 128) return dispatch_rows<D, 128>(plan, qp, kp, vp, blk_idx, blk_cnt, out, lse, scatter, st);
-  if (plan->info.block_k == 64) return dispatch_rows<D, 64>(plan, qp, kp, vp, blk_idx, blk_cnt, out, lse, scatter, st);
+int dispatch_blocks(const rf2_plan* plan, const AttnArgs& a, hipStream_t st) {
+  if (plan->info.block_k == 128) return dispatch_cut<D, 128>(plan, a, st);
+  if (plan->info.block_k == 64) return dispatch_cut<D, 64>(plan, a, st);
   return RF2_ERR_UNSUPPORTED;
 }
 
@@ -628,8 +1048,9 @@ int dispatch_attn(const rf2_plan* plan, const void* qp, const void* kp, const vo
   if (!plan || !qp || !kp || !vp || !blk_idx || !blk_cnt || !out) return RF2_ERR_INVALID_ARG;
   if (const int rc = rf2_check_device(plan)) return rc;
   hipStream_t st = (hipStream_t)stream;
-  if (plan->cfg.head_dim == 128) return dispatch_blocks<128>(plan, qp, kp, vp, blk_idx, blk_cnt, out, lse, scatter, st);
-  if (plan->cfg.head_dim == 64) return dispatch_blocks<64>(plan, qp, kp, vp, blk_idx, blk_cnt, out, lse, scatter, st);
+  const AttnArgs a{qp, kp, vp, blk_idx, blk_cnt, out, lse, scatter};
+  if (plan->cfg.head_dim == 128) return dispatch_blocks<128>(plan, a, st);
+  if (plan->cfg.head_dim == 64) return dispatch_blocks<64>(plan, a, st);
   return RF2_ERR_UNSUPPORTED;
 }
 

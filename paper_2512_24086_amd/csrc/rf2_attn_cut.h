@@ -3,9 +3,13 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <functional>
+#include <queue>
+#include <vector>
 
 #include "rf2.h"
 
+// The cut of the kernel with rings in LDS (block_sparse_attn_kernel; launches at d = 128 take rf2_cut_stream's, below).
 // How a launch is cut, from the sizes of the plan alone (so that both exits of a layer give the same bits).
 // A row of the mask is one workgroup of `groups` (KS) groups of wavefronts that share its list (KS = 1: no merge); a Q block
 // of 256 rows is one workgroup of eight wavefronts or two of 128 rows.
@@ -48,8 +52,9 @@
 // 118 -> 92, 195 123 -> 129, 260 217 -> 183, 390 233 -> 251, 455 247 -> 263, 520 361 -> 329.  Lists under 20 parts always gain, 3 % or
 // more; at d = 64 the halves of long sequences read past an XCD's L2 (16,640 tokens 404 -> 338, 31,160 tokens 237 -> 252).
 struct rf2_attn_cut {
-  int rows;         // query rows of a workgroup: those of a Q block, or 128 of 256
+  int rows;         // query rows of a workgroup: those of a Q block, or a half or a quarter of them
   int groups;       // groups of wavefronts that share a list
+  bool whole_heads; // ordinary rows are numbered head by head and dealt to the XCDs in 8 runs (else every head in 8 shares)
 };
 
 // Workgroups of a launch that its busiest shader engine gets, `share` workgroups to a row of the mask.  The hardware deals
@@ -112,4 +117,85 @@ inline rf2_attn_cut rf2_cut_attn(const rf2_config& c, const rf2_info& in) {
   const bool full = c.head_dim == 64 ? (whole > 4 && whole < 8) || (whole > 11 && whole <= 16) || (whole > 8 && in.N > 19456)
                                      : (busiest + 7) / 8 >= 2 * ((whole + 7) / 8);
   return {full && parts >= 20 && !spread ? 256 : 128, 1};
+}
+
+// ---- the cut of stream_attn_kernel (d = 128) -----------------------------------------------------------------------
+// A workgroup has QH x KS wavefronts, QH = rows / 64, KS = groups, one to a SIMD.  Which QH and KS: the pair with the shortest
+// launch in a small model of it, made of what a launch is: jobs of two lengths (all-column sink rows first, then the others),
+// dealt in order to places that take the next job when they are done.
+//   * The busiest shader engine is looked at: 1/8 of the rows go to an XCD, 1/4 of its workgroups to each engine of 8 compute
+//     units = 32 wavefronts, 32 / (QH KS) workgroups.
+//   * A job lasts 2 (parts / KS) units of a wavefront, plus the start of a row, plus the merge, all counted in units.
+//   * A unit takes 0.49 us where up to a third of the wavefront places are taken and 0.83 us where all are (clock under the power
+//     limit, shared L2), on a line between; QH = 2 or 4 takes 3 or 4 % less (tiles met in L1), KS = 2 or 4 1 or 5 % (fewer
+//     rows in flight on an XCD).
+// The constants are fitted to 140 launches of 600 to 40,000 tokens, 1 to 40 heads, blocks of 64, 128 and 256 rows, sparsity
+// 0.5 to 0.9, with and without sink rows and text, each timed with every cut: the model is 4 % off on average, its choice
+// 0.2 % slower than the best cut (5.7 % at most), and 1.28 times as fast as the former kernel's cut (1.04 to 2.3 times).
+// E.g. (us, QH x KS = 1x1, 1x2, 1x4, 2x1, 2x2): image of 4,096 tokens, 1 head 38, 24, 19, 39, 26; 8 heads 41, 36, 42, 41, 36;
+// 16 heads 66, 70, 84, 67, 72; 24 heads 104, 102, 124, 107, 105; 480p 5 heads 672, 492, 532, 665, 493, 40 heads 3,926, 3,974,
+// 4,251, 3,731, 3,936.
+struct rf2_stream_jobs {
+  int64_t sinks, plain;          // jobs of a shader engine
+  double sink_units, plain_units;
+};
+inline double rf2_stream_time(rf2_stream_jobs j, int qh, int ks) {
+  constexpr int WAVES = 32;      // of a shader engine
+  const int places = WAVES / (qh * ks);
+  const double idle = 0.489, full = 0.828 * (qh == 4 ? 0.963 : qh == 2 ? 0.974 : 1.0) * (ks == 4 ? 0.952 : ks == 2 ? 0.986 : 1.0);
+  const double start = 3.9 + (qh == 4 ? 4.5 : qh == 2 ? 1.1 : 0.0) + (ks == 4 ? 4.9 : ks == 2 ? 2.8 : 0.0);
+  const double sink = j.sink_units / ks + start, plain = j.plain_units / ks + start;
+  // (many rounds of equal jobs: all but the last sixteen at the full rate)
+  double us = 5.3;
+  const auto rounds = [&](int64_t& jobs, double units) {
+    const int64_t skip = std::max<int64_t>(jobs / places - 16, 0);
+    jobs -= skip * places;
+    us += (double)skip * units * full;
+  };
+  rounds(j.sinks, sink);
+  rounds(j.plain, plain);
+  std::priority_queue<double, std::vector<double>, std::greater<double>> busy;     // ends of the jobs under way
+  std::vector<double> starts, ends;
+  for (int64_t i = 0; i < j.sinks + j.plain; ++i) {
+    double at = 0.0;
+    if ((int)busy.size() == places) { at = busy.top(); busy.pop(); }
+    starts.push_back(at);
+    ends.push_back(at + (i < j.sinks ? sink : plain));
+    busy.push(ends.back());
+  }
+  std::sort(ends.begin(), ends.end());
+  double last = 0.0;             // (starts ascend)
+  for (size_t s = 0, e = 0; e < ends.size();) {
+    const bool begins = s < starts.size() && starts[s] < ends[e];
+    const double at = begins ? starts[s] : ends[e];
+    const double taken = (double)((s - e) * qh * ks) / WAVES;
+    us += (at - last) * (idle + (full - idle) * std::max(0.0, (taken - 0.354) / (1.0 - 0.354)));
+    last = at;
+    begins ? ++s : ++e;
+  }
+  return us;
+}
+
+// Ordinary rows: with whole heads on an XCD its L2 fetches 1/8 of the K and V that it does where every XCD has rows of every
+// head, but the Infinity Cache (256 MB) has to hold those of 8 heads at a time.  (every head in 8 shares -> whole heads: 4,096
+// tokens x 24 heads, 112 -> 106 us; 480p, 17 MB a head, 3.56 -> 3.52 ms; 48,384 tokens, 25 MB, 4.62 -> 4.61; 60,480 tokens, 31 MB,
+// 7.16 -> 7.16; 720p, 39 MB, 18.5 -> 18.8; long video, 61 MB, 13.7 -> 14.1.)  Launches of 64-row blocks have the more different
+// lists in flight and gain at 720p too (20 heads 11.6 -> 10.8 ms; long video, 6 heads, 3.77 -> 3.81).
+inline rf2_attn_cut rf2_cut_stream(const rf2_config& c, const rf2_info& in) {
+  const int64_t lists = (int64_t)c.batch * c.heads, sink_rows = in.sink_block_end - in.sink_block_begin;
+  const int64_t sinks = (lists * sink_rows + 7) / 8, plain = (lists * (in.n_blocks - sink_rows) + 7) / 8;      // of an XCD
+  const double units = in.block_k / 32;
+  double keeps = in.k_row;
+  // (cumulative mass: a row is taken to keep what a flat one does)
+  if (in.kept_pairs_per_head < 0) keeps = std::max(1.0, (double)in.k_row * 0.5 * c.cdf_threshold * (1.0 + c.cdf_threshold));
+  rf2_attn_cut best{64, 1, false};
+  double least = 0.0;
+  for (int qh = 1; 64 * qh <= c.block; qh *= 2)
+    for (int ks = 1; qh * ks <= 4; ks *= 2) {
+      const int64_t share = c.block / (64 * qh), of_sinks = (sinks * share + 3) / 4, all = ((sinks + plain) * share + 3) / 4;
+      const double us = rf2_stream_time({of_sinks, all - of_sinks, in.n_blocks_k * units, keeps * units}, qh, ks);
+      if (least == 0.0 || us < least) least = us, best = {64 * qh, ks, false};
+    }
+  best.whole_heads = c.block == 64 || in.N_pad_k * c.head_dim * 4 <= (int64_t)32 << 20;
+  return best;
 }

@@ -1,0 +1,55 @@
+"""The d = 128 attention kernel in every way a launch is cut (64-row tiles of a workgroup, wavefronts that share a list), on the
+lists, logits and bounds of test_gpu_attn_cut: rows of no block up to all, a ragged last block with and without a part that holds
+no key, a reference that moves.  Launches of 256-row workgroups are as large as a 720p layer: test_gpu_fullsize has them."""
+import ctypes as C
+import os
+import subprocess
+
+import pytest
+
+from paper_2512_24086_amd import build as b
+from paper_2512_24086_amd import rf2
+from tests import test_gpu_attn_cut as cut_tests
+
+# (tokens, block, block_k, head_dim, heads) -> (rows of a workgroup, wavefronts that share a list)
+SHAPES = {(330, 64, 64, 128, 200): (64, 1), (330, 64, 128, 128, 200): (64, 1), (600, 64, 64, 128, 12): (64, 2),
+          (2450, 64, 128, 128, 8): (64, 2), (600, 64, 64, 128, 3): (64, 4), (657, 64, 128, 128, 2): (64, 4),
+          (2500, 128, 64, 128, 24): (128, 1), (2450, 128, 128, 128, 24): (128, 1), (4001, 128, 64, 128, 8): (128, 2),
+          (4000, 256, 128, 128, 8): (128, 2), (2500, 256, 64, 128, 3): (64, 4), (900, 256, 128, 128, 2): (64, 4)}
+
+SOURCE = """#include "rf2_attn_cut.h"
+extern "C" void cut(const rf2_config* c, const rf2_info* i, int* out) {
+  const rf2_attn_cut x = rf2_cut_stream(*c, *i);
+  out[0] = x.rows, out[1] = x.groups, out[2] = x.whole_heads;
+}
+"""
+
+
+def test_cuts(tmp_path):
+    (tmp_path / "cut.cpp").write_text(SOURCE)
+    lib = str(tmp_path / "cut.so")
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-O1", "-shared", "-fPIC", "-I", os.path.join(b.ROOT, "include"),
+                    "-I", b.CSRC, str(tmp_path / "cut.cpp"), "-o", lib], check=True)
+    fn, out = C.CDLL(lib).cut, (C.c_int * 3)()
+
+    def cut(**kw):
+        plan = rf2.Plan(**dict(dict(batch=1, head_dim=128, T=1, H=1, sparsity=0.3, window=(1, 1, 16)), **kw))
+        fn(C.byref(plan.cfg), C.byref(plan.info), out)
+        plan.close()
+        return tuple(out)
+
+    for (tokens, block, block_k, _, heads), want in SHAPES.items():
+        assert cut(W=tokens, block=block, block_k=block_k, heads=heads)[:2] == want, (tokens, block, block_k, heads)
+    video = dict(T=21, H=45, W=80, sparsity=0.8, sink_frames=1, window=(0, 0, 0))
+    assert cut(**video, heads=40, block=128) == (128, 1, 0)          # 8 heads' K and V are larger than the Infinity Cache
+    assert cut(**video, heads=40, block=256, block_k=128) == (256, 1, 0)
+    assert cut(**dict(video, H=30, W=52), heads=40, block=128) == (128, 1, 1)
+    assert cut(**video, heads=1, block=128)[:2] == (64, 4)
+    # a launch of the largest size the limits allow is cut without walking through its rows
+    assert cut(T=1, H=1, W=2048 * 64, heads=65535, block=64)[:1] == (64,)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_every_cut(shape):
+    cut_tests.test_lists_of_every_length(shape, 24.0)
