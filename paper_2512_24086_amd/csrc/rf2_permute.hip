@@ -11,14 +11,32 @@ typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 
 // Every row is read once and written once: non-temporal accesses keep the stream from displacing
 // other data in the caches on its way (measured on the 720p layer: loads alone -4 %, stores alone
-// +0.5 %, both -9 % of the time).
+// +0.5 %, both -9 % of the time).  Layers small beside the Infinity Cache (256 MB) are better kept in it: the attention
+// finds qp, kp, vp there, and the inputs, which the program has just made, are.  Measured on image layers of 4,096 tokens, the
+// buffers of three layers in turn (us, layer / permutation alone; bytes read and written):
+//   non-temporal     stores kept      both kept
+//   70.5 /  -        67.4 /  -        64.6 /  -         10 heads,  63 MB
+//   76.6 / 15.3      75.2 / 15.8      73.4 / 12.6       12 heads,  75 MB
+//   91.2 / 19.3      88.6 / 18.8      89.6 / 21.8       16 heads, 101 MB
+//   145  / 28.7      140  / 28.5      140  / 31.3       24 heads, 151 MB
+//   169  / 36.6      165  / 38.5      166  / 40.5       32 heads, 201 MB
+// Both are kept up to 80 MB, stores alone up to 160 MB (beyond, the permutation itself gets slower, up to 8 %).
+constexpr int64_t KEEP_ALL = (int64_t)80 << 20, KEEP_STORES = (int64_t)160 << 20;
+// The inverse permutation reads what the attention has just written (non-temporal -> kept loads, us, token-major and not: 50 MB
+// 13.8 -> 9.6, 84 MB 17.1 -> 13.8, 118 MB 22.0 -> 19.0, 166 MB 35.3 -> 26.8, 258 MB 49.8 -> 51.4, 335 MB 115 -> 121).
+constexpr int64_t KEEP_UNPERMUTE = (int64_t)192 << 20;
+
+template <bool KEEP>
 __device__ __forceinline__ uint4 ld_stream(const uint4* p) {
-  const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+  const u32x4* const from = reinterpret_cast<const u32x4*>(p);
+  const u32x4 v = KEEP ? *from : __builtin_nontemporal_load(from);
   return make_uint4(v.x, v.y, v.z, v.w);
 }
+template <bool KEEP>
 __device__ __forceinline__ void st_stream(uint4* p, uint4 v) {
   const u32x4 w = {v.x, v.y, v.z, v.w};
-  __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(p));
+  if constexpr (KEEP) *reinterpret_cast<u32x4*>(p) = w;
+  else __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(p));
 }
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
@@ -32,7 +50,7 @@ __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w 
 // operand reads walk it (a part holds one 32-key tile of each key half).
 template <int D>
 using pool_rows = float[256 / (D / 8)][D + 1];
-template <int D, int BLK, bool IS_K>
+template <int D, int BLK, bool IS_K, int KEEP>
 __device__ __forceinline__ void permute_pool_block(
     const uint4* __restrict__ x, uint4* __restrict__ xp, float* __restrict__ mean, const int32_t* __restrict__ perm,
     int n_blocks, int last_valid, int heads, const rf2_strides& st, int blk, int bh, pool_rows<D>& part) {
@@ -55,10 +73,10 @@ __device__ __forceinline__ void permute_pool_block(
   for (int r = rg; r < BLK; r += RG) {
     const int n = perm[blk * BLK + r];
     uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (n >= 0) v = ld_stream(&src[(size_t)n * st.token * CH + c]);
+    if (n >= 0) v = ld_stream<KEEP == 2>(&src[(size_t)n * st.token * CH + c]);
     constexpr int KH = BLK / 2;
     const int kslot = ((r % KH) / 32 * CH + c) * 64 + (r / KH) * 32 + r % 32;
-    st_stream(&dst[IS_K ? kslot : r * CH + c], v);
+    st_stream<KEEP >= 1>(&dst[IS_K ? kslot : r * CH + c], v);
     acc[0] += bf16_lo(v.x); acc[1] += bf16_hi(v.x);
     acc[2] += bf16_lo(v.y); acc[3] += bf16_hi(v.y);
     acc[4] += bf16_lo(v.z); acc[5] += bf16_hi(v.z);
@@ -89,7 +107,7 @@ __device__ __forceinline__ int rho(int r) { return (r & 3) | ((r & 4) << 1) | ((
 // KH + 32*part .. KH + 32*part + 31 (the reordering stays inside a 16-key group).
 template <int D>
 using v_rows = u16[64 * (D + 2)];
-template <int D, int BLK>
+template <int D, int BLK, int KEEP>
 __device__ __forceinline__ void permute_vtile_part(
     const uint4* __restrict__ v, uint4* __restrict__ vp, const int32_t* __restrict__ perm, int n_blocks, int heads,
     const rf2_strides& st, int block_part, int bh, v_rows<D>& tile) {
@@ -105,7 +123,7 @@ __device__ __forceinline__ void permute_vtile_part(
     const int r = (lr / 32) * KH + part * 32 + lr % 32;
     const int n = perm[blk * BLK + r];
     uint4 x = make_uint4(0u, 0u, 0u, 0u);
-    if (n >= 0) x = ld_stream(&src[(size_t)n * st.token * CH + c]);
+    if (n >= 0) x = ld_stream<KEEP == 2>(&src[(size_t)n * st.token * CH + c]);
     uint32_t* row = reinterpret_cast<uint32_t*>(tile + lr * PITCH + c * 8);  // 4-byte aligned: PITCH, c*8 even
     row[0] = x.x; row[1] = x.y; row[2] = x.z; row[3] = x.w;
   }
@@ -121,7 +139,7 @@ __device__ __forceinline__ void permute_vtile_part(
       const int k0 = (s0 & ~15) + rho(s0 & 15), k1 = (s1 & ~15) + rho(s1 & 15);
       w[e] = (uint32_t)tile[k0 * PITCH + ch] | ((uint32_t)tile[k1 * PITCH + ch] << 16);
     }
-    st_stream(&dst[o], make_uint4(w[0], w[1], w[2], w[3]));
+    st_stream<KEEP >= 1>(&dst[o], make_uint4(w[0], w[1], w[2], w[3]));
   }
 }
 
@@ -140,26 +158,27 @@ struct PermuteArgs {
   int last_q, last_k, heads;
   rf2_strides st;
 };
-template <int D, int BQ, int BK>
+// KEEP: 0 streams past the caches, 1 keeps what it writes, 2 also what it reads.
+template <int D, int BQ, int BK, int KEEP>
 __global__ void __launch_bounds__(256) permute_kernel(PermuteArgs a) {
   __shared__ __attribute__((aligned(16))) union { pool_rows<D> sums; v_rows<D> tile; } lds;
   uint32_t id = blockIdx.y * gridDim.x + blockIdx.x;
   if (id < a.q_wgs) {
-    permute_pool_block<D, BQ, false>(a.q, a.qp, a.qbar, a.perm, a.n_q, a.last_q, a.heads, a.st, id % a.n_q, id / a.n_q, lds.sums);
+    permute_pool_block<D, BQ, false, KEEP>(a.q, a.qp, a.qbar, a.perm, a.n_q, a.last_q, a.heads, a.st, id % a.n_q, id / a.n_q, lds.sums);
     return;
   }
   id -= a.q_wgs;
   if (id < a.k_wgs) {
-    permute_pool_block<D, BK, true>(a.k, a.kp, a.kbar, a.perm, a.n_k, a.last_k, a.heads, a.st, id % a.n_k, id / a.n_k, lds.sums);
+    permute_pool_block<D, BK, true, KEEP>(a.k, a.kp, a.kbar, a.perm, a.n_k, a.last_k, a.heads, a.st, id % a.n_k, id / a.n_k, lds.sums);
     return;
   }
   id -= a.k_wgs;
   const uint32_t parts = a.n_k * (BK / 64);
-  if (id < a.v_wgs) permute_vtile_part<D, BK>(a.v, a.vp, a.perm, a.n_k, a.heads, a.st, id % parts, id / parts, lds.tile);
+  if (id < a.v_wgs) permute_vtile_part<D, BK, KEEP>(a.v, a.vp, a.perm, a.n_k, a.heads, a.st, id % parts, id / parts, lds.tile);
 }
 
 // o[n] = op[inv[n]]: gathered reads, fully sequential writes.
-template <int D>
+template <int D, bool KEEP>
 __global__ void __launch_bounds__(256) unpermute_kernel(
     const uint4* __restrict__ op, uint4* __restrict__ o, const int32_t* __restrict__ inv, int N, size_t N_pad,
     int heads, rf2_strides st) {
@@ -173,7 +192,7 @@ __global__ void __launch_bounds__(256) unpermute_kernel(
 #pragma unroll 4
   for (int r = rg; r < 128; r += RG) {
     const int n = n0 + r;
-    if (n < N) st_stream(&dst[(size_t)n * st.token * CH + c], ld_stream(&src[(size_t)inv[n] * CH + c]));
+    if (n < N) st_stream<false>(&dst[(size_t)n * st.token * CH + c], ld_stream<KEEP>(&src[(size_t)inv[n] * CH + c]));
   }
 }
 
@@ -199,12 +218,16 @@ bool tensors_overlap(const rf2_plan* plan, const PermuteArgs& a) {
 }
 
 template <int D, int BQ, int BK>
-int launch_permute(PermuteArgs a, uint32_t q_wgs, uint32_t k_wgs, uint32_t v_wgs, hipStream_t st) {
+int launch_permute(const rf2_plan* plan, PermuteArgs a, uint32_t q_wgs, uint32_t k_wgs, uint32_t v_wgs, hipStream_t st) {
   // at most (2,048 + 2,048 + 4,096) x 65,535 workgroups, in equal rows of at most 65,536 (a grid dimension holds fewer
   // than 2^32 threads)
   const uint32_t n = q_wgs + k_wgs + v_wgs, rows = (n + 65535u) / 65536u;
   a.q_wgs = q_wgs, a.k_wgs = k_wgs, a.v_wgs = v_wgs;
-  permute_kernel<D, BQ, BK><<<dim3((n + rows - 1) / rows, rows), 256, 0, st>>>(a);
+  const dim3 grid((n + rows - 1) / rows, rows);
+  const int64_t bytes = (3 * plan->info.N + plan->info.N_pad + 2 * plan->info.N_pad_k) * (int64_t)a.bh * D * 2;
+  if (bytes <= KEEP_ALL) permute_kernel<D, BQ, BK, 2><<<grid, 256, 0, st>>>(a);
+  else if (bytes <= KEEP_STORES) permute_kernel<D, BQ, BK, 1><<<grid, 256, 0, st>>>(a);
+  else permute_kernel<D, BQ, BK, 0><<<grid, 256, 0, st>>>(a);
   RF2_LAUNCH_CHECK();
   return RF2_OK;
 }
@@ -212,10 +235,10 @@ int launch_permute(PermuteArgs a, uint32_t q_wgs, uint32_t k_wgs, uint32_t v_wgs
 template <int D, int BQ, int BK>
 int permute_all(const rf2_plan* plan, const PermuteArgs& a, hipStream_t st) {
   const uint32_t q = a.n_q * a.bh, k = a.n_k * a.bh, v = k * (BK / 64);
-  if (!tensors_overlap(plan, a)) return launch_permute<D, BQ, BK>(a, q, k, v, st);
-  if (const int rc = launch_permute<D, BQ, BK>(a, q, 0, 0, st)) return rc;
-  if (const int rc = launch_permute<D, BQ, BK>(a, 0, k, 0, st)) return rc;
-  return launch_permute<D, BQ, BK>(a, 0, 0, v, st);
+  if (!tensors_overlap(plan, a)) return launch_permute<D, BQ, BK>(plan, a, q, k, v, st);
+  if (const int rc = launch_permute<D, BQ, BK>(plan, a, q, 0, 0, st)) return rc;
+  if (const int rc = launch_permute<D, BQ, BK>(plan, a, 0, k, 0, st)) return rc;
+  return launch_permute<D, BQ, BK>(plan, a, 0, 0, v, st);
 }
 
 template <int D>
@@ -257,12 +280,12 @@ extern "C" int rf2_unpermute(const rf2_plan* plan, const void* op, void* o, void
   const rf2_info& in = plan->info;
   hipStream_t st = (hipStream_t)stream;
   const dim3 grid((unsigned)((in.N + 127) / 128), c.batch * c.heads, 1);
-  if (c.head_dim == 128)
-    unpermute_kernel<128><<<grid, 256, 0, st>>>((const uint4*)op, (uint4*)o, plan->d_inv, (int)in.N, (size_t)in.N_pad,
-                                         c.heads, rf2_qkv_strides(plan));
-  else
-    unpermute_kernel<64><<<grid, 256, 0, st>>>((const uint4*)op, (uint4*)o, plan->d_inv, (int)in.N, (size_t)in.N_pad,
-                                         c.heads, rf2_qkv_strides(plan));
+  const bool keep = 2 * in.N * c.batch * c.heads * (int64_t)c.head_dim * 2 <= KEEP_UNPERMUTE;
+  const auto launch = [&](auto kernel) {
+    kernel<<<grid, 256, 0, st>>>((const uint4*)op, (uint4*)o, plan->d_inv, (int)in.N, (size_t)in.N_pad, c.heads, rf2_qkv_strides(plan));
+  };
+  if (c.head_dim == 128) keep ? launch(unpermute_kernel<128, true>) : launch(unpermute_kernel<128, false>);
+  else keep ? launch(unpermute_kernel<64, true>) : launch(unpermute_kernel<64, false>);
   RF2_LAUNCH_CHECK();
   return RF2_OK;
 }
