@@ -3,13 +3,15 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <cmath>
 #include <functional>
 #include <queue>
 #include <vector>
 
 #include "rf2.h"
 
-// The cut of the kernel with rings in LDS (block_sparse_attn_kernel; launches at d = 128 take rf2_cut_stream's, below).
+// rf2_cut_attn: the rule of thresholds for the former kernel, with rings in LDS and wavefronts of 32 rows.  No launch takes it any
+// more (rf2_cut_stream, below, does that); a host test still holds it to its measurements.
 // How a launch is cut, from the sizes of the plan alone (so that both exits of a layer give the same bits).
 // A row of the mask is one workgroup of `groups` (KS) groups of wavefronts that share its list (KS = 1: no merge); a Q block
 // of 256 rows is one workgroup of eight wavefronts or two of 128 rows.
@@ -119,34 +121,50 @@ inline rf2_attn_cut rf2_cut_attn(const rf2_config& c, const rf2_info& in) {
   return {full && parts >= 20 && !spread ? 256 : 128, 1};
 }
 
-// ---- the cut of stream_attn_kernel (d = 128) -----------------------------------------------------------------------
-// A workgroup has QH x KS wavefronts, QH = rows / 64, KS = groups, one to a SIMD.  Which QH and KS: the pair with the shortest
-// launch in a small model of it, made of what a launch is: jobs of two lengths (all-column sink rows first, then the others),
-// dealt in order to places that take the next job when they are done.
+// ---- the cut of stream_attn_kernel -----------------------------------------------------------------------------------
+// A workgroup has QH x KS wavefronts, QH = rows / 64, KS = groups.  Which QH and KS: the pair with the shortest launch in a
+// small model of it, made of what a launch is: jobs of two lengths (all-column sink rows first, then the others), dealt in order to
+// places that take the next job when they are done.
 //   * The busiest shader engine is looked at: 1/8 of the rows go to an XCD, 1/4 of its workgroups to each engine of 8 compute
-//     units = 32 wavefronts, 32 / (QH KS) workgroups.
+//     units, which hold 32 wavefronts at d = 128 and 64 at d = 64.
 //   * A job lasts 2 (parts / KS) units of a wavefront, plus the start of a row, plus the merge, all counted in units.
-//   * A unit takes 0.49 us where up to a third of the wavefront places are taken and 0.83 us where all are (clock under the power
-//     limit, shared L2), on a line between; QH = 2 or 4 takes 3 or 4 % less (tiles met in L1), KS = 2 or 4 1 or 5 % (fewer
-//     rows in flight on an XCD).
-// The constants are fitted to 140 launches of 600 to 40,000 tokens, 1 to 40 heads, blocks of 64, 128 and 256 rows, sparsity
-// 0.5 to 0.9, with and without sink rows and text, each timed with every cut: the model is 4 % off on average, its choice
-// 0.2 % slower than the best cut (5.7 % at most), and 1.28 times as fast as the former kernel's cut (1.04 to 2.3 times).
-// E.g. (us, QH x KS = 1x1, 1x2, 1x4, 2x1, 2x2): image of 4,096 tokens, 1 head 38, 24, 19, 39, 26; 8 heads 41, 36, 42, 41, 36;
+//   * A unit takes `idle` us where up to `knee` of the wavefront places are taken and `full` where all are (shared vector issue at d = 64,
+//     clock under the power limit, shared L2), along a line with a bow between.  By and large QH = 2 meets tiles in L1, KS = 2 and
+//     4 have fewer rows in flight on an XCD: factors of `full`.
+// The constants are fitted to launches of 600 to 40,000 tokens, 1 to 40 heads, blocks of 64, 128 and 256 rows, sparsity 0.5 to 0.9,
+// with and without sink rows and text (d = 128: 140 launches, d = 64: 125), and to 30 of 480p to long-video layers, each timed with
+// several cuts.  d = 128: the model is 4 % off on average, its choice 0.1 % slower than the best cut (6 % at most); d = 64: 7 % off,
+// 0.6 % slower (14 % at most, on launches under 100 us).  Against a rule of thresholds for a kernel with rings in LDS, d = 128,
+// 1.28 times as fast in the geometric mean.
+// E.g. d = 128 (us, QH x KS = 1x1, 1x2, 1x4, 2x1, 2x2): image of 4,096 tokens, 1 head 38, 24, 19, 39, 26; 8 heads 41, 36, 42, 41, 36;
 // 16 heads 66, 70, 84, 67, 72; 24 heads 104, 102, 124, 107, 105; 480p 5 heads 672, 492, 532, 665, 493, 40 heads 3,926, 3,974,
-// 4,251, 3,731, 3,936.
+// 4,251, 3,506, 3,800; 256-row blocks, 480p, 40 heads, 2x1 3,425, 4x1 3,394, 720p 18,067 and 17,653.  d = 64 (1x1, 1x2, 1x4, 1x8, 2x2): image,
+// 2 heads 34, -, -, 15, 21; 24 heads 63, 71, 66, 83, 57; 480p, 2 heads 495, -, -, 140, 263; 40 heads 2,133, 2,206, 2,258, 2,570, 2,107.
+struct rf2_stream_model {
+  double idle, full, knee, bow;                  // us per unit
+  double start, start2, start4;                  // units: start of a row, more of it for QH = 2 and 4
+  double merge2, merge4, merge8;                 // units: merge of KS shares
+  double rate2, rate4, of2, of4, of8, square;    // factors of `full`: QH = 2, 4; KS = 2, 4, 8; QH = KS = 2 (on top)
+  double launch;                                 // us
+  int waves;                                     // places of a shader engine
+};
+inline const rf2_stream_model& rf2_model_of(int head_dim) {
+  static const rf2_stream_model d128{0.507, 0.843, 0.372, -0.532, 4.04, 1.95, 6.58, 2.06, 5.02, 0.0, 0.957, 0.918, 0.984, 0.937, 1.0, 1.01, 5.1, 32};
+  static const rf2_stream_model d64{0.448, 0.931, 0.21, 0.084, 2.02, 0.85, 0.0, 2.42, 2.85, 6.57, 1.042, 1.0, 1.066, 1.003, 0.97, 0.865, 4.4, 64};
+  return head_dim == 128 ? d128 : d64;
+}
 struct rf2_stream_jobs {
   int64_t sinks, plain;          // jobs of a shader engine
-  double sink_units, plain_units;
+  double sink_parts, plain_parts;
 };
-inline double rf2_stream_time(rf2_stream_jobs j, int qh, int ks) {
-  constexpr int WAVES = 32;      // of a shader engine
-  const int places = WAVES / (qh * ks);
-  const double idle = 0.489, full = 0.828 * (qh == 4 ? 0.963 : qh == 2 ? 0.974 : 1.0) * (ks == 4 ? 0.952 : ks == 2 ? 0.986 : 1.0);
-  const double start = 3.9 + (qh == 4 ? 4.5 : qh == 2 ? 1.1 : 0.0) + (ks == 4 ? 4.9 : ks == 2 ? 2.8 : 0.0);
-  const double sink = j.sink_units / ks + start, plain = j.plain_units / ks + start;
+inline double rf2_stream_time(const rf2_stream_model& m, rf2_stream_jobs j, int qh, int ks) {
+  const int places = m.waves / (qh * ks);
+  const double full = m.full * (qh == 4 ? m.rate4 : qh == 2 ? m.rate2 : 1.0) * (ks == 8 ? m.of8 : ks == 4 ? m.of4 : ks == 2 ? m.of2 : 1.0) *
+                      (qh == 2 && ks == 2 ? m.square : 1.0);
+  const double more = m.start + (qh == 4 ? m.start4 : qh == 2 ? m.start2 : 0.0) + (ks == 8 ? m.merge8 : ks == 4 ? m.merge4 : ks == 2 ? m.merge2 : 0.0);
+  const double sink = 2.0 * std::ceil(j.sink_parts / ks) + more, plain = 2.0 * std::ceil(j.plain_parts / ks) + more;
+  double us = m.launch;
   // (many rounds of equal jobs: all but the last sixteen at the full rate)
-  double us = 5.3;
   const auto rounds = [&](int64_t& jobs, double units) {
     const int64_t skip = std::max<int64_t>(jobs / places - 16, 0);
     jobs -= skip * places;
@@ -168,8 +186,8 @@ inline double rf2_stream_time(rf2_stream_jobs j, int qh, int ks) {
   for (size_t s = 0, e = 0; e < ends.size();) {
     const bool begins = s < starts.size() && starts[s] < ends[e];
     const double at = begins ? starts[s] : ends[e];
-    const double taken = (double)((s - e) * qh * ks) / WAVES;
-    us += (at - last) * (idle + (full - idle) * std::max(0.0, (taken - 0.354) / (1.0 - 0.354)));
+    const double taken = (double)((s - e) * qh * ks) / m.waves, x = std::max(0.0, (taken - m.knee) / (1.0 - m.knee));
+    us += (at - last) * (m.idle + (full - m.idle) * (x + m.bow * x * (1.0 - x)));
     last = at;
     begins ? ++s : ++e;
   }
@@ -179,23 +197,29 @@ inline double rf2_stream_time(rf2_stream_jobs j, int qh, int ks) {
 // Ordinary rows: with whole heads on an XCD its L2 fetches 1/8 of the K and V that it does where every XCD has rows of every
 // head, but the Infinity Cache (256 MB) has to hold those of 8 heads at a time.  (every head in 8 shares -> whole heads: 4,096
 // tokens x 24 heads, 112 -> 106 us; 480p, 17 MB a head, 3.56 -> 3.52 ms; 48,384 tokens, 25 MB, 4.62 -> 4.61; 60,480 tokens, 31 MB,
-// 7.16 -> 7.16; 720p, 39 MB, 18.5 -> 18.8; long video, 61 MB, 13.7 -> 14.1.)  Launches of 64-row blocks have the more different
-// lists in flight and gain at 720p too (20 heads 11.6 -> 10.8 ms; long video, 6 heads, 3.77 -> 3.81).
+// 7.16 -> 7.16; 720p, 39 MB, 18.5 -> 18.8; long video, 61 MB, 13.7 -> 14.1; d = 64: 480p, 8 MB, 2.126 -> 2.107 ms, 720p, 19 MB, 10.98 ->
+// 10.87, long video, 30 MB, 8.24 -> 8.31.)  Launches of 64-row blocks have the more different lists in flight and gain at 720p too
+// (20 heads 11.6 -> 10.8 ms, d = 64, 40 heads 11.46 -> 11.22; long video, 6 heads, 3.77 -> 3.81).
 inline rf2_attn_cut rf2_cut_stream(const rf2_config& c, const rf2_info& in) {
+  const rf2_stream_model& m = rf2_model_of(c.head_dim);
   const int64_t lists = (int64_t)c.batch * c.heads, sink_rows = in.sink_block_end - in.sink_block_begin;
   const int64_t sinks = (lists * sink_rows + 7) / 8, plain = (lists * (in.n_blocks - sink_rows) + 7) / 8;      // of an XCD
-  const double units = in.block_k / 32;
+  const double parts = in.block_k / 64;
   double keeps = in.k_row;
   // (cumulative mass: a row is taken to keep what a flat one does)
   if (in.kept_pairs_per_head < 0) keeps = std::max(1.0, (double)in.k_row * 0.5 * c.cdf_threshold * (1.0 + c.cdf_threshold));
+  // (the pairs that were the best of all cuts for some size: at d = 64 2 x 1, 4 x 1 and 2 x 4 never by more than 1 %)
+  static const int pairs128[][2] = {{1, 1}, {1, 2}, {1, 4}, {2, 1}, {2, 2}, {4, 1}}, pairs64[][2] = {{1, 1}, {1, 2}, {1, 4}, {1, 8}, {2, 2}};
+  const auto* pairs = c.head_dim == 128 ? pairs128 : pairs64;
   rf2_attn_cut best{64, 1, false};
   double least = 0.0;
-  for (int qh = 1; 64 * qh <= c.block; qh *= 2)
-    for (int ks = 1; qh * ks <= 4; ks *= 2) {
-      const int64_t share = c.block / (64 * qh), of_sinks = (sinks * share + 3) / 4, all = ((sinks + plain) * share + 3) / 4;
-      const double us = rf2_stream_time({of_sinks, all - of_sinks, in.n_blocks_k * units, keeps * units}, qh, ks);
-      if (least == 0.0 || us < least) least = us, best = {64 * qh, ks, false};
-    }
-  best.whole_heads = c.block == 64 || in.N_pad_k * c.head_dim * 4 <= (int64_t)32 << 20;
+  for (int i = 0; i < (c.head_dim == 128 ? 6 : 5); ++i) {
+    const int qh = pairs[i][0], ks = pairs[i][1];
+    if (64 * qh > c.block) continue;
+    const int64_t share = c.block / (64 * qh), of_sinks = (sinks * share + 3) / 4, all = ((sinks + plain) * share + 3) / 4;
+    const double us = rf2_stream_time(m, {of_sinks, all - of_sinks, in.n_blocks_k * parts, keeps * parts}, qh, ks);
+    if (least == 0.0 || us < least) least = us, best = {64 * qh, ks, false};
+  }
+  best.whole_heads = c.block == 64 || in.N_pad_k * c.head_dim * 4 <= (int64_t)24 << 20;
   return best;
 }

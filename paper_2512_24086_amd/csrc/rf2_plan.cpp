@@ -157,7 +157,7 @@ int rf2_plan_create(const rf2_config* cfg, rf2_plan** out) {
 
   // Cut of the attention launches; permutation tables from the closed form.
   try {
-    p->cut = c.head_dim == 128 ? rf2_cut_stream(c, in) : rf2_cut_attn(c, in);
+    p->cut = rf2_cut_stream(c, in);
     p->perm.assign((size_t)N, -1);
     p->inv.assign((size_t)N, -1);
   } catch (...) { delete p; return RF2_ERR_ALLOC; }

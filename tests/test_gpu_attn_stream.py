@@ -1,4 +1,4 @@
-"""The d = 128 attention kernel in every way a launch is cut (64-row tiles of a workgroup, wavefronts that share a list), on the
+"""The attention kernel in every way a launch is cut (64-row tiles of a workgroup, wavefronts that share a list), on the
 lists, logits and bounds of test_gpu_attn_cut: rows of no block up to all, a ragged last block with and without a part that holds
 no key, a reference that moves.  Launches of 256-row workgroups are as large as a 720p layer: test_gpu_fullsize has them."""
 import ctypes as C
@@ -12,10 +12,14 @@ from paper_2512_24086_amd import rf2
 from tests import test_gpu_attn_cut as cut_tests
 
 # (tokens, block, block_k, head_dim, heads) -> (rows of a workgroup, wavefronts that share a list)
-SHAPES = {(330, 64, 64, 128, 200): (64, 1), (330, 64, 128, 128, 200): (64, 1), (600, 64, 64, 128, 12): (64, 2),
-          (2450, 64, 128, 128, 8): (64, 2), (600, 64, 64, 128, 3): (64, 4), (657, 64, 128, 128, 2): (64, 4),
-          (2500, 128, 64, 128, 24): (128, 1), (2450, 128, 128, 128, 24): (128, 1), (4001, 128, 64, 128, 8): (128, 2),
-          (4000, 256, 128, 128, 8): (128, 2), (2500, 256, 64, 128, 3): (64, 4), (900, 256, 128, 128, 2): (64, 4)}
+SHAPES = {(330, 64, 64, 128, 200): (64, 1), (330, 64, 128, 128, 200): (64, 1), (2450, 128, 64, 128, 12): (64, 2),
+          (2450, 64, 128, 128, 8): (64, 2), (657, 64, 64, 128, 1): (64, 4), (2450, 256, 128, 128, 2): (64, 4),
+          (4000, 128, 64, 128, 41): (128, 1), (4001, 128, 128, 128, 41): (128, 1), (6177, 128, 64, 128, 5): (128, 2),
+          (6200, 256, 128, 128, 5): (128, 2),
+          (999, 64, 64, 64, 100): (64, 1), (2450, 128, 128, 64, 41): (64, 1), (1500, 64, 64, 64, 23): (64, 2),
+          (600, 128, 128, 64, 24): (64, 2), (657, 64, 64, 64, 17): (64, 4), (900, 128, 128, 64, 3): (64, 4),
+          (2450, 64, 64, 64, 1): (64, 8), (4000, 128, 128, 64, 1): (64, 8), (2450, 128, 64, 64, 24): (128, 2),
+          (2450, 128, 128, 64, 24): (128, 2), (900, 256, 64, 64, 64): (128, 2)}
 
 SOURCE = """#include "rf2_attn_cut.h"
 extern "C" void cut(const rf2_config* c, const rf2_info* i, int* out) {
@@ -38,8 +42,8 @@ def test_cuts(tmp_path):
         plan.close()
         return tuple(out)
 
-    for (tokens, block, block_k, _, heads), want in SHAPES.items():
-        assert cut(W=tokens, block=block, block_k=block_k, heads=heads)[:2] == want, (tokens, block, block_k, heads)
+    for (tokens, block, block_k, d, heads), want in SHAPES.items():
+        assert cut(W=tokens, block=block, block_k=block_k, head_dim=d, heads=heads)[:2] == want, (tokens, block, block_k, d, heads)
     video = dict(T=21, H=45, W=80, sparsity=0.8, sink_frames=1, window=(0, 0, 0))
     assert cut(**video, heads=40, block=128) == (128, 1, 0)          # 8 heads' K and V are larger than the Infinity Cache
     assert cut(**video, heads=40, block=256, block_k=128) == (256, 1, 0)
