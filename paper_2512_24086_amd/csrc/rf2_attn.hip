@@ -114,9 +114,9 @@ __global__ void __launch_bounds__(64 * QH * KS, D == 128 ? 1 : 2) stream_attn_ke
     const __bf16* __restrict__ qp, const __bf16* __restrict__ kp, const __bf16* __restrict__ vp,
     const int32_t* __restrict__ blk_idx, const int32_t* __restrict__ blk_cnt, __bf16* __restrict__ op,
     float* __restrict__ lse, RowOrder order, int Tb, int k_row, int last_valid, float scale_log2,
-    const int32_t* __restrict__ scatter, int n_tokens, int heads, rf2_strides st, int split) {
+    const int32_t* __restrict__ perm, int n_tokens, int heads, rf2_strides st, int split, bool fused) {
   // split: log2 of the workgroups that share a Q block; they are neighbours on one XCD.  Tb: K/V blocks per head (columns of
-  // the block mask); last_valid: tokens in the last one.
+  // the block mask); last_valid: tokens in the last one; perm: token of a permuted row; fused: output in the caller's token order.
   constexpr int BQ = 64 * QH, KH = BK / 2, PB = BK / 64, DS = D / 16, DT = D / 32;
   constexpr int TILE_BYTES = BK * D * 2, PART_BYTES = 64 * D * 2;
   const int xcd = blockIdx.x & 7, share = (int)(blockIdx.x >> 3) & ((1 << split) - 1), slot = (int)(blockIdx.x >> 3) >> split;
@@ -124,26 +124,44 @@ __global__ void __launch_bounds__(64 * QH * KS, D == 128 ? 1 : 2) stream_attn_ke
   if (!row_of(order, xcd, slot, bh, qi)) return;
   const int Tq = order.rows;
   const size_t row_id = (size_t)bh * Tq + qi;
+  const int32_t* __restrict__ list = blk_idx + row_id * k_row;
+  const int wave = QH * KS > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) : 0;
+  const int half = wave % QH, grp = wave / QH;
+  const int lane = (int)threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
+  // The start of a row is a chain of latencies that nothing covers, so what can be asked for at once is: the count, the list's
+  // entries of the wavefront's first three parts and its last one as if it were full (behind the count lies whatever the caller
+  // left, inside the list and clamped like any entry; it is replaced or never multiplied), Q, and the rows of the output.  (One
+  // after the other: tiny layer 21.9 us, now 21.2, image of 24 heads 137.9, now 135.0; 480p and larger layers +0.0 to +0.4 %.)
   int cnt = blk_cnt[row_id];
+  int ahead[3];
+#pragma unroll
+  for (int p = 0; p < 3; ++p) ahead[p] = list[min((p * KS + grp) / PB, k_row - 1)];
+  int tail = list[k_row - 1];
+  __builtin_amdgcn_sched_barrier(0);
+  const size_t q_head_off = (size_t)bh * (Tq << split) * BQ * D;             // elements; qp and op
+  const int q_row = ((qi << split) + share) * BQ + 64 * half + l32;          // this lane's query row of tile 0 in its head
+  bf16x8 qf[2][DS];
+  const __bf16* const q_from = qp + q_head_off + (size_t)q_row * D + 8 * lh;
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+#pragma unroll
+    for (int ds = 0; ds < DS; ++ds) qf[q][ds] = *reinterpret_cast<const bf16x8*>(q_from + q * 32 * D + 16 * ds);
+  const int token[2] = {perm[q_row], perm[q_row + 32]};                      // -1: padding of the last block
+  __builtin_amdgcn_sched_barrier(0);
+  asm("" : "+s"(cnt), "+s"(tail), "+s"(ahead[0]), "+s"(ahead[1]), "+s"(ahead[2]));   // (left alone, the entries wait for the count)
   const bool dense = (cnt == Tb);
   cnt = dense ? Tb : min(max(cnt, 0), k_row);
-  const int32_t* __restrict__ list = blk_idx + row_id * k_row;
   // Only the last listed block can be the ragged last block of the sequence (lists ascend).
   bool ragged = false;
   if (cnt > 0 && last_valid < BK) {
-    const int jl = dense ? cnt - 1 : list[cnt - 1];
+    const int jl = dense ? cnt - 1 : cnt == k_row ? tail : list[cnt - 1];
     ragged = min(max(jl, 0), Tb - 1) == Tb - 1;
   }
   int NPARTS = cnt * PB;
   // (a last part without any valid key is left out, so that every wavefront has a valid key in its first unit)
   if (KS > 1 && PB > 1 && ragged && last_valid <= 32) --NPARTS;
-  const int wave = QH * KS > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) : 0;
-  const int half = wave % QH, grp = wave / QH;
   const int parts = KS > 1 ? max(NPARTS - grp + KS - 1, 0) / KS : NPARTS;    // this wavefront's: grp, grp + KS, ...
   const int U = 2 * parts;                                                   // its 32-key units (even)
-  const int lane = (int)threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
-  const size_t q_head_off = (size_t)bh * (Tq << split) * BQ * D;             // elements; qp and op
-  const int q_row = ((qi << split) + share) * BQ + 64 * half + l32;          // this lane's query row of tile 0 in its head
   const size_t k_head_off = (size_t)bh * Tb * BK * D;                        // kp and vp
   // (buffer loads: scalar offsets of tile and operand beside a constant per-lane one; nothing past a head's K or V is read)
   const unsigned head_bytes = (unsigned)Tb * (unsigned)TILE_BYTES;
@@ -170,7 +188,6 @@ __global__ void __launch_bounds__(64 * QH * KS, D == 128 ? 1 : 2) stream_attn_ke
   auto part_of = [&](int P) { return P * KS + grp; };    // list part of this wavefront's part P
   const int partial_begin = ragged ? 2 * (max((cnt - 1) * PB - grp + KS - 1, 0) / KS) : U;   // first unit of the ragged block
 
-  bf16x8 qf[2][DS];
   f32x16 o[2][DT];
 #pragma unroll
   for (int q = 0; q < 2; ++q)
@@ -266,13 +283,10 @@ __global__ void __launch_bounds__(64 * QH * KS, D == 128 ? 1 : 2) stream_attn_ke
       nmc[q] = -m_ref[q] * scale_log2;
     }
   };
-  auto load_q = [&]() {
-    const __bf16* qrow = qp + q_head_off + (size_t)q_row * D + 8 * lh;
-#pragma unroll
-    for (int q = 0; q < 2; ++q)
-#pragma unroll
-      for (int ds = 0; ds < DS; ++ds) qf[q][ds] = *reinterpret_cast<const bf16x8*>(qrow + q * 32 * D + 16 * ds);
-    asm volatile("" ::: "memory");
+  // Offset of this wavefront's part p < 3, from the entry that was asked for ahead (past the end of the list: any part in bounds).
+  auto first_off = [&](int p) {
+    const int P = part_of(p), j = min(max(dense ? P / PB : ahead[p], 0), Tb - 1);
+    return (uint32_t)j * (uint32_t)TILE_BYTES + (unsigned)(P % PB) * (uint32_t)PART_BYTES;
   };
   // Two wavefronts that ask for the same tiles meet every 16 parts: left alone they drift apart, out of reach of each other's
   // tiles in L1 (d = 128, 720p, 24 heads, 11.25 -> 10.99 ms, 480p 3.59 -> 3.56; every part or every 4th: no more, and dearer on
@@ -334,15 +348,16 @@ __global__ void __launch_bounds__(64 * QH * KS, D == 128 ? 1 : 2) stream_attn_ke
       slow = redo || (s + 1 >= partial_begin);
     };
     if (U > 0) {
-      uint32_t off0 = part_off(list_entry(part_of(0)), part_of(0)), off1 = part_off(list_entry(part_of(1)), part_of(1));   // parts P, P + 1
+      uint32_t off0 = first_off(0), off1 = first_off(1);   // parts P, P + 1
       bf16x8 k0[NQ];
 #pragma unroll
       for (int c = 0; c < NQ; ++c) k0[c] = k_load(off0, c);
 #pragma unroll
       for (int c = 0; c < NQ; ++c) kr[0][c] = k_load(off0 + K_TILE, c);
-      load_q();
+      asm volatile("" ::: "memory");
 #pragma unroll
       for (int c = 0; c < NQ; ++c) kr[1][c] = k_load(off1, c);
+      asm volatile("" ::: "memory");
 #pragma unroll
       for (int j = 0; j < NP; ++j) {
         vr[1][j] = v_load(off0, j);
@@ -352,6 +367,9 @@ __global__ void __launch_bounds__(64 * QH * KS, D == 128 ? 1 : 2) stream_attn_ke
       f32x16 Sa[2], Sb[2];
       uint32_t Pa[2][8], Pb[2][8];
       first_unit(Sa, k0);
+      // (arrived before the loop, whose waits would else be those of its first round: vr[0] is not on its way yet)
+#pragma unroll
+      for (int c = 0; c < NQ; ++c) asm volatile("" : "+v"(kr[0][c]));
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
 #pragma unroll
@@ -360,7 +378,7 @@ __global__ void __launch_bounds__(64 * QH * KS, D == 128 ? 1 : 2) stream_attn_ke
         for (int i = 0; i < 16; ++i) Sb[q][i] = 0.f;
       }
       // A list entry is read a round before it is turned into an offset, so that no step waits for a scalar memory load.
-      int entry = list_entry(part_of(2));
+      int entry = dense ? part_of(2) / PB : ahead[2];
       for (int s = 0; s < U; s += 2) {
         const int P = s >> 1;
         meet(P);
@@ -432,12 +450,12 @@ __global__ void __launch_bounds__(64 * QH * KS, D == 128 ? 1 : 2) stream_attn_ke
     const int most = (NPARTS + KS - 1) / KS;        // of the wavefronts that share the list
     if (KS > 1 && U == 0 && most > 0) meet(0);
     if (U > 0) {
-      const uint32_t off0 = part_off(list_entry(part_of(0)), part_of(0));
-      uint32_t off1 = part_off(list_entry(part_of(1)), part_of(1));      // part P + 1
+      const uint32_t off0 = first_off(0);
+      uint32_t off1 = first_off(1);                                      // part P + 1
       bf16x8 k0[NQ];
 #pragma unroll
       for (int c = 0; c < NQ; ++c) k0[c] = k_load(off0, c);
-      load_q();
+      asm volatile("" ::: "memory");
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
 #pragma unroll
@@ -452,7 +470,7 @@ __global__ void __launch_bounds__(64 * QH * KS, D == 128 ? 1 : 2) stream_attn_ke
       redo_tile(0, S[0], P[0]);                     // probabilities of tile 0 of the first unit (the reference stays where it is)
 #pragma unroll
       for (int e = 0; e < 8; ++e) P[1][e] = 0u;
-      int entry = list_entry(part_of(2));
+      int entry = dense ? part_of(2) / PB : ahead[2];
       for (int s = 0; s < U; s += 2) {
         const int p = s >> 1;
         meet(p);
@@ -540,9 +558,9 @@ __global__ void __launch_bounds__(64 * QH * KS, D == 128 ? 1 : 2) stream_attn_ke
     const float f = l_tot[q] > 0.f ? 1.0f / l_tot[q] : 0.f;   // a row with no kept key yields zeros
     const size_t row = (size_t)q_row + 32 * q;
     // plain output: row `row` of the permuted layout; fused inverse permutation: the token's raster row
-    const int target = scatter ? scatter[row] : (int)row;
+    const int target = fused ? token[q] : (int)row;
     if (target < 0) continue;                                 // padding row of the last block
-    __bf16* orow = scatter ? op + ((bh / heads) * st.batch + (bh % heads) * st.head + (long long)target * st.token) * D
+    __bf16* orow = fused ? op + ((bh / heads) * st.batch + (bh % heads) * st.head + (long long)target * st.token) * D
                            : op + q_head_off + row * D;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
@@ -555,7 +573,7 @@ __global__ void __launch_bounds__(64 * QH * KS, D == 128 ? 1 : 2) stream_attn_ke
           *reinterpret_cast<bf16x4*>(orow + 32 * dt + 8 * g + 4 * lh) = pk;
         }
     if (lse != nullptr && lh == 0 && finishes(q, 0))
-      lse[scatter ? (size_t)bh * n_tokens + target : (size_t)bh * (Tq << split) * BQ + row] =
+      lse[fused ? (size_t)bh * n_tokens + target : (size_t)bh * (Tq << split) * BQ + row] =
           m_ref[q] * scale_log2 * 0.6931471805599453f + __logf(l_tot[q]);
   }
 }
@@ -590,7 +608,7 @@ int launch_stream(const rf2_plan* plan, const AttnArgs& a, hipStream_t st) {
   stream_attn_kernel<D, BK, QH, KS><<<dim3((8u * slots) << split), dim3(64 * QH * KS), 0, st>>>(
       (const __bf16*)a.qp, (const __bf16*)a.kp, (const __bf16*)a.vp, a.blk_idx, a.blk_cnt, (__bf16*)a.out, a.lse, order,
       in.n_blocks_k, in.k_row, in.last_block_valid_k, (float)(1.4426950408889634 / sqrt((double)D)),
-      a.scatter ? plan->d_perm : nullptr, (int)in.N, plan->cfg.heads, rf2_qkv_strides(plan), split);
+      plan->d_perm, (int)in.N, plan->cfg.heads, rf2_qkv_strides(plan), split, a.scatter);
   RF2_LAUNCH_CHECK();
   return RF2_OK;
 }

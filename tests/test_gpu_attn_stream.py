@@ -6,9 +6,11 @@ import os
 import subprocess
 
 import pytest
+import torch
 
 from paper_2512_24086_amd import build as b
 from paper_2512_24086_amd import rf2
+from tests import helpers as hp
 from tests import test_gpu_attn_cut as cut_tests
 
 # (tokens, block, block_k, head_dim, heads) -> (rows of a workgroup, wavefronts that share a list)
@@ -57,3 +59,29 @@ def test_cuts(tmp_path):
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
 def test_every_cut(shape):
     cut_tests.test_lists_of_every_length(shape, 24.0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [(2450, 128, 64, 128, 12), (657, 64, 64, 128, 1), (4001, 128, 128, 128, 41), (6177, 128, 64, 128, 5),
+                                   (2450, 128, 128, 64, 41), (2450, 64, 64, 64, 1), (2450, 128, 128, 64, 24)], ids=lambda s: "x".join(map(str, s)))
+def test_entries_behind_the_count(shape):
+    """A row's first and last entries are asked for before its count is known: what a list holds behind its count, and at all
+    where a row keeps every column, changes no bit of the result."""
+    tokens, block, block_k, d, heads = shape
+    print(f"[case] {shape}", flush=True)
+    plan = rf2.Plan(batch=1, heads=heads, head_dim=d, T=1, H=1, W=tokens, block=block, block_k=block_k, sparsity=0.3, window=(1, 1, 16))
+    i = plan.info
+    g = torch.Generator(device="cuda").manual_seed(11)
+    q, k, v = (torch.randn(1, heads, tokens, d, generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    idx, cnt = hp.lists_to_device(cut_tests.lists(plan, 5), i.k_row, i.n_blocks, "cuda")
+    buf = plan.alloc("cuda", lse=True)
+    plan.rf2_permute(q, k, v, buf["qp"], buf["kp"], buf["vp"])
+    unused = (torch.arange(i.k_row, device="cuda") >= cnt[..., None]) | (cnt[..., None] == i.n_blocks_k)
+    results = []
+    for fill in (0, -1, i.n_blocks_k - 1, 2**31 - 1, -2**31):
+        plan.rf2_block_sparse_attn(buf["qp"], buf["kp"], buf["vp"], idx.masked_fill(unused, fill), cnt, buf["op"], buf["lse"])
+        results.append((buf["op"].view(torch.int16).clone(), buf["lse"].clone()))
+    assert unused.any()
+    for op, lse in results[1:]:
+        assert torch.equal(op, results[0][0]) and torch.equal(lse, results[0][1])
+    plan.close()
