@@ -17,7 +17,10 @@
 // search costs a compare and a population count per 64 keys; on bell-shaped rows, as smooth fields give, the
 // normal-distribution guess and interpolation need 4 or 5 of them where a bitwise search that stops at the first exact
 // count needs 15.5 (other rows: see MAX_GUIDED).  720p: 104 -> 70 us; cumulative mass on the long video (929 x 929, 24
-// heads): 291 -> 143 us; with few workgroups 12-50 -> 8-15 us.  Wavefronts that share a K tile (32, 48 or 64 rows per
+// heads): 291 -> 146 us; with few workgroups 12-50 -> 8-15 us.  No load of K, no read of a key and no store of a list entry
+// stands behind a branch: buffers drop what lies outside of kbar or of the list.  (Behind branches the compiler waited for the
+// whole next K tile at the end of each, and every entry cost four scalar instructions: 720p 70.1 -> 68.7 us, long video,
+// cumulative mass, 146.8 -> 135.8.)  Wavefronts that share a K tile (32, 48 or 64 rows per
 // workgroup) halve the L2 reads and are slower (98-122 us on 720p).
 #include "rf2_internal.h"
 
@@ -155,7 +158,11 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 && EMAX <= 12 ? 6 : 4) predic
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lr = lane & 15, lk = lane >> 4;
   const float* __restrict__ qb = qbar + (size_t)bh * Tq * D;
-  const float* __restrict__ kb = kbar + (size_t)bh * Tb * D;
+  // kbar of the head as a buffer: columns past the row read as zero and cost nothing, so no load stands behind a branch.
+  const auto kbuf = __builtin_amdgcn_make_buffer_rsrc((void*)(kbar + (size_t)bh * Tb * D), 0, (unsigned)Tb * D * 4, 0x00020000);
+  auto k_load = [&](int ct, int kk) {
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(kbuf, ((ct * 16 + lr) * D + 4 * lk) * 4 + 64 * kk, 0, 0));
+  };
 
   // ---- scores: 16 x 16 tiles with v_mfma_f32_16x16x4_f32 -------------------------------
   // Lane (lr, lk) feeds row lr of each operand.  Per 16 channels it loads 4 consecutive
@@ -163,10 +170,8 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 && EMAX <= 12 ? 6 : 4) predic
   // 16*kk + 4*lk + e in both operands (a dot product does not care about summation order).
   const int n_ct = (Tb + 15) / 16;
   f32x4 b[D / 16];
-  const float* __restrict__ kcol = kb + 4 * lk;
 #pragma unroll
-  for (int kk = 0; kk < D / 16; ++kk)
-    b[kk] = *reinterpret_cast<const f32x4*>(kcol + (size_t)min(wave * 16 + lr, Tb - 1) * D + 16 * kk);
+  for (int kk = 0; kk < D / 16; ++kk) b[kk] = k_load(wave, kk);
   for (int c = threadIdx.x; c < R * (D / 4); c += NW * 64) {
     const int row = c / (D / 4), ch = c % (D / 4) * 4;
     *reinterpret_cast<f32x4*>(&qs[row][ch]) = *reinterpret_cast<const f32x4*>(qb + (size_t)min(i0 + row, Tq - 1) * D + ch);
@@ -175,16 +180,15 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 && EMAX <= 12 ? 6 : 4) predic
   float sum[4] = {}, sum2[4] = {};
   for (int ct = wave; ct < n_ct; ct += NW) {
     // the registers of a chunk are reloaded for the wavefront's next column tile as soon as its products are issued
-    const bool more = ct + NW < n_ct;
-    const float* __restrict__ knext = kcol + (size_t)min((ct + NW) * 16 + lr, Tb - 1) * D;
     f32x4 acc = {}, a = *reinterpret_cast<const f32x4*>(&qs[lr][4 * lk]);
 #pragma unroll
     for (int kk = 0; kk < D / 16; ++kk) {
       const f32x4 a_now = a;
       if (kk + 1 < D / 16) a = *reinterpret_cast<const f32x4*>(&qs[lr][16 * (kk + 1) + 4 * lk]);
+      __builtin_amdgcn_sched_barrier(0);      // (left alone, the read comes behind three of the products, into their registers)
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a_now[e], b[kk][e], acc, 0, 0, 0);
-      if (more) b[kk] = *reinterpret_cast<const f32x4*>(knext + 16 * kk);
+      b[kk] = k_load(ct + NW, kk);
       __builtin_amdgcn_sched_barrier(0);      // (left alone, the loads of all chunks are gathered in twice the registers)
     }
     // acc[i] = S_hat[i0 + 4*lk + i][ct*16 + lr]
@@ -234,7 +238,11 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 && EMAX <= 12 ? 6 : 4) predic
     }
     uint32_t key[EMAX];
 #pragma unroll
-    for (int e = 0; e < EMAX; ++e) key[e] = 64 * e + lane < Tb ? keys[r * LD + 64 * e + lane] : PAST_KEY;
+    for (int e = 0; e < EMAX; ++e) {
+      // (read in any case: without a branch; what lies behind the row is in the strip or in the words allocated behind it)
+      key[e] = keys[r * LD + 64 * e + lane];
+      key[e] = 64 * e + lane < Tb ? key[e] : PAST_KEY;
+    }
     float sum_r = 0.f, sum2_r = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) { sum_r += stat[w][r][0]; sum2_r += stat[w][r][1]; }
@@ -267,7 +275,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 && EMAX <= 12 ? 6 : 4) predic
         if (p == 0) t += (float)(cnt - k_row) * sigma * guess.slope;
         else if (lo == PAST_KEY + 1u) t = fh - sigma * (0.25f * (float)(1 << min(p, 12)));      // no lower (upper) end yet
         else if (top == SINK_KEY - 1u) t = fl + sigma * (0.25f * (float)(1 << min(p, 12)));
-        else t = fl + (fh - fl) * ((stalled & 1) ? 0.5f : (float)(n_lo - k_row) / (float)(n_lo - n_top));
+        else t = fl + (fh - fl) * ((stalled & 1) ? 0.5f : (float)(n_lo - k_row) * __builtin_amdgcn_rcpf((float)(n_lo - n_top)));
       }
       for (int p = 0; !exact && lo < top; ++p) {
         if (p % TIGHTEN == 0) draw_in(key, lo, top);
@@ -319,7 +327,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 && EMAX <= 12 ? 6 : 4) predic
         const float fl = key_value(lo), fh = key_value(top);
         if (p == 0) t += (mass / total - tau) * sigma * guess.slope;
         else if (lo == PAST_KEY + 1u) t = fh - sigma * (0.25f * (float)(1 << min(p, 12)));
-        else t = fl + (fh - fl) * (halve ? 0.5f : (m_lo - target) / (m_lo - m_top));
+        else t = fl + (fh - fl) * (halve ? 0.5f : (m_lo - target) * __builtin_amdgcn_rcpf(m_lo - m_top));
       }
       for (int p = 0; n_lo - n_top > 1 && lo < top; ++p) {
         if (p % TIGHTEN == TIGHTEN / 2) draw_in(key, lo, top);    // (first after four: mostly two or three are left to do)
@@ -345,12 +353,14 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 && EMAX <= 12 ? 6 : 4) predic
         run += popc64(eq_m);
       }
     }
+    // (lanes without an entry store past the end of the row's list, which a buffer drops: no branch around each store)
+    const auto list = __builtin_amdgcn_make_buffer_rsrc((void*)out, 0, k_row * 4, 0x00020000);
     int out_run = 0;
 #pragma unroll
     for (int e = 0; e < EMAX; ++e) {
       const bool sel = key[e] > T;
       const unsigned long long sel_m = __builtin_amdgcn_ballot_w64(sel);
-      if (sel) out[out_run + rank_below(sel_m)] = 64 * e + lane;
+      __builtin_amdgcn_raw_buffer_store_b32((uint32_t)(64 * e + lane), list, sel ? (out_run + rank_below(sel_m)) * 4 : 1 << 30, 0, 0);
       out_run += popc64(sel_m);
     }
     if (mrow) {
@@ -372,9 +382,9 @@ struct MaskLaunch {
 // The kernel is instantiated for a few row widths (EMAX keys per lane): the search loops run over
 // EMAX keys without bounds checks (keys past the row are 0), so a snug width saves compares.
 template <int D, int NW>
-const void* mask_kernel_for(int E, bool cdf) {
+const void* mask_kernel_for(int E, bool cdf, int* width) {
 #define RF2_MASK_CASE(W) \
-  if (E <= W) return cdf ? (const void*)predict_mask_kernel<D, W, true, NW> : (const void*)predict_mask_kernel<D, W, false, NW>;
+  if (E <= W) return *width = W, cdf ? (const void*)predict_mask_kernel<D, W, true, NW> : (const void*)predict_mask_kernel<D, W, false, NW>;
   RF2_MASK_CASE(2)
   RF2_MASK_CASE(4)
   RF2_MASK_CASE(6)
@@ -393,15 +403,17 @@ MaskLaunch mask_launch(const rf2_plan* plan) {
   MaskLaunch m;
   m.E = (plan->info.n_blocks_k + 63) / 64;
   m.LD = (plan->info.n_blocks_k + 15) / 16 * 16 + 4;   // +4: the 4 row groups of a tile store hit distinct banks
-  m.lds = (size_t)16 * m.LD * sizeof(uint32_t);
   // Up to one workgroup per compute unit a row's search is latency: 16 wavefronts search one row each.  Beyond, a
   // compute unit holds three workgroups of 8 wavefronts but only one of 16 (up to about 690 columns: LDS).  (16 against 8 wavefronts: 9.5 / 10.3 us
   // at 28 workgroups, 12.4 / 13.0 at 35, 20.3 / 21.2 at 136; 21.2 / 19.7 us at 320, 92 / 72 us at 1,480.)
   const int64_t strips = (int64_t)((plan->info.n_blocks + 15) / 16) * plan->cfg.batch * plan->cfg.heads;
   m.NW = strips <= 256 ? 16 : 8;
   const bool cdf = (plan->cfg.select_mode == RF2_SELECT_CDF);
-  if (plan->cfg.head_dim == 128) m.kernel = m.NW == 8 ? mask_kernel_for<128, 8>(m.E, cdf) : mask_kernel_for<128, 16>(m.E, cdf);
-  else m.kernel = m.NW == 8 ? mask_kernel_for<64, 8>(m.E, cdf) : mask_kernel_for<64, 16>(m.E, cdf);
+  int width = 0;
+  if (plan->cfg.head_dim == 128) m.kernel = m.NW == 8 ? mask_kernel_for<128, 8>(m.E, cdf, &width) : mask_kernel_for<128, 16>(m.E, cdf, &width);
+  else m.kernel = m.NW == 8 ? mask_kernel_for<64, 8>(m.E, cdf, &width) : mask_kernel_for<64, 16>(m.E, cdf, &width);
+  // the strip, and what the last row's 64 x width key reads reach behind it
+  m.lds = ((size_t)16 * m.LD + std::max(64 * width - m.LD, 0)) * sizeof(uint32_t);
   return m;
 }
 
