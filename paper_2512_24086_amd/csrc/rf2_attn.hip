@@ -109,17 +109,21 @@ __device__ __forceinline__ bool row_of(const RowOrder& w, int xcd, int slot, int
   return qi >= 0;
 }
 
+// Parameters of both kernels.  split: log2 of the workgroups that share a Q block; they are neighbours on one XCD.  Tb: K/V blocks
+// per head (columns of the block mask); last_valid: tokens in the last one; perm: token of a permuted row; fused: output in the
+// caller's token order.
+#define RF2_STREAM_PARAMS \
+  const __bf16 *__restrict__ qp, const __bf16 *__restrict__ kp, const __bf16 *__restrict__ vp, const int32_t *__restrict__ blk_idx, \
+      const int32_t *__restrict__ blk_cnt, __bf16 *__restrict__ op, float *__restrict__ lse, RowOrder order, int Tb, int k_row, \
+      int last_valid, float scale_log2, const int32_t *__restrict__ perm, int n_tokens, int heads, rf2_strides st, int split, bool fused
+#define RF2_STREAM_ARGS \
+  qp, kp, vp, blk_idx, blk_cnt, op, lse, order, Tb, k_row, last_valid, scale_log2, perm, n_tokens, heads, st
+
+// One workgroup: number `share` of those of a Q block, number `slot` of the XCD's rows.
 template <int D, int BK, int QH, int KS>
-__global__ void __launch_bounds__(64 * QH * KS, D == 128 ? 1 : 2) stream_attn_kernel(
-    const __bf16* __restrict__ qp, const __bf16* __restrict__ kp, const __bf16* __restrict__ vp,
-    const int32_t* __restrict__ blk_idx, const int32_t* __restrict__ blk_cnt, __bf16* __restrict__ op,
-    float* __restrict__ lse, RowOrder order, int Tb, int k_row, int last_valid, float scale_log2,
-    const int32_t* __restrict__ perm, int n_tokens, int heads, rf2_strides st, int split, bool fused) {
-  // split: log2 of the workgroups that share a Q block; they are neighbours on one XCD.  Tb: K/V blocks per head (columns of
-  // the block mask); last_valid: tokens in the last one; perm: token of a permuted row; fused: output in the caller's token order.
+__device__ __forceinline__ void attend(RF2_STREAM_PARAMS, int xcd, int slot, int share) {
   constexpr int BQ = 64 * QH, KH = BK / 2, PB = BK / 64, DS = D / 16, DT = D / 32;
   constexpr int TILE_BYTES = BK * D * 2, PART_BYTES = 64 * D * 2;
-  const int xcd = blockIdx.x & 7, share = (int)(blockIdx.x >> 3) & ((1 << split) - 1), slot = (int)(blockIdx.x >> 3) >> split;
   int bh, qi;
   if (!row_of(order, xcd, slot, bh, qi)) return;
   const int Tq = order.rows;
@@ -578,6 +582,22 @@ __global__ void __launch_bounds__(64 * QH * KS, D == 128 ? 1 : 2) stream_attn_ke
   }
 }
 
+template <int D, int BK, int QH, int KS>
+__global__ void __launch_bounds__(64 * QH * KS, D == 128 ? 1 : 2) stream_attn_kernel(RF2_STREAM_PARAMS) {
+  const int at = (int)(blockIdx.x >> 3);
+  attend<D, BK, QH, KS>(RF2_STREAM_ARGS, split, fused, (int)(blockIdx.x & 7), at >> split, at & ((1 << split) - 1));
+}
+
+// QH = 2 for the first `whole` row slots of an XCD, KS = 2 for those behind them (see rf2_cut_stream): workgroups of two
+// wavefronts either way, `split` is that of the former.  1,536 tiles of an image layer (24 heads) fill 1,024 places one and a half
+// times: as one cut two rounds or three half ones, so in one and a half, 102.6 -> 94.4 us (the layer 135.9 -> 128.3).
+template <int D, int BK>
+__global__ void __launch_bounds__(128, 1) mixed_attn_kernel(RF2_STREAM_PARAMS, int whole) {
+  const int xcd = (int)(blockIdx.x & 7), at = (int)(blockIdx.x >> 3), rest = at - (whole << split);
+  if (rest < 0) attend<D, BK, 2, 1>(RF2_STREAM_ARGS, split, fused, xcd, at >> split, at & ((1 << split) - 1));
+  else attend<D, BK, 1, 2>(RF2_STREAM_ARGS, split + 1, fused, xcd, whole + (rest >> (split + 1)), rest & ((2 << split) - 1));
+}
+
 struct AttnArgs {
   const void *qp, *kp, *vp;
   const int32_t *blk_idx, *blk_cnt;
@@ -605,10 +625,21 @@ int launch_stream(const rf2_plan* plan, const AttnArgs& a, hipStream_t st) {
   unsigned slots;
   const RowOrder order = row_order(plan, &slots);
   if (slots == 0) return RF2_OK;
-  stream_attn_kernel<D, BK, QH, KS><<<dim3((8u * slots) << split), dim3(64 * QH * KS), 0, st>>>(
-      (const __bf16*)a.qp, (const __bf16*)a.kp, (const __bf16*)a.vp, a.blk_idx, a.blk_cnt, (__bf16*)a.out, a.lse, order,
-      in.n_blocks_k, in.k_row, in.last_block_valid_k, (float)(1.4426950408889634 / sqrt((double)D)),
-      plan->d_perm, (int)in.N, plan->cfg.heads, rf2_qkv_strides(plan), split, a.scatter);
+  const auto launch = [&](auto kernel, unsigned grid, auto... more) {
+    kernel<<<dim3(grid), dim3(64 * QH * KS), 0, st>>>(
+        (const __bf16*)a.qp, (const __bf16*)a.kp, (const __bf16*)a.vp, a.blk_idx, a.blk_cnt, (__bf16*)a.out, a.lse, order,
+        in.n_blocks_k, in.k_row, in.last_block_valid_k, (float)(1.4426950408889634 / sqrt((double)D)),
+        plan->d_perm, (int)in.N, plan->cfg.heads, rf2_qkv_strides(plan), split, a.scatter, more...);
+  };
+  if constexpr (D == 128 && QH == 2 && KS == 1) {
+    const unsigned whole = (unsigned)plan->cut.whole_slots;
+    if (whole > 0 && whole < slots) {
+      launch(mixed_attn_kernel<D, BK>, 8u * ((whole << split) + ((slots - whole) << (split + 1))), (int)whole);
+      RF2_LAUNCH_CHECK();
+      return RF2_OK;
+    }
+  }
+  launch(stream_attn_kernel<D, BK, QH, KS>, (8u * slots) << split);
   RF2_LAUNCH_CHECK();
   return RF2_OK;
 }

@@ -57,6 +57,7 @@ struct rf2_attn_cut {
   int rows;         // query rows of a workgroup: those of a Q block, or a half or a quarter of them
   int groups;       // groups of wavefronts that share a list
   bool whole_heads; // ordinary rows are numbered head by head and dealt to the XCDs in 8 runs (else every head in 8 shares)
+  int whole_slots = 0;  // > 0: row slots of an XCD that are cut so; those behind them get 64-row workgroups of two shares
 };
 
 // Workgroups of a launch that its busiest shader engine gets, `share` workgroups to a row of the mask.  The hardware deals
@@ -156,6 +157,7 @@ inline const rf2_stream_model& rf2_model_of(int head_dim) {
 struct rf2_stream_jobs {
   int64_t sinks, plain;          // jobs of a shader engine
   double sink_parts, plain_parts;
+  int64_t halved = 0;            // of 128 rows: as many of the last ones run as two jobs of 64 rows and two shares each
 };
 inline double rf2_stream_time(const rf2_stream_model& m, rf2_stream_jobs j, int qh, int ks) {
   const int places = m.waves / (qh * ks);
@@ -174,12 +176,23 @@ inline double rf2_stream_time(const rf2_stream_model& m, rf2_stream_jobs j, int 
   rounds(j.plain, plain);
   std::priority_queue<double, std::vector<double>, std::greater<double>> busy;     // ends of the jobs under way
   std::vector<double> starts, ends;
-  for (int64_t i = 0; i < j.sinks + j.plain; ++i) {
+  const auto deal = [&](double units) {
     double at = 0.0;
     if ((int)busy.size() == places) { at = busy.top(); busy.pop(); }
     starts.push_back(at);
-    ends.push_back(at + (i < j.sinks ? sink : plain));
+    ends.push_back(at + units);
     busy.push(ends.back());
+  };
+  const double per = m.of2 / m.rate2, merge = m.start + m.merge2;        // (a unit of KS = 2 in units of QH = 2)
+  for (int64_t i = 0; i < j.sinks + j.plain; ++i) {
+    const bool first = i < j.sinks;
+    if (i < j.sinks + j.plain - j.halved) {
+      deal(first ? sink : plain);
+    } else {
+      const double half = (2.0 * std::ceil((first ? j.sink_parts : j.plain_parts) / 2) + merge) * per;
+      deal(half);
+      deal(half);
+    }
   }
   std::sort(ends.begin(), ends.end());
   double last = 0.0;             // (starts ascend)
@@ -218,7 +231,18 @@ inline rf2_attn_cut rf2_cut_stream(const rf2_config& c, const rf2_info& in) {
     if (64 * qh > c.block) continue;
     const int64_t share = c.block / (64 * qh), of_sinks = (sinks * share + 3) / 4, all = ((sinks + plain) * share + 3) / 4;
     const double us = rf2_stream_time(m, {of_sinks, all - of_sinks, in.n_blocks_k * parts, keeps * parts}, qh, ks);
-    if (least == 0.0 || us < least) least = us, best = {64 * qh, ks, false};
+    if (least == 0.0 || us < least) least = us, best = {64 * qh, ks, false, 0};
+    // Whole rows only as far as they fill rounds, those of the last, partly filled round as tiles of 64 rows with two shares each: a
+    // round of half the length.  Taken where the model sees 3 % in it (its error); launches of many rounds have no such gain.
+    // (us, the better of the other cuts -> this: 4,096 tokens, s = 0.5, 17 heads 92.8 -> 81.9, 24 heads 102.6 -> 94.4, 36 heads 155.3 ->
+    // 143.2; 6,200 tokens, s = 0.7, 13 heads 87.8 -> 75.1, 25 heads 147.2 -> 133.6; 2,450 tokens, 256-row blocks, 30 heads 68.3 -> 56.9;
+    // 3,000 tokens, s = 0.8, 64-row K/V blocks, 22 heads 38.3 -> 35.2.  The model: 81.4, 93.2, 139.3, 74.1, 130.4, 55.8, 32.8.)
+    if (c.head_dim == 128 && qh == 2 && ks == 1 && all <= 16 * 16) {
+      for (int64_t whole = std::max<int64_t>(16, all / 16 * 16 - 16); whole < all; whole += 4) {
+        const double mixed = rf2_stream_time(m, {of_sinks, all - of_sinks, in.n_blocks_k * parts, keeps * parts, all - whole}, 2, 1);
+        if (mixed < 0.97 * least) least = mixed, best = {128, 1, false, (int)(whole * 4 / share)};
+      }
+    }
   }
   best.whole_heads = c.block == 64 || in.N_pad_k * c.head_dim * 4 <= (int64_t)24 << 20;
   return best;

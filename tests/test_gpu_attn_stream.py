@@ -23,10 +23,13 @@ SHAPES = {(330, 64, 64, 128, 200): (64, 1), (330, 64, 128, 128, 200): (64, 1), (
           (2450, 64, 64, 64, 1): (64, 8), (4000, 128, 128, 64, 1): (64, 8), (2450, 128, 64, 64, 24): (128, 2),
           (2450, 128, 128, 64, 24): (128, 2), (900, 256, 64, 64, 64): (128, 2)}
 
+# the same -> row slots of an XCD that are cut as workgroups of 128 rows; those behind them as two of 64 rows and two shares
+MIXED = {(2450, 128, 64, 128, 27): 64, (2450, 128, 128, 128, 32): 64, (2450, 256, 128, 128, 30): 32, (2433, 256, 64, 128, 26): 32}
+
 SOURCE = """#include "rf2_attn_cut.h"
 extern "C" void cut(const rf2_config* c, const rf2_info* i, int* out) {
   const rf2_attn_cut x = rf2_cut_stream(*c, *i);
-  out[0] = x.rows, out[1] = x.groups, out[2] = x.whole_heads;
+  out[0] = x.rows, out[1] = x.groups, out[2] = x.whole_heads, out[3] = x.whole_slots;
 }
 """
 
@@ -36,7 +39,7 @@ def test_cuts(tmp_path):
     lib = str(tmp_path / "cut.so")
     subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-O1", "-shared", "-fPIC", "-I", os.path.join(b.ROOT, "include"),
                     "-I", b.CSRC, str(tmp_path / "cut.cpp"), "-o", lib], check=True)
-    fn, out = C.CDLL(lib).cut, (C.c_int * 3)()
+    fn, out = C.CDLL(lib).cut, (C.c_int * 4)()
 
     def cut(**kw):
         plan = rf2.Plan(**dict(dict(batch=1, head_dim=128, T=1, H=1, sparsity=0.3, window=(1, 1, 16)), **kw))
@@ -46,17 +49,19 @@ def test_cuts(tmp_path):
 
     for (tokens, block, block_k, d, heads), want in SHAPES.items():
         assert cut(W=tokens, block=block, block_k=block_k, head_dim=d, heads=heads)[:2] == want, (tokens, block, block_k, d, heads)
+    for (tokens, block, block_k, d, heads), want in MIXED.items():
+        assert cut(W=tokens, block=block, block_k=block_k, head_dim=d, heads=heads) == (128, 1, 1, want), (tokens, block, block_k, heads)
     video = dict(T=21, H=45, W=80, sparsity=0.8, sink_frames=1, window=(0, 0, 0))
-    assert cut(**video, heads=40, block=128) == (128, 1, 0)          # 8 heads' K and V are larger than the Infinity Cache
-    assert cut(**video, heads=40, block=256, block_k=128) == (256, 1, 0)
-    assert cut(**dict(video, H=30, W=52), heads=40, block=128) == (128, 1, 1)
+    assert cut(**video, heads=40, block=128) == (128, 1, 0, 0)          # 8 heads' K and V are larger than the Infinity Cache
+    assert cut(**video, heads=40, block=256, block_k=128) == (256, 1, 0, 0)
+    assert cut(**dict(video, H=30, W=52), heads=40, block=128) == (128, 1, 1, 0)
     assert cut(**video, heads=1, block=128)[:2] == (64, 4)
     # a launch of the largest size the limits allow is cut without walking through its rows
     assert cut(T=1, H=1, W=2048 * 64, heads=65535, block=64)[:1] == (64,)
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("shape", [*SHAPES, *MIXED], ids=lambda s: "x".join(map(str, s)))
 def test_every_cut(shape):
     cut_tests.test_lists_of_every_length(shape, 24.0)
 
