@@ -36,6 +36,7 @@
 // multiply-add, one exp2, one add and half a bf16 pack per probability.
 #include "rf2_internal.h"
 
+#include <algorithm>
 #include <cfloat>
 #include <type_traits>
 
@@ -588,14 +589,20 @@ __global__ void __launch_bounds__(64 * QH * KS, D == 128 ? 1 : 2) stream_attn_ke
   attend<D, BK, QH, KS>(RF2_STREAM_ARGS, split, fused, (int)(blockIdx.x & 7), at >> split, at & ((1 << split) - 1));
 }
 
-// QH = 2 for the first `whole` row slots of an XCD, KS = 2 for those behind them (see rf2_cut_stream): workgroups of two
-// wavefronts either way, `split` is that of the former.  1,536 tiles of an image layer (24 heads) fill 1,024 places one and a half
-// times: as one cut two rounds or three half ones, so in one and a half, 102.6 -> 94.4 us (the layer 135.9 -> 128.3).
+// QH = 2 for the row slots `lead` to `whole` of an XCD, KS = 2 in front of them (its sink rows, or none) and behind them (see
+// rf2_cut_stream): workgroups of two wavefronts either way, `split` is that of the former.  1,536 tiles of an image layer (24 heads) fill 1,024 places one and a half
+// times: as one cut two rounds or three half ones, so in one and a half, 102.6 -> 94.4 us (the layer 135.9 -> 128.3).  With 77 text
+// tokens, whose rows are three times as long as the others, 98.4 -> 84.3 us (the layer 145.8 -> 132.1).
 template <int D, int BK>
-__global__ void __launch_bounds__(128, 1) mixed_attn_kernel(RF2_STREAM_PARAMS, int whole) {
-  const int xcd = (int)(blockIdx.x & 7), at = (int)(blockIdx.x >> 3), rest = at - (whole << split);
-  if (rest < 0) attend<D, BK, 2, 1>(RF2_STREAM_ARGS, split, fused, xcd, at >> split, at & ((1 << split) - 1));
-  else attend<D, BK, 1, 2>(RF2_STREAM_ARGS, split + 1, fused, xcd, whole + (rest >> (split + 1)), rest & ((2 << split) - 1));
+__global__ void __launch_bounds__(128, 1) mixed_attn_kernel(RF2_STREAM_PARAMS, int lead, int whole) {
+  const int xcd = (int)(blockIdx.x & 7), at = (int)(blockIdx.x >> 3);
+  const int inside = at - (lead << (split + 1)), behind = inside - ((whole - lead) << split);
+  if (inside >= 0 && behind < 0) {
+    attend<D, BK, 2, 1>(RF2_STREAM_ARGS, split, fused, xcd, lead + (inside >> split), inside & ((1 << split) - 1));
+  } else {
+    const int half = inside < 0 ? at : behind;
+    attend<D, BK, 1, 2>(RF2_STREAM_ARGS, split + 1, fused, xcd, (inside < 0 ? 0 : whole) + (half >> (split + 1)), half & ((2 << split) - 1));
+  }
 }
 
 struct AttnArgs {
@@ -632,9 +639,10 @@ int launch_stream(const rf2_plan* plan, const AttnArgs& a, hipStream_t st) {
         plan->d_perm, (int)in.N, plan->cfg.heads, rf2_qkv_strides(plan), split, a.scatter, more...);
   };
   if constexpr (D == 128 && QH == 2 && KS == 1) {
-    const unsigned whole = (unsigned)plan->cut.whole_slots;
-    if (whole > 0 && whole < slots) {
-      launch(mixed_attn_kernel<D, BK>, 8u * ((whole << split) + ((slots - whole) << (split + 1))), (int)whole);
+    const unsigned lead = plan->cut.halved_sinks ? (unsigned)order.sink_slots : 0u;
+    const unsigned whole = std::max(lead, std::min(slots, (unsigned)plan->cut.whole_slots));
+    if (plan->cut.whole_slots > 0 && (lead > 0 || whole < slots)) {
+      launch(mixed_attn_kernel<D, BK>, 8u * (((whole - lead) << split) + ((slots - whole + lead) << (split + 1))), (int)lead, (int)whole);
       RF2_LAUNCH_CHECK();
       return RF2_OK;
     }

@@ -57,7 +57,8 @@ struct rf2_attn_cut {
   int rows;         // query rows of a workgroup: those of a Q block, or a half or a quarter of them
   int groups;       // groups of wavefronts that share a list
   bool whole_heads; // ordinary rows are numbered head by head and dealt to the XCDs in 8 runs (else every head in 8 shares)
-  int whole_slots = 0;  // > 0: row slots of an XCD that are cut so; those behind them get 64-row workgroups of two shares
+  int whole_slots = 0;  // > 0: row slots of an XCD that are cut so; those behind them get 64-row workgroups of two shares,
+  bool halved_sinks = false;      // and so do its sink rows (not then counted as cut so)
 };
 
 // Workgroups of a launch that its busiest shader engine gets, `share` workgroups to a row of the mask.  The hardware deals
@@ -157,7 +158,8 @@ inline const rf2_stream_model& rf2_model_of(int head_dim) {
 struct rf2_stream_jobs {
   int64_t sinks, plain;          // jobs of a shader engine
   double sink_parts, plain_parts;
-  int64_t halved = 0;            // of 128 rows: as many of the last ones run as two jobs of 64 rows and two shares each
+  int64_t halved = 0;            // of 128 rows: as many of the last ones run as two jobs of 64 rows and two shares each,
+  bool halved_sinks = false;     // and so do the sink rows
 };
 inline double rf2_stream_time(const rf2_stream_model& m, rf2_stream_jobs j, int qh, int ks) {
   const int places = m.waves / (qh * ks);
@@ -186,7 +188,7 @@ inline double rf2_stream_time(const rf2_stream_model& m, rf2_stream_jobs j, int 
   const double per = m.of2 / m.rate2, merge = m.start + m.merge2;        // (a unit of KS = 2 in units of QH = 2)
   for (int64_t i = 0; i < j.sinks + j.plain; ++i) {
     const bool first = i < j.sinks;
-    if (i < j.sinks + j.plain - j.halved) {
+    if (i < j.sinks + j.plain - j.halved && !(first && j.halved_sinks)) {
       deal(first ? sink : plain);
     } else {
       const double half = (2.0 * std::ceil((first ? j.sink_parts : j.plain_parts) / 2) + merge) * per;
@@ -237,10 +239,22 @@ inline rf2_attn_cut rf2_cut_stream(const rf2_config& c, const rf2_info& in) {
     // (us, the better of the other cuts -> this: 4,096 tokens, s = 0.5, 17 heads 92.8 -> 81.9, 24 heads 102.6 -> 94.4, 36 heads 155.3 ->
     // 143.2; 6,200 tokens, s = 0.7, 13 heads 87.8 -> 75.1, 25 heads 147.2 -> 133.6; 2,450 tokens, 256-row blocks, 30 heads 68.3 -> 56.9;
     // 3,000 tokens, s = 0.8, 64-row K/V blocks, 22 heads 38.3 -> 35.2.  The model: 81.4, 93.2, 139.3, 74.1, 130.4, 55.8, 32.8.)
+    // All-column sink rows among short ones run as halves, too, where their length is what the launch waits for.  (us, before ->
+    // halves: image of 4,087 tokens and 77 of text, s = 0.6, 24 heads 98.4 -> 84.3, 28 heads 104.3 -> 101.1; 2,450 and 200, s = 0.7, 33
+    // heads 54.5 -> 44.6, 256-row blocks, 39 heads 67.8 -> 57.4; 9 frames of 900 tokens, the first a sink, s = 0.8, 24 heads 192.7 -> 175.8, 16
+    // heads 126.5 -> 119.3; where the model sees less than 3 % nothing changes: of 22 launches none got slower.)
     if (c.head_dim == 128 && qh == 2 && ks == 1 && all <= 16 * 16) {
-      for (int64_t whole = std::max<int64_t>(16, all / 16 * 16 - 16); whole < all; whole += 4) {
-        const double mixed = rf2_stream_time(m, {of_sinks, all - of_sinks, in.n_blocks_k * parts, keeps * parts, all - whole}, 2, 1);
-        if (mixed < 0.97 * least) least = mixed, best = {128, 1, false, (int)(whole * 4 / share)};
+      for (const bool halved_sinks : {false, true}) {
+        if (halved_sinks && of_sinks == 0) break;
+        for (int64_t whole = std::max<int64_t>(16, all / 16 * 16 - 16);; whole += 4) {
+          whole = std::min(whole, all);
+          if (whole == all && !halved_sinks) break;
+          const double mixed = rf2_stream_time(
+              m, {of_sinks, all - of_sinks, in.n_blocks_k * parts, keeps * parts, all - whole, halved_sinks}, 2, 1);
+          if (mixed < 0.97 * least)
+            least = mixed, best = {128, 1, false, whole == all ? INT32_MAX : (int)(whole * 4 / share), halved_sinks};
+          if (whole == all) break;
+        }
       }
     }
   }

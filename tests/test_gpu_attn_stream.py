@@ -26,10 +26,13 @@ SHAPES = {(330, 64, 64, 128, 200): (64, 1), (330, 64, 128, 128, 200): (64, 1), (
 # the same -> row slots of an XCD that are cut as workgroups of 128 rows; those behind them as two of 64 rows and two shares
 MIXED = {(2450, 128, 64, 128, 27): 64, (2450, 128, 128, 128, 32): 64, (2450, 256, 128, 128, 30): 32, (2433, 256, 64, 128, 26): 32}
 
+# (tokens, text tokens, block, block_k, heads) -> the same, with all-column text rows in two shares, too
+HALVED = {(2450, 200, 128, 128, 27): 64, (2450, 77, 128, 64, 39): 96, (2450, 200, 256, 128, 36): 40, (2433, 77, 256, 64, 30): 32}
+
 SOURCE = """#include "rf2_attn_cut.h"
 extern "C" void cut(const rf2_config* c, const rf2_info* i, int* out) {
   const rf2_attn_cut x = rf2_cut_stream(*c, *i);
-  out[0] = x.rows, out[1] = x.groups, out[2] = x.whole_heads, out[3] = x.whole_slots;
+  out[0] = x.rows, out[1] = x.groups, out[2] = x.whole_heads, out[3] = x.whole_slots, out[4] = x.halved_sinks;
 }
 """
 
@@ -39,7 +42,7 @@ def test_cuts(tmp_path):
     lib = str(tmp_path / "cut.so")
     subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-O1", "-shared", "-fPIC", "-I", os.path.join(b.ROOT, "include"),
                     "-I", b.CSRC, str(tmp_path / "cut.cpp"), "-o", lib], check=True)
-    fn, out = C.CDLL(lib).cut, (C.c_int * 4)()
+    fn, out = C.CDLL(lib).cut, (C.c_int * 5)()
 
     def cut(**kw):
         plan = rf2.Plan(**dict(dict(batch=1, head_dim=128, T=1, H=1, sparsity=0.3, window=(1, 1, 16)), **kw))
@@ -50,11 +53,13 @@ def test_cuts(tmp_path):
     for (tokens, block, block_k, d, heads), want in SHAPES.items():
         assert cut(W=tokens, block=block, block_k=block_k, head_dim=d, heads=heads)[:2] == want, (tokens, block, block_k, d, heads)
     for (tokens, block, block_k, d, heads), want in MIXED.items():
-        assert cut(W=tokens, block=block, block_k=block_k, head_dim=d, heads=heads) == (128, 1, 1, want), (tokens, block, block_k, heads)
+        assert cut(W=tokens, block=block, block_k=block_k, head_dim=d, heads=heads) == (128, 1, 1, want, 0), (tokens, block, block_k, heads)
+    for (tokens, text, block, block_k, heads), want in HALVED.items():
+        assert cut(W=tokens, text_tokens=text, block=block, block_k=block_k, heads=heads, sparsity=0.7) == (128, 1, 1, want, 1), (tokens, heads)
     video = dict(T=21, H=45, W=80, sparsity=0.8, sink_frames=1, window=(0, 0, 0))
-    assert cut(**video, heads=40, block=128) == (128, 1, 0, 0)          # 8 heads' K and V are larger than the Infinity Cache
-    assert cut(**video, heads=40, block=256, block_k=128) == (256, 1, 0, 0)
-    assert cut(**dict(video, H=30, W=52), heads=40, block=128) == (128, 1, 1, 0)
+    assert cut(**video, heads=40, block=128) == (128, 1, 0, 0, 0)          # 8 heads' K and V are larger than the Infinity Cache
+    assert cut(**video, heads=40, block=256, block_k=128) == (256, 1, 0, 0, 0)
+    assert cut(**dict(video, H=30, W=52), heads=40, block=128) == (128, 1, 1, 0, 0)
     assert cut(**video, heads=1, block=128)[:2] == (64, 4)
     # a launch of the largest size the limits allow is cut without walking through its rows
     assert cut(T=1, H=1, W=2048 * 64, heads=65535, block=64)[:1] == (64,)
@@ -89,4 +94,42 @@ def test_entries_behind_the_count(shape):
     assert unused.any()
     for op, lse in results[1:]:
         assert torch.equal(op, results[0][0]) and torch.equal(lse, results[0][1])
+    plan.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", HALVED, ids=lambda s: "x".join(map(str, s)))
+def test_sink_rows_in_halves(shape):
+    """A layer whose all-column rows, and last rows, run as halves beside whole ones: every row is written, as softmax attention
+    over its kept blocks."""
+    tokens, text, block, block_k, heads = shape
+    print(f"[case] {shape}", flush=True)
+    n, d = tokens + text, 128
+    plan = rf2.Plan(batch=1, heads=heads, head_dim=d, T=1, H=1, W=tokens, text_tokens=text, block=block, block_k=block_k, sparsity=0.7,
+                    window=(1, 1, 16))
+    i = plan.info
+    g = torch.Generator().manual_seed(13)
+    q, k, v = (torch.randn(1, heads, n, d, generator=g).to(torch.bfloat16) for _ in range(3))
+    buf = plan.alloc("cuda", lse=True)
+    plan.rf2_permute(*(x.cuda() for x in (q, k, v)), *(buf[x] for x in ("qp", "kp", "vp", "qbar", "kbar")))
+    mask = torch.empty(1, heads, i.n_blocks, i.n_blocks_k, dtype=torch.uint8, device="cuda")
+    plan.rf2_predict_mask(buf["qbar"], buf["kbar"], buf["blk_idx"], buf["blk_cnt"], mask)
+    buf["op"].fill_(float("nan"))
+    plan.rf2_block_sparse_attn(buf["qp"], buf["kp"], buf["vp"], buf["blk_idx"], buf["blk_cnt"], buf["op"], buf["lse"])
+    o, lse = torch.full_like(buf["o"], float("nan")), torch.full((1, heads, n), float("nan"), device="cuda")
+    plan.rf2_block_sparse_attn_unpermuted(buf["qp"], buf["kp"], buf["vp"], buf["blk_idx"], buf["blk_cnt"], o, lse)
+    torch.cuda.synchronize()
+    perm = plan.rf2_plan_perm()[0]
+    assert torch.equal(o[:, :, perm].view(torch.int16), buf["op"][:, :, :n].view(torch.int16))
+    assert torch.equal(lse[:, :, perm], buf["lse"][:, :, :n])
+    for h in range(heads):
+        Q, K, V = (x[0, h][perm].double() for x in (q, k, v))
+        keep = mask[0, h].cpu().bool().repeat_interleave(block, 0).repeat_interleave(block_k, 1)[:n, :n]
+        S = (Q @ K.T / d ** 0.5).masked_fill(~keep, -torch.inf)
+        P = torch.softmax(S, 1)
+        want = P @ V
+        err = (buf["op"][0, h, :n].cpu().double() - want).abs()
+        # probabilities and outputs rounded to bf16 (2^-8 each, relative); logits below 10 in fp32
+        assert (err <= 2.0 ** -8 * (P @ V.abs() + want.abs()) + 1e-4).all(), (h, err.max())
+        assert (buf["lse"][0, h, :n].cpu().double() - torch.logsumexp(S, 1)).abs().max() <= 1e-4, h
     plan.close()
