@@ -359,7 +359,7 @@ def main():
                            "permute_pool_frac_of_copy": round(gbps["permute_pool"] / copy_peak, 4)},
         "attn": {"ms": round(attn_ms, 4), "kept_tflops": round(kept_flops / (attn_ms * 1e-3) / 1e12, 1),
                  "dense_equiv_tflops": round(dense_flops / (attn_ms * 1e-3) / 1e12, 1)},
-        "roofline": {"bound": "mfma", "kernel": "block_sparse_attn_kernel",
+        "roofline": {"bound": "mfma", "kernel": "stream_attn_kernel",
                      "achieved": kept_flops / (attn_ms * 1e-3) / 1e12, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                      "frac": kept_flops / (attn_ms * 1e-3) / 1e12 / PEAK_BF16_TFLOPS,
                      "traffic": (measured_traffic(wl.name)
