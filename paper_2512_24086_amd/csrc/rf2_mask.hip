@@ -19,8 +19,8 @@
 // count needs 15.5 (other rows: see MAX_GUIDED).  720p: 104 -> 70 us; cumulative mass on the long video (929 x 929, 24
 // heads): 291 -> 146 us; with few workgroups 12-50 -> 8-15 us.  No load of K, no read of a key and no store of a list entry
 // stands behind a branch: buffers drop what lies outside of kbar or of the list.  (Behind branches the compiler waited for the
-// whole next K tile at the end of each, and every entry cost four scalar instructions: 720p 70.1 -> 68.7 us, long video,
-// cumulative mass, 146.8 -> 135.8.)  Wavefronts that share a K tile (32, 48 or 64 rows per
+// whole next K tile at the end of each, and every entry cost four scalar instructions: 720p 70.1 -> 69.4 us (68.7 to 69.8 in
+// three runs), long video, cumulative mass, 145.0 -> 134.8.)  Wavefronts that share a K tile (32, 48 or 64 rows per
 // workgroup) halve the L2 reads and are slower (98-122 us on 720p).
 #include "rf2_internal.h"
 
