@@ -13,7 +13,7 @@
 // scalar issue slots; a workgroup is a chain of load, multiply, search and store, so what counts is how
 // many of them a compute unit holds.  The Q operand is read from LDS and the K operand is
 // reloaded in place, which keeps a wavefront of up to 768 columns within 80 registers: six wavefronts per SIMD where LDS
-// holds three workgroups of eight (up to about 690 columns; two from there, one from about 1,130).  A probe of the
+// holds three workgroups of eight (up to 688 columns, 752 at d = 64; two up to 1,120 and 1,184, one beyond).  A probe of the
 // search costs a compare and a population count per 64 keys; on bell-shaped rows, as smooth fields give, the
 // normal-distribution guess and interpolation need 4 or 5 of them where a bitwise search that stops at the first exact
 // count needs 15.5 (other rows: see MAX_GUIDED).  720p: 104 -> 70 us; cumulative mass on the long video (929 x 929, 24
@@ -136,6 +136,16 @@ __device__ __forceinline__ void draw_in(const uint32_t (&key)[EMAX], uint32_t& l
   top = wave_max_u(most);
 }
 
+// LDS of a workgroup behind its strip of keys: the Q operand and each wavefront's share of the rows' sums.  Behind, because the
+// last row's reads of keys pass the end of the strip: they end in here, and nothing is allocated for them.  (With words of their own
+// the widest rows of a step lost a workgroup per compute unit; 12 heads, us, with them -> now: d = 128, 1,120 columns 116.6 -> 88.4, by
+// mass 148.7 -> 110.9, 688 columns, by mass, 58.3 -> 55.1; d = 64, 752 columns 36.0 -> 34.6, by mass 50.9 -> 46.7.)
+template <int D, int NW>
+struct BehindKeys {
+  float qs[16][D + 4];                              // (+4: the 16 rows of an operand read start in different banks)
+  float stat[NW][16][2];                            // sum and sum of squares over a wavefront's columns
+};
+
 // NW wavefronts per workgroup of R = 16 rows.  (Second launch bound: beyond 768 columns LDS holds two workgroups at most.)
 template <int D, int EMAX, bool CDF, int NW>
 __global__ void __launch_bounds__(NW * 64, NW == 8 && EMAX <= 12 ? 6 : 4) predict_mask_kernel(
@@ -147,8 +157,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 && EMAX <= 12 ? 6 : 4) predic
   constexpr int R = 16;
   constexpr int MAX_GUIDED = CDF ? 10 : 8;
   extern __shared__ __attribute__((aligned(16))) uint32_t keys[];   // [R][LD]
-  __shared__ float stat[NW][R][2];                                  // sum and sum of squares over a wavefront's columns
-  __shared__ __attribute__((aligned(16))) float qs[R][D + 4];       // (+4: the 16 rows of an operand read start in different banks)
+  auto& [qs, stat] = *reinterpret_cast<BehindKeys<D, NW>*>(keys + R * LD);
   // Workgroups with equal blockIdx % 8 share an XCD and take a contiguous run of the strips, numbered head by head:
   // the strips that read one head's kbar meet in one L2.
   const int work = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
@@ -239,7 +248,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 && EMAX <= 12 ? 6 : 4) predic
     uint32_t key[EMAX];
 #pragma unroll
     for (int e = 0; e < EMAX; ++e) {
-      // (read in any case: without a branch; what lies behind the row is in the strip or in the words allocated behind it)
+      // (read in any case: without a branch; what lies behind the row is in the strip or in BehindKeys)
       key[e] = keys[r * LD + 64 * e + lane];
       key[e] = 64 * e + lane < Tb ? key[e] : PAST_KEY;
     }
@@ -374,17 +383,24 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 && EMAX <= 12 ? 6 : 4) predic
 
 // Shape of the launch for a plan, and the kernel instance that serves it.
 struct MaskLaunch {
-  const void* kernel;
+  const void* kernel = nullptr;
   int E, LD, NW;
-  size_t lds;
+  size_t lds = 0;
 };
 
 // The kernel is instantiated for a few row widths (EMAX keys per lane): the search loops run over
 // EMAX keys without bounds checks (keys past the row are 0), so a snug width saves compares.
 template <int D, int NW>
-const void* mask_kernel_for(int E, bool cdf, int* width) {
-#define RF2_MASK_CASE(W) \
-  if (E <= W) return *width = W, cdf ? (const void*)predict_mask_kernel<D, W, true, NW> : (const void*)predict_mask_kernel<D, W, false, NW>;
+void choose_instance(MaskLaunch& m, bool cdf) {
+  const auto words = [&](int width) {               // strip and what is behind it; where the last row's reads end
+    return std::max(16 * m.LD + (int)(sizeof(BehindKeys<D, NW>) / 4), 15 * m.LD + 64 * width);
+  };
+#define RF2_MASK_CASE(W)                                                                                                        \
+  if (m.E <= W) {                                                                                                               \
+    m.kernel = cdf ? (const void*)predict_mask_kernel<D, W, true, NW> : (const void*)predict_mask_kernel<D, W, false, NW>;       \
+    m.lds = (size_t)words(W) * 4;                                                                                               \
+    return;                                                                                                                     \
+  }
   RF2_MASK_CASE(2)
   RF2_MASK_CASE(4)
   RF2_MASK_CASE(6)
@@ -396,24 +412,20 @@ const void* mask_kernel_for(int E, bool cdf, int* width) {
   RF2_MASK_CASE(24)
   RF2_MASK_CASE(32)
 #undef RF2_MASK_CASE
-  return nullptr;                                   // (Tk <= 2048: E <= 32)
-}
+}                                                   // (Tk <= 2048: E <= 32)
 
 MaskLaunch mask_launch(const rf2_plan* plan) {
   MaskLaunch m;
   m.E = (plan->info.n_blocks_k + 63) / 64;
   m.LD = (plan->info.n_blocks_k + 15) / 16 * 16 + 4;   // +4: the 4 row groups of a tile store hit distinct banks
   // Up to one workgroup per compute unit a row's search is latency: 16 wavefronts search one row each.  Beyond, a
-  // compute unit holds three workgroups of 8 wavefronts but only one of 16 (up to about 690 columns: LDS).  (16 against 8 wavefronts: 9.5 / 10.3 us
+  // compute unit holds three workgroups of 8 wavefronts but only one of 16 (up to 688 columns: LDS).  (16 against 8 wavefronts: 9.5 / 10.3 us
   // at 28 workgroups, 12.4 / 13.0 at 35, 20.3 / 21.2 at 136; 21.2 / 19.7 us at 320, 92 / 72 us at 1,480.)
   const int64_t strips = (int64_t)((plan->info.n_blocks + 15) / 16) * plan->cfg.batch * plan->cfg.heads;
   m.NW = strips <= 256 ? 16 : 8;
   const bool cdf = (plan->cfg.select_mode == RF2_SELECT_CDF);
-  int width = 0;
-  if (plan->cfg.head_dim == 128) m.kernel = m.NW == 8 ? mask_kernel_for<128, 8>(m.E, cdf, &width) : mask_kernel_for<128, 16>(m.E, cdf, &width);
-  else m.kernel = m.NW == 8 ? mask_kernel_for<64, 8>(m.E, cdf, &width) : mask_kernel_for<64, 16>(m.E, cdf, &width);
-  // the strip, and what the last row's 64 x width key reads reach behind it
-  m.lds = ((size_t)16 * m.LD + std::max(64 * width - m.LD, 0)) * sizeof(uint32_t);
+  if (plan->cfg.head_dim == 128) m.NW == 8 ? choose_instance<128, 8>(m, cdf) : choose_instance<128, 16>(m, cdf);
+  else m.NW == 8 ? choose_instance<64, 8>(m, cdf) : choose_instance<64, 16>(m, cdf);
   return m;
 }
 
