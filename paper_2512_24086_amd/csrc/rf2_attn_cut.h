@@ -29,6 +29,12 @@ struct rf2_attn_cut {
 //   * A unit takes `idle` us where up to `knee` of the wavefront places are taken and `full` where all are (shared vector issue at d = 64,
 //     clock under the power limit, shared L2), along a line with a bow between.  By and large QH = 2 meets tiles in L1, KS = 2 and
 //     4 have fewer rows in flight on an XCD: factors of `full`.
+//   * At d = 64 a SIMD holds two wavefronts.  Workgroups of one wavefront spread over the SIMDs; beyond half of the places some share
+//     one, run at nearly the full rate's pace, `shared` of it, and the launch waits for them: 1,100 of them take a fifth longer than a
+//     line has it.  (Launches whose last round is half to three quarters full, us, the cut without this -> with it: 8 heads of 8,424
+//     tokens, 256-row blocks, s = 0.6, 88.7 -> 70.8, 10 x 6,972, s = 0.7, 58.9 -> 49.2, 12 x 6,090, s = 0.6, 69.6 -> 61.7, 3 x 29,412, 92.7 ->
+//     83.7, 19 x 10,626, 237.4 -> 216.5; the former kernel, with rings, took 75.1, 52.0, 62.5, 83.7, 223.9.  Of 720 random launches 39 are
+//     cut differently, 31 of them faster, by 2 to 20 %, 4 slower, by 3 to 4 %.)
 // The constants are fitted to launches of 600 to 40,000 tokens, 1 to 40 heads, blocks of 64, 128 and 256 rows, sparsity 0.5 to 0.9,
 // with and without sink rows and text (d = 128: 140 launches, d = 64: 125), and to 30 of 480p to long-video layers, each timed with
 // several cuts.  d = 128: the model is 4 % off on average, its choice 0.1 % slower than the best cut (6 % at most); d = 64: 7 % off,
@@ -45,10 +51,11 @@ struct rf2_stream_model {
   double rate2, rate4, of2, of4, of8, square;    // factors of `full`: QH = 2, 4; KS = 2, 4, 8; QH = KS = 2 (on top)
   double launch;                                 // us
   int waves;                                     // places of a shader engine
+  double shared;                                 // of `full`: rate where the first SIMDs are shared (0: they never are)
 };
 inline const rf2_stream_model& rf2_model_of(int head_dim) {
-  static const rf2_stream_model d128{0.507, 0.843, 0.372, -0.532, 4.04, 1.95, 6.58, 2.06, 5.02, 0.0, 0.957, 0.918, 0.984, 0.937, 1.0, 1.01, 5.1, 32};
-  static const rf2_stream_model d64{0.448, 0.931, 0.21, 0.084, 2.02, 0.85, 0.0, 2.42, 2.85, 6.57, 1.042, 1.0, 1.066, 1.003, 0.97, 0.865, 4.4, 64};
+  static const rf2_stream_model d128{0.507, 0.843, 0.372, -0.532, 4.04, 1.95, 6.58, 2.06, 5.02, 0.0, 0.957, 0.918, 0.984, 0.937, 1.0, 1.01, 5.1, 32, 0.0};
+  static const rf2_stream_model d64{0.448, 0.931, 0.21, 0.084, 2.02, 0.85, 0.0, 2.42, 2.85, 6.57, 1.042, 1.0, 1.066, 1.003, 0.97, 0.865, 4.4, 64, 0.9};
   return head_dim == 128 ? d128 : d64;
 }
 struct rf2_stream_jobs {
@@ -98,7 +105,9 @@ inline double rf2_stream_time(const rf2_stream_model& m, rf2_stream_jobs j, int 
     const bool begins = s < starts.size() && starts[s] < ends[e];
     const double at = begins ? starts[s] : ends[e];
     const double taken = (double)((s - e) * qh * ks) / m.waves, x = std::max(0.0, (taken - m.knee) / (1.0 - m.knee));
-    us += (at - last) * (m.idle + (full - m.idle) * (x + m.bow * x * (1.0 - x)));
+    double unit = m.idle + (full - m.idle) * (x + m.bow * x * (1.0 - x));
+    if (m.shared > 0.0 && qh * ks == 1 && taken > 0.5) unit = std::max(unit, full * (m.shared + (1.0 - m.shared) * (2.0 * taken - 1.0)));
+    us += (at - last) * unit;
     last = at;
     begins ? ++s : ++e;
   }

@@ -76,3 +76,24 @@ def test_the_shapes_of_the_non_finite_tests_share_lists_in_every_way(cut):
     want = {(d, q, k, False) for d, q, k in instances() if q < 4} | {(128, 2, 1, True)}
     got = {(c[0], *c[2:]) for c in map(cut, map(plan_of, NONFINITE))}
     assert got == want, (sorted(want - got), sorted(got - want))
+
+
+# equal rows at d = 64, (tokens, heads, block, block_k, sparsity) -> one wavefront to a workgroup?  With more such workgroups than
+# SIMDs, or than whole rounds and as many again, some SIMDs run two and the launch waits for those (us, 64 rows x 1 wavefront / best
+# cut); with half of the places or nearly all of them taken it is the best cut, or as good
+@pytest.mark.parametrize("shape, alone", [
+    ((8424, 8, 256, 128, 0.61), False),         # 87.8 / 70.8
+    ((6972, 10, 128, 0, 0.70), False),          # 58.8 / 49.2
+    ((6090, 12, 128, 0, 0.59), False),          # 69.5 / 58.4
+    ((11760, 6, 128, 0, 0.77), False),          # 76.8 / 63.8
+    ((29412, 3, 128, 64, 0.89), False),         # 94.0 / 83.7
+    ((10626, 19, 128, 0, 0.62), False),         # 237.5 / 216.5
+    ((16256, 21, 256, 128, 0.61), False),       # 557.5 / 525.0
+    ((2016, 32, 128, 0, 0.76), True),           # 13.5, the others 14.3 and more
+    ((2450, 45, 256, 128, 0.65), True),         # 36.0, 38.5
+    ((3025, 39, 256, 128, 0.83), True),         # 25.9, 28.8
+    ((4320, 30, 128, 0, 0.66), True)],          # 55.6, 57.9
+    ids=lambda x: "x".join(map(str, x)) if isinstance(x, tuple) else "")
+def test_single_wavefronts_where_no_few_simds_hold_two(cut, shape, alone):
+    tokens, heads, block, block_k, sparsity = shape
+    assert (cut(plan_of((tokens, block, block_k, 64, heads), sparsity=sparsity))[2:4] == (1, 1)) is alone
