@@ -28,20 +28,26 @@ METRIC = "ms/layer + effective TFLOPS of block-sparse attn @80% sparsity, 75.6K 
 PEAK_BF16_TFLOPS = 2500.0      # MI355X dense bf16 MFMA
 # HBM/fabric bytes per launch of the attention kernel come from rocprofv3 --pmc runs (FETCH_SIZE and
 # WRITE_SIZE, scaled by a copy kernel of known size).  They are kept in a small table beside the profile
-# summaries, one line per measurement: workload, hash of the kernel source it was measured on, bytes.
+# summaries, one line per measurement: workload, hash of the sources it was measured on, bytes.
 TRAFFIC_TABLE = os.path.join(ROOT, "profiles", "attn_traffic.txt")
-ATTN_SOURCE = os.path.join(ROOT, "paper_2512_24086_amd", "csrc", "rf2_attn.hip")
+# What sets the bytes of a launch: the kernel, the cut of the launch, the work table of the rows.
+ATTN_SOURCES = [os.path.join(ROOT, "paper_2512_24086_amd", "csrc", n) for n in ("rf2_attn.hip", "rf2_attn_cut.h", "rf2_plan.cpp")]
 
 
 def attn_source_hash() -> str:
+    """Of the code alone: comments and white space move no bytes."""
     import hashlib
-    with open(ATTN_SOURCE, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+    import re
+    h = hashlib.sha256()
+    for path in ATTN_SOURCES:
+        with open(path) as f:
+            h.update(re.sub(r"//[^\n]*|\s+", "", f.read()).encode())
+    return h.hexdigest()[:16]
 
 
 def measured_traffic(workload: str):
-    """Bytes per launch measured for `workload` on exactly the kernel source that is in the tree, else None
-    (a figure measured on another version of the kernel says nothing about this one)."""
+    """Bytes per launch measured for `workload` on exactly the code that is in the tree, else None
+    (a figure measured on another version of the kernel, or with another cut, says nothing about this one)."""
     try:
         here = attn_source_hash()
         with open(TRAFFIC_TABLE) as f:

@@ -206,3 +206,25 @@ def test_bench_reports_traffic_only_for_the_kernel_source_it_was_measured_on(tmp
     # the table in the tree has an entry for the source in the tree
     monkeypatch.undo()
     assert bench.measured_traffic("video720p") is not None, "profiles/attn_traffic.txt is stale: re-measure FETCH_SIZE / WRITE_SIZE"
+
+
+def test_the_hash_of_the_attention_sources_follows_code_and_not_comments(tmp_path, monkeypatch):
+    """The bytes of a launch depend on its cut and work table, too: a change of either makes a figure stale."""
+    import sys
+    sys.path.insert(0, ROOT)
+    import bench
+    here = bench.attn_source_hash()
+    copies = []
+    for path in bench.ATTN_SOURCES:
+        copies.append(tmp_path / os.path.basename(path))
+        copies[-1].write_text(open(path).read())
+    assert {c.name for c in copies} >= {"rf2_attn.hip", "rf2_attn_cut.h", "rf2_plan.cpp"}
+    monkeypatch.setattr(bench, "ATTN_SOURCES", [str(c) for c in copies])
+    assert bench.attn_source_hash() == here
+    for c in copies:
+        text = c.read_text()
+        c.write_text("// another comment\n\n" + text)
+        assert bench.attn_source_hash() == here, c.name
+        c.write_text(text + "\nstatic int more;\n")
+        assert bench.attn_source_hash() != here, c.name
+        c.write_text(text)
