@@ -20,10 +20,11 @@ typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 //   91.2 / 19.3      88.6 / 18.8      89.6 / 21.8       16 heads, 101 MB
 //   145  / 28.7      140  / 28.5      140  / 31.3       24 heads, 151 MB
 //   169  / 36.6      165  / 38.5      166  / 40.5       32 heads, 201 MB
-// Both are kept up to 80 MB, stores alone up to 160 MB (beyond, the permutation itself gets slower, up to 8 %).
+// Both are kept up to 80 MiB (84 MB), stores alone up to 160 MiB (168 MB; beyond, the permutation itself gets slower, up to 8 %).
+// Bytes read and written, rows of the last, partly filled blocks included.
 constexpr int64_t KEEP_ALL = (int64_t)80 << 20, KEEP_STORES = (int64_t)160 << 20;
 // The inverse permutation reads what the attention has just written (non-temporal -> kept loads, us, token-major and not: 50 MB
-// 13.8 -> 9.6, 84 MB 17.1 -> 13.8, 118 MB 22.0 -> 19.0, 166 MB 35.3 -> 26.8, 258 MB 49.8 -> 51.4, 335 MB 115 -> 121).
+// 13.8 -> 9.6, 84 MB 17.1 -> 13.8, 118 MB 22.0 -> 19.0, 166 MB 35.3 -> 26.8, 258 MB 49.8 -> 51.4, 335 MB 115 -> 121): up to 192 MiB (201 MB).
 constexpr int64_t KEEP_UNPERMUTE = (int64_t)192 << 20;
 
 template <bool KEEP>
