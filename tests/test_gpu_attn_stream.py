@@ -29,6 +29,13 @@ MIXED = {(2450, 128, 64, 128, 27): 64, (2450, 128, 128, 128, 32): 64, (2450, 256
 # (tokens, text tokens, block, block_k, heads) -> the same, with all-column text rows in two shares, too
 HALVED = {(2450, 200, 128, 128, 27): 64, (2450, 77, 128, 64, 39): 96, (2450, 200, 256, 128, 36): 40, (2433, 77, 256, 64, 30): 32}
 
+# plan -> the same for heads whose K and V are too large to stay whole on an XCD: ordinary rows dealt by the work table, 8 shares of a
+# head of slightly different size, so that slots without work lie among the whole rows and the halves
+TABLE = {(("W", 50003), ("heads", 3), ("sparsity", 0.7), ("block", 128)): (128, 0),
+         (("W", 52003), ("heads", 4), ("sparsity", 0.8), ("block", 256), ("block_k", 64)): (80, 0),
+         (("T", 13), ("H", 62), ("W", 62), ("heads", 4), ("sparsity", 0.8), ("block", 128), ("block_k", 64), ("sink_frames", 1)): (128, 1),
+         (("T", 21), ("H", 45), ("W", 80), ("heads", 5), ("sparsity", 0.9), ("block", 256), ("block_k", 128), ("sink_frames", 1)): (128, 1)}
+
 SOURCE = """#include "rf2_attn_cut.h"
 extern "C" void cut(const rf2_config* c, const rf2_info* i, int* out) {
   const rf2_attn_cut x = rf2_cut_stream(*c, *i);
@@ -56,6 +63,8 @@ def test_cuts(tmp_path):
         assert cut(W=tokens, block=block, block_k=block_k, head_dim=d, heads=heads) == (128, 1, 1, want, 0), (tokens, block, block_k, heads)
     for (tokens, text, block, block_k, heads), want in HALVED.items():
         assert cut(W=tokens, text_tokens=text, block=block, block_k=block_k, heads=heads, sparsity=0.7) == (128, 1, 1, want, 1), (tokens, heads)
+    for case, (whole, halved) in TABLE.items():
+        assert cut(**dict(case)) == (128, 1, 0, whole, halved), case
     video = dict(T=21, H=45, W=80, sparsity=0.8, sink_frames=1, window=(0, 0, 0))
     assert cut(**video, heads=40, block=128) == (128, 1, 0, 0, 0)          # 8 heads' K and V are larger than the Infinity Cache
     assert cut(**video, heads=40, block=256, block_k=128) == (256, 1, 0, 0, 0)
@@ -132,4 +141,46 @@ def test_sink_rows_in_halves(shape):
         # probabilities and outputs rounded to bf16 (2^-8 each, relative); logits below 10 in fp32
         assert (err <= 2.0 ** -8 * (P @ V.abs() + want.abs()) + 1e-4).all(), (h, err.max())
         assert (buf["lse"][0, h, :n].cpu().double() - torch.logsumexp(S, 1)).abs().max() <= 1e-4, h
+    plan.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", TABLE, ids=lambda c: "x".join(str(v) for _, v in c))
+def test_halves_of_rows_dealt_by_the_work_table(case):
+    """Every row of every head is written, by both exits alike, as softmax attention over its kept blocks."""
+    print(f"[case] {case}", flush=True)
+    plan = rf2.Plan(**dict(dict(batch=1, head_dim=128, T=1, H=1, window=(1, 1, 16)), **dict(case)))
+    i, c, d = plan.info, plan.cfg, 128
+    n, heads, block, block_k = i.N, c.heads, c.block, i.block_k
+    g = torch.Generator(device="cuda").manual_seed(17)
+    q, k, v = (torch.randn(1, heads, n, d, generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    buf = plan.alloc("cuda", lse=True)
+    plan.rf2_permute(q, k, v, *(buf[x] for x in ("qp", "kp", "vp", "qbar", "kbar")))
+    plan.rf2_predict_mask(buf["qbar"], buf["kbar"], buf["blk_idx"], buf["blk_cnt"])
+    buf["op"].fill_(float("nan"))
+    plan.rf2_block_sparse_attn(buf["qp"], buf["kp"], buf["vp"], buf["blk_idx"], buf["blk_cnt"], buf["op"], buf["lse"])
+    o, lse = torch.full_like(buf["o"], float("nan")), torch.full((1, heads, n), float("nan"), device="cuda")
+    plan.rf2_block_sparse_attn_unpermuted(buf["qp"], buf["kp"], buf["vp"], buf["blk_idx"], buf["blk_cnt"], o, lse)
+    perm = torch.from_numpy(plan.rf2_plan_perm()[0]).cuda().long()
+    assert torch.equal(o[:, :, perm].view(torch.int16), buf["op"][:, :, :n].view(torch.int16))
+    assert torch.equal(lse[:, :, perm], buf["lse"][:, :, :n])
+    idx, cnt = buf["blk_idx"].cpu(), buf["blk_cnt"].cpu()
+    inside = torch.arange(block_k)
+    for h in range(heads):
+        Q, K, V = (x[0, h][perm].double() for x in (q, k, v))
+        over, off = [], []
+        for r in range(i.n_blocks):
+            rows = slice(r * block, min((r + 1) * block, n))
+            cols = torch.arange(i.n_blocks_k) if cnt[0, h, r] == i.n_blocks_k else idx[0, h, r, :cnt[0, h, r]].long()
+            keys = (cols[:, None] * block_k + inside).flatten()
+            keys = keys[keys < n].cuda()
+            S = Q[rows] @ K[keys].T.contiguous() / d ** 0.5
+            P = torch.softmax(S, 1)
+            want = P @ V[keys]
+            err = (buf["op"][0, h, rows].double() - want).abs()
+            # probabilities and outputs rounded to bf16 (2^-8 each, relative); logits below 10 in fp32.  (No number: not below)
+            over.append((~(err <= 2.0 ** -8 * (P @ V[keys].abs() + want.abs()) + 1e-4)).any())
+            off.append((buf["lse"][0, h, rows].double() - torch.logsumexp(S, 1)).abs().max())
+        assert not torch.stack(over).any(), (h, torch.stack(over).nonzero().flatten()[:8])
+        assert torch.stack(off).max() <= 1e-4, h
     plan.close()
