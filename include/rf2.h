@@ -168,8 +168,9 @@ int rf2_plan_perm(const rf2_plan* plan, int32_t* perm_host, int32_t* inv_host);
  *                 (blk, part = (s % KH) / 32, g = (s / KH)*4 + (s % 32) / 8, ch, s % 8);
  *             rows >= N zero                                               (out)
  *             kp and vp are the layouts the attention kernel's matrix-core operand
- *             reads consume: every part (64 keys x d, contiguous) is copied to
- *             on-chip memory verbatim.  For b = 64 there is one part per block.
+ *             reads consume: a part (64 keys x d, contiguous) is read straight into
+ *             registers, 1 KiB at a time, each of which is one operand of a
+ *             wavefront.  For b = 64 there is one part per block.
  *   qbar, kbar : [B, Hh, Tb, d] fp32 means over the valid rows of each block of
  *             qp / kp (the last block divides by last_block_valid).  Pass both
  *             NULL to skip pooling.                                        (out)

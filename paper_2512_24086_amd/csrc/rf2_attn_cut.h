@@ -1,4 +1,4 @@
-// How a launch of the attention kernel is cut (host only; also compiled into a test).
+// How a launch of the attention kernel is cut (host only; also compiled into tests).
 #pragma once
 #include <stdint.h>
 
@@ -37,9 +37,11 @@ struct rf2_attn_cut {
 //     cut differently, 31 of them faster, by 2 to 20 %, 4 slower, by 3 to 4 %.)
 // The constants are fitted to launches of 600 to 40,000 tokens, 1 to 40 heads, blocks of 64, 128 and 256 rows, sparsity 0.5 to 0.9,
 // with and without sink rows and text (d = 128: 140 launches, d = 64: 125), and to 30 of 480p to long-video layers, each timed with
-// several cuts.  d = 128: the model is 4 % off on average, its choice 0.1 % slower than the best cut (6 % at most); d = 64: 7 % off,
-// 0.6 % slower (14 % at most, on launches under 100 us).  Against a rule of thresholds for a kernel with rings in LDS, d = 128,
-// 1.28 times as fast in the geometric mean.
+// several cuts.  On launches it is not fitted to: d = 128 (130 of them), 5 % off on average, its choice, mixed cuts among them, 0.3 %
+// faster than the best single cut, up to 7 % slower, on one (64-row blocks, 46,920 tokens x 46 heads) 22 %; d = 64 (720, of which
+// `shared` is taken), 7 % off, the choice 1.3 % slower than the best cut, up to 18 %, under 20 us 24 %.  Against the former kernel,
+// with rings in LDS and a rule of thresholds, they are 1.27 and 1.16 times as fast in the geometric mean; none at d = 128 is slower, six
+// at d = 64 by more than 5 % (8 % at most).
 // E.g. d = 128 (us, QH x KS = 1x1, 1x2, 1x4, 2x1, 2x2): image of 4,096 tokens, 1 head 38, 24, 19, 39, 26; 8 heads 41, 36, 42, 41, 36;
 // 16 heads 66, 70, 84, 67, 72; 24 heads 104, 102, 124, 107, 105; 480p 5 heads 672, 492, 532, 665, 493, 40 heads 3,926, 3,974,
 // 4,251, 3,506, 3,800; 256-row blocks, 480p, 40 heads, 2x1 3,425, 4x1 3,394, 720p 18,067 and 17,653.  d = 64 (1x1, 1x2, 1x4, 1x8, 2x2): image,

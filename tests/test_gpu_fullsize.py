@@ -27,13 +27,13 @@ CASES = {
     "longvideo_s50": ("longvideo", 0.5, (5,)),
     # cumulative-mass selection with 512 text tokens: variable row lengths at full size
     "video720p_cdf_text": ("video720p", 0.8, (7,)),
-    # 64-token blocks: 1,182 blocks per head (the mask kernel's wide-row path), two wavefronts per workgroup
+    # 64-token blocks: 1,182 blocks per head (the mask kernel's wide-row path), one tile of 64 rows per workgroup
     "video720p_b64": ("video720p", 0.8, (21,)),
-    # 256-row Q blocks over 128-row K/V blocks: eight wavefronts per workgroup, rectangular 296 x 591 mask
+    # 256-row Q blocks over 128-row K/V blocks: four wavefronts, a tile each, per workgroup, rectangular 296 x 591 mask
     "video720p_q256_k128": ("video720p", 0.8, (33,)),
-    # the remaining shapes of the kernels at the size the work tables and rings are built for:
-    # head_dim 64 (one or two direct-to-LDS loads per wavefront and part), token-major q/k/v/o
-    # (strided gathers and scatter over 75,600 tokens), 64-row K/V blocks under 128- and 256-row Q blocks
+    # the remaining shapes of the kernels at the size the work tables are built for: head_dim 64 (two wavefronts
+    # per SIMD, two to a list), token-major q/k/v/o (strided gathers and scatter over 75,600 tokens), 64-row K/V
+    # blocks under 128- and 256-row Q blocks
     "video720p_d64": ("video720p", 0.8, (12,)),
     "video720p_bnhd": ("video720p", 0.8, (29,)),
     "video720p_q128_k64": ("video720p", 0.8, (5,)),
