@@ -18,7 +18,7 @@
 // no barrier between the wavefronts in the loop.  Against rings in LDS with wavefronts of 32 rows, 4 to a workgroup, an operand
 // is moved half as often and nothing passes through LDS, which the power limit turns into clock.  d = 128 (one wavefront per
 // SIMD, 440 to 446 of its 512 registers, matrix cores 76 % busy on 720p where the rings kept two wavefronts 69 % busy): 720p, 40
-// heads, 20.7 -> 19.1 ms on one box (18.0 to 19.7 by box, 1,292 to 1,181 TFLOP/s), 480p 4.00 -> 3.54 ms; with 64-row Q blocks, where the rings left one wavefront of 32
+// heads, 20.7 -> 19.1 ms on one card (18.0 to 20.1 from card to card, 1,292 to 1,158 TFLOP/s), 480p 4.00 -> 3.54 ms; with 64-row Q blocks, where the rings left one wavefront of 32
 // rows per SIMD, 480p 5.13 -> 3.98 ms and 720p, 20 heads, 13.3 -> 10.8 ms.  d = 64 (two wavefronts per SIMD, 244 to 256 registers of 256 each) is
 // bound by vector issue and power either way: 480p 2.12 -> 2.07 ms, 720p, 20 heads, 5.48 -> 5.38; with 64-row Q blocks 2.47 ->
 // 2.12 ms.
