@@ -14,6 +14,8 @@ SOURCES = ["rf2_plan.cpp", "rf2_permute.hip", "rf2_mask.hip", "rf2_attn.hip", "r
 # Packed-fp32 VALU forms are switched off on purpose (they have misbehaved on the target machines).
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-x", "hip",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # the first kernel arguments arrive in scalar registers with the wavefront instead of being read from memory
+         "-mllvm", "-amdgpu-kernarg-preload-count=16",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-Wall", "-Wno-unused-command-line-argument"]
 
 

@@ -17,9 +17,9 @@
 // rf2_permute writes is read in 1 KiB pieces, each of which is one A operand and feeds two MFMAs.  There is no LDS and
 // no barrier between the wavefronts in the loop.  Against rings in LDS with wavefronts of 32 rows, 4 to a workgroup, an operand
 // is moved half as often and nothing passes through LDS, which the power limit turns into clock.  d = 128 (one wavefront per
-// SIMD, 440 to 446 of its 512 registers, matrix cores 76 % busy on 720p where the rings kept two wavefronts 69 % busy): 720p, 40
+// SIMD, 442 to 446 of its 512 registers, matrix cores 76 % busy on 720p where the rings kept two wavefronts 69 % busy): 720p, 40
 // heads, 20.7 -> 19.1 ms on one card (18.0 to 20.1 from card to card, 1,292 to 1,158 TFLOP/s), 480p 4.00 -> 3.54 ms; with 64-row Q blocks, where the rings left one wavefront of 32
-// rows per SIMD, 480p 5.13 -> 3.98 ms and 720p, 20 heads, 13.3 -> 10.8 ms.  d = 64 (two wavefronts per SIMD, 244 to 256 registers of 256 each) is
+// rows per SIMD, 480p 5.13 -> 3.98 ms and 720p, 20 heads, 13.3 -> 10.8 ms.  d = 64 (two wavefronts per SIMD, 246 to 256 registers of 256 each) is
 // bound by vector issue and power either way: 480p 2.12 -> 2.07 ms, 720p, 20 heads, 5.48 -> 5.38; with 64-row Q blocks 2.47 ->
 // 2.12 ms.
 //
@@ -75,6 +75,18 @@ __device__ __forceinline__ const unsigned char* uniform_ptr(const void* p) {
   return (const unsigned char*)(((uint64_t)hi << 32) | lo);
 }
 
+// Place of 16-byte chunk `chunk` of row `row` among rows of CPR chunks in LDS: 16 lanes that move the same chunk of neighbouring
+// rows, or the chunks of a row in turn, meet different banks.
+template <int CPR>
+__device__ __forceinline__ int row_slot(int row, int chunk) {
+  return row * CPR + (chunk ^ (row / (16 / CPR) % CPR));
+}
+// LDS accesses of a wavefront before and behind stay so (they are carried out in order, so nothing is waited for).
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Head and Q block of a workgroup, from its XCD and its number there.  False: no work.
 // Workgroups with equal blockIdx % 8 share an XCD (which of the eight it is varies from launch to launch).  Slots of an XCD, in
 // issue order: the all-column sink rows of every head first, then the ordinary rows head by head.  A sink row is several times
@@ -110,15 +122,18 @@ __device__ __forceinline__ bool row_of(const RowOrder& w, int xcd, int slot, int
   return qi >= 0;
 }
 
-// Parameters of both kernels.  split: log2 of the workgroups that share a Q block; they are neighbours on one XCD.  Tb: K/V blocks
+// Parameters of both kernels, what a row needs first in front: the first 14 words arrive in registers (see the flags of the
+// build), the others are read from memory.  shares to sink_slots: RowOrder.  split: log2 of the workgroups that share a Q block; they are neighbours on one XCD.  Tb: K/V blocks
 // per head (columns of the block mask); last_valid: tokens in the last one; perm: token of a permuted row; fused: output in the
 // caller's token order.
 #define RF2_STREAM_PARAMS \
-  const __bf16 *__restrict__ qp, const __bf16 *__restrict__ kp, const __bf16 *__restrict__ vp, const int32_t *__restrict__ blk_idx, \
-      const int32_t *__restrict__ blk_cnt, __bf16 *__restrict__ op, float *__restrict__ lse, RowOrder order, int Tb, int k_row, \
-      int last_valid, float scale_log2, const int32_t *__restrict__ perm, int n_tokens, int heads, rf2_strides st, int split, bool fused
-#define RF2_STREAM_ARGS \
-  qp, kp, vp, blk_idx, blk_cnt, op, lse, order, Tb, k_row, last_valid, scale_log2, perm, n_tokens, heads, st
+  const int32_t *__restrict__ shares, int per_xcd, int n_bh, int rows, int sink_begin, int n_sink, int sink_slots, int split, int k_row, \
+      const int32_t *__restrict__ blk_idx, const int32_t *__restrict__ blk_cnt, const __bf16 *__restrict__ qp, \
+      const __bf16 *__restrict__ kp, const __bf16 *__restrict__ vp, const int32_t *__restrict__ perm, __bf16 *__restrict__ op, \
+      float *__restrict__ lse, int Tb, int last_valid, float scale_log2, int n_tokens, int heads, bool fused, rf2_strides st
+#define RF2_STREAM_ARGS(split) \
+  shares, per_xcd, n_bh, rows, sink_begin, n_sink, sink_slots, split, k_row, blk_idx, blk_cnt, qp, kp, vp, perm, op, lse, Tb, last_valid, \
+      scale_log2, n_tokens, heads, fused, st
 
 // One workgroup: number `share` of those of a Q block, number `slot` of the XCD's rows.
 template <int D, int BK, int QH, int KS>
@@ -126,8 +141,8 @@ __device__ __forceinline__ void attend(RF2_STREAM_PARAMS, int xcd, int slot, int
   constexpr int BQ = 64 * QH, KH = BK / 2, PB = BK / 64, DS = D / 16, DT = D / 32;
   constexpr int TILE_BYTES = BK * D * 2, PART_BYTES = 64 * D * 2;
   int bh, qi;
-  if (!row_of(order, xcd, slot, bh, qi)) return;
-  const int Tq = order.rows;
+  if (!row_of({shares, per_xcd, n_bh, rows, sink_begin, n_sink, sink_slots}, xcd, slot, bh, qi)) return;
+  const int Tq = rows;
   const size_t row_id = (size_t)bh * Tq + qi;
   const int32_t* __restrict__ list = blk_idx + row_id * k_row;
   const int wave = QH * KS > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) : 0;
@@ -145,14 +160,18 @@ __device__ __forceinline__ void attend(RF2_STREAM_PARAMS, int xcd, int slot, int
   __builtin_amdgcn_sched_barrier(0);
   const size_t q_head_off = (size_t)bh * (Tq << split) * BQ * D;             // elements; qp and op
   const int q_row = ((qi << split) + share) * BQ + 64 * half + l32;          // this lane's query row of tile 0 in its head
-  bf16x8 qf[2][DS];
-  const __bf16* const q_from = qp + q_head_off + (size_t)q_row * D + 8 * lh;
+  bf16x8 q_in[2][DS];
+  const __bf16* const q_from = qp + q_head_off + (size_t)(q_row - l32) * D + 8 * lane;
 #pragma unroll
   for (int q = 0; q < 2; ++q)
 #pragma unroll
-    for (int ds = 0; ds < DS; ++ds) qf[q][ds] = *reinterpret_cast<const bf16x8*>(q_from + q * 32 * D + 16 * ds);
-  const int token[2] = {perm[q_row], perm[q_row + 32]};                      // -1: padding of the last block
+    for (int i = 0; i < DS; ++i) q_in[q][i] = *reinterpret_cast<const bf16x8*>(q_from + q * 32 * D + i * 512);
+  int token = perm[q_row - l32 + lane];                                      // of the wavefront's row `lane`; -1: padding of the last block
+  // where the head's rows go, and how far they are apart
+  uint64_t out_at = (uint64_t)(fused ? op + ((bh / heads) * st.batch + (bh % heads) * st.head) * D : op + q_head_off);
+  uint32_t out_pitch = fused ? (uint32_t)st.token * (D * 2) : D * 2;
   __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" : "+s"(out_at), "+s"(out_pitch));
   asm("" : "+s"(cnt), "+s"(tail), "+s"(ahead[0]), "+s"(ahead[1]), "+s"(ahead[2]));   // (left alone, the entries wait for the count)
   const bool dense = (cnt == Tb);
   cnt = dense ? Tb : min(max(cnt, 0), k_row);
@@ -192,6 +211,38 @@ __device__ __forceinline__ void attend(RF2_STREAM_PARAMS, int xcd, int slot, int
   };
   auto part_of = [&](int P) { return P * KS + grp; };    // list part of this wavefront's part P
   const int partial_begin = ragged ? 2 * (max((cnt - 1) * PB - grp + KS - 1, 0) / KS) : U;   // first unit of the ragged block
+
+  // Q and O pass through LDS on their way between memory, where a wavefront moves whole rows, and registers, where a lane has
+  // pieces of one row: 16 or 8 bytes a lane at a stride of a row keep the address unit of a compute unit busy for 64 cycles an
+  // instruction, 2,048 of them for the O of a wavefront, where whole rows take 16.  (480p, us from row to row of a place, beside a
+  // loop of 125: last product to last store acknowledged 3.2 -> 2.0, end to next start 1.7 -> 0.9, start to first unit 2.8 -> 2.6,
+  // with the arguments in registers.  Layers: tiny 21.0 -> 19.5 us, image 130 -> 126.5, 480p 3,867 -> 3,840, with 64-row blocks 4,136 ->
+  // 4,089; attention alone, d = 64 480p 2,129 -> 2,103, ten heads of 256-row blocks 463.6 -> 455.4, long video +0.5 %.)
+  constexpr int TILES = 2 * DT, OWN = TILES >= KS ? TILES / KS : 1;          // 32 x 32 tiles of O, those that a wavefront finishes
+  constexpr int OC = 4 * std::min(OWN, DT);                                  // 16-byte chunks of a row that it finishes
+  __shared__ uint4 out_rows[QH * KS][32 * OC];
+  __shared__ int targets[QH * KS][64];                                       // where these rows go
+  __shared__ float4 tiles[QH][KS][KS > 1 ? TILES - TILES / KS : 1][KS > 1 ? 4 : 1][KS > 1 ? 64 : 1];
+  bf16x8 qf[2][DS];
+  // plain output: the row of the permuted layout; fused inverse permutation: the token's raster row
+  auto note_targets = [&] {
+    asm volatile("" : "+v"(token));          // (left alone, it is waited for before the first tiles are asked for)
+    targets[wave][lane] = fused ? token : q_row - l32 + lane;
+  };
+  auto spread_q = [&] {
+    note_targets();
+    uint4* const staged = KS > 1 ? reinterpret_cast<uint4*>(&tiles[half][grp]) : out_rows[wave];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+#pragma unroll
+      for (int i = 0; i < DS; ++i)
+        staged[row_slot<D / 8>(lane / (D / 8) + i * (512 / D), lane % (D / 8))] = __builtin_bit_cast(uint4, q_in[q][i]);
+      wave_fence();
+#pragma unroll
+      for (int ds = 0; ds < DS; ++ds) qf[q][ds] = __builtin_bit_cast(bf16x8, staged[row_slot<D / 8>(l32, 2 * ds + lh)]);
+      wave_fence();
+    }
+  };
 
   f32x16 o[2][DT];
 #pragma unroll
@@ -371,6 +422,7 @@ __device__ __forceinline__ void attend(RF2_STREAM_PARAMS, int xcd, int slot, int
       }
       f32x16 Sa[2], Sb[2];
       uint32_t Pa[2][8], Pb[2][8];
+      spread_q();
       first_unit(Sa, k0);
       // (arrived before the loop, whose waits would else be those of its first round: vr[0] is not on its way yet)
 #pragma unroll
@@ -471,6 +523,7 @@ __device__ __forceinline__ void attend(RF2_STREAM_PARAMS, int xcd, int slot, int
           asm volatile("" ::: "memory");
         }
       }
+      spread_q();
       first_unit(S, k0);
       redo_tile(0, S[0], P[0]);                     // probabilities of tile 0 of the first unit (the reference stays where it is)
 #pragma unroll
@@ -492,6 +545,8 @@ __device__ __forceinline__ void attend(RF2_STREAM_PARAMS, int xcd, int slot, int
     }
   }
 
+  if (U == 0) note_targets();
+
   // ---- normalise (the final division of eq. 4) and write this wavefront's rows ------------------------------------
   float l_tot[2];
 #pragma unroll
@@ -502,10 +557,8 @@ __device__ __forceinline__ void attend(RF2_STREAM_PARAMS, int xcd, int slot, int
   // ---- merge of the shares: wavefront x KS / TILES finishes 32 x 32 tile x = q DT + dt ----------------------------
   // Every wavefront leaves the tiles it does not finish and its row statistics in LDS and rescales what it reads to the
   // largest reference of the row.
-  constexpr int TILES = 2 * DT;
   auto finishes = [&](int q, int dt) { return KS == 1 || grp == (q * DT + dt) * KS / TILES; };
   if constexpr (KS > 1) {
-    __shared__ float4 tiles[QH][KS][TILES - TILES / KS][4][64];
     __shared__ float2 stats[QH][KS][2][32];
     auto place = [&](int owner, int x) { return x < owner * TILES / KS ? x : x - TILES / KS; };   // (its own tiles take no place)
 #pragma unroll
@@ -561,32 +614,60 @@ __device__ __forceinline__ void attend(RF2_STREAM_PARAMS, int xcd, int slot, int
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
     const float f = l_tot[q] > 0.f ? 1.0f / l_tot[q] : 0.f;   // a row with no kept key yields zeros
-    const size_t row = (size_t)q_row + 32 * q;
-    // plain output: row `row` of the permuted layout; fused inverse permutation: the token's raster row
-    const int target = fused ? token[q] : (int)row;
-    if (target < 0) continue;                                 // padding row of the last block
-    __bf16* orow = fused ? op + ((bh / heads) * st.batch + (bh % heads) * st.head + (long long)target * st.token) * D
-                           : op + q_head_off + row * D;
+    if (KS == 1 || grp * TILES / KS / DT == q) {                // (of more wavefronts than tiles some have none)
+      if (KS <= TILES || grp * TILES % KS == 0) {
+        uint4* const staged = out_rows[wave];
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-      if (finishes(q, dt))
+        for (int dt = 0; dt < DT; ++dt)
+          if (finishes(q, dt))
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          bf16x4 pk;
+            for (int g = 0; g < 4; ++g) {
+              bf16x4 pk;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) pk[e] = (__bf16)(o[q][dt][4 * g + e] * f);
-          *reinterpret_cast<bf16x4*>(orow + 32 * dt + 8 * g + 4 * lh) = pk;
+              for (int e = 0; e < 4; ++e) pk[e] = (__bf16)(o[q][dt][4 * g + e] * f);
+              reinterpret_cast<bf16x4*>(&staged[row_slot<OC>(l32, (4 * dt + g) % OC)])[lh] = pk;
+            }
+        wave_fence();
+        // (all reads ahead of the stores, which may stand behind branches: rows past the last token are not written)
+        __attribute__((address_space(1))) unsigned char* const to = (__attribute__((address_space(1))) unsigned char*)out_at + (OC < D / 8 ? 64 * (grp * TILES / KS % DT) : 0) + 16 * (lane % OC);
+        uint4 piece[OC / 2];
+        int row_to[OC / 2];
+#pragma unroll
+        for (int i = 0; i < OC / 2; ++i) {
+          const int r = lane / OC + i * (64 / OC);
+          piece[i] = staged[row_slot<OC>(r, lane % OC)];
+          row_to[i] = targets[wave][32 * q + r];
         }
-    if (lse != nullptr && lh == 0 && finishes(q, 0))
-      lse[fused ? (size_t)bh * n_tokens + target : (size_t)bh * (Tq << split) * BQ + row] =
-          m_ref[q] * scale_log2 * 0.6931471805599453f + __logf(l_tot[q]);
+#pragma unroll
+        for (int i = 0; i < OC / 2; ++i) asm volatile("" : "+v"(piece[i].x), "+v"(piece[i].y), "+v"(piece[i].z), "+v"(piece[i].w), "+v"(row_to[i]));
+        auto store = [&](int i) {
+          const u32x4 x = {piece[i].x, piece[i].y, piece[i].z, piece[i].w};
+          *reinterpret_cast<__attribute__((address_space(1))) u32x4*>(to + (uint64_t)(uint32_t)row_to[i] * out_pitch) = x;
+        };
+        if (!fused || q_row - l32 + 64 <= n_tokens) {
+#pragma unroll
+          for (int i = 0; i < OC / 2; ++i) store(i);
+        } else {
+#pragma unroll
+          for (int i = 0; i < OC / 2; ++i)
+            if (row_to[i] >= 0) store(i);
+        }
+        wave_fence();
+      }
+    }
+    if (lse != nullptr && lh == 0 && finishes(q, 0)) {
+      const int t = targets[wave][32 * q + l32];
+      if (t >= 0)
+        lse[fused ? (size_t)bh * n_tokens + t : (size_t)bh * (Tq << split) * BQ + t] =
+            m_ref[q] * scale_log2 * 0.6931471805599453f + __logf(l_tot[q]);
+    }
   }
 }
 
 template <int D, int BK, int QH, int KS>
 __global__ void __launch_bounds__(64 * QH * KS, D == 128 ? 1 : 2) stream_attn_kernel(RF2_STREAM_PARAMS) {
   const int at = (int)(blockIdx.x >> 3);
-  attend<D, BK, QH, KS>(RF2_STREAM_ARGS, split, fused, (int)(blockIdx.x & 7), at >> split, at & ((1 << split) - 1));
+  attend<D, BK, QH, KS>(RF2_STREAM_ARGS(split), (int)(blockIdx.x & 7), at >> split, at & ((1 << split) - 1));
 }
 
 // QH = 2 for the row slots `lead` to `whole` of an XCD, KS = 2 in front of them (its sink rows, or none) and behind them (see
@@ -598,10 +679,10 @@ __global__ void __launch_bounds__(128, 1) mixed_attn_kernel(RF2_STREAM_PARAMS, i
   const int xcd = (int)(blockIdx.x & 7), at = (int)(blockIdx.x >> 3);
   const int inside = at - (lead << (split + 1)), behind = inside - ((whole - lead) << split);
   if (inside >= 0 && behind < 0) {
-    attend<D, BK, 2, 1>(RF2_STREAM_ARGS, split, fused, xcd, lead + (inside >> split), inside & ((1 << split) - 1));
+    attend<D, BK, 2, 1>(RF2_STREAM_ARGS(split), xcd, lead + (inside >> split), inside & ((1 << split) - 1));
   } else {
     const int half = inside < 0 ? at : behind;
-    attend<D, BK, 1, 2>(RF2_STREAM_ARGS, split + 1, fused, xcd, (inside < 0 ? 0 : whole) + (half >> (split + 1)), half & ((2 << split) - 1));
+    attend<D, BK, 1, 2>(RF2_STREAM_ARGS(split + 1), xcd, (inside < 0 ? 0 : whole) + (half >> (split + 1)), half & ((2 << split) - 1));
   }
 }
 
@@ -634,9 +715,10 @@ int launch_stream(const rf2_plan* plan, const AttnArgs& a, hipStream_t st) {
   if (slots == 0) return RF2_OK;
   const auto launch = [&](auto kernel, unsigned grid, auto... more) {
     kernel<<<dim3(grid), dim3(64 * QH * KS), 0, st>>>(
-        (const __bf16*)a.qp, (const __bf16*)a.kp, (const __bf16*)a.vp, a.blk_idx, a.blk_cnt, (__bf16*)a.out, a.lse, order,
-        in.n_blocks_k, in.k_row, in.last_block_valid_k, (float)(1.4426950408889634 / sqrt((double)D)),
-        plan->d_perm, (int)in.N, plan->cfg.heads, rf2_qkv_strides(plan), split, a.scatter, more...);
+        order.shares, order.per_xcd, order.n_bh, order.rows, order.sink_begin, order.n_sink, order.sink_slots, split, in.k_row, a.blk_idx,
+        a.blk_cnt, (const __bf16*)a.qp, (const __bf16*)a.kp, (const __bf16*)a.vp, plan->d_perm, (__bf16*)a.out, a.lse, in.n_blocks_k,
+        in.last_block_valid_k, (float)(1.4426950408889634 / sqrt((double)D)), (int)in.N, plan->cfg.heads, a.scatter, rf2_qkv_strides(plan),
+        more...);
   };
   if constexpr (D == 128 && QH == 2 && KS == 1) {
     const unsigned lead = plan->cut.halved_sinks ? (unsigned)order.sink_slots : 0u;

@@ -184,3 +184,32 @@ def test_halves_of_rows_dealt_by_the_work_table(case):
         assert not torch.stack(over).any(), (h, torch.stack(over).nonzero().flatten()[:8])
         assert torch.stack(off).max() <= 1e-4, h
     plan.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [(330, 64, 64, 128, 200), (2450, 128, 64, 128, 12), (657, 64, 64, 128, 1), (4001, 128, 128, 128, 41),
+                                   (2450, 128, 64, 128, 27), (999, 64, 64, 64, 100), (1500, 64, 64, 64, 23), (657, 64, 64, 64, 17),
+                                   (2450, 64, 64, 64, 1)], ids=lambda s: "x".join(map(str, s)))
+def test_rows_land_where_they_belong(shape):
+    """Output rows leave a wavefront whole, 16 bytes a lane: token-major, behind an address that is a multiple of 8 bytes only, with a
+    ragged last block, they are those of the plain exit, and nothing beside them is written."""
+    tokens, block, block_k, d, heads = shape
+    print(f"[case] {shape}", flush=True)
+    plan = rf2.Plan(batch=1, heads=heads, head_dim=d, T=1, H=1, W=tokens, block=block, block_k=block_k, sparsity=0.3, window=(1, 1, 24),
+                    qkv_layout=rf2.RF2_LAYOUT_BNHD)
+    i = plan.info
+    g = torch.Generator(device="cuda").manual_seed(19)
+    q, k, v = (torch.randn(1, tokens, heads, d, generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    idx, cnt = hp.lists_to_device(cut_tests.lists(plan, 7), i.k_row, i.n_blocks, "cuda")
+    buf = plan.alloc("cuda")
+    plan.rf2_permute(q, k, v, buf["qp"], buf["kp"], buf["vp"])
+    plan.rf2_block_sparse_attn(buf["qp"], buf["kp"], buf["vp"], idx, cnt, buf["op"])
+    n = tokens * heads * d
+    around = torch.full((n + 512,), 7.5, dtype=torch.bfloat16, device="cuda")
+    o = around[260:260 + n].view(1, tokens, heads, d)
+    assert o.data_ptr() % 16 == 8
+    plan.rf2_block_sparse_attn_unpermuted(buf["qp"], buf["kp"], buf["vp"], idx, cnt, o)
+    perm = torch.from_numpy(plan.rf2_plan_perm()[0]).cuda().long()
+    assert torch.equal(o[:, perm].transpose(1, 2).view(torch.int16), buf["op"][:, :, :tokens].view(torch.int16))
+    assert (around[:260] == 7.5).all() and (around[260 + n:] == 7.5).all()
+    plan.close()
