@@ -17,7 +17,7 @@
 // rf2_permute writes is read in 1 KiB pieces, each of which is one A operand and feeds two MFMAs.  There is no LDS and
 // no barrier between the wavefronts in the loop.  Against rings in LDS with wavefronts of 32 rows, 4 to a workgroup, an operand
 // is moved half as often and nothing passes through LDS, which the power limit turns into clock.  d = 128 (one wavefront per
-// SIMD, 442 to 446 of its 512 registers, matrix cores 76 % busy on 720p where the rings kept two wavefronts 69 % busy): 720p, 40
+// SIMD, 442 to 444 of its 512 registers, matrix cores 76 % busy on 720p where the rings kept two wavefronts 69 % busy): 720p, 40
 // heads, 20.7 -> 19.1 ms on one card (18.0 to 20.1 from card to card, 1,292 to 1,158 TFLOP/s), 480p 4.00 -> 3.54 ms; with 64-row Q blocks, where the rings left one wavefront of 32
 // rows per SIMD, 480p 5.13 -> 3.98 ms and 720p, 20 heads, 13.3 -> 10.8 ms.  d = 64 (two wavefronts per SIMD, 246 to 256 registers of 256 each) is
 // bound by vector issue and power either way: 480p 2.12 -> 2.07 ms, 720p, 20 heads, 5.48 -> 5.38; with 64-row Q blocks 2.47 ->
@@ -144,7 +144,7 @@ __device__ __forceinline__ void attend(RF2_STREAM_PARAMS, int xcd, int slot, int
   if (!row_of({shares, per_xcd, n_bh, rows, sink_begin, n_sink, sink_slots}, xcd, slot, bh, qi)) return;
   const int Tq = rows;
   const size_t row_id = (size_t)bh * Tq + qi;
-  const int32_t* __restrict__ list = blk_idx + row_id * k_row;
+  const auto* const list = (const __attribute__((address_space(4))) int32_t*)(blk_idx + row_id * k_row);   // (scalar loads)
   const int wave = QH * KS > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) : 0;
   const int half = wave % QH, grp = wave / QH;
   const int lane = (int)threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
@@ -201,12 +201,11 @@ __device__ __forceinline__ void attend(RF2_STREAM_PARAMS, int xcd, int slot, int
     return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(vbuf, v_lane + j / 2 * 512, off + j % 2 * 2 * D * 16, 0));
   };
   // Part P of the list is part P % PB of listed block P / PB (P clamped: loads past the end fetch the last part again).
-  auto list_entry = [&](int P) {
-    const int it = (int)((unsigned)min(P, NPARTS - 1) / (unsigned)PB);
-    return dense ? it : list[it];
-  };
+  // (its entry is read without a branch and, where the row keeps all blocks, not used)
+  auto list_entry = [&](int P) { return list[min((int)((unsigned)min(P, NPARTS - 1) / (unsigned)PB), k_row - 1)]; };
   auto part_off = [&](int entry, int P) {
-    const int j = min(max(entry, 0), Tb - 1);            // a corrupt list can give wrong results, never a fault
+    const int it = (int)((unsigned)min(P, NPARTS - 1) / (unsigned)PB);
+    const int j = min(max(dense ? it : entry, 0), Tb - 1);     // a corrupt list can give wrong results, never a fault
     return (uint32_t)j * (uint32_t)TILE_BYTES + ((unsigned)min(P, NPARTS - 1) % (unsigned)PB) * (uint32_t)PART_BYTES;
   };
   auto part_of = [&](int P) { return P * KS + grp; };    // list part of this wavefront's part P
@@ -348,34 +347,37 @@ __device__ __forceinline__ void attend(RF2_STREAM_PARAMS, int xcd, int slot, int
   // tiles in L1 (d = 128, 720p, 24 heads, 11.25 -> 10.99 ms, 480p 3.59 -> 3.56; every part or every 4th: no more, and dearer on
   // short lists; d = 64, KS = 2, 480p 2.122 -> 2.109 ms.  Four wavefronts of a 256-row Q block lose 2 %).
   constexpr int MEET = QH == 2 && (D == 64 || KS == 1) ? 16 : 0;
-  auto meet = [&](int part) {
+  auto meet = [&](int part = 0) {
     if (MEET > 0 && part % std::max(MEET, 1) == 0) __builtin_amdgcn_s_barrier();
   };
   // The order of the loads in front of the loops is that of the loops: the compiler's wait counts are the smaller of the two.
 
   if constexpr (D == 128) {
     // Registers: O^T 128 and Q 64 accumulation registers, S^T of two units 64, P of two units 32, operands of two steps 128.
-    bool slow = partial_begin == 0, redo = false;   // mask the coming unit / the latest unit must be redone
     bf16x8 kr[2][NQ], vr[2][NP];                    // operands of the coming even and odd step
     // Step s: products S_{s+1} and V P_{s-1} around the softmax arithmetic of unit s, operand by operand.  Its registers are
     // reloaded for step s+2 (K tile at k_off, V^T tile at v_off) as soon as both MFMAs that read them are issued.  An MFMA
-    // takes eight issue slots of the SIMD; behind the first of an operand come the exponentials of a pair of
-    // probabilities, behind the second its sum and packing and the load.
+    // takes eight issue slots of the SIMD, two of them its own; behind the first of an operand come the exponentials of a pair of
+    // probabilities (two slots each) and their arguments, which fills it, behind the second its sum and packing and the load, and what
+    // else there is to do: `spare(g)`.
+    // The wavefront issues one instruction after the other, so what stood between two steps (offsets, the list, the checks of the
+    // last unit, branches around the rare cases) held up the MFMAs; in their open slots it does not (attention at 480p 3,496 -> 3,404
+    // us, 720p +1.3 to 2.6 %, ten heads of 256-row blocks 454.5 -> 449.7, 480p with 64-row blocks, whose operands come late, 3,854 ->
+    // 3,856).  K and V through rings in LDS, filled for both wavefronts at once, was 9 % slower (480p): writes to LDS take
+    // longer to issue than the loads that they save.
     auto step = [&](auto odd_tag, int s, f32x16 (&Scur)[2], f32x16 (&Snext)[2], uint32_t (&Pprev)[2][8], uint32_t (&Pcur)[2][8],
-                    uint32_t k_off, uint32_t v_off) {
+                    uint32_t k_off, uint32_t v_off, auto spare) {
       constexpr int ODD = decltype(odd_tag)::value ? 1 : 0;
-      if (slow) {
-        // (the accumulators of unit s-1 are still in the buffer this step overwrites)
-        if (redo) redo_tile(0, Snext[0], Pprev[0]), redo_tile(1, Snext[1], Pprev[1]);
-        if (s > 0 && s >= partial_begin) mask_tile(Scur[0], s), mask_tile(Scur[1], s);
-      }
-      l_run[0] += rs_last[0];
-      l_run[1] += rs_last[1];
       __builtin_amdgcn_sched_barrier(0);
       float rs[2] = {}, e0 = 0.f, e1 = 0.f;
+      int limit = 0;
 #pragma unroll
       for (int g = 0; g < NQ + NP; ++g) {
         const int tile = g / 8, i = 2 * (g % 8), j = g - NQ;
+        if (g % 2 == 0) {                         // (one wait for two operands)
+          if (g < NQ) asm volatile("" ::"v"(kr[ODD][g + 1]));
+          else asm volatile("" ::"v"(vr[ODD][j + 1]));
+        }
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
           if (g < NQ) qk<true>(Snext[q], kr[ODD][g], qf[q][g], g == 0);
@@ -394,14 +396,26 @@ __device__ __forceinline__ void attend(RF2_STREAM_PARAMS, int xcd, int slot, int
             rs[tile] = (i == 0) ? e0 + e1 : rs[tile] + (e0 + e1);
             asm volatile("" : "+v"(w), "+v"(rs[tile]));
             Pcur[tile][i / 2] = w;
+            if (i == 0) {
+              l_run[tile] += rs_last[tile];
+              asm volatile("" : "+v"(l_run[tile]));
+            }
+            if (g == 13) {
+              limit = s + 1 >= partial_begin ? __builtin_bit_cast(int, -1.f) : __builtin_bit_cast(int, RANGE);
+              asm volatile("" : "+s"(limit));
+            }
+            spare(g);
           }
           __builtin_amdgcn_sched_barrier(0);      // the slots stay in this order
         }
       }
       rs_last[0] = rs[0];
       rs_last[1] = rs[1];
-      redo = __builtin_amdgcn_ballot_w64(!(rs[0] + rs[1] <= RANGE)) != 0ull;
-      slow = redo || (s + 1 >= partial_begin);
+      // One branch, hardly ever taken: unit s is out of range, or unit s+1 has keys past the end of the sequence.
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(rs[0] + rs[1] <= __builtin_bit_cast(float, limit))) != 0ull, 0)) {
+        if (__builtin_amdgcn_ballot_w64(!(rs[0] + rs[1] <= RANGE)) != 0ull) redo_tile(0, Scur[0], Pcur[0]), redo_tile(1, Scur[1], Pcur[1]);
+        if (s + 1 >= partial_begin) mask_tile(Snext[0], s + 1), mask_tile(Snext[1], s + 1);
+      }
     };
     if (U > 0) {
       uint32_t off0 = first_off(0), off1 = first_off(1);   // parts P, P + 1
@@ -435,21 +449,30 @@ __device__ __forceinline__ void attend(RF2_STREAM_PARAMS, int xcd, int slot, int
         for (int i = 0; i < 16; ++i) Sb[q][i] = 0.f;
       }
       // A list entry is read a round before it is turned into an offset, so that no step waits for a scalar memory load.
-      int entry = dense ? part_of(2) / PB : ahead[2];
-      for (int s = 0; s < U; s += 2) {
-        const int P = s >> 1;
-        meet(P);
-        const uint32_t off2 = part_off(entry, part_of(P + 2));
-        entry = list_entry(part_of(P + 3));
-        // even step: S of unit s+1 (part P, tile 1), V P of unit s-1; loads K of part P+1, tile 1 and V of part P, tile 1
-        step(std::false_type{}, s, Sa, Sb, Pb, Pa, off1 + K_TILE, off0 + V_TILE);
-        // odd step: S of unit s+2 (part P+1, tile 0), V P of unit s; loads K of part P+2, tile 0 and V of part P+1, tile 0
-        step(std::true_type{}, s + 1, Sb, Sa, Pa, Pb, off2, off1);
-        off0 = off1;
-        off1 = off2;
+      int entry = ahead[2];
+      for (int s = 0; s < U;) {
+        meet();
+        const int end = MEET > 0 ? min(U, s + 2 * MEET) : U;
+        do {
+          const int P = s >> 1;
+          uint32_t off2 = 0;
+          // even step: S of unit s+1 (part P, tile 1), V P of unit s-1; loads K of part P+1, tile 1 and V of part P, tile 1
+          step(std::false_type{}, s, Sa, Sb, Pb, Pa, off1 + K_TILE, off0 + V_TILE, [&](int g) {
+            if (g == 3) {
+              off2 = part_off(entry, part_of(P + 2));
+              asm volatile("" : "+s"(off2));
+            } else if (g == 5) {
+              entry = list_entry(part_of(P + 3));
+            }
+          });
+          // odd step: S of unit s+2 (part P+1, tile 0), V P of unit s; loads K of part P+2, tile 0 and V of part P+1, tile 0
+          step(std::true_type{}, s + 1, Sb, Sa, Pa, Pb, off2, off1, [](int) {});
+          off0 = off1;
+          off1 = off2;
+          s += 2;
+        } while (s < end);
       }
       // last product: O += V P_{U-1}
-      if (redo) redo_tile(0, Sb[0], Pb[0]), redo_tile(1, Sb[1], Pb[1]);
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
         l_run[q] += rs_last[q];
@@ -464,17 +487,16 @@ __device__ __forceinline__ void attend(RF2_STREAM_PARAMS, int xcd, int slot, int
     bf16x8 kr[2][NQ], vr[2][NP];                    // operands of even and odd units
     f32x16 S[2];
     uint32_t P[2][8];
-    bool redo = false;
     // Half of step s for tile T: S_T of unit s+1 and O_T += V P_T of unit s, in turn, around the softmax arithmetic of the other
     // tile X (unit s of tile 1 in the first half, unit s+1 of tile 0 in the second).  In the second half the operands'
     // registers are reloaded for step s+2.
-    auto half_step = [&](auto tile_tag, auto odd_tag, int s, uint32_t k_off, uint32_t v_off) {
+    // (checks, offsets and the list between MFMAs as above: 480p 2,078 -> 2,027 us, tiny layer 19.4 -> 19.1, with 64-row blocks 480p
+    // 2,117 -> 2,108.)
+    auto half_step = [&](auto tile_tag, auto odd_tag, int s, uint32_t k_off, uint32_t v_off, auto spare) {
       constexpr int T = decltype(tile_tag)::value ? 1 : 0, X = 1 - T, ODD = decltype(odd_tag)::value ? 1 : 0;
-      if (redo) redo_tile(T, S[T], P[T]);
-      l_run[T] += rs_last[T];
-      if (s + T >= partial_begin) mask_tile(S[X], s + T);
       __builtin_amdgcn_sched_barrier(0);
       float rs = 0.f, e[2][2];
+      int limit = 0;
       // sum and packing of pair p, a slot behind its exponentials: no instruction waits for the one before it
       auto finish_pair = [&](int p) {
         const bf16x2 pk = {(__bf16)e[p & 1][0], (__bf16)e[p & 1][1]};
@@ -495,6 +517,15 @@ __device__ __forceinline__ void attend(RF2_STREAM_PARAMS, int xcd, int slot, int
           asm volatile("" ::: "memory");
         }
         if (g > 0) finish_pair(g - 1);
+        if (g == 0) {
+          l_run[T] += rs_last[T];
+          asm volatile("" : "+v"(l_run[T]));
+        }
+        if (g == 5) {
+          limit = s + 1 >= partial_begin ? __builtin_bit_cast(int, -1.f) : __builtin_bit_cast(int, RANGE);
+          asm volatile("" : "+s"(limit));
+        }
+        spare(g);
         e[g & 1][0] = __builtin_amdgcn_exp2f(fmaf(S[X][2 * g], scale_log2, nmc[X]));
         e[g & 1][1] = __builtin_amdgcn_exp2f(fmaf(S[X][2 * g + 1], scale_log2, nmc[X]));
         asm volatile("" : "+v"(e[g & 1][0]), "+v"(e[g & 1][1]));
@@ -502,7 +533,12 @@ __device__ __forceinline__ void attend(RF2_STREAM_PARAMS, int xcd, int slot, int
         __builtin_amdgcn_sched_barrier(0);
       }
       rs_last[X] = rs;
-      redo = __builtin_amdgcn_ballot_w64(!(rs <= RANGE)) != 0ull;
+      // One branch, hardly ever taken: the unit of X is out of range, or unit s+1 of T has keys past the end of the sequence.
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(rs <= __builtin_bit_cast(float, limit))) != 0ull, 0)) {
+        // (a unit past the end of the list is none of this wavefront's)
+        if ((X == 1 || s + 1 < U) && __builtin_amdgcn_ballot_w64(!(rs <= RANGE)) != 0ull) redo_tile(X, S[X], P[X]);
+        if (s + 1 >= partial_begin) mask_tile(S[T], s + 1);
+      }
     };
     const int most = (NPARTS + KS - 1) / KS;        // of the wavefronts that share the list
     if (KS > 1 && U == 0 && most > 0) meet(0);
@@ -528,18 +564,29 @@ __device__ __forceinline__ void attend(RF2_STREAM_PARAMS, int xcd, int slot, int
       redo_tile(0, S[0], P[0]);                     // probabilities of tile 0 of the first unit (the reference stays where it is)
 #pragma unroll
       for (int e = 0; e < 8; ++e) P[1][e] = 0u;
-      int entry = dense ? part_of(2) / PB : ahead[2];
-      for (int s = 0; s < U; s += 2) {
-        const int p = s >> 1;
-        meet(p);
-        const uint32_t off2 = part_off(entry, part_of(p + 2));
-        entry = list_entry(part_of(p + 3));
-        // loads in step s (part P, tile 0): K of part P+1, tile 1, V of part P+1, tile 0; in step s+1: K of part P+2, tile 0, V of part P+1, tile 1
-        half_step(std::false_type{}, std::false_type{}, s, 0, 0);
-        half_step(std::true_type{}, std::false_type{}, s, off1 + K_TILE, off1);
-        half_step(std::false_type{}, std::true_type{}, s + 1, 0, 0);
-        half_step(std::true_type{}, std::true_type{}, s + 1, off2, off1 + V_TILE);
-        off1 = off2;
+      int entry = ahead[2];
+      const auto nothing = [](int) {};
+      for (int s = 0; s < U;) {
+        meet();
+        const int end = MEET > 0 ? min(U, s + 2 * MEET) : U;
+        do {
+          const int p = s >> 1;
+          uint32_t off2 = 0;
+          // loads in step s (part P, tile 0): K of part P+1, tile 1, V of part P+1, tile 0; in step s+1: K of part P+2, tile 0, V of part P+1, tile 1
+          half_step(std::false_type{}, std::false_type{}, s, 0, 0, [&](int g) {
+            if (g == 3) {
+              off2 = part_off(entry, part_of(p + 2));
+              asm volatile("" : "+s"(off2));
+            } else if (g == 4) {
+              entry = list_entry(part_of(p + 3));
+            }
+          });
+          half_step(std::true_type{}, std::false_type{}, s, off1 + K_TILE, off1, nothing);
+          half_step(std::false_type{}, std::true_type{}, s + 1, 0, 0, nothing);
+          half_step(std::true_type{}, std::true_type{}, s + 1, off2, off1 + V_TILE, nothing);
+          off1 = off2;
+          s += 2;
+        } while (s < end);
       }
       if (KS > 1 && parts < most) meet(parts);
     }

@@ -213,3 +213,53 @@ def test_rows_land_where_they_belong(shape):
     assert torch.equal(o[:, perm].transpose(1, 2).view(torch.int16), buf["op"][:, :, :tokens].view(torch.int16))
     assert (around[:260] == 7.5).all() and (around[260 + n:] == 7.5).all()
     plan.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [(330, 64, 64, 128, 200), (2450, 128, 64, 128, 12), (657, 64, 64, 128, 1), (4001, 128, 128, 128, 41),
+                                   (6177, 128, 64, 128, 5), (999, 64, 64, 64, 100), (1500, 64, 64, 64, 23), (657, 64, 64, 64, 17),
+                                   (2450, 64, 64, 64, 1), (2450, 128, 128, 64, 24)], ids=lambda s: "x".join(map(str, s)))
+def test_reference_moves_in_any_unit(shape):
+    """Keys that outweigh all before them by more than 2^40 in one, two and three units of 32: the first ones of a head, the last
+    ones with the ragged end, any others; also in units of the last block that lie behind the end of a wavefront's share."""
+    tokens, block, block_k, d, heads = shape
+    print(f"[case] {shape}", flush=True)
+    plan = rf2.Plan(batch=1, heads=heads, head_dim=d, T=1, H=1, W=tokens, block=block, block_k=block_k, sparsity=0.3, window=(1, 1, 16))
+    i = plan.info
+    g = torch.Generator(device="cuda").manual_seed(23)
+    q, k, v = (torch.randn(1, heads, tokens, d, generator=g, device="cuda") for _ in range(3))
+    perm = torch.from_numpy(plan.rf2_plan_perm()[0]).cuda().long()
+    units = (tokens + 31) // 32
+    factor = torch.ones(heads, units, device="cuda")
+    for h in range(heads):
+        at = torch.randperm(units, generator=torch.Generator().manual_seed(h))[:3].sort()[0]
+        at = torch.arange(3) if h == heads - 1 and heads > 1 else torch.arange(units - 3, units) if h == 0 else at
+        factor[h, at] = torch.tensor([8.0, 20.0, 50.0], device="cuda")
+    k[0][:, perm] *= factor.repeat_interleave(32, 1)[:, :tokens, None]
+    q, k, v = (x.to(torch.bfloat16) for x in (q, k, v))
+    idx, cnt = hp.lists_to_device(cut_tests.lists(plan, 11), i.k_row, i.n_blocks, "cuda")
+    buf = plan.alloc("cuda", lse=True)
+    plan.rf2_permute(q, k, v, buf["qp"], buf["kp"], buf["vp"])
+    buf["op"].fill_(float("nan"))
+    plan.rf2_block_sparse_attn(buf["qp"], buf["kp"], buf["vp"], idx, cnt, buf["op"], buf["lse"])
+    inside = torch.arange(block_k)
+    for h in sorted({0, 1 % heads, heads // 2, heads - 1}):
+        Q, K, V = (x[0, h][perm].double() for x in (q, k, v))
+        for r in range(i.n_blocks):
+            rows = slice(r * block, min((r + 1) * block, tokens))
+            count = int(cnt[0, h, r])
+            cols = torch.arange(i.n_blocks_k) if count == i.n_blocks_k else idx[0, h, r, :count].long().cpu()
+            keys = (cols[:, None] * block_k + inside).flatten()
+            keys = keys[keys < tokens].cuda()
+            if len(keys) == 0:
+                assert not buf["op"][0, h, rows].any(), (h, r)
+                continue
+            S = Q[rows] @ K[keys].T.contiguous() / d ** 0.5
+            P = torch.softmax(S, 1)
+            want = P @ V[keys]
+            err = (buf["op"][0, h, rows].double() - want).abs()
+            # probabilities and outputs rounded to bf16 (2^-8 each, relative); logits of 300 in fp32: 2^-24 x 300 a rounding, sums of
+            # up to 128 products, the scale and the difference among them: 2e-3 of a probability
+            assert (err <= (2.0 ** -8 + 2e-3) * (P @ V[keys].abs()) + 2.0 ** -8 * want.abs() + 1e-4).all(), (h, r, err.max())
+            assert (buf["lse"][0, h, rows].double() - torch.logsumexp(S, 1)).abs().max() <= 2e-3, (h, r)
+    plan.close()
