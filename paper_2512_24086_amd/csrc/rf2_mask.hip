@@ -12,12 +12,17 @@
 // matrix cores at full rate, the search and the emission about as much of the vector and of the
 // scalar issue slots; a workgroup is a chain of load, multiply, search and store, so what counts is how
 // many of them a compute unit holds.  The Q operand is read from LDS and the K operand is
-// reloaded in place, which keeps a wavefront of up to 768 columns within 80 registers: six wavefronts per SIMD where LDS
-// holds three workgroups of eight (up to 688 columns, 752 at d = 64; two up to 1,120 and 1,184, one beyond).  A probe of the
+// reloaded in place, four chunks of 16 channels ahead, which keeps a wavefront of up to 768 columns within 72 registers: six
+// wavefronts per SIMD where LDS holds three workgroups of eight (up to 688 columns, 752 at d = 64; two up to 1,120 and 1,184, one
+// beyond).  K is loaded four lanes to 64 bytes of a row and turned into the operand's order, 16 rows to a quarter of the lanes, through
+// the place in LDS where the tile's keys go afterwards: loaded in that order, each lane's 16 bytes lie in a line of their own, and the address
+// unit of a compute unit was busy with 64 cycles an instruction, 46 us of the 720p layer (without the search and the lists 54 us).  720p
+// 69.0 -> 56.1 us, d = 64 46.5 -> 43.7, one head 17.2 -> 14.2, long video by count 103.6 -> 86.9, by mass 131.9 -> 117.2.  (Turned by
+// DPP moves within quads, 67 and 134.5 us; with eight chunks ahead, 57.0 and 118.2.)  A probe of the
 // search costs a compare and a population count per 64 keys; on bell-shaped rows, as smooth fields give, the
 // normal-distribution guess and interpolation need 4 or 5 of them where a bitwise search that stops at the first exact
 // count needs 15.5 (other rows: see MAX_GUIDED).  720p: 104 -> 70 us; cumulative mass on the long video (929 x 929, 24
-// heads): 291 -> 146 us; with few workgroups 12-50 -> 8-15 us.  No load of K, no read of a key and no store of a list entry
+// heads): 291 -> 146 us; with few workgroups 12-50 -> 8-15 us, all before K came so.  No load of K, no read of a key and no store of a list entry
 // stands behind a branch: buffers drop what lies outside of kbar or of the list.  (Behind branches the compiler waited for the
 // whole next K tile at the end of each, and every entry cost four scalar instructions: 720p 70.1 -> 69.4 us (68.7 to 69.8 in
 // three runs), long video, cumulative mass, 145.0 -> 134.8.)  Wavefronts that share a K tile (32, 48 or 64 rows per
@@ -29,7 +34,7 @@
 
 namespace {
 
-typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4), may_alias)) float f32x4;
 
 // Order-preserving map float -> uint32 (larger float <=> larger key); -0 is folded into +0.
 __device__ __forceinline__ uint32_t order_key(float x) {
@@ -169,18 +174,20 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 && EMAX <= 12 ? 6 : 4) predic
   const float* __restrict__ qb = qbar + (size_t)bh * Tq * D;
   // kbar of the head as a buffer: columns past the row read as zero and cost nothing, so no load stands behind a branch.
   const auto kbuf = __builtin_amdgcn_make_buffer_rsrc((void*)(kbar + (size_t)bh * Tb * D), 0, (unsigned)Tb * D * 4, 0x00020000);
+  // Lane l has 16 bytes of row l / 4 of the tile.
   auto k_load = [&](int ct, int kk) {
-    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(kbuf, ((ct * 16 + lr) * D + 4 * lk) * 4 + 64 * kk, 0, 0));
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(kbuf, ((ct * 16 + lane / 4) * D + 4 * (lane & 3)) * 4 + 64 * kk, 0, 0));
   };
 
   // ---- scores: 16 x 16 tiles with v_mfma_f32_16x16x4_f32 -------------------------------
-  // Lane (lr, lk) feeds row lr of each operand.  Per 16 channels it loads 4 consecutive
-  // floats at 16*kk + 4*lk; MFMA step e uses element e, so "k slot lk" stands for channel
+  // Lane (lr, lk) feeds row lr of each operand.  Per 16 channels it has 4 consecutive
+  // floats from 16*kk + 4*lk on; MFMA step e uses element e, so "k slot lk" stands for channel
   // 16*kk + 4*lk + e in both operands (a dot product does not care about summation order).
   const int n_ct = (Tb + 15) / 16;
-  f32x4 b[D / 16];
+  constexpr int NC = D / 16, NB = 4;              // chunks of 16 channels; those on their way
+  f32x4 b[NB];
 #pragma unroll
-  for (int kk = 0; kk < D / 16; ++kk) b[kk] = k_load(wave, kk);
+  for (int kk = 0; kk < NB; ++kk) b[kk] = k_load(wave, kk);
   for (int c = threadIdx.x; c < R * (D / 4); c += NW * 64) {
     const int row = c / (D / 4), ch = c % (D / 4) * 4;
     *reinterpret_cast<f32x4*>(&qs[row][ch]) = *reinterpret_cast<const f32x4*>(qb + (size_t)min(i0 + row, Tq - 1) * D + ch);
@@ -188,16 +195,26 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 && EMAX <= 12 ? 6 : 4) predic
   __syncthreads();
   float sum[4] = {}, sum2[4] = {};
   for (int ct = wave; ct < n_ct; ct += NW) {
-    // the registers of a chunk are reloaded for the wavefront's next column tile as soon as its products are issued
+    // the registers of a chunk are reloaded with the one NB chunks on, at last of the wavefront's next column tile, as soon as
+    // its products are issued (its copy in LDS is read before the next chunk's is written: LDS serves a wavefront in order)
+    uint32_t* const tile = &keys[ct * 16];
+    f32x4* const put = reinterpret_cast<f32x4*>(tile + lane / 4 * LD + 4 * (lane & 3));
+    const f32x4* const get = reinterpret_cast<const f32x4*>(tile + lr * LD + 4 * lk);
     f32x4 acc = {}, a = *reinterpret_cast<const f32x4*>(&qs[lr][4 * lk]);
+    *put = b[0];
+    f32x4 k = *get;
 #pragma unroll
-    for (int kk = 0; kk < D / 16; ++kk) {
-      const f32x4 a_now = a;
-      if (kk + 1 < D / 16) a = *reinterpret_cast<const f32x4*>(&qs[lr][16 * (kk + 1) + 4 * lk]);
+    for (int kk = 0; kk < NC; ++kk) {
+      const f32x4 a_now = a, k_now = k;
+      if (kk + 1 < NC) {
+        *put = b[(kk + 1) % NB];
+        k = *get;
+        a = *reinterpret_cast<const f32x4*>(&qs[lr][16 * (kk + 1) + 4 * lk]);
+      }
       __builtin_amdgcn_sched_barrier(0);      // (left alone, the read comes behind three of the products, into their registers)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a_now[e], b[kk][e], acc, 0, 0, 0);
-      b[kk] = k_load(ct + NW, kk);
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a_now[e], k_now[e], acc, 0, 0, 0);
+      b[kk % NB] = kk + NB < NC ? k_load(ct, kk + NB) : k_load(ct + NW, kk + NB - NC);
       __builtin_amdgcn_sched_barrier(0);      // (left alone, the loads of all chunks are gathered in twice the registers)
     }
     // acc[i] = S_hat[i0 + 4*lk + i][ct*16 + lr]
