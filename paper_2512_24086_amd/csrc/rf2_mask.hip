@@ -125,7 +125,7 @@ constexpr int TIGHTEN = 8;
 __device__ __forceinline__ uint32_t halfway(uint32_t lo, uint32_t top) { return lo + ((top - lo) >> 1) + 1u; }
 __device__ __forceinline__ uint32_t next_probe(float t, uint32_t lo, uint32_t top) {
   const uint32_t k = order_key(t);
-  return (k > lo && k <= top) ? k : halfway(lo, top);      // any float, NaN too, is safe here
+  return k - lo - 1u < top - lo ? k : halfway(lo, top);    // lo < k <= top; any float, NaN too, is safe here
 }
 // The smallest and the largest key of the bracket (which holds one) become its ends.
 template <int EMAX>
@@ -161,6 +161,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 && EMAX <= 12 ? 6 : 4) predic
   // Tb, sink_begin, sink_end describe the COLUMNS (K blocks) from here on; rows use Tq and row_sink_*.
   constexpr int R = 16;
   constexpr int MAX_GUIDED = CDF ? 10 : 8;
+  constexpr int FULL = EMAX <= 12 ? EMAX - 2 : EMAX == 32 ? 24 : EMAX - 4;    // a row has more than 64 FULL columns (choose_instance)
   extern __shared__ __attribute__((aligned(16))) uint32_t keys[];   // [R][LD]
   auto& [qs, stat] = *reinterpret_cast<BehindKeys<D, NW>*>(keys + R * LD);
   // Workgroups with equal blockIdx % 8 share an XCD and take a contiguous run of the strips, numbered head by head:
@@ -267,46 +268,51 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 && EMAX <= 12 ? 6 : 4) predic
     for (int e = 0; e < EMAX; ++e) {
       // (read in any case: without a branch; what lies behind the row is in the strip or in BehindKeys)
       key[e] = keys[r * LD + 64 * e + lane];
-      key[e] = 64 * e + lane < Tb ? key[e] : PAST_KEY;
+      if (e >= FULL) key[e] = 64 * e + lane < Tb ? key[e] : PAST_KEY;
     }
-    float sum_r = 0.f, sum2_r = 0.f;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) { sum_r += stat[w][r][0]; sum2_r += stat[w][r][1]; }
-    const float inv_n = 1.0f / (float)max(n_cand, 1), mean = uniform(sum_r * inv_n);
-    const float sigma = uniform(__builtin_amdgcn_sqrtf(fmaxf(sum2_r * inv_n - mean * mean, 0.f)));
+    // (16 lanes over the NW wavefronts' shares; with eight of them every share counts twice)
+    const float in_all = (NW == 8 ? 0.5f : 1.0f) / (float)max(n_cand, 1);
+    const float sum_r = row_sum(stat[lane % NW][r][0]), sum2_r = row_sum(stat[lane % NW][r][1]);
+    const float mean = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(sum_r * in_all), 15));
+    const float square = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(sum2_r * in_all), 15));
+    const float sigma = uniform(__builtin_amdgcn_sqrtf(fmaxf(square - mean * mean, 0.f)));
     // The threshold T: every key above it is taken, of the keys equal to it the need_eq lowest columns.
     uint32_t T, lo = PAST_KEY + 1u, top = SINK_KEY - 1u;      // bracket: the answer is in [lo, top]
     int need_eq = 0;
     int n_lo = Tb, n_top = Tb - n_cand;             // keys >= lo, keys > top
     if constexpr (!CDF) {
-      int stalled = 0;                              // probes in a row that left more than half of the bracket's keys
       // Largest T with |{key >= T}| >= k_row (sink columns count); a probe with exactly k_row keys at or above it ends
-      // the search early: any T between the k_row-th and the next key gives the same set.
-      bool exact = (n_lo == k_row);
-      float t = mean + guess.z * sigma;
-      if (n_top == k_row) { lo = SINK_KEY; exact = true; }    // only the sink columns
+      // the search early: any T between the k_row-th and the next key gives the same set.  (The scalar
+      // unit is as busy as the vector unit, 450 instructions a row, most of them what decides and not what counts: with the first
+      // probe on its own, the ends of the loop as one minimum and no flag, and the rows' sums added across lanes, 720p 56.2 ->
+      // 55.5 us, d = 64 43.7 -> 42.2, five heads 14.7 -> 14.2, long video 86.8 -> 84.9.)
+      if (n_top == k_row) lo = SINK_KEY, n_lo = k_row;        // only the sink columns
       const auto probe = [&](uint32_t cand) {
         int cnt = 0;
 #pragma unroll
         for (int e = 0; e < EMAX; ++e) cnt += popc64(__builtin_amdgcn_ballot_w64(key[e] >= cand));
         if (cnt >= k_row) { lo = cand; n_lo = cnt; } else { top = cand - 1u; n_top = cnt; }
-        exact = (cnt == k_row);
         return cnt;
       };
-      for (int p = 0; !exact && lo < top && p < MAX_GUIDED && stalled < 3; ++p) {
-        const int before = n_lo - n_top;
-        const int cnt = probe(next_probe(t, lo, top));
-        stalled = p > 0 && 2 * (n_lo - n_top) > before ? stalled + 1 : 0;
-        const float fl = key_value(lo), fh = key_value(top);
-        if (p == 0) t += (float)(cnt - k_row) * sigma * guess.slope;
-        else if (lo == PAST_KEY + 1u) t = fh - sigma * (0.25f * (float)(1 << min(p, 12)));      // no lower (upper) end yet
-        else if (top == SINK_KEY - 1u) t = fl + sigma * (0.25f * (float)(1 << min(p, 12)));
-        else t = fl + (fh - fl) * ((stalled & 1) ? 0.5f : (float)(n_lo - k_row) * __builtin_amdgcn_rcpf((float)(n_lo - n_top)));
+      if (n_lo != k_row && lo < top) {
+        float t = mean + guess.z * sigma;
+        t += (float)(probe(next_probe(t, lo, top)) - k_row) * sigma * guess.slope;
+        int stalled = 0;                            // probes in a row that left more than half of the bracket's keys
+        for (int p = 1; min(n_lo - k_row, min(MAX_GUIDED - p, 3 - stalled)) > 0 && lo < top; ++p) {
+          const int before = n_lo - n_top;
+          probe(next_probe(t, lo, top));
+          stalled = 2 * (n_lo - n_top) > before ? stalled + 1 : 0;
+          const float fl = key_value(lo), fh = key_value(top);
+          if (lo == PAST_KEY + 1u) t = fh - sigma * (0.25f * (float)(1 << p));      // no lower (upper) end yet
+          else if (top == SINK_KEY - 1u) t = fl + sigma * (0.25f * (float)(1 << p));
+          else t = fl + (fh - fl) * ((stalled & 1) ? 0.5f : (float)(n_lo - k_row) * __builtin_amdgcn_rcpf((float)(n_lo - n_top)));
+        }
       }
-      for (int p = 0; !exact && lo < top; ++p) {
+      for (int p = 0; n_lo != k_row && lo < top; ++p) {
         if (p % TIGHTEN == 0) draw_in(key, lo, top);
         if (lo < top) probe(halfway(lo, top));
       }
+      const bool exact = n_lo == k_row;
       T = exact ? lo - 1u : lo;
       need_eq = exact ? 0 : k_row - n_top;          // lo == top: the keys equal to lo share the places left
     } else {
