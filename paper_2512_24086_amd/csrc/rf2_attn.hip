@@ -122,8 +122,8 @@ __device__ __forceinline__ bool row_of(const RowOrder& w, int xcd, int slot, int
   return qi >= 0;
 }
 
-// Parameters of both kernels, what a row needs first in front: the first 14 words arrive in registers (see the flags of the
-// build), the others are read from memory.  shares to sink_slots: RowOrder.  split: log2 of the workgroups that share a Q block; they are neighbours on one XCD.  Tb: K/V blocks
+// Parameters of both kernels, what a row needs first in front: the first 14 words arrive in registers (a compiler flag in
+// build.py), the others are read from memory.  shares to sink_slots: RowOrder.  split: log2 of the workgroups that share a Q block; they are neighbours on one XCD.  Tb: K/V blocks
 // per head (columns of the block mask); last_valid: tokens in the last one; perm: token of a permuted row; fused: output in the
 // caller's token order.
 #define RF2_STREAM_PARAMS \
