@@ -81,11 +81,6 @@ template <int CPR>
 __device__ __forceinline__ int row_slot(int row, int chunk) {
   return row * CPR + (chunk ^ (row / (16 / CPR) % CPR));
 }
-// LDS accesses of a wavefront before and behind stay so (they are carried out in order, so nothing is waited for).
-__device__ __forceinline__ void wave_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
 
 // Head and Q block of a workgroup, from its XCD and its number there.  False: no work.
 // Workgroups with equal blockIdx % 8 share an XCD (which of the eight it is varies from launch to launch).  Slots of an XCD, in

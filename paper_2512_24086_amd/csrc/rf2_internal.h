@@ -55,5 +55,12 @@ inline int rf2_check_device(const rf2_plan* plan) {
   return current == plan->device ? RF2_OK : RF2_ERR_INVALID_ARG;
 }
 
+// LDS accesses of a wavefront before and behind stay so: what its lanes hand each other through LDS is written before it is read
+// (they are carried out in order, so nothing is waited for; only the compiler is held).
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Launch check used after every kernel launch.
 #define RF2_LAUNCH_CHECK() RF2_HIP(hipGetLastError())

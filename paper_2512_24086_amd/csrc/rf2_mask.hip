@@ -197,19 +197,23 @@ __global__ void __launch_bounds__(NW * 64, NW == 8 && EMAX <= 12 ? 6 : 4) predic
   float sum[4] = {}, sum2[4] = {};
   for (int ct = wave; ct < n_ct; ct += NW) {
     // the registers of a chunk are reloaded with the one NB chunks on, at last of the wavefront's next column tile, as soon as
-    // its products are issued (its copy in LDS is read before the next chunk's is written: LDS serves a wavefront in order)
+    // its products are issued (its copy in LDS is read by other lanes than wrote it, and before the next chunk's is written: the fences)
     uint32_t* const tile = &keys[ct * 16];
     f32x4* const put = reinterpret_cast<f32x4*>(tile + lane / 4 * LD + 4 * (lane & 3));
     const f32x4* const get = reinterpret_cast<const f32x4*>(tile + lr * LD + 4 * lk);
     f32x4 acc = {}, a = *reinterpret_cast<const f32x4*>(&qs[lr][4 * lk]);
     *put = b[0];
+    wave_fence();
     f32x4 k = *get;
+    wave_fence();
 #pragma unroll
     for (int kk = 0; kk < NC; ++kk) {
       const f32x4 a_now = a, k_now = k;
       if (kk + 1 < NC) {
         *put = b[(kk + 1) % NB];
+        wave_fence();
         k = *get;
+        wave_fence();
         a = *reinterpret_cast<const f32x4*>(&qs[lr][16 * (kk + 1) + 4 * lk]);
       }
       __builtin_amdgcn_sched_barrier(0);      // (left alone, the read comes behind three of the products, into their registers)

@@ -16,3 +16,22 @@ def test_no_instance_uses_scratch_memory(source, tmp_path):
     found = re.findall(r"Function Name: (\S+).*?ScratchSize \[bytes/lane\]: (\d+).*?VGPRs Spill: (\d+)", out.stderr, re.S)
     assert len(found) >= 10
     assert not [f for f in found if f[1:] != ("0", "0")]
+
+
+def test_lanes_of_the_mask_kernel_exchange_keys_in_order(tmp_path):
+    """Lanes turn a tile of K through LDS: whatever one writes 16 bytes at a time another may read next, so a barrier of the
+    wavefront or the workgroup stands between every such write and the next such read of the compiled code, in each instance, and
+    behind the read of a tile's chunk, whose place the next chunk takes."""
+    out = tmp_path / "mask.s"
+    subprocess.run([b.hipcc(), *b.FLAGS, "--cuda-device-only", "-S", os.path.join(b.CSRC, "rf2_mask.hip"), "-o", str(out)], check=True,
+                   capture_output=True)
+    kernels = re.findall(r"^(\S*predict_mask_kernelILi(\d+)\S*):(.*?)^\.Lfunc_end", out.read_text(), re.S | re.M)
+    assert len(kernels) == 80
+    for name, d, body in kernels:
+        events = re.findall(r"\b(ds_write_b128|ds_read_b128|s_barrier|wave barrier)\b", body)
+        writes = [i for i, e in enumerate(events) if e == "ds_write_b128"]
+        assert len(writes) >= int(d) // 16, name
+        for i in writes:
+            rest = [e for e in events[i + 1:] if e != "ds_write_b128"]
+            assert rest[0] != "ds_read_b128", name
+        assert events.count("wave barrier") == 2 * (int(d) // 16), name
