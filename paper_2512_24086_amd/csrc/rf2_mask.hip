@@ -151,9 +151,14 @@ struct BehindKeys {
   float stat[NW][16][2];                            // sum and sum of squares over a wavefront's columns
 };
 
-// NW wavefronts per workgroup of R = 16 rows.  (Second launch bound: beyond 768 columns LDS holds two workgroups at most.)
+// NW wavefronts per workgroup of R = 16 rows.  Second launch bound, wavefronts per SIMD: up to 768 columns LDS holds three workgroups
+// of eight (six), beyond two.  At d = 64 it holds four where rows have up to 512 columns; for that many a wavefront may have 64 vector
+// registers and, as the trap handler has 16 of its own, 80 scalar ones (eight).  Left alone the kernel takes 67 and up to 93: three
+// workgroups.  (By count, us, three -> four: 200 columns x 1,014 strips 19.5 -> 18.1, 304 x 1,007 23.6 -> 21.8, 512 x 1,024 30.9 -> 28.2;
+// where three are enough 304 x 760 18.2 -> 18.3, 300 x 266 13.4 -> 13.5.  By mass four cost up to 1 % where three are
+// enough, 304 x 760 29.5 -> 29.8: left at three.)
 template <int D, int EMAX, bool CDF, int NW>
-__global__ void __launch_bounds__(NW * 64, NW == 8 && EMAX <= 12 ? 6 : 4) predict_mask_kernel(
+__global__ void __launch_bounds__(NW * 64, NW == 8 ? (D == 64 && EMAX <= 8 && !CDF ? 8 : EMAX <= 12 ? 6 : 4) : 4) predict_mask_kernel(
     const float* __restrict__ qbar, const float* __restrict__ kbar, int32_t* __restrict__ blk_idx,
     int32_t* __restrict__ blk_cnt, uint8_t* __restrict__ mask_dense, float* __restrict__ scores,
     int Tq, int Tb, int LD, int row_sink_begin, int row_sink_end, int sink_begin, int sink_end, int k_row,

@@ -18,6 +18,16 @@ def test_no_instance_uses_scratch_memory(source, tmp_path):
     assert not [f for f in found if f[1:] != ("0", "0")]
 
 
+def test_four_workgroups_of_the_mask_kernel(tmp_path):
+    """At d = 64 LDS holds four workgroups of eight wavefronts for rows of up to 512 columns, which is eight wavefronts per SIMD:
+    1/8 of its 512 vector registers each, and of its 800 scalar ones in steps of 16, less 16 for the trap handler."""
+    out = subprocess.run([b.hipcc(), *b.FLAGS, "--cuda-device-only", "-Rpass-analysis=kernel-resource-usage", "-c",
+                          os.path.join(b.CSRC, "rf2_mask.hip"), "-o", str(tmp_path / "device.o")], check=True, capture_output=True, text=True)
+    found = re.findall(r"Function Name: \S+predict_mask_kernelILi64ELi([2468])ELb0ELi8E.*?TotalSGPRs: (\d+).*?VGPRs: (\d+)", out.stderr, re.S)
+    assert len(found) == 4
+    assert all(int(s) <= 80 and int(v) <= 64 for _, s, v in found), found
+
+
 def test_lanes_of_the_mask_kernel_exchange_keys_in_order(tmp_path):
     """Lanes turn a tile of K through LDS: whatever one writes 16 bytes at a time another may read next, so a barrier of the
     wavefront or the workgroup stands between every such write and the next such read of the compiled code, in each instance, and
