@@ -120,15 +120,15 @@ __device__ __forceinline__ bool row_of(const RowOrder& w, int xcd, int slot, int
 // Parameters of both kernels, what a row needs first in front: the first 14 words arrive in registers (a compiler flag in
 // build.py), the others are read from memory.  shares to sink_slots: RowOrder.  split: log2 of the workgroups that share a Q block; they are neighbours on one XCD.  Tb: K/V blocks
 // per head (columns of the block mask); last_valid: tokens in the last one; perm: token of a permuted row; fused: output in the
-// caller's token order.
+// caller's token order; meets: wavefronts of four shares meet (see rf2_cut_stream).
 #define RF2_STREAM_PARAMS \
   const int32_t *__restrict__ shares, int per_xcd, int n_bh, int rows, int sink_begin, int n_sink, int sink_slots, int split, int k_row, \
       const int32_t *__restrict__ blk_idx, const int32_t *__restrict__ blk_cnt, const __bf16 *__restrict__ qp, \
       const __bf16 *__restrict__ kp, const __bf16 *__restrict__ vp, const int32_t *__restrict__ perm, __bf16 *__restrict__ op, \
-      float *__restrict__ lse, int Tb, int last_valid, float scale_log2, int n_tokens, int heads, bool fused, rf2_strides st
+      float *__restrict__ lse, int Tb, int last_valid, float scale_log2, int n_tokens, int heads, bool fused, bool meets, rf2_strides st
 #define RF2_STREAM_ARGS(split) \
   shares, per_xcd, n_bh, rows, sink_begin, n_sink, sink_slots, split, k_row, blk_idx, blk_cnt, qp, kp, vp, perm, op, lse, Tb, last_valid, \
-      scale_log2, n_tokens, heads, fused, st
+      scale_log2, n_tokens, heads, fused, meets, st
 
 // One workgroup: number `share` of those of a Q block, number `slot` of the XCD's rows.
 template <int D, int BK, int QH, int KS>
@@ -341,10 +341,14 @@ __device__ __forceinline__ void attend(RF2_STREAM_PARAMS, int xcd, int slot, int
   // Two wavefronts that ask for the same tiles meet every 16 parts: left alone they drift apart, out of reach of each other's
   // tiles in L1 (d = 128, 720p, 24 heads, 11.25 -> 10.99 ms, 480p 3.59 -> 3.56; every part or every 4th: no more, and dearer on
   // short lists; d = 64, KS = 2, 480p 2.122 -> 2.109 ms.  Four wavefronts of a 256-row Q block lose 2 %).
-  constexpr int MEET = QH == 2 && (D == 64 || KS == 1) ? 16 : 0;
+  // Four shares of a long list: at every part, for its tiles in L2 (rf2_cut_stream says where).
+  constexpr int MEET = QH == 2 && (D == 64 || KS == 1) ? 16 : D == 128 && KS == 4 ? 1 : 0;
+  const bool meeting = MEET == 16 || (MEET > 0 && meets);
   auto meet = [&](int part = 0) {
-    if (MEET > 0 && part % std::max(MEET, 1) == 0) __builtin_amdgcn_s_barrier();
+    if (meeting && part % std::max(MEET, 1) == 0) __builtin_amdgcn_s_barrier();
   };
+  // Every wavefront of a list meets as often as the one with the most parts: also one that has a part less, or none.
+  const int most = (NPARTS + KS - 1) / KS;
   // The order of the loads in front of the loops is that of the loops: the compiler's wait counts are the smaller of the two.
 
   if constexpr (D == 128) {
@@ -412,6 +416,7 @@ __device__ __forceinline__ void attend(RF2_STREAM_PARAMS, int xcd, int slot, int
         if (s + 1 >= partial_begin) mask_tile(Snext[0], s + 1), mask_tile(Snext[1], s + 1);
       }
     };
+    if (KS > 1 && U == 0 && most > 0) meet(0);
     if (U > 0) {
       uint32_t off0 = first_off(0), off1 = first_off(1);   // parts P, P + 1
       bf16x8 k0[NQ];
@@ -447,7 +452,7 @@ __device__ __forceinline__ void attend(RF2_STREAM_PARAMS, int xcd, int slot, int
       int entry = ahead[2];
       for (int s = 0; s < U;) {
         meet();
-        const int end = MEET > 0 ? min(U, s + 2 * MEET) : U;
+        const int end = meeting ? min(U, s + 2 * MEET) : U;
         do {
           const int P = s >> 1;
           uint32_t off2 = 0;
@@ -467,6 +472,7 @@ __device__ __forceinline__ void attend(RF2_STREAM_PARAMS, int xcd, int slot, int
           s += 2;
         } while (s < end);
       }
+      if (KS > 1 && parts < most) meet(parts);
       // last product: O += V P_{U-1}
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
@@ -535,7 +541,6 @@ __device__ __forceinline__ void attend(RF2_STREAM_PARAMS, int xcd, int slot, int
         if (s + 1 >= partial_begin) mask_tile(S[T], s + 1);
       }
     };
-    const int most = (NPARTS + KS - 1) / KS;        // of the wavefronts that share the list
     if (KS > 1 && U == 0 && most > 0) meet(0);
     if (U > 0) {
       const uint32_t off0 = first_off(0);
@@ -563,7 +568,7 @@ __device__ __forceinline__ void attend(RF2_STREAM_PARAMS, int xcd, int slot, int
       const auto nothing = [](int) {};
       for (int s = 0; s < U;) {
         meet();
-        const int end = MEET > 0 ? min(U, s + 2 * MEET) : U;
+        const int end = meeting ? min(U, s + 2 * MEET) : U;
         do {
           const int p = s >> 1;
           uint32_t off2 = 0;
@@ -759,8 +764,8 @@ int launch_stream(const rf2_plan* plan, const AttnArgs& a, hipStream_t st) {
     kernel<<<dim3(grid), dim3(64 * QH * KS), 0, st>>>(
         order.shares, order.per_xcd, order.n_bh, order.rows, order.sink_begin, order.n_sink, order.sink_slots, split, in.k_row, a.blk_idx,
         a.blk_cnt, (const __bf16*)a.qp, (const __bf16*)a.kp, (const __bf16*)a.vp, plan->d_perm, (__bf16*)a.out, a.lse, in.n_blocks_k,
-        in.last_block_valid_k, (float)(1.4426950408889634 / sqrt((double)D)), (int)in.N, plan->cfg.heads, a.scatter, rf2_qkv_strides(plan),
-        more...);
+        in.last_block_valid_k, (float)(1.4426950408889634 / sqrt((double)D)), (int)in.N, plan->cfg.heads, a.scatter, plan->cut.meets,
+        rf2_qkv_strides(plan), more...);
   };
   if constexpr (D == 128 && QH == 2 && KS == 1) {
     const unsigned lead = plan->cut.halved_sinks ? (unsigned)order.sink_slots : 0u;

@@ -17,6 +17,7 @@ struct rf2_attn_cut {
   bool whole_heads; // ordinary rows are numbered head by head and dealt to the XCDs in 8 runs (else every head in 8 shares)
   int whole_slots = 0;  // > 0: row slots of an XCD that are cut so; those behind them get 64-row workgroups of two shares,
   bool halved_sinks = false;      // and so do its sink rows (not then counted as cut so)
+  bool meets = false;             // the wavefronts of four shares meet at every part
 };
 
 // ---- the cut of stream_attn_kernel -----------------------------------------------------------------------------------
@@ -165,6 +166,18 @@ inline rf2_attn_cut rf2_cut_stream(const rf2_config& c, const rf2_info& in) {
       }
     }
   }
+  // Four wavefronts that share a list drift apart on long ones, and the workgroups of an XCD then have a wider stretch of K and V in
+  // use than its L2 holds.  Meeting at every part keeps them together (requests that miss L2, 118,800 tokens x 3 heads: 660 -> 236 of 1,329
+  // million, 73,750 x 5: 226 -> 93 of 599).  Taken where the drift costs more than the meetings: 64-row blocks
+  // (no two workgroups with one list), lists of one length, of 256 parts and more, and fewer heads than XCDs, whose K and V are of 28 MB a
+  // head, near the 32 MB of all L2s, 44 MB with six and seven heads, and of 40 MB together.
+  // (us, without -> with, tokens x heads, sparsity: 118,800 x 3, 0.5, 12,480 -> 9,343; 119,280 x 3, 0.55, 12,699 -> 8,415; 100,800 x 2, 0.5,
+  // 128-row K/V blocks, 5,236 -> 4,310; 118,800 x 2, the same, 9,219 -> 8,766; 73,750 x 5, 0.65, 4,898 -> 4,150; 93,492 x 6, 0.5, 15,712 ->
+  // 12,170; 62,092 x 3, 0.59, 2,420 -> 2,188; 91,584 x 1, 0.64, 1,915 -> 1,764.  Beyond these lines: 128-row Q blocks,
+  // 118,800 x 1, 0.5, 2,894 -> 2,957; by mass, 57,792 x 3, 3,776 -> 3,894; lists of 138 parts, 63,000 x 3, 735 -> 748; 118,800 x 8, 0.8,
+  // 11,236 -> 11,465; 44,928 x 1, 0.43, 485 -> 497; 64,428 x 1, 0.62, 709 -> 726; 85,690 x 7, 0.68, 7,362 -> 7,530.)
+  best.meets = c.head_dim == 128 && best.rows == 64 && best.groups == 4 && c.block == 64 && lists < 8 && in.k_row < in.n_blocks_k &&
+               in.k_row * parts >= 256 && in.N_pad_k * 512 >= (int64_t)(lists <= 5 ? 28 : 44) << 20 && in.N_pad_k * 512 * lists >= (int64_t)40 << 20;
   best.whole_heads = c.block == 64 || in.N_pad_k * c.head_dim * 4 <= (int64_t)24 << 20;
   return best;
 }

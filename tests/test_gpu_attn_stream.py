@@ -263,3 +263,76 @@ def test_reference_moves_in_any_unit(shape):
             assert (err <= (2.0 ** -8 + 2e-3) * (P @ V[keys].abs()) + 2.0 ** -8 * want.abs() + 1e-4).all(), (h, r, err.max())
             assert (buf["lse"][0, h, rows].double() - torch.logsumexp(S, 1)).abs().max() <= 2e-3, (h, r)
     plan.close()
+
+
+def test_where_shares_meet(tmp_path):
+    """Four shares of a list meet in launches of long lists over a long sequence, and only there."""
+    (tmp_path / "cut.cpp").write_text("""#include "rf2_attn_cut.h"
+extern "C" int meets(const rf2_config* c, const rf2_info* i) { return rf2_cut_stream(*c, *i).meets; }
+""")
+    lib = str(tmp_path / "cut.so")
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-O1", "-shared", "-fPIC", "-I", os.path.join(b.ROOT, "include"),
+                    "-I", b.CSRC, str(tmp_path / "cut.cpp"), "-o", lib], check=True)
+    fn = C.CDLL(lib).meets
+
+    def meets(**kw):
+        plan = rf2.Plan(**dict(dict(batch=1, heads=2, head_dim=128, T=1, H=1, W=57344, block=64, sparsity=0.5, window=(1, 1, 16)), **kw))
+        found = fn(C.byref(plan.cfg), C.byref(plan.info)), plan.info.k_row
+        plan.close()
+        return found
+
+    assert meets() == (1, 448) and meets(block_k=128) == (1, 224) and meets(batch=2, heads=1) == (1, 448)           # 28 MB of a head's K and V, 40 of all
+    assert meets(W=57280) == (0, 447)
+    assert meets(sparsity=0.7142) == (1, 256) and meets(sparsity=0.715) == (0, 255)      # 256 parts
+    assert meets(block_k=128, sparsity=0.7142) == (1, 128) and meets(block_k=128, sparsity=0.715) == (0, 127)
+    assert meets(heads=1, W=81920)[0] == 1 and meets(heads=1, W=81856)[0] == 0
+    assert meets(heads=5)[0] == 1 and meets(heads=6)[0] == 0 and meets(batch=3, heads=2)[0] == 0
+    assert meets(heads=6, W=90112)[0] == 1 and meets(heads=7, W=90048)[0] == 0 and meets(heads=8, W=118784)[0] == 0     # 44 MB each
+    assert meets(cdf_threshold=0.7)[0] == 0 and meets(head_dim=64, W=118784)[0] == 0
+    assert meets(block=128)[0] == 0 and meets(block=256, block_k=128)[0] == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [(236, 243, 64, 2), (236, 243, 128, 3), (280, 205, 128, 2)], ids=lambda s: "x".join(map(str, s)))
+def test_shares_that_meet(shape):
+    """Lists of none, one to three, k_row and all blocks, with a last block of 4 keys (whose second part no wavefront has, of 128-key blocks) or 56:
+    wavefronts with no part, with a part less than others and with many, as softmax attention over the kept blocks, by both exits."""
+    rows_of_grid, columns, block_k, heads = shape
+    print(f"[case] {shape}", flush=True)
+    tokens, d = rows_of_grid * columns, 128
+    plan = rf2.Plan(batch=1, heads=heads, head_dim=d, T=1, H=rows_of_grid, W=columns, block=64, block_k=block_k, sparsity=0.6, window=(1, 8, 8))
+    i = plan.info
+    assert i.k_row * block_k >= 256 * 64 and i.N_pad_k * 512 >= 28 << 20       # (as test_where_shares_meet has it)
+    g = torch.Generator(device="cuda").manual_seed(29)
+    q, k, v = (torch.randn(1, heads, tokens, d, generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    idx, cnt = hp.lists_to_device(cut_tests.lists(plan, 13), i.k_row, i.n_blocks, "cuda")
+    buf = plan.alloc("cuda", lse=True)
+    plan.rf2_permute(q, k, v, buf["qp"], buf["kp"], buf["vp"])
+    buf["op"].fill_(float("nan"))
+    plan.rf2_block_sparse_attn(buf["qp"], buf["kp"], buf["vp"], idx, cnt, buf["op"], buf["lse"])
+    o, lse = torch.full_like(buf["o"], float("nan")), torch.full((1, heads, tokens), float("nan"), device="cuda")
+    plan.rf2_block_sparse_attn_unpermuted(buf["qp"], buf["kp"], buf["vp"], idx, cnt, o, lse)
+    perm = torch.from_numpy(plan.rf2_plan_perm()[0]).cuda().long()
+    assert (perm != torch.arange(tokens, device="cuda")).any()
+    assert torch.equal(o[:, :, perm].view(torch.int16), buf["op"][:, :, :tokens].view(torch.int16))
+    assert torch.equal(lse[:, :, perm], buf["lse"][:, :, :tokens])
+    inside = torch.arange(block_k)
+    for h in range(heads):
+        Q, K, V = (x[0, h][perm].double() for x in (q, k, v))
+        for r in (*range(0, i.n_blocks, 13), *range(i.n_blocks - 6, i.n_blocks)):
+            rows = slice(r * 64, min((r + 1) * 64, tokens))
+            count = int(cnt[0, h, r])
+            cols = torch.arange(i.n_blocks_k) if count == i.n_blocks_k else idx[0, h, r, :count].long().cpu()
+            keys = (cols[:, None] * block_k + inside).flatten()
+            keys = keys[keys < tokens].cuda()
+            if len(keys) == 0:
+                assert not buf["op"][0, h, rows].any() and torch.isneginf(buf["lse"][0, h, rows]).all(), (h, r)
+                continue
+            S = Q[rows] @ K[keys].T.contiguous() / d ** 0.5
+            P = torch.softmax(S, 1)
+            want = P @ V[keys]
+            err = (buf["op"][0, h, rows].double() - want).abs()
+            # probabilities and outputs rounded to bf16 (2^-8 each, relative); logits below 10 in fp32
+            assert (err <= 2.0 ** -8 * (P @ V[keys].abs() + want.abs()) + 1e-4).all(), (h, r, err.max())
+            assert (buf["lse"][0, h, rows].double() - torch.logsumexp(S, 1)).abs().max() <= 1e-4, (h, r)
+    plan.close()
