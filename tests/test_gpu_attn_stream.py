@@ -186,32 +186,83 @@ def test_halves_of_rows_dealt_by_the_work_table(case):
     plan.close()
 
 
-@pytest.mark.gpu
-@pytest.mark.parametrize("shape", [(330, 64, 64, 128, 200), (2450, 128, 64, 128, 12), (657, 64, 64, 128, 1), (4001, 128, 128, 128, 41),
-                                   (2450, 128, 64, 128, 27), (999, 64, 64, 64, 100), (1500, 64, 64, 64, 23), (657, 64, 64, 64, 17),
-                                   (2450, 64, 64, 64, 1)], ids=lambda s: "x".join(map(str, s)))
-def test_rows_land_where_they_belong(shape):
-    """Output rows leave a wavefront whole, 16 bytes a lane: token-major, behind an address that is a multiple of 8 bytes only, with a
-    ragged last block, they are those of the plain exit, and nothing beside them is written."""
-    tokens, block, block_k, d, heads = shape
-    print(f"[case] {shape}", flush=True)
-    plan = rf2.Plan(batch=1, heads=heads, head_dim=d, T=1, H=1, W=tokens, block=block, block_k=block_k, sparsity=0.3, window=(1, 1, 24),
+# (rows and columns of the grid, block, block_k, head_dim, heads) -> (rows of a workgroup, wavefronts that share a list)
+GRIDS = {(15, 22, 64, 64, 128, 200): (64, 1), (49, 50, 128, 64, 128, 12): (64, 2), (9, 73, 64, 64, 128, 1): (64, 4),
+         (58, 69, 128, 128, 128, 41): (128, 1), (71, 87, 128, 64, 128, 5): (128, 2), (49, 50, 128, 64, 128, 27): (128, 1),
+         (270, 280, 256, 128, 128, 40): (256, 1), (27, 37, 64, 64, 64, 100): (64, 1), (30, 50, 64, 64, 64, 23): (64, 2),
+         (9, 73, 64, 64, 64, 17): (64, 4), (49, 50, 64, 64, 64, 1): (64, 8), (49, 50, 128, 128, 64, 24): (128, 2)}
+
+
+def grid_plan(shape):
+    h, w, block, block_k, d, heads = shape
+    return rf2.Plan(batch=1, heads=heads, head_dim=d, T=1, H=h, W=w, block=block, block_k=block_k, sparsity=0.3, window=(1, 8, 8),
                     qkv_layout=rf2.RF2_LAYOUT_BNHD)
+
+
+def test_cuts_of_the_grids(tmp_path):
+    (tmp_path / "cut.cpp").write_text(SOURCE)
+    lib = str(tmp_path / "cut.so")
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-O1", "-shared", "-fPIC", "-I", os.path.join(b.ROOT, "include"),
+                    "-I", b.CSRC, str(tmp_path / "cut.cpp"), "-o", lib], check=True)
+    fn, out = C.CDLL(lib).cut, (C.c_int * 5)()
+    for shape, want in GRIDS.items():
+        plan = grid_plan(shape)
+        fn(C.byref(plan.cfg), C.byref(plan.info), out)
+        assert tuple(out)[:2] == want and (out[3] > 0) == (shape[:2] == (49, 50) and shape[5] == 27), shape
+        assert plan.info.N % shape[2], shape                          # a ragged last block
+        assert plan.rf2_plan_perm()[0].tolist() != list(range(plan.info.N)), shape
+        plan.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", GRIDS, ids=lambda s: "x".join(map(str, s)))
+def test_rows_land_where_they_belong(shape):
+    """Output rows leave a wavefront whole, 16 bytes a lane: of a permuted grid, token-major, behind an address that is a multiple of 8
+    bytes only, with a ragged last block, they are those of the plain exit in the tokens' own places, so are the log-sum-exps, nothing
+    beside them is written, and they are softmax attention over the kept blocks."""
+    block, block_k, d, heads = shape[2:]
+    print(f"[case] {shape}", flush=True)
+    plan = grid_plan(shape)
     i = plan.info
+    tokens = i.N
     g = torch.Generator(device="cuda").manual_seed(19)
     q, k, v = (torch.randn(1, tokens, heads, d, generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
     idx, cnt = hp.lists_to_device(cut_tests.lists(plan, 7), i.k_row, i.n_blocks, "cuda")
-    buf = plan.alloc("cuda")
+    buf = plan.alloc("cuda", lse=True)
     plan.rf2_permute(q, k, v, buf["qp"], buf["kp"], buf["vp"])
-    plan.rf2_block_sparse_attn(buf["qp"], buf["kp"], buf["vp"], idx, cnt, buf["op"])
+    plan.rf2_block_sparse_attn(buf["qp"], buf["kp"], buf["vp"], idx, cnt, buf["op"], buf["lse"])
     n = tokens * heads * d
     around = torch.full((n + 512,), 7.5, dtype=torch.bfloat16, device="cuda")
     o = around[260:260 + n].view(1, tokens, heads, d)
     assert o.data_ptr() % 16 == 8
-    plan.rf2_block_sparse_attn_unpermuted(buf["qp"], buf["kp"], buf["vp"], idx, cnt, o)
+    lse_around = torch.full((heads * tokens + 128,), 7.5, device="cuda")
+    lse = lse_around[64:64 + heads * tokens].view(1, heads, tokens)
+    plan.rf2_block_sparse_attn_unpermuted(buf["qp"], buf["kp"], buf["vp"], idx, cnt, o, lse)
     perm = torch.from_numpy(plan.rf2_plan_perm()[0]).cuda().long()
+    assert (perm != torch.arange(tokens, device="cuda")).any()
     assert torch.equal(o[:, perm].transpose(1, 2).view(torch.int16), buf["op"][:, :, :tokens].view(torch.int16))
+    assert torch.equal(lse[:, :, perm], buf["lse"][:, :, :tokens])
     assert (around[:260] == 7.5).all() and (around[260 + n:] == 7.5).all()
+    assert (lse_around[:64] == 7.5).all() and (lse_around[64 + heads * tokens:] == 7.5).all()
+    inside = torch.arange(block_k)
+    for h in sorted({0, heads - 1}):
+        Q, K, V = (x[0, :, h][perm].double() for x in (q, k, v))
+        for r in sorted({*range(0, i.n_blocks, max(1, i.n_blocks // 60 | 1)), i.n_blocks - 1}):
+            rows = slice(r * block, min((r + 1) * block, tokens))
+            count = int(cnt[0, h, r])
+            cols = torch.arange(i.n_blocks_k) if count == i.n_blocks_k else idx[0, h, r, :count].long().cpu()
+            keys = (cols[:, None] * block_k + inside).flatten()
+            keys = keys[keys < tokens].cuda()
+            got, got_lse = o[0, perm[rows], h].double(), lse[0, h, perm[rows]].double()
+            if len(keys) == 0:
+                assert not got.any() and torch.isneginf(got_lse).all(), (h, r)
+                continue
+            S = Q[rows] @ K[keys].T.contiguous() / d ** 0.5
+            P = torch.softmax(S, 1)
+            want = P @ V[keys]
+            # probabilities and outputs rounded to bf16 (2^-8 each, relative); logits below 10 in fp32
+            assert ((got - want).abs() <= 2.0 ** -8 * (P @ V[keys].abs() + want.abs()) + 1e-4).all(), (h, r)
+            assert (got_lse - torch.logsumexp(S, 1)).abs().max() <= 1e-4, (h, r)
     plan.close()
 
 
