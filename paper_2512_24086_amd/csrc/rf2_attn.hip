@@ -14,12 +14,12 @@
 // per lane (one query column) plus one exchange with lane l^32.
 //
 // Operands come straight from memory into registers, 1.5 to 2 steps ahead of their use: a part (64 keys) of the layout that
-// rf2_permute writes is read in 1 KiB pieces, each of which is one A operand and feeds two MFMAs.  There is no LDS and
-// no barrier between the wavefronts in the loop.  Against rings in LDS with wavefronts of 32 rows, 4 to a workgroup, an operand
+// rf2_permute writes is read in 1 KiB pieces, each of which is one A operand and feeds two MFMAs.  There is no LDS in the
+// loop, and no barrier except where wavefronts that share tiles or a list meet now and then (MEET).  Against rings in LDS with wavefronts of 32 rows, 4 to a workgroup, an operand
 // is moved half as often and nothing passes through LDS, which the power limit turns into clock.  d = 128 (one wavefront per
-// SIMD, 442 to 444 of its 512 registers, matrix cores 76 % busy on 720p where the rings kept two wavefronts 69 % busy): 720p, 40
+// SIMD, 442 to 446 of its 512 registers, matrix cores 76 % busy on 720p where the rings kept two wavefronts 69 % busy): 720p, 40
 // heads, 20.7 -> 19.1 ms on one card (18.0 to 20.1 from card to card, 1,292 to 1,158 TFLOP/s), 480p 4.00 -> 3.54 ms; with 64-row Q blocks, where the rings left one wavefront of 32
-// rows per SIMD, 480p 5.13 -> 3.98 ms and 720p, 20 heads, 13.3 -> 10.8 ms.  d = 64 (two wavefronts per SIMD, 246 to 256 registers of 256 each) is
+// rows per SIMD, 480p 5.13 -> 3.98 ms and 720p, 20 heads, 13.3 -> 10.8 ms.  d = 64 (two wavefronts per SIMD, 242 to 249 registers of 256 each) is
 // bound by vector issue and power either way: 480p 2.12 -> 2.07 ms, 720p, 20 heads, 5.48 -> 5.38; with 64-row Q blocks 2.47 ->
 // 2.12 ms.
 //
@@ -362,7 +362,9 @@ __device__ __forceinline__ void attend(RF2_STREAM_PARAMS, int xcd, int slot, int
     // The wavefront issues one instruction after the other, so what stood between two steps (offsets, the list, the checks of the
     // last unit, branches around the rare cases) held up the MFMAs; in their open slots it does not (attention at 480p 3,496 -> 3,404
     // us, 720p +1.3 to 2.6 %, ten heads of 256-row blocks 454.5 -> 449.7, 480p with 64-row blocks, whose operands come late, 3,854 ->
-    // 3,856).  K and V through rings in LDS, filled for both wavefronts at once, was 9 % slower (480p): writes to LDS take
+    // 3,856).  Wavefronts that share a long list drift further apart at this pace: four shares meet for that, two were left 1 to 3 %
+    // slower on long launches of 64-row blocks (12 heads of 75,600 tokens 6,630 -> 6,780, 16 of 69,012 10,236 -> 10,551; meeting every 4 or
+    // 16 parts and one wait per operand change that by less than launches of one binary differ).  K and V through rings in LDS, filled for both wavefronts at once, was 9 % slower (480p): writes to LDS take
     // longer to issue than the loads that they save.
     auto step = [&](auto odd_tag, int s, f32x16 (&Scur)[2], f32x16 (&Snext)[2], uint32_t (&Pprev)[2][8], uint32_t (&Pcur)[2][8],
                     uint32_t k_off, uint32_t v_off, auto spare) {

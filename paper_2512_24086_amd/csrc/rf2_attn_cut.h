@@ -42,7 +42,8 @@ struct rf2_attn_cut {
 // faster than the best single cut, up to 7 % slower, on one (64-row blocks, 46,920 tokens x 46 heads) 22 %; d = 64 (720, of which
 // `shared` is taken), 7 % off, the choice 1.3 % slower than the best cut, up to 18 %, under 20 us 24 %.  Against the former kernel,
 // with rings in LDS and a rule of thresholds, they are 1.27 and 1.16 times as fast in the geometric mean; none at d = 128 is slower, six
-// at d = 64 by more than 5 % (8 % at most).
+// at d = 64 by more than 5 % (8 % at most).  (All of this was measured when a row's start and end took half as long again and a unit 2 to 3 %
+// longer than they do now that Q and O move as whole rows and the checks of a unit stand between its MFMAs; not refitted since.)
 // E.g. d = 128 (us, QH x KS = 1x1, 1x2, 1x4, 2x1, 2x2): image of 4,096 tokens, 1 head 38, 24, 19, 39, 26; 8 heads 41, 36, 42, 41, 36;
 // 16 heads 66, 70, 84, 67, 72; 24 heads 104, 102, 124, 107, 105; 480p 5 heads 672, 492, 532, 665, 493, 40 heads 3,926, 3,974,
 // 4,251, 3,506, 3,800; 256-row blocks, 480p, 40 heads, 2x1 3,425, 4x1 3,394, 720p 18,067 and 17,653.  d = 64 (1x1, 1x2, 1x4, 1x8, 2x2): image,
